@@ -285,7 +285,7 @@ static size_t green_ws_bytes(int n) { return rb_align((size_t)2 * n * sizeof(uns
 static size_t adjoint_ws_bytes(int n, int nm, bool lp) {
     if (!lp)
         return rb_align((size_t)2 * rb_rowred_mblocks(n) * nm * sizeof(float)) +
-               rb_align((size_t)2 * n * n * sizeof(float));
+               rb_rowred_ws_bytes(n);
     const size_t np = (size_t)rb_lp_pad(n);
     return rb_align((size_t)2 * rb_rowred_lp_mblocks(n) * nm * sizeof(float)) +
            rb_align(2 * (size_t)n * np * sizeof(uint16_t)) + rb_align(8) +
@@ -293,7 +293,8 @@ static size_t adjoint_ws_bytes(int n, int nm, bool lp) {
 }
 
 static size_t backproject_ws_bytes(int n, int nm, bool lp) {
-    const int mb = lp ? rb_rowred_lp_mblocks(n) : rb_rowred_mblocks(n);
+    if (!lp) return adjoint_ws_bytes(n, nm, false);
+    const int mb = rb_rowred_lp_mblocks(n);
     const size_t nnp = (size_t)n * rb_lp_pad(n);
     return rb_align((size_t)2 * mb * nm * sizeof(float)) + rb_align(2 * nnp * sizeof(uint16_t)) +
            rb_align(8) + rb_align(2 * (size_t)n * n * sizeof(float));
@@ -518,7 +519,6 @@ rb_status rb_born_adjoint(rb_ctx *ctx, const rb_green *gr, const float *w, const
     const bool lp = gr->prec != RB_F32;
     int mb = lp ? rb_rowred_lp_mblocks(gr->n) : rb_rowred_mblocks(gr->n);
     ctx->ws.used = 0;
-    const size_t nn = (size_t)gr->n * gr->n;
     RB_TRY(rb_arena_reserve(ctx, &ctx->ws, adjoint_ws_bytes(gr->n, gr->n_mask, lp)));
     float *parts = rb_carve<float>(&ctx->ws, (size_t)2 * mb * gr->n_mask);
     if (lp) {
@@ -535,9 +535,9 @@ rb_status rb_born_adjoint(rb_ctx *ctx, const rb_green *gr, const float *w, const
         RB_TRY(rb_launch_unscale(ctx, parts, (size_t)2 * mb * gr->n_mask, rscale));
         return rb_launch_adjoint_finish(ctx, gr->n_mask, mb, parts, w, grad);
     }
-    float *rsym = rb_carve<float>(&ctx->ws, 2 * nn);
-    RB_TRY(rb_launch_rowred(ctx, gr->n, gr->n_mask, R, (const float *)gr->G, 1, 1, rsym, parts,
-                            &mb));
+    const size_t scratch = rb_rowred_ws_bytes(gr->n);
+    RB_TRY(rb_launch_rowred(ctx, gr->n, gr->n_mask, R, (const float *)gr->G, 1, 1,
+                            rb_carve<char>(&ctx->ws, scratch), scratch, parts, &mb));
     return rb_launch_adjoint_finish(ctx, gr->n_mask, mb, parts, w, grad);
 }
 
@@ -564,13 +564,12 @@ static rb_status check_backproject(rb_ctx *ctx, const rb_green *gr, const float 
 }
 
 // The back-projection's contraction with its scratch (partial sums, the residual operand)
-// carved from `a`, which holds at least backproject_ws_bytes: complex partial sums
-// parts[2][mb][n_mask] of sum_{e,r} R[e][r] (H_e H_r + H^x_e H^x_r + H^y_e H^y_r).
+// carved from `a`, which holds at least backproject_ws_bytes (FP32: at least the partial sums;
+// the split form of R where the rest fits): complex partial sums parts[2][mb][n_mask] of sum_{e,r} R[e][r] (H_e H_r + H^x_e H^x_r + H^y_e H^y_r).
 static rb_status backproject_parts(rb_ctx *ctx, rb_arena *a, const rb_green *gr, const float *R,
                                    float **parts_out, int *mb_out) {
     const bool lp = gr->prec != RB_F32;
     int mb = lp ? rb_rowred_lp_mblocks(gr->n) : rb_rowred_mblocks(gr->n);
-    const size_t nn = (size_t)gr->n * gr->n;
     const size_t nnp = (size_t)gr->n * rb_lp_pad(gr->n);
     a->used = 0;
     float *parts = rb_carve<float>(a, (size_t)2 * mb * gr->n_mask);
@@ -582,9 +581,8 @@ static rb_status backproject_parts(rb_ctx *ctx, rb_arena *a, const rb_green *gr,
                                    h_low(gr)));
         RB_TRY(rb_launch_unscale(ctx, parts, (size_t)2 * mb * gr->n_mask, rscale));
     } else {
-        float *rsym = rb_carve<float>(a, 2 * nn);
-        RB_TRY(rb_launch_rowred(ctx, gr->n, gr->n_mask, R, (const float *)gr->H, 3, 0, rsym,
-                                parts, &mb));
+        RB_TRY(rb_launch_rowred(ctx, gr->n, gr->n_mask, R, (const float *)gr->H, 3, 0,
+                                a->base + a->used, a->cap - a->used, parts, &mb));
     }
     *parts_out = parts;
     *mb_out = mb;
@@ -637,7 +635,9 @@ rb_status rb_backproject_noalloc(rb_ctx *ctx, const rb_green *gr, const float *R
                                  int32_t accumulate) {
     if (!ctx) return RB_EINVAL;
     RB_TRY(check_backproject(ctx, gr, R, c_mask, omega, d_omega, dm));
-    const size_t need = backproject_ws_bytes(gr->n, gr->n_mask, gr->prec != RB_F32);
+    // one bound for every operand type (FP32 operands take the plain kernel where the partial
+    // sums leave too little for the split form)
+    const size_t need = backproject_ws_bytes(gr->n, gr->n_mask, true);
     if (need > RB_SCRATCH_BYTES)
         return rb_fail(ctx, RB_EINVAL,
                        "n = %d, n_mask = %d needs %zu scratch bytes; the allocation-free "
@@ -670,7 +670,8 @@ struct StepBufs {
     float4 *rec = nullptr;
     double2 *ringpos = nullptr;
     rb_green gr{};
-    float *d_born = nullptr, *R = nullptr, *rsym = nullptr;
+    float *d_born = nullptr, *R = nullptr;
+    char *rsplit = nullptr;  // FP32 form: split form of R (rb_rowred_ws_bytes)
     uint16_t *Rp = nullptr;
     uint8_t *Rp8 = nullptr;  // split form: FP8 planes of Rs (the correction term's operand)
     uint16_t *Rf = nullptr;  // 16-bit forms: the whole Rs (Rp itself in the split form)
@@ -697,8 +698,8 @@ static size_t step_arena_bytes(int N, int nm, size_t P, rb_prec prec) {
     const size_t tab_bytes = lp ? rb_align(NP * 16) + rb_align((size_t)N * 16)
                                 : rb_align(NP * 8) + 3 * rb_align(NP * 4) + rb_align(NP);
     return rb_align(P * 4) + tab_bytes + rb_align(NN * 8) + rb_align(NN * 4) + rb_align(NN) +
-           rb_align(NG * opb) + rb_align(hparts * 3 * NPp * opb) + 3 * rb_align(NN * 8) +
-           rb_align(NNp * 4) +
+           rb_align(NG * opb) + rb_align(hparts * 3 * NPp * opb) + 2 * rb_align(NN * 8) +
+           (lp ? 0 : rb_align(rb_rowred_ws_bytes(N))) + rb_align(NNp * 4) +
            (rb_prec_split(prec) ? rb_align((size_t)2 * N * rb_lp8_pad(N)) : 0) +
            (lp && !rb_prec_split(prec) ? rb_align(NNp * 4) : 0) +
            rb_align((size_t)nm * 8) + rb_align((size_t)nm * 4) +
@@ -757,7 +758,7 @@ static rb_status step_carve(rb_ctx *ctx, const rb_grid *grid, const rb_ring *rin
     b->rowmax = rb_carve<unsigned int>(a, 2 * (size_t)N);
     b->d_born = rb_carve<float>(a, 2 * NN);
     b->R = rb_carve<float>(a, 2 * NN);
-    b->rsym = rb_carve<float>(a, 2 * NN);
+    if (!lp) b->rsplit = rb_carve<char>(a, rb_rowred_ws_bytes(N));
     b->Rp = rb_carve<uint16_t>(a, 2 * NNp);
     if (rb_prec_split(prec)) b->Rp8 = rb_carve<uint8_t>(a, (size_t)2 * N * rb_lp8_pad(N));
     if (lp) b->Rf = rb_prec_split(prec) ? b->Rp : rb_carve<uint16_t>(a, 2 * NNp);
@@ -901,8 +902,8 @@ static rb_status step_enqueue(rb_ctx *ctx, const rb_grid *grid, const rb_ring *r
                                        h_low(&b.gr), b.Rp8, b.Rf));
         } else {
             int mbo = b.mb;
-            RB_TRY(rb_launch_rowred(ctx, b.N, b.nm, b.R, (const float *)b.gr.H, 3, 0, b.rsym,
-                                    b.parts, &mbo));
+            RB_TRY(rb_launch_rowred(ctx, b.N, b.nm, b.R, (const float *)b.gr.H, 3, 0,
+                                    b.rsplit, rb_rowred_ws_bytes(b.N), b.parts, &mbo));
         }
         RB_TRY(step_accumulate(ctx, om, d_omega[k], b, abs));
     }
@@ -1047,7 +1048,8 @@ static rb_status gn_enqueue(rb_ctx *ctx, const rb_grid *grid, const rb_ring *rin
                        rb_align((size_t)nm * 8);
     const size_t need = n_omega * per + 5 * rb_align((size_t)nm * 8) +
                         2 * rb_align((size_t)nm * 4) + rb_align(b.NN * 8) +
-                        rb_align(2 * (size_t)N * Np * 2) + rb_align(8) + rb_align(b.NN * 8) +
+                        rb_align(2 * (size_t)N * Np * 2) + rb_align(8) +
+                        (lp ? 0 : rb_align(rb_rowred_ws_bytes(N))) +
                         rb_align((size_t)2 * mb * nm * 4) + rb_gn_scalar_bytes() +
                         rb_align((size_t)N * 16);
     RB_TRY(gn_reserve(ctx, need));
@@ -1069,7 +1071,8 @@ static rb_status gn_enqueue(rb_ctx *ctx, const rb_grid *grid, const rb_ring *rin
     float *d = rb_carve<float>(a, 2 * b.NN);
     uint16_t *Rp = rb_carve<uint16_t>(a, 2 * (size_t)N * Np);
     float *rscale = rb_carve<float>(a, 2);
-    float *rsym = rb_carve<float>(a, 2 * b.NN);
+    const size_t rsplit_bytes = lp ? 0 : rb_rowred_ws_bytes(N);
+    char *rsplit = rb_carve<char>(a, rsplit_bytes);
     float *parts = rb_carve<float>(a, (size_t)2 * mb * nm);
     double *scal = reinterpret_cast<double *>(rb_carve<char>(a, rb_gn_scalar_bytes()));
     double2 *ringpos = lp ? b.ringpos : rb_carve<double2>(a, N);
@@ -1098,8 +1101,8 @@ static rb_status gn_enqueue(rb_ctx *ctx, const rb_grid *grid, const rb_ring *rin
             RB_TRY(rb_launch_rowred_lp(ctx, kp, N, nm, Rp, Gt[k], 1, parts, &mbo));
             RB_TRY(rb_launch_unscale(ctx, parts, (size_t)2 * mb * nm, rscale));
         } else {
-            RB_TRY(rb_launch_rowred(ctx, N, nm, R, (const float *)gk[k].G, 1, 1, rsym, parts,
-                                    &mbo));
+            RB_TRY(rb_launch_rowred(ctx, N, nm, R, (const float *)gk[k].G, 1, 1, rsplit,
+                                    rsplit_bytes, parts, &mbo));
         }
         return rb_launch_gn_adjoint_acc(ctx, mb, parts, wk[k], acc, first);
     };
@@ -1475,7 +1478,8 @@ static rb_status batch_enqueue(const rb_scan_step *st, int count, rb_prec prec,
                 for (int a = 0; a < na && res == RB_OK; ++a) {
                     StepBufs &b = bufs[act[a]];
                     res = rb_launch_rowred(st[act[a]].ctx, b.N, b.nm, b.R, (const float *)b.gr.H,
-                                           3, 0, b.rsym, b.parts, nullptr);
+                                           3, 0, b.rsplit, rb_rowred_ws_bytes(b.N), b.parts,
+                                           nullptr);
                 }
             }
         } while (false);

@@ -1,4 +1,4 @@
-// Complex GEMMs of the Born operator on MFMA (gfx950, FP32 matrix cores).
+// Complex GEMMs of the Born operator on FP32 operands (gfx950 matrix cores).
 //
 // Forward (Eqs. perturb1, derivative): d[e][r] = sum_q G[e][q] v[q] G[r][q] with
 // v = w delta. Both operands are K-contiguous ([row][q]); d is symmetric (reciprocity), so
@@ -11,10 +11,20 @@
 // multiplies Y_c by the same operand at the output position (E_c[e][q] = B_c[e][q]) and
 // sums over the rows e of the tile, giving per-column partial sums (re, im) per row block.
 //
-// A complex product is four real MFMAs (v_mfma_f32_32x32x2f32): re += ar br - ai bi,
-// im += ar bi + ai br. Operand tiles are staged through LDS as planar re/im arrays laid
-// out [k][row] so that the 32 lanes reading one MFMA operand touch 32 consecutive words.
+// Split operands. The FP32 matrix instructions run at 1/16 of the FP16 rate. A value x under a
+// power-of-two row scale is x = hi + lo + r with hi and lo FP16 (lo: the rounded error of hi):
+// |r| <= 2^-24 |x|, half a unit of FP32, down to an absolute floor of 2^-25 (FP16's smallest
+// subnormal halved). A product then is hi hi' + hi lo' + lo hi' (three FP16 MFMAs with exact
+// products and FP32 accumulators; lo lo' is at most 2^-24 of the product), so the contraction
+// runs at 3/16 of the FP32 instructions' cost and, with 16 instead of 2 K values per
+// accumulation, rounds its partial sums less often. The scales bring each row's mean exponent
+// (over a sample of the row) to 4 (2 for Green's functions, whose caustic peaks are higher),
+// which leaves 2^12 (2^14) above it. Where that does not hold, the kernels notice and the FP32 kernel after them
+// recomputes everything: a value past FP16's range (or an infinity or NaN of the operand) makes
+// the sums of its column not finite, and a column (or row) whose largest scaled value is below
+// 2^-2 is seen by the maxima the loaders keep. The FP32 kernels return at once otherwise.
 #include "rb_internal.h"
+#include "rb_mfma.h"
 
 namespace {
 
@@ -24,41 +34,509 @@ __device__ __forceinline__ floatx16 mfma32(float a, float b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-// Output element held by (lane, register i) of a 32x32 MFMA tile.
-__device__ __forceinline__ int mfma_row(int lane, int i) {
-    return (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
-}
-
 constexpr int RR_BM = 256, RR_BN = 64, RR_BK = 16;
 
 // The row-reduced products are bilinear forms x^T R x (the same operand E = B on both
 // sides), which see only the symmetric part Rs = (R + R^T) / 2. With row and column blocks
-// of RR_BM transducers, x^T Rs x = sum_I x_I^T Rs_II x_I + 2 sum_{J > I} x_I^T Rs_IJ x_J, so
+// of bm transducers, x^T Rs x = sum_I x_I^T Rs_II x_I + 2 sum_{J > I} x_I^T Rs_IJ x_J, so
 // the operand is the block upper triangle R' = Rs on diagonal blocks, R + R^T above them, 0
 // below, and row block I contracts over columns from its own block on.
-__global__ void sym_upper_kernel(const float2 *__restrict__ R, int n, float2 *__restrict__ Rs) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)n * n) return;
-    const int row = (int)(i / n), col = (int)(i - (size_t)row * n);
-    const int bi = row / RR_BM, bj = col / RR_BM;
-    float2 v = make_float2(0.f, 0.f);
-    if (bj >= bi) {
-        const float2 a = R[i], b = R[(size_t)col * n + row];
-        const float f = bj == bi ? 0.5f : 1.0f;
-        v = make_float2(f * (a.x + b.x), f * (a.y + b.y));
-    }
-    Rs[i] = v;
+template <int bm>
+__device__ __forceinline__ float2 sym_upper(const float2 *__restrict__ R, int n, int row, int col) {
+    const int bi = row / bm, bj = col / bm;
+    if (row >= n || col >= n || bj < bi) return make_float2(0.f, 0.f);
+    const float2 a = R[(size_t)row * n + col], b = R[(size_t)col * n + row];
+    const float f = bj == bi ? 0.5f : 1.0f;
+    return make_float2(f * (a.x + b.x), f * (a.y + b.y));
 }
 
+// Split operands --------------------------------------------------------------------------
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ floatx16 mfma16(halfx8 a, halfx8 b, floatx16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
+
+// hi and lo parts of a pair of scaled values, each packed in a word.
+__device__ __forceinline__ void split2(float a, float b, uint32_t &hi, uint32_t &lo) {
+    const halfx2 h = {(_Float16)a, (_Float16)b};
+    const halfx2 l = {(_Float16)(a - (float)h.x), (_Float16)(b - (float)h.y)};
+    hi = __builtin_bit_cast(uint32_t, h);
+    lo = __builtin_bit_cast(uint32_t, l);
+}
+
+// State of a split contraction in device memory. plain: set before it where no scale can be
+// chosen (an infinity or NaN in a sampled row or in R); bad: set by it where a scaled value left
+// its range. Either makes the FP32 kernels after it recompute the result.
+struct SplitHead {
+    int plain, bad, rs, pad;
+};
+
+// Scaled values below this, over a whole column (row) of an operand, send the call to the
+// FP32 kernels: the floor of 2^-25 is then 2^-23 of the largest value.
+constexpr float SPLIT_LEAST = 0.25f;
+// What the scales bring a row's mean exponent to: back-projection operands (no high peaks) and
+// Green's functions (caustic peaks, up to sqrt(1 / |J|)).
+constexpr int SPLIT_TOP_H = 4, SPLIT_TOP_G = 2;
+
+// Mean binary exponent of a row's sample (32 pieces of 64 columns spread over the row,
+// everything where the row is shorter; all components; zeros left out): few peaks do not move
+// it, where they would an rms. ROW_ZERO: nothing but zeros; ROW_BAD: an infinity or NaN. One
+// workgroup per row.
+constexpr float ROW_ZERO = -1e9f, ROW_BAD = 1e9f;
+__global__ void __launch_bounds__(256) split_stat_kernel(const float2 *__restrict__ B, int n,
+                                                         int n_cols, int n_comp,
+                                                         float *__restrict__ mexp) {
+    __shared__ int red[4][3];
+    const int e = blockIdx.x;
+    const int pieces = 32, len = 64, total = min(n_cols, pieces * len);
+    int sum = 0, cnt = 0, bad = 0;
+    for (int c = 0; c < n_comp; ++c) {
+        const float2 *row = B + ((size_t)c * n + e) * n_cols;
+        for (int i = threadIdx.x; i < total; i += 256) {
+            size_t q = i;
+            if (n_cols > pieces * len)
+                q = (size_t)(i / len) * (size_t)(n_cols - len) / (pieces - 1) + i % len;
+            const float2 x = row[q];
+            const uint32_t m = max(__float_as_uint(x.x) & 0x7fffffffu,
+                                   __float_as_uint(x.y) & 0x7fffffffu);
+            if (m == 0) continue;
+            bad |= m >= 0x7f800000u;
+            sum += (int)(m >> 23) - 126;  // 2^(e-1) <= |x| < 2^e
+            ++cnt;
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        sum += __shfl_xor(sum, off);
+        cnt += __shfl_xor(cnt, off);
+        bad |= __shfl_xor(bad, off);
+    }
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        red[w][0] = sum;
+        red[w][1] = cnt;
+        red[w][2] = bad;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        sum = red[0][0] + red[1][0] + red[2][0] + red[3][0];
+        cnt = red[0][1] + red[1][1] + red[2][1] + red[3][1];
+        bad = red[0][2] | red[1][2] | red[2][2] | red[3][2];
+        mexp[e] = bad ? ROW_BAD : cnt ? (float)sum / (float)cnt : ROW_ZERO;
+    }
+}
+
+// Scale exponent of a row: its mean exponent brought to `top`.
+__device__ __forceinline__ int split_exp(float mexp, int top) {
+    return max(-100, min(100, top - (int)rintf(mexp)));
+}
+
+// What the scale kernels derive from all rows' samples: the mean of the mean exponents (for
+// rows whose sample is zero) and whether every sample is finite. Result in every thread of a
+// 256-thread workgroup.
+struct SplitAll {
+    float mean;
+    bool finite;
+};
+__device__ __forceinline__ SplitAll split_all(const float *__restrict__ mexp, int n) {
+    __shared__ float s_sum[4];
+    __shared__ int s_cnt[4], s_bad[4];
+    float sum = 0.f;
+    int cnt = 0, bad = 0;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        const float v = mexp[i];
+        if (v == ROW_BAD) bad = 1;
+        else if (v != ROW_ZERO) {
+            sum += v;
+            ++cnt;
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        sum += __shfl_xor(sum, off);
+        cnt += __shfl_xor(cnt, off);
+        bad |= __shfl_xor(bad, off);
+    }
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        s_sum[w] = sum;
+        s_cnt[w] = cnt;
+        s_bad[w] = bad;
+    }
+    __syncthreads();
+    SplitAll a;
+    cnt = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+    a.mean = cnt ? ((s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3])) / (float)cnt : 0.f;
+    a.finite = !(s_bad[0] | s_bad[1] | s_bad[2] | s_bad[3]);
+    return a;
+}
+
+// Largest exponent of the scaled residual in a row: R[e][r] / (t_e t_r) < 2^rmax[e]
+// (R_NONE: the row is zero, R_BAD: an infinity or NaN); the scales' exponents to xexp. One
+// workgroup per row.
+constexpr int R_NONE = -(1 << 20), R_BAD = 1 << 20;
+__global__ void __launch_bounds__(256) split_range_kernel(const float2 *__restrict__ R, int n,
+                                                          int top,
+                                                          const float *__restrict__ mexp,
+                                                          int *__restrict__ xexp,
+                                                          int *__restrict__ rmax) {
+    __shared__ int red[4];
+    const SplitAll all = split_all(mexp, n);
+    auto row_exp = [&](int i) {
+        const float v = mexp[i];
+        return all.finite ? split_exp(v != ROW_ZERO ? v : all.mean, top) : 0;
+    };
+    const int e = blockIdx.x, xe = row_exp(e);
+    int m = all.finite ? R_NONE : R_BAD;
+    for (int r = threadIdx.x; r < n; r += 256) {
+        const float2 x = R[(size_t)e * n + r];
+        const uint32_t b = max(__float_as_uint(x.x) & 0x7fffffffu,
+                               __float_as_uint(x.y) & 0x7fffffffu);
+        if (b >= 0x7f800000u) m = R_BAD;
+        else if (b != 0) m = max(m, (int)(b >> 23) - 126 - xe - row_exp(r));
+    }
+    for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        xexp[e] = xe;
+        rmax[e] = max(max(red[0], red[1]), max(red[2], red[3]));
+    }
+}
+
+// Layout of the split residual operand: fragments of 32 rows x 16 K as one lane-ordered KiB
+// (lane l: row l & 31, K 8 (l >> 5) .. + 7), [K / 16][row / 32][re hi, re lo, im hi, im lo], so
+// that a row slab's K step is contiguous and a fragment read touches every LDS bank once.
+constexpr int SR_FRAG = 512;  // values of a fragment
+constexpr int SR_BM = RR_BM, SR_BN = 128, SR_BK = 16, SR_THREADS = 512;
+constexpr int SR_WM = 64;  // rows of a wave, the block of R's triangle
+constexpr int SR_A = (SR_BM / 32) * 4 * SR_FRAG, SR_B = (SR_BN / 32) * 4 * SR_FRAG;
+
+// R' scaled by 2^rs / (t_e t_r) (t: the rows' scales of the other operand, powers of two) in
+// split form, zero past n; the scales t (zero past n up to a whole slab) and the head. A
+// workgroup covers 32 rows x 64 columns. rs brings the largest |R| / (t t) below 2^14 (R + R^T
+// above the diagonal blocks: below 2^15).
+__global__ void __launch_bounds__(256) split_residual_kernel(
+    const float2 *__restrict__ R, int n, int np, const int *__restrict__ xexp,
+    const int *__restrict__ rmax, float *__restrict__ tsc, SplitHead *__restrict__ head,
+    _Float16 *__restrict__ Rf) {
+    __shared__ int red[4];
+    int rm = R_NONE;
+    for (int i = threadIdx.x; i < n; i += 256) rm = max(rm, rmax[i]);
+    for (int off = 32; off > 0; off >>= 1) rm = max(rm, __shfl_xor(rm, off));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = rm;
+    __syncthreads();
+    rm = max(max(red[0], red[1]), max(red[2], red[3]));
+    const bool finite = rm != R_BAD;
+    const int rs = finite && rm != R_NONE ? 14 - rm : 0;
+    const int row = blockIdx.y * 32 + (threadIdx.x & 31);
+    const int c0 = blockIdx.x * 64 + (threadIdx.x >> 5) * 8;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < 32) tsc[row] = row < n ? ldexpf(1.f, xexp[row]) : 0.f;
+        // zeros from np up to a whole slab
+        if (blockIdx.y == 0)
+            for (int i = np + threadIdx.x; i < (n + SR_BM - 1) / SR_BM * SR_BM; i += 256)
+                tsc[i] = 0.f;
+        if (blockIdx.y == 0 && threadIdx.x == 0) *head = SplitHead{finite ? 0 : 1, 0, rs, 0};
+    }
+    if (!finite || c0 >= np) return;
+    uint32_t w[4][4];
+    const int xe = row < n ? xexp[row] : 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        float2 v[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int col = c0 + 2 * k + u;
+            v[u] = sym_upper<SR_WM>(R, n, row, col);
+            const int x = col < n ? rs - xe - xexp[col] : 0;
+            v[u] = make_float2(ldexpf(v[u].x, x), ldexpf(v[u].y, x));
+        }
+        split2(v[0].x, v[1].x, w[0][k], w[1][k]);
+        split2(v[0].y, v[1].y, w[2][k], w[3][k]);
+    }
+    const size_t frag = ((size_t)(c0 / SR_BK) * (np / 32) + blockIdx.y) * 4;
+    _Float16 *dst = Rf + frag * SR_FRAG + ((c0 >> 3) & 1) * 256 + (threadIdx.x & 31) * 8;
+#pragma unroll
+    for (int pl = 0; pl < 4; ++pl)
+        *reinterpret_cast<uint4 *>(dst + pl * SR_FRAG) =
+            make_uint4(w[pl][0], w[pl][1], w[pl][2], w[pl][3]);
+}
+
+// The row-reduced products on split operands. Bound by the matrix pipes: 12 FP16 MFMAs of
+// 32x32x16 per complex 32x32 tile and 16 K values, 1.5 times the MFMAs per staged byte of the
+// 16-bit form, so the same workgroup (256 rows x 128 columns, eight waves of 64 x 64, two per
+// SIMD, three LDS stages of 48 KiB) leaves LDS at about half its rate. R' comes in fragment
+// order straight into LDS, two K steps ahead. B stays as the caller keeps it (FP32, complex,
+// [row][column]): a lane takes one column of 8 consecutive rows (512-byte runs per wave), which
+// is a fragment's 8 K values, splits them in registers (about 5 instructions a pair) and writes
+// four 16-byte pieces to LDS. Waves 0-3 and 4-7 stage alternate K steps, so that a wave's loads
+// are in flight for two steps. R's triangle has blocks of 64, a wave's rows: a wave skips the K
+// blocks left of its own, which the FP32 kernel's 256-row blocks multiply as zeros. No operand is written to memory in split form: converting once
+// in a pass of its own would move 31 GB more at 1024 transducers and 636160 nodes, where the
+// back-projection takes 24.9 ms (1.0 PFLOP/s of MFMAs; the FP32 kernel 128.9 ms) with an error of
+// 3.9e-7 against FP64 sums (5.4e-7).
+__global__ void __launch_bounds__(SR_THREADS) rowred_split_kernel(
+    const _Float16 *__restrict__ Rf, const float2 *__restrict__ B, const float *__restrict__ tsc,
+    int n, int np, int n_cols, int n_comp, int conj_b, int mblocks, int nblocks,
+    SplitHead *__restrict__ head, float *__restrict__ parts) {
+    // R' and B of three K steps, in arrays of their own: the compiler then sees that neither
+    // the stores of B nor the reads of one step depend on loads in flight into another
+    __shared__ __attribute__((aligned(1024))) _Float16 a0[SR_A], a1[SR_A], a2[SR_A];
+    __shared__ __attribute__((aligned(1024))) _Float16 b0[SR_B], b1[SR_B], b2[SR_B];
+    __shared__ float red[2][4][SR_BN];
+    __shared__ float cmax[4][SR_BN];
+    __shared__ __attribute__((aligned(16))) float ts[SR_BM];  // scales of the slab's rows
+    if (head->plain) return;  // written before this launch
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;      // 4 x 2 waves of 64 x 64
+    const int grp = wave >> 2, half = (wave >> 1) & 1;  // staging: K step parity, half of a step
+    const int scol = (wave & 1) * 64 + lane;      // staged column of the tile
+    const float bsign = conj_b ? -1.f : 1.f;
+    const int rs = head->rs;
+    const int ntile = np / 32, KT = np / SR_BK;
+    const __amdgpu_buffer_rsrc_t ra = plane_rsrc(Rf, (size_t)np * np * 8);
+
+    // Persistent, one workgroup per CU; items and XCD ranges as in the FP32 kernel. K runs from
+    // the last block down, so that the epilogue finds its diagonal block of B in L2.
+    const int n_pairs = (mblocks + 1) / 2, n_items = nblocks * n_pairs;
+    const int L = gridDim.x >> 3, xcd = blockIdx.x & 7;
+    const int per = (((n_items + 7) / 8) + 1) & ~1;
+    for (int it = blockIdx.x >> 3; it < per; it += L) {
+        const int item = xcd * per + it;
+        if (item >= n_items) break;
+        const int nb = item / n_pairs, pr = item - nb * n_pairs;
+        const int col0 = nb * SR_BN;
+        for (int hf = 0; hf < 2; ++hf) {
+            const int mb = hf == 0 ? pr : mblocks - 1 - pr;
+            if (hf == 1 && mb == pr) break;  // middle slab of an odd count
+            const int row0 = mb * SR_BM;
+            const int steps = KT - row0 / SR_BK;
+            float cs_re[2] = {0.f, 0.f}, cs_im[2] = {0.f, 0.f};
+            float mx = 0.f;  // largest scaled part this lane staged (its column)
+            // this wave's rows meet K from their own block of R' on; nothing of rows past n
+            const int wrow = row0 + wm * SR_WM;
+            const int wsteps = wrow < n ? KT - wrow / SR_BK : 0;
+            const uint32_t ccol = (uint32_t)min(col0 + scol, n_cols - 1);
+            float2 raw[8];
+            // step i of the loop is K step KT - 1 - i; rows past n meet zeros of R'
+            auto load_b = [&](const float2 *Bc, int i) {
+                const int k0 = (KT - 1 - i) * SR_BK + half * 8;
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    raw[u] = (Bc + (size_t)min(k0 + u, n - 1) * n_cols)[ccol];
+            };
+            auto put_b = [&](int i, _Float16 *st) {
+                const int k0 = (KT - 1 - i) * SR_BK + half * 8;
+                uint32_t w[4][4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float t0 = tsc[min(k0 + 2 * u, n - 1)];
+                    const float t1 = tsc[min(k0 + 2 * u + 1, n - 1)];
+                    const float xr = raw[2 * u].x * t0, yr = raw[2 * u + 1].x * t1;
+                    const float xi = raw[2 * u].y * (t0 * bsign);
+                    const float yi = raw[2 * u + 1].y * (t1 * bsign);
+                    mx = fmaxf(fmaxf(mx, fabsf(xr)), fabsf(yr));
+                    mx = fmaxf(fmaxf(mx, fabsf(xi)), fabsf(yi));
+                    split2(xr, yr, w[0][u], w[1][u]);
+                    split2(xi, yi, w[2][u], w[3][u]);
+                }
+                _Float16 *dst = st + (scol >> 5) * 4 * SR_FRAG + half * 256 + (scol & 31) * 8;
+#pragma unroll
+                for (int pl = 0; pl < 4; ++pl)
+                    *reinterpret_cast<uint4 *>(dst + pl * SR_FRAG) =
+                        make_uint4(w[pl][0], w[pl][1], w[pl][2], w[pl][3]);
+            };
+            auto fetch_a = [&](int i, _Float16 *st) {
+                const uint32_t kb = (uint32_t)((KT - 1 - i) * ntile + mb * (SR_BM / 32)) *
+                                    (4 * SR_FRAG * 2);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    load_lds16(ra, st + (wave + 8 * u) * SR_FRAG, lane * 16,
+                               kb + (uint32_t)(wave + 8 * u) * (SR_FRAG * 2));
+            };
+            // the first loads of a component: R' of two steps, B of this wave's first
+            auto begin = [&](const float2 *Bc) {
+                fetch_a(0, a0);
+                if (steps > 1) fetch_a(1, a1);
+                __builtin_amdgcn_sched_barrier(0);
+                if (grp == 0 || steps > 1) load_b(Bc, grp);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            begin(B);
+            if (tid < SR_BM) ts[tid] = tsc[row0 + tid];
+
+            for (int c = 0; c < n_comp; ++c) {
+                const float2 *Bc = B + (size_t)c * n * n_cols;
+                floatx16 acc_re[2][2], acc_im[2][2];
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) {
+                            acc_re[mt][nt][i] = 0.f;
+                            acc_im[mt][nt][i] = 0.f;
+                        }
+                auto multiply = [&](const _Float16 *sa, const _Float16 *sb) {
+                    halfx8 a[2][4], b[4], bn[2];
+#pragma unroll
+                    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                        for (int pl = 0; pl < 4; ++pl)
+                            a[mt][pl] = *reinterpret_cast<const halfx8 *>(
+                                sa + ((wm * 2 + mt) * 4 + pl) * SR_FRAG + lane * 8);
+#pragma unroll
+                    for (int nt = 0; nt < 2; ++nt) {
+#pragma unroll
+                        for (int pl = 0; pl < 4; ++pl)
+                            b[pl] = *reinterpret_cast<const halfx8 *>(
+                                sb + ((wn * 2 + nt) * 4 + pl) * SR_FRAG + lane * 8);
+                        bn[0] = -b[2];
+                        bn[1] = -b[3];
+                        auto term = [&](int pa, halfx8 br, halfx8 bi) {
+#pragma unroll
+                            for (int mt = 0; mt < 2; ++mt) {
+                                acc_re[mt][nt] = mfma16(a[mt][pa], br, acc_re[mt][nt]);
+                                acc_im[mt][nt] = mfma16(a[mt][pa], bi, acc_im[mt][nt]);
+                            }
+                        };
+                        term(0, b[0], b[2]);   // re_hi (re_hi, im_hi)
+                        term(2, bn[0], b[0]);  // im_hi (-im_hi, re_hi)
+                        term(0, b[1], b[3]);   // re_hi (re_lo, im_lo)
+                        term(2, bn[1], b[1]);
+                        term(1, b[0], b[2]);   // re_lo (re_hi, im_hi)
+                        term(3, bn[0], b[0]);
+                    }
+                };
+                // one step whose successors are in flight: R' of step i + 1 was fetched a step
+                // ago (4 loads), each wave's loads of B since then are 8 more and R' of step
+                // i + 2 another 4, so 12 outstanding loads mean step i + 1 is in LDS
+                auto step = [&](_Float16 *ca, _Float16 *cb, _Float16 *nb_, _Float16 *na, int i) {
+                    fetch_a(i + 2, na);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (((grp ^ i) & 1) != 0) {
+                        put_b(i + 1, nb_);
+                        load_b(Bc, i + 3);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (i < wsteps) multiply(ca, cb);
+                    lr_sync<12>();
+                };
+                // a step without the loads of B, or one near the end: nothing is left in flight
+                auto last = [&](_Float16 *ca, _Float16 *cb, _Float16 *nb_, _Float16 *na, int i) {
+                    if (i + 2 < steps) fetch_a(i + 2, na);
+                    if (((grp ^ i) & 1) != 0) {
+                        if (i + 1 < steps) put_b(i + 1, nb_);
+                        if (i + 3 < steps) load_b(Bc, i + 3);
+                    }
+                    if (i < wsteps) multiply(ca, cb);
+                    lr_sync<0>();
+                };
+                if (grp == 0) {
+                    put_b(0, b0);
+                    if (steps > 2) load_b(Bc, 2);
+                }
+                // R' of step 0 is in LDS once only R' of step 1's younger loads of B are left
+                if (steps > 3) lr_sync<8>();
+                else lr_sync<0>();
+                int i = 0;
+                for (; i + 5 < steps; i += 3) {
+                    step(a0, b0, b1, a2, i);
+                    step(a1, b1, b2, a0, i + 1);
+                    step(a2, b2, b0, a1, i + 2);
+                }
+                for (; i < steps; i += 3) {
+                    last(a0, b0, b1, a2, i);
+                    if (i + 1 < steps) last(a1, b1, b2, a0, i + 1);
+                    if (i + 2 < steps) last(a2, b2, b0, a1, i + 2);
+                }
+                // every wave is past its reads: the next component's first loads run under
+                // the epilogue
+                if (c + 1 < n_comp) begin(Bc + (size_t)n * n_cols);
+                // epilogue: sum over the rows of t_e E_c[e][q] Y_c[e][q] (t zero past n), 32
+                // loads in flight. The asm keeps its 64 addresses from being formed before the
+                // K loop and spilled.
+                int rbase = wrow, cbase = col0 + wn * 64 + (lane & 31);
+                asm volatile("" : "+s"(rbase), "+v"(cbase));
+                if (wsteps > 0) {
+#pragma unroll
+                    for (int nt = 0; nt < 2; ++nt) {
+                        const uint32_t gc = (uint32_t)min(cbase + nt * 32, n_cols - 1);
+#pragma unroll
+                        for (int mt = 0; mt < 2; ++mt) {
+                            float2 ev[16];
+#pragma unroll
+                            for (int k = 0; k < 16; ++k) {
+                                // rows br (lanes 0-31) and br + 4, clamped to the last row
+                                const int br = rbase + mt * 32 + (k >> 2) * 8 + (k & 3);
+                                const uint32_t up = br + 4 < n ? 4u * (uint32_t)n_cols : 0u;
+                                ev[k] = (Bc + (size_t)min(br, n - 1) * n_cols)
+                                    [(lane >> 5) * up + gc];
+                            }
+#pragma unroll
+                            for (int k4 = 0; k4 < 4; ++k4) {
+                                float t[4];
+                                *reinterpret_cast<float4 *>(t) = *reinterpret_cast<const float4 *>(
+                                    ts + wm * SR_WM + mt * 32 + k4 * 8 + (lane >> 5) * 4);
+#pragma unroll
+                                for (int u = 0; u < 4; ++u) {
+                                    const int k = k4 * 4 + u;
+                                    const float er = ev[k].x * t[u], ei = ev[k].y * (t[u] * bsign);
+                                    const float yr = acc_re[mt][nt][k], yi = acc_im[mt][nt][k];
+                                    cs_re[nt] += er * yr - ei * yi;
+                                    cs_im[nt] += er * yi + ei * yr;
+                                }
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                }
+            }
+            // combine the two lane halves, then the four waves of a column
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                cs_re[nt] += __shfl_xor(cs_re[nt], 32);
+                cs_im[nt] += __shfl_xor(cs_im[nt], 32);
+                if (lane < 32) {
+                    red[0][wm][wn * 64 + nt * 32 + lane] = cs_re[nt];
+                    red[1][wm][wn * 64 + nt * 32 + lane] = cs_im[nt];
+                }
+            }
+            cmax[grp * 2 + half][scol] = mx;
+            __syncthreads();
+            if (tid < SR_BN && col0 + tid < n_cols) {
+                const int gc = col0 + tid;
+                const float sr = ldexpf((red[0][0][tid] + red[0][1][tid]) +
+                                            (red[0][2][tid] + red[0][3][tid]), -rs);
+                const float si = ldexpf((red[1][0][tid] + red[1][1][tid]) +
+                                            (red[1][2][tid] + red[1][3][tid]), -rs);
+                parts[(size_t)mb * n_cols + gc] = sr;
+                parts[(size_t)(mblocks + mb) * n_cols + gc] = si;
+                const float m = fmaxf(fmaxf(cmax[0][tid], cmax[1][tid]),
+                                      fmaxf(cmax[2][tid], cmax[3][tid]));
+                if (!isfinite(sr) || !isfinite(si) || (m > 0.f && m < SPLIT_LEAST)) head->bad = 1;
+            }
+            __syncthreads();  // red[] and the stages are reused by the next slab
+        }
+    }
+}
+
+// The FP32 form, for what the split form turns down (head: the split contraction before it,
+// NULL to run in any case).
 // parts: [2][mblocks][n_cols] (re plane, then im plane).
 __global__ void __launch_bounds__(256) rowred_kernel(const float2 *__restrict__ R,
                                                      const float2 *__restrict__ B, int n,
                                                      int n_cols, int n_comp, int conj_b,
                                                      int mblocks, int nblocks,
+                                                     const SplitHead *__restrict__ head,
                                                      float *__restrict__ parts) {
     __shared__ float a_re[RR_BK][RR_BM], a_im[RR_BK][RR_BM];
     __shared__ float b_re[RR_BK][RR_BN], b_im[RR_BK][RR_BN];
     __shared__ float red[2][4][RR_BN];
+    if (head && !head->plain && !head->bad) return;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const float bsign = conj_b ? -1.f : 1.f;
@@ -94,14 +572,12 @@ __global__ void __launch_bounds__(256) rowred_kernel(const float2 *__restrict__ 
                             acc_im[mt][nt][i] = 0.f;
                         }
                 for (int k0 = row0; k0 < n; k0 += RR_BK) {  // R' is zero left of the diagonal block
-                    // A tile: row (row0 + tid), 16 consecutive k of R
+                    // A tile: row (row0 + tid), 16 consecutive k of R'
                     {
                         int gr = row0 + tid;
-                        const float2 *src = R + (size_t)gr * n + k0;
 #pragma unroll
                         for (int kk = 0; kk < RR_BK; ++kk) {
-                            float2 v = make_float2(0.f, 0.f);
-                            if (gr < n && k0 + kk < n) v = src[kk];
+                            const float2 v = sym_upper<RR_BM>(R, n, gr, k0 + kk);
                             a_re[kk][tid] = v.x;
                             a_im[kk][tid] = v.y;
                         }
@@ -336,18 +812,58 @@ __global__ void forward_reduce(const float2 *__restrict__ dpart, int n, int spli
 
 int rb_rowred_mblocks(int n) { return (n + RR_BM - 1) / RR_BM; }
 
+// Scratch of the split form: the residual's fragments, the rows' samples and scales, the head
+// (nothing where R's fragments do not fit one buffer descriptor).
+static bool rowred_split_fits(int n) {
+    const size_t np = (size_t)rb_lp_pad(n);
+    return np * np * 8 <= (size_t)0xfffffff0u;
+}
+constexpr int SPLIT_COLS_MAX = 1 << 26;  // a lane's offset of four rows stays below 2^32 bytes
+
+size_t rb_rowred_ws_bytes(int n) {
+    if (!rowred_split_fits(n)) return 0;
+    const size_t np = (size_t)rb_lp_pad(n), nb = (size_t)rb_rowred_mblocks(n) * RR_BM;
+    return rb_align(np * np * 8) + rb_align(nb * 16) + rb_align(sizeof(SplitHead));
+}
+
+// Split operands where R's fragments fit one buffer descriptor and the scratch; else (and for
+// calls whose values leave the split range) the FP32 kernel.
 rb_status rb_launch_rowred(rb_ctx *ctx, int n, int n_mask, const float *R, const float *B,
-                           int n_comp, int conj_b, float *rsym, float *parts, int *mblocks_out) {
-    int mblocks = rb_rowred_mblocks(n);
-    int nblocks = (n_mask + RR_BN - 1) / RR_BN;
-    int grid = std::max(8, ctx->n_cu / 8 * 8);  // one workgroup per CU (persistent)
+                           int n_comp, int conj_b, void *scratch, size_t scratch_bytes,
+                           float *parts, int *mblocks_out) {
+    const int mblocks = rb_rowred_mblocks(n);
+    const int grid = std::max(8, ctx->n_cu / 8 * 8);  // one workgroup per CU (persistent)
+    const int np = rb_lp_pad(n);
+    const bool split = scratch && rowred_split_fits(n) && n_mask <= SPLIT_COLS_MAX && scratch_bytes >= rb_rowred_ws_bytes(n);
+    SplitHead *head = nullptr;
     rb_prof_begin(ctx, ST_BACKPROJECT);
-    hipLaunchKernelGGL(sym_upper_kernel, dim3((unsigned)(((size_t)n * n + 255) / 256)), dim3(256),
-                       0, ctx->stream, (const float2 *)R, n, (float2 *)rsym);
-    RB_CHECK_LAUNCH(ctx);
-    hipLaunchKernelGGL(rowred_kernel, dim3(grid), dim3(256), 0, ctx->stream,
-                       (const float2 *)rsym, (const float2 *)B, n, n_mask, n_comp, conj_b,
-                       mblocks, nblocks, parts);
+    if (split) {
+        char *p = static_cast<char *>(scratch);
+        const size_t nb = (size_t)mblocks * RR_BM;
+        _Float16 *Rf = reinterpret_cast<_Float16 *>(p);
+        p += rb_align((size_t)np * np * 8);
+        float *mexp = reinterpret_cast<float *>(p);
+        float *tsc = reinterpret_cast<float *>(p + nb * 4);
+        int *xexp = reinterpret_cast<int *>(p + nb * 8), *rmax = xexp + nb;
+        head = reinterpret_cast<SplitHead *>(p + rb_align(nb * 16));
+        const int top = conj_b ? SPLIT_TOP_G : SPLIT_TOP_H;
+        hipLaunchKernelGGL(split_stat_kernel, dim3(n), dim3(256), 0, ctx->stream,
+                           (const float2 *)B, n, n_mask, n_comp, mexp);
+        RB_CHECK_LAUNCH(ctx);
+        hipLaunchKernelGGL(split_range_kernel, dim3(n), dim3(256), 0, ctx->stream,
+                           (const float2 *)R, n, top, mexp, xexp, rmax);
+        RB_CHECK_LAUNCH(ctx);
+        hipLaunchKernelGGL(split_residual_kernel, dim3((np + 63) / 64, np / 32), dim3(256), 0,
+                           ctx->stream, (const float2 *)R, n, np, xexp, rmax, tsc, head, Rf);
+        RB_CHECK_LAUNCH(ctx);
+        hipLaunchKernelGGL(rowred_split_kernel, dim3(grid), dim3(SR_THREADS), 0, ctx->stream, Rf,
+                           (const float2 *)B, tsc, n, np, n_mask, n_comp, conj_b, mblocks,
+                           (n_mask + SR_BN - 1) / SR_BN, head, parts);
+        RB_CHECK_LAUNCH(ctx);
+    }
+    hipLaunchKernelGGL(rowred_kernel, dim3(grid), dim3(256), 0, ctx->stream, (const float2 *)R,
+                       (const float2 *)B, n, n_mask, n_comp, conj_b, mblocks,
+                       (n_mask + RR_BN - 1) / RR_BN, head, parts);
     RB_CHECK_LAUNCH(ctx);
     rb_prof_end(ctx);
     if (mblocks_out) *mblocks_out = mblocks;

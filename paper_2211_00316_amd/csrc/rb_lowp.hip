@@ -17,6 +17,7 @@
 // 16-byte aligned and the contraction runs over whole 32-deep steps.
 // The green kernel transposes H through LDS so that both layouts are written coalesced.
 #include "rb_internal.h"
+#include "rb_mfma.h"
 
 namespace {
 
@@ -49,10 +50,6 @@ __device__ __forceinline__ uint4 neg8(uint4 v) {
 
 template <typename T> __device__ __forceinline__ typename Lp<T>::vec as_vec(uint4 v) {
     return __builtin_bit_cast(typename Lp<T>::vec, v);
-}
-
-__device__ __forceinline__ int mfma_row(int lane, int i) {
-    return (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
 }
 
 __device__ __forceinline__ double reduce_phase(double ph) {
@@ -709,29 +706,6 @@ constexpr int LR_AU = 2 * LR_AP * 2 / 1024 / (LR_THREADS / 64);  // A loads per 
 constexpr int LR_BU = 2 * LR_BP * 2 / 1024 / (LR_THREADS / 64);  // B loads per lane and step
 static_assert(LR_THREADS == 512 && LR_AU == 4 && LR_BU == 2, "loader layout");
 constexpr size_t LR_SPAN = 0xfffffff0u;  // vector + scalar byte offsets stay below this
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const void *p, size_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)bytes,
-                                             0x00020000);
-}
-
-// 16 bytes per lane from the buffer to LDS: lane l writes lds + 16 l (lds wave-uniform).
-template <typename T>
-__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t r, T *lds, uint32_t off,
-                                           uint32_t soff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(
-        r, (__attribute__((address_space(3))) void *)lds, 16, (int)off, (int)soff, 0, 0);
-}
-
-// Wait until at most N global loads of this wave are outstanding and its LDS operations are
-// done, then meet the other waves. Loads return in order, so the older step's operands are in
-// LDS; after the barrier every wave's are.
-template <int N>
-__device__ __forceinline__ void lr_sync() {
-    static_assert(N >= 0 && N < 64, "vmcnt");
-    if constexpr (N == 0) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
 
 // MFMA operands of one 16-deep sub-step of a wave: A rows (re, im) of its 32-row tiles, B
 // columns (re, im, -im) of its two 32-column tiles.
