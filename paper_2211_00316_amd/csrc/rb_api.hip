@@ -1329,7 +1329,7 @@ rb_status rb_autotune(rb_ctx *ctx, const rb_grid *grid, const rb_ring *ring, rb_
     for (int ti = prec == RB_F32 ? 1 : 0; ti < 2; ++ti) {
         std::vector<int> splits;
         for (int s = 8; s <= RB_TUNE_SPLITK_MAX; s += 8) splits.push_back(s);
-        splits.push_back(prec == RB_F32 ? rb_forward_default_splitk(N, nm)
+        splits.push_back(prec == RB_F32 ? rb_forward_default_splitk(N, nm, ctx->n_cu)
                                         : rb_forward_lp_default_splitk(N, nm, ti == 0,
                                                                        ctx->n_cu));
         std::sort(splits.begin(), splits.end());

@@ -25,6 +25,7 @@
 // 2^-2 is seen by the maxima the loaders keep. The FP32 kernels return at once otherwise.
 #include "rb_internal.h"
 #include "rb_mfma.h"
+#include "rb_fwd.h"
 
 namespace {
 
@@ -66,6 +67,26 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t &hi, uint32_t 
     lo = __builtin_bit_cast(uint32_t, l);
 }
 
+// A stage's products for the column tile nt of a wave: planes (re hi, re lo, im hi, im lo) of the
+// two row tiles and of the columns, bn the negated imaginary planes of the columns.
+__device__ __forceinline__ void split_terms(const halfx8 (&a)[2][4], const halfx8 (&b)[4],
+                                            const halfx8 (&bn)[2], floatx16 (&acc_re)[2][2],
+                                            floatx16 (&acc_im)[2][2], int nt) {
+    auto term = [&](int pa, halfx8 br, halfx8 bi) {
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            acc_re[mt][nt] = mfma16(a[mt][pa], br, acc_re[mt][nt]);
+            acc_im[mt][nt] = mfma16(a[mt][pa], bi, acc_im[mt][nt]);
+        }
+    };
+    term(0, b[0], b[2]);   // re_hi (re_hi, im_hi)
+    term(2, bn[0], b[0]);  // im_hi (-im_hi, re_hi)
+    term(0, b[1], b[3]);   // re_hi (re_lo, im_lo)
+    term(2, bn[1], b[1]);
+    term(1, b[0], b[2]);   // re_lo (re_hi, im_hi)
+    term(3, bn[0], b[0]);
+}
+
 // State of a split contraction in device memory. plain: set before it where no scale can be
 // chosen (an infinity or NaN in a sampled row or in R); bad: set by it where a scaled value left
 // its range. Either makes the FP32 kernels after it recompute the result.
@@ -94,6 +115,7 @@ __global__ void __launch_bounds__(256) split_stat_kernel(const float2 *__restric
     int sum = 0, cnt = 0, bad = 0;
     for (int c = 0; c < n_comp; ++c) {
         const float2 *row = B + ((size_t)c * n + e) * n_cols;
+#pragma unroll 4
         for (int i = threadIdx.x; i < total; i += 256) {
             size_t q = i;
             if (n_cols > pieces * len)
@@ -272,8 +294,8 @@ __global__ void __launch_bounds__(256) split_residual_kernel(
 // is a fragment's 8 K values, splits them in registers (about 5 instructions a pair) and writes
 // four 16-byte pieces to LDS. Waves 0-3 and 4-7 stage alternate K steps, so that a wave's loads
 // are in flight for two steps. R's triangle has blocks of 64, a wave's rows: a wave skips the K
-// blocks left of its own, which the FP32 kernel's 256-row blocks multiply as zeros. No operand is written to memory in split form: converting once
-// in a pass of its own would move 31 GB more at 1024 transducers and 636160 nodes, where the
+// blocks left of its own, which the FP32 kernel's 256-row blocks multiply as zeros. No operand is
+// written to memory in split form: converting once in a pass of its own would move 31 GB more at 1024 transducers and 636160 nodes, where the
 // back-projection takes 24.9 ms (1.0 PFLOP/s of MFMAs; the FP32 kernel 128.9 ms) with an error of
 // 3.9e-7 against FP64 sums (5.4e-7).
 __global__ void __launch_bounds__(SR_THREADS) rowred_split_kernel(
@@ -396,19 +418,7 @@ __global__ void __launch_bounds__(SR_THREADS) rowred_split_kernel(
                                 sb + ((wn * 2 + nt) * 4 + pl) * SR_FRAG + lane * 8);
                         bn[0] = -b[2];
                         bn[1] = -b[3];
-                        auto term = [&](int pa, halfx8 br, halfx8 bi) {
-#pragma unroll
-                            for (int mt = 0; mt < 2; ++mt) {
-                                acc_re[mt][nt] = mfma16(a[mt][pa], br, acc_re[mt][nt]);
-                                acc_im[mt][nt] = mfma16(a[mt][pa], bi, acc_im[mt][nt]);
-                            }
-                        };
-                        term(0, b[0], b[2]);   // re_hi (re_hi, im_hi)
-                        term(2, bn[0], b[0]);  // im_hi (-im_hi, re_hi)
-                        term(0, b[1], b[3]);   // re_hi (re_lo, im_lo)
-                        term(2, bn[1], b[1]);
-                        term(1, b[0], b[2]);   // re_lo (re_hi, im_hi)
-                        term(3, bn[0], b[0]);
+                        split_terms(a, b, bn, acc_re, acc_im, nt);
                     }
                 };
                 // one step whose successors are in flight: R' of step i + 1 was fetched a step
@@ -671,26 +681,246 @@ __global__ void __launch_bounds__(256) rowred_kernel(const float2 *__restrict__ 
 }
 
 constexpr int FW_B = 128, FW_BK = 16;
+using rb_fwd::upper_tile;
 
-// Upper-triangular tile index -> (tm, tn) with tm <= tn.
-__device__ __forceinline__ void upper_tile(int idx, int T, int &tm, int &tn) {
-    int r = 0, rem = idx;
-    while (rem >= T - r) {
-        rem -= T - r;
-        ++r;
+// Forward on split operands ------------------------------------------------------------------
+// Mean squares for the scales: of each row's sample (workgroups 0 .. n - 1; 128 pieces of 64
+// columns spread over the row) and, with weights, of v = w delta (the workgroups from n on, one
+// partial sum each). Here every sum runs along the row, so what counts is a row's rms, which
+// bounds a peak by the root of its length: rows near 2^2 and v near 1 leave 2^14 above them.
+constexpr int FS_PARTS = 64;
+__global__ void __launch_bounds__(256) split_fwd_stat_kernel(const float2 *__restrict__ G, int n,
+                                                             int K, const float2 *__restrict__ w,
+                                                             const float *__restrict__ delta,
+                                                             double *__restrict__ ms,
+                                                             double *__restrict__ vs) {
+    __shared__ double red[4];
+    double v = 0.0;
+    const int e = blockIdx.x;
+    if (e < n) {
+        const int pieces = 128, len = 64, total = min(K, pieces * len);
+        const float2 *row = G + (size_t)e * K;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < total; i += 256) {
+            size_t q = i;
+            if (K > pieces * len)
+                q = (size_t)(i / len) * (size_t)(K - len) / (pieces - 1) + i % len;
+            const float2 x = row[q];
+            v += (double)x.x * x.x + (double)x.y * x.y;
+        }
+        v /= 2.0 * total;
+    } else {
+        for (int k = (e - n) * 256 + threadIdx.x; k < K; k += FS_PARTS * 256) {
+            const double dl = delta[k], a = w[k].x * dl, b = w[k].y * dl;
+            v += a * a + b * b;
+        }
+        v /= (double)K;
     }
-    tm = r;
-    tn = r + rem;
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        v = (red[0] + red[1]) + (red[2] + red[3]);
+        if (e < n) ms[e] = v;
+        else vs[e - n] = v;
+    }
 }
 
-// dpart: [splitk][n][n] complex partial sums (only upper tiles written).
+// Exponent of the scale that brings the root of a mean square into [2^(top-1), 2^top).
+__device__ __forceinline__ int rms_exp(double ms, int top) {
+    int e = 0;
+    if (ms > 0.0) (void)frexp(sqrt(ms), &e);
+    return max(-100, min(100, top - e));
+}
+
+// Scales of the rows (a row whose sample is zero: that of the mean), v = w delta scaled (rounded
+// as a product of FP32 values, then by a power of two), zeros of the rows' maxima, and the head.
+__global__ void __launch_bounds__(256) split_fwd_scale_kernel(
+    int n, int K, const float2 *__restrict__ w, const float *__restrict__ delta,
+    const double *__restrict__ ms, const double *__restrict__ vs, float *__restrict__ tsc,
+    uint32_t *__restrict__ rmax, float2 *__restrict__ v, SplitHead *__restrict__ head) {
+    __shared__ double red[4];
+    double sum = 0.0, vsum = 0.0;
+    for (int i = threadIdx.x; i < n; i += 256) sum += ms[i];
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    sum = ((red[0] + red[1]) + (red[2] + red[3])) / n;
+    if (w)
+        for (int i = 0; i < FS_PARTS; ++i) vsum += vs[i];
+    const bool finite = isfinite(sum) && isfinite(vsum);
+    const int xv = w && finite ? rms_exp(vsum, 0) : 0;
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i == 0) *head = SplitHead{finite ? 0 : 1, 0, xv, 0};
+    if (i < n) {
+        tsc[i] = finite ? ldexpf(1.f, rms_exp(ms[i] > 0.0 ? ms[i] : sum, SPLIT_TOP_G)) : 1.f;
+        rmax[i] = rmax[n + i] = 0;
+    }
+    if (w && i < K) {
+        const float2 wv = w[i];
+        const float dl = delta[i];
+        v[i] = make_float2(ldexpf(wv.x * dl, xv), ldexpf(wv.y * dl, xv));
+    }
+}
+
+// FP32 rows G [n][K] (complex) for rb_fwd::forward_reg_kernel: a stage is 16 K as fragments
+// (re hi, re lo, im hi, im lo); WEIGHTS: the A side is G v. A lane's quarter of a stage is 32
+// consecutive bytes of a row. Bound by the matrix pipes: 512 transducers and 152 053 nodes take
+// 0.65 ms (0.92 PFLOP/s of MFMAs) where the FP32 kernel took 2.41 ms, and the error against FP64
+// sums is 2.6e-7 (3.7e-7), the sum of 16 products being rounded once per MFMA instead of every 2.
+template <bool WEIGHTS>
+struct SplitFwd {
+    static constexpr int BK = 16, Q = 4;
+    const float2 *G, *v;
+    const float *tsc;
+    uint32_t *rmax;  // bits of the rows' largest scaled part: A [n], B [n]
+    const SplitHead *head;
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(8)));
+    struct Raw {
+        f4 a[2][2], b[2][2], w[2];
+    };
+    struct Rows {
+        const float2 *a[2], *b[2];
+        float ta[2], tb[2], ma[2], mb[2];
+    };
+    __device__ bool skip() const { return head->plain; }
+    __device__ void rows(Rows &o, int n, int K, int ra, int rb, int) const {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int ea = min(ra + 64 * u, n - 1), eb = min(rb + 64 * u, n - 1);
+            o.a[u] = G + (size_t)ea * K;
+            o.b[u] = G + (size_t)eb * K;
+            o.ta[u] = tsc[ea];
+            o.tb[u] = tsc[eb];
+            o.ma[u] = o.mb[u] = 0.f;
+        }
+    }
+    // four consecutive values of a row, zero from kend on
+    static __device__ __forceinline__ void get(const float2 *row, int k, int kend, f4 (&x)[2]) {
+        if (k + 4 <= kend) {
+            x[0] = *reinterpret_cast<const f4 *>(row + k);
+            x[1] = *reinterpret_cast<const f4 *>(row + k + 2);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float2 z = k + i < kend ? row[k + i] : make_float2(0.f, 0.f);
+                x[i >> 1][2 * (i & 1)] = z.x;
+                x[i >> 1][2 * (i & 1) + 1] = z.y;
+            }
+        }
+    }
+    __device__ __forceinline__ void load(Raw &x, const Rows &o, int k, int kend) const {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            get(o.a[u], k, kend, x.a[u]);
+            get(o.b[u], k, kend, x.b[u]);
+        }
+        if constexpr (WEIGHTS) get(v, k, kend, x.w);
+    }
+    static __device__ __forceinline__ void put(const f4 (&x)[2], float t, int q, float &m,
+                                               char *dst) {
+        uint32_t w[4][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const float ar = x[i][0] * t, ai = x[i][1] * t, br = x[i][2] * t, bi = x[i][3] * t;
+            m = fmaxf(fmaxf(m, fabsf(ar)), fabsf(ai));
+            m = fmaxf(fmaxf(m, fabsf(br)), fabsf(bi));
+            split2(ar, br, w[0][i], w[1][i]);
+            split2(ai, bi, w[2][i], w[3][i]);
+        }
+        dst += (q >> 1) * rb_fwd::FH + (q & 1) * 8;
+#pragma unroll
+        for (int pl = 0; pl < 4; ++pl)
+            *reinterpret_cast<uint2 *>(dst + pl * rb_fwd::FF) = make_uint2(w[pl][0], w[pl][1]);
+    }
+    __device__ __forceinline__ void put_a(const Raw &x, Rows &o, int u, int q, char *dst) const {
+        if constexpr (WEIGHTS) {
+            f4 y[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int h = 0; h < 4; h += 2) {
+                    const float gx = x.a[u][i][h], gy = x.a[u][i][h + 1];
+                    const float vx = x.w[i][h], vy = x.w[i][h + 1];
+                    y[i][h] = gx * vx - gy * vy;
+                    y[i][h + 1] = gx * vy + gy * vx;
+                }
+            put(y, o.ta[u], q, o.ma[u], dst);
+        } else {
+            put(x.a[u], o.ta[u], q, o.ma[u], dst);
+        }
+    }
+    __device__ __forceinline__ void put_b(const Raw &x, Rows &o, int u, int q, char *dst) const {
+        put(x.b[u], o.tb[u], q, o.mb[u], dst);
+    }
+    __device__ __forceinline__ void multiply(const char *pa, const char *pb,
+                                             floatx16 (&acc_re)[2][2],
+                                             floatx16 (&acc_im)[2][2]) const {
+        halfx8 a[2][4], b[4], bn[2];
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int pl = 0; pl < 4; ++pl)
+                a[mt][pl] = *reinterpret_cast<const halfx8 *>(pa + (mt * 4 + pl) * rb_fwd::FF);
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+#pragma unroll
+            for (int pl = 0; pl < 4; ++pl)
+                b[pl] = *reinterpret_cast<const halfx8 *>(pb + (nt * 4 + pl) * rb_fwd::FF);
+            bn[0] = -b[2];
+            bn[1] = -b[3];
+            split_terms(a, b, bn, acc_re, acc_im, nt);
+        }
+    }
+    __device__ void finish(Rows &o, int n, int ra, int rb, int q) const {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            float a = o.ma[u], b = o.mb[u];
+            a = fmaxf(a, __shfl_xor(a, 1));
+            a = fmaxf(a, __shfl_xor(a, 2));
+            b = fmaxf(b, __shfl_xor(b, 1));
+            b = fmaxf(b, __shfl_xor(b, 2));
+            if (q == 0 && ra + 64 * u < n) atomicMax(rmax + ra + 64 * u, __float_as_uint(a));
+            if (q == 1 && rb + 64 * u < n) atomicMax(rmax + n + rb + 64 * u, __float_as_uint(b));
+        }
+    }
+};
+
+// The reduction's look at a split result: not finite, or a row of either side below its range.
+struct SplitCheck {
+    const uint32_t *rmax;
+    SplitHead *head;
+    int n;
+    __device__ bool skip() const { return head->plain; }
+    __device__ float2 unscale(float2 v) const {  // the weights' power of two
+        return make_float2(ldexpf(v.x, -head->rs), ldexpf(v.y, -head->rs));
+    }
+    __device__ void see(int e, int r, float2 v) const {
+        const float a = __uint_as_float(rmax[e]), b = __uint_as_float(rmax[n + r]);
+        if (!isfinite(v.x) || !isfinite(v.y) || (a > 0.f && a < SPLIT_LEAST) ||
+            (b > 0.f && b < SPLIT_LEAST))
+            head->bad = 1;
+    }
+};
+// The reduction after the FP32 kernel: only where that ran.
+struct PlainCheck {
+    const SplitHead *head;
+    __device__ bool skip() const { return !head->plain && !head->bad; }
+    __device__ float2 unscale(float2 v) const { return v; }
+    __device__ void see(int, int, float2) const {}
+};
+
+// The FP32 form, for what the split form turns down. dpart: [splitk][n][n] complex partial sums
+// (only upper tiles written).
 __global__ void __launch_bounds__(256) forward_kernel(const float2 *__restrict__ G,
                                                       const float2 *__restrict__ w,
                                                       const float *__restrict__ delta, int n,
                                                       int K, int T, int kchunk,
+                                                      const SplitHead *__restrict__ head,
                                                       float2 *__restrict__ dpart) {
     __shared__ float a_re[FW_BK][FW_B], a_im[FW_BK][FW_B];
     __shared__ float b_re[FW_BK][FW_B], b_im[FW_BK][FW_B];
+    if (!head->plain && !head->bad) return;
     int tm, tn;
     upper_tile(blockIdx.x, T, tm, tn);
     const int split = blockIdx.y;
@@ -791,23 +1021,6 @@ __global__ void __launch_bounds__(256) forward_kernel(const float2 *__restrict__
         }
 }
 
-// d[e][r] = d[r][e] = sum over splits of the partial at (min(e,r), max(e,r)), which lies in
-// a computed upper tile; both entries come from the same sums, so d is exactly symmetric.
-__global__ void forward_reduce(const float2 *__restrict__ dpart, int n, int splitk,
-                               const float *__restrict__ gscale, float2 *__restrict__ d) {
-    int r = blockIdx.x * blockDim.x + threadIdx.x, e = blockIdx.y;
-    if (r >= n) return;
-    size_t src = (e <= r) ? (size_t)e * n + r : (size_t)r * n + e;
-    float sr = 0.f, si = 0.f;
-    for (int s = 0; s < splitk; ++s) {
-        float2 v = dpart[(size_t)s * n * n + src];
-        sr += v.x;
-        si += v.y;
-    }
-    float inv = gscale ? gscale[1] * gscale[1] : 1.f;  // the operand carried sqrt(v) s
-    d[(size_t)e * n + r] = make_float2(sr * inv, si * inv);
-}
-
 }  // namespace
 
 int rb_rowred_mblocks(int n) { return (n + RR_BM - 1) / RR_BM; }
@@ -870,48 +1083,71 @@ rb_status rb_launch_rowred(rb_ctx *ctx, int n, int n_mask, const float *R, const
     return RB_OK;
 }
 
-// K split of the FP32 forward: the built-in rule, or `want` (a tuned configuration).
-static int forward_splitk(int n, int n_mask, int want, int *kchunk_out) {
-    const int T = (n + FW_B - 1) / FW_B;
-    const int tiles = T * (T + 1) / 2;
-    const int ksteps = (n_mask + FW_BK - 1) / FW_BK;
-    int splitk = want > 0 ? want : (1024 + tiles - 1) / tiles;
-    splitk = want > 0 ? std::max(1, std::min(splitk, ksteps))
-                      : std::max(1, std::min(splitk, std::max(1, ksteps / 4)));
-    const int kchunk = ((ksteps + splitk - 1) / splitk) * FW_BK;
-    if (kchunk_out) *kchunk_out = kchunk;
-    return (n_mask + kchunk - 1) / kchunk;
+int rb_forward_default_splitk(int n, int n_mask, int n_cu) {
+    return rb_fwd::make_shape(n, n_mask, FW_BK, n_cu, 0).splitk;
 }
 
-int rb_forward_default_splitk(int n, int n_mask) { return forward_splitk(n, n_mask, 0, nullptr); }
+// Workspace of the FP32 forward: partial sums, the scaled weights, the rows' mean squares, scales
+// and maxima, the weights' partial sums, the head.
+static size_t forward_bytes(int n, int K, int splitk) {
+    return rb_align((size_t)splitk * n * n * sizeof(float2)) +
+           rb_align((size_t)K * sizeof(float2)) + rb_align((size_t)n * 20 + FS_PARTS * 8) +
+           rb_align(sizeof(SplitHead));
+}
 
 size_t rb_forward_ws_bytes(int n, int n_mask) {
-    const int spk = std::max(rb_forward_default_splitk(n, n_mask),
-                             forward_splitk(n, n_mask, RB_TUNE_SPLITK_MAX, nullptr));
-    return rb_align((size_t)spk * n * n * sizeof(float2));
+    const int T = (n + FW_B - 1) / FW_B;
+    return forward_bytes(n, n_mask,
+                         std::max(RB_TUNE_SPLITK_MAX, rb_fwd::splitk_most(T * (T + 1) / 2)));
 }
 
 rb_status rb_launch_forward(rb_ctx *ctx, const rb_green *gr, const float *w, const float *delta,
                             float *d, const float *gscale) {
     const int n = gr->n, K = gr->n_mask;
-    const int T = (n + FW_B - 1) / FW_B;
-    const int tiles = T * (T + 1) / 2;
     const rb_tuning *t = rb_tuned(ctx, n, K, RB_F32);
-    int kchunk = 0;
-    const int splitk = forward_splitk(n, K, t ? t->fwd_splitk : 0, &kchunk);
+    const rb_fwd::Shape s = rb_fwd::make_shape(n, K, FW_BK, ctx->n_cu, t ? t->fwd_splitk : 0);
     ctx->ws.used = 0;
-    size_t bytes = rb_align((size_t)splitk * n * n * sizeof(float2));
-    rb_status st = rb_arena_reserve(ctx, &ctx->ws, bytes);
-    if (st != RB_OK) return st;
-    float2 *dpart = rb_carve<float2>(&ctx->ws, (size_t)splitk * n * n);
+    RB_TRY(rb_arena_reserve(ctx, &ctx->ws, forward_bytes(n, K, s.splitk)));
+    float2 *dpart = rb_carve<float2>(&ctx->ws, (size_t)s.splitk * n * n);
+    float2 *v = rb_carve<float2>(&ctx->ws, K);
+    double *ms = reinterpret_cast<double *>(rb_carve<char>(&ctx->ws, (size_t)n * 20 + FS_PARTS * 8));
+    double *vs = ms + n;
+    float *tsc = reinterpret_cast<float *>(vs + FS_PARTS);
+    uint32_t *rmax = reinterpret_cast<uint32_t *>(tsc + n);
+    SplitHead *head = rb_carve<SplitHead>(&ctx->ws, 1);
+    const float2 *G = (const float2 *)gr->G, *wp = (const float2 *)w;
     rb_prof_begin(ctx, ST_FORWARD);
-    hipLaunchKernelGGL(forward_kernel, dim3(tiles, splitk), dim3(256), 0, ctx->stream,
-                       (const float2 *)gr->G, (const float2 *)w, delta, n, K, T, kchunk, dpart);
+    hipLaunchKernelGGL(split_fwd_stat_kernel, dim3(n + (w ? FS_PARTS : 0)), dim3(256), 0,
+                       ctx->stream, G, n, K, wp, delta, ms, vs);
+    RB_CHECK_LAUNCH(ctx);
+    const int items = w ? std::max(n, K) : n;
+    hipLaunchKernelGGL(split_fwd_scale_kernel, dim3((items + 255) / 256), dim3(256), 0,
+                       ctx->stream, n, K, wp, delta, ms, vs, tsc, rmax, v, head);
+    RB_CHECK_LAUNCH(ctx);
+    if (w) {
+        const SplitFwd<true> op{G, v, tsc, rmax, head};
+        hipLaunchKernelGGL(rb_fwd::forward_reg_kernel<SplitFwd<true>>, dim3(rb_fwd::grid_of(s)),
+                           dim3(rb_fwd::FTHREADS), 0, ctx->stream, op, s, dpart);
+    } else {
+        const SplitFwd<false> op{G, v, tsc, rmax, head};
+        hipLaunchKernelGGL(rb_fwd::forward_reg_kernel<SplitFwd<false>>, dim3(rb_fwd::grid_of(s)),
+                           dim3(rb_fwd::FTHREADS), 0, ctx->stream, op, s, dpart);
+    }
     RB_CHECK_LAUNCH(ctx);
     rb_prof_end(ctx);
     rb_prof_begin(ctx, ST_FORWARD_REDUCE);
-    hipLaunchKernelGGL(forward_reduce, dim3((n + 255) / 256, n), dim3(256), 0, ctx->stream, dpart,
-                       n, splitk, gscale, (float2 *)d);
+    // the operand may carry sqrt(v) gscale[0]
+    hipLaunchKernelGGL(rb_fwd::reduce_kernel<SplitCheck>, dim3(rb_fwd::reduce_grid(n)), dim3(256),
+                       0, ctx->stream, dpart, n, s.splitk, gscale, 2, tsc,
+                       SplitCheck{rmax, head, n},
+                       (float2 *)d);
+    RB_CHECK_LAUNCH(ctx);
+    hipLaunchKernelGGL(forward_kernel, dim3(s.tiles, s.splitk), dim3(256), 0, ctx->stream, G, wp,
+                       delta, n, K, s.nT, s.kchunk * FW_BK, head, dpart);
+    RB_CHECK_LAUNCH(ctx);
+    hipLaunchKernelGGL(rb_fwd::reduce_kernel<PlainCheck>, dim3(rb_fwd::reduce_grid(n)), dim3(256),
+                       0, ctx->stream, dpart, n, s.splitk, gscale, 2, (const float *)nullptr,
+                       PlainCheck{head}, (float2 *)d);
     RB_CHECK_LAUNCH(ctx);
     rb_prof_end(ctx);
     return RB_OK;

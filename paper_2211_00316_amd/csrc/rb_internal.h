@@ -338,7 +338,7 @@ inline const rb_tuning *rb_tuned(const rb_ctx *ctx, int n, int n_mask, rb_prec p
 rb_status rb_launch_tune_fill(rb_ctx *ctx, const rb_green *gr, float *gscale);
 // Built-in K splits of the forwards (the autotuner's reference candidates).
 int rb_forward_lp_default_splitk(int n, int n_mask, int pipe, int n_cu);
-int rb_forward_default_splitk(int n, int n_mask);
+int rb_forward_default_splitk(int n, int n_mask, int n_cu);
 // scale[0] = 2^(top - e), scale[1] = 1 / scale[0] with 2^(e-1) <= max |x| < 2^e (complex x).
 rb_status rb_launch_range_scale(rb_ctx *ctx, const float *x, size_t count, int top, float *scale);
 int rb_rowred_lp_mblocks(int n);

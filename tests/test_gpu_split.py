@@ -115,3 +115,70 @@ def test_backproject_outside_the_split_range(ctx, case):
             assert rel(dm[part], ref[part]) <= tol(n) * math.sqrt(3)
         assert float(((dm[live].double() - ref[live]).abs() / scale).median()) <= tol(n) * 4
         assert rel(dm[ok], ref[ok]) <= tol(n) * math.sqrt(3)
+
+
+def product(G, v):
+    G = G.to(torch.complex128)
+    return (G * v) @ G.t().contiguous()
+
+
+# tile remainders, one to a few stages of 16 nodes and K chunks with a partial last stage
+@pytest.mark.parametrize("n, nm", [(3, 1), (5, 3), (64, 17), (127, 64), (128, 1000), (129, 4100),
+                                   (200, 333), (257, 9001)])
+@pytest.mark.parametrize("weights", [True, False])
+def test_forward_matches_fp64(ctx, n, nm, weights):
+    from paper_2211_00316_amd import _lib
+
+    g = torch.Generator(device="cuda:0").manual_seed(n * 7 + nm)
+    amp = torch.exp(torch.randn(n, 1, generator=g, device="cuda:0"))
+    G = (randc(g, n, nm) * amp * 0.03).contiguous()
+    w = delta = None
+    v = torch.ones(nm, dtype=torch.complex128, device="cuda:0")
+    if weights:
+        w = randc(g, nm) * 1e4
+        delta = torch.randn(nm, generator=g, device="cuda:0") * 1e-9
+        v = w.to(torch.complex128) * delta.double()
+    d = ctx.born_forward(_lib.Green(G, G, _lib.RB_F32), w, delta)
+    assert torch.equal(d, d.t())
+    # the FP32 products w delta and G v add three roundings
+    assert rel(torch.view_as_real(d), torch.view_as_real(product(G, v))) <= tol(nm) + 6 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("case", ["inf", "spike", "row", "point", "decades", "weight_inf"])
+def test_forward_outside_the_split_range(ctx, case):
+    from paper_2211_00316_amd import _lib
+
+    n, nm = 70, 20000
+    g = torch.Generator(device="cuda:0").manual_seed(6)
+    G = randc(g, n, nm)
+    w = torch.ones(nm, dtype=torch.complex64, device="cuda:0")
+    delta = torch.randn(nm, generator=g, device="cuda:0")
+    bad = torch.zeros(n, n, dtype=torch.bool, device="cuda:0")
+    if case == "inf":
+        G[7, 33] = complex(math.inf, 0.0)
+        bad[7] = bad[:, 7] = True
+    elif case == "spike":          # far past the rms of its row's sample
+        G[11, 4001] = 3e7
+    elif case == "row":            # a row whose sample is zero, and tiny elsewhere
+        keep = G[5, 10001].clone()
+        G[5] = 0
+        G[5, 10001] = keep * 1e-9
+    elif case == "point":          # a single scatterer
+        delta.zero_()
+        delta[777] = 2.5
+    elif case == "decades":        # weights over many decades
+        delta *= torch.exp(-30.0 * torch.rand(nm, generator=g, device="cuda:0"))
+    elif case == "weight_inf":
+        delta[3] = math.inf
+        bad[:] = True
+    d = ctx.born_forward(_lib.Green(G, G, _lib.RB_F32), w, delta)
+    assert not torch.isfinite(torch.view_as_real(d[bad])).all(-1).any()
+    ok = ~bad
+    if ok.any():
+        ref = product(G, w.to(torch.complex128) * delta.double())[ok]
+        x = d[ok]
+        assert torch.isfinite(torch.view_as_real(x)).all()
+        assert rel(torch.view_as_real(x), torch.view_as_real(ref)) <= tol(nm) + 6 * 2.0 ** -24
+        if case == "row":
+            assert rel(torch.view_as_real(d[5]), torch.view_as_real(
+                product(G, w.to(torch.complex128) * delta.double())[5])) <= tol(nm)
