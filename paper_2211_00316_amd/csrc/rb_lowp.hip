@@ -18,6 +18,7 @@
 // The green kernel transposes H through LDS so that both layouts are written coalesced.
 #include "rb_internal.h"
 #include "rb_mfma.h"
+#include "rb_fwd.h"
 
 namespace {
 
@@ -1333,161 +1334,139 @@ __global__ void __launch_bounds__(LR_THREADS) rowred_lp_kernel(const RowGroup gr
 }
 
 // Forward: d[e][r] = sum_q G[e][q] v[q] G[r][q] on 16-bit operands, split-K, upper tiles ----
-constexpr int LF_B = 128, LF_BK = 32, LF_LD = LF_BK + 8;
 
-__device__ __forceinline__ void upper_tile(int idx, int T_, int &tm, int &tn) {
-    int r = 0, rem = idx;
-    while (rem >= T_ - r) {
-        rem -= T_ - r;
-        ++r;
+// v = w delta vscale[0] (FP32 products), zeros past the last node.
+__global__ void __launch_bounds__(256) node_weight_kernel(const float2 *__restrict__ w,
+                                                          const float *__restrict__ delta, int K,
+                                                          int ld,
+                                                          const float *__restrict__ vscale,
+                                                          float2 *__restrict__ v) {
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k >= ld) return;
+    float2 o = make_float2(0.f, 0.f);
+    if (k < K) {
+        const float dl = delta[k] * vscale[0];
+        o = make_float2(w[k].x * dl, w[k].y * dl);
     }
-    tm = r;
-    tn = r + rem;
+    v[k] = o;
 }
 
-template <typename T>
-__global__ void __launch_bounds__(256) forward_lp_kernel(const T *__restrict__ Gp,
-                                                         const float2 *__restrict__ w,
-                                                         const float *__restrict__ delta, int n,
-                                                         int K, int ld, int nT, int kchunk,
-                                                         int splitk,
-                                                         const float *__restrict__ vscale,
-                                                         float2 *__restrict__ dpart) {
-    __shared__ __attribute__((aligned(16))) T a_s[2][LF_B][LF_LD];
-    const float vs = vscale[0];
-    __shared__ __attribute__((aligned(16))) T b_s[2][LF_B][LF_LD];
-    // Workgroups are dealt to the 8 XCDs round-robin. Every tile of one K chunk goes to the
-    // same XCD (chunk s to XCD s mod 8), so the chunk's columns of G come from HBM once and
-    // serve all tiles from that XCD's L2.
-    const int tiles = nT * (nT + 1) / 2;
-    const int kq = blockIdx.x >> 3;
-    const int split = (kq / tiles) * 8 + (blockIdx.x & 7);
-    if (split >= splitk) return;
-    int tm, tn;
-    upper_tile(kq % tiles, nT, tm, tn);
-    const int kbeg = split * kchunk, kend = min(K, kbeg + kchunk);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int row0 = tm * LF_B, col0 = tn * LF_B;
-    const size_t gplane = (size_t)n * ld;
-
-    floatx16 acc_re[2][2], acc_im[2][2];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                acc_re[mt][nt][i] = 0.f;
-                acc_im[mt][nt][i] = 0.f;
-            }
-
-    // each tile: 128 rows x 4 chunks of 8 K = 512 (row, chunk) pairs, 2 per thread
-    const bool kvec = (ld % 8) == 0;
-    for (int k0 = kbeg; k0 < kend; k0 += LF_BK) {
+// 16-bit rows G [2 (re, im)][n][ld] for rb_fwd::forward_reg_kernel: a stage is 32 K as fragments
+// (re, im of its first 16 K, re, im of the others). WEIGHTS: the A side is G v, the complex
+// product in FP32 rounded once to the operand type; else the kernel only copies rows (operands
+// that carry sqrt(v) beyond one buffer descriptor, or a tuned tile). Bound by the matrix pipes and
+// the conversions beside them (about 130 vector instructions for 32 MFMAs of a wave): 1024
+// transducers and 636 160 nodes with weights take 3.9 ms (0.73 PFLOP/s), where a kernel that
+// loaded, converted and multiplied in turn, its weights node by node, took 9.6 ms.
+template <typename T, bool WEIGHTS>
+struct LpFwd {
+    static constexpr int BK = 32, Q = 8;
+    const T *G;
+    const float2 *v;
+    int ld;
+    struct Raw {
+        uint4 are[2], aim[2], bre[2], bim[2];
+        float4 w[4];
+    };
+    struct Rows {
+        const T *a[2], *b[2];
+        size_t plane;
+    };
+    __device__ bool skip() const { return false; }
+    __device__ void rows(Rows &o, int n, int, int ra, int rb, int) const {
+        o.plane = (size_t)n * ld;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            int idx = tid + u * 256;
-            int ch = idx & 3, row = idx >> 2;
-            int gk = k0 + ch * 8;
-            int ge = row0 + row, gr = col0 + row;
-            // v = w delta for the 8 node indices of this chunk (absent: G carries it)
-            float vr[8], vi[8];
-            if (w) {
-#pragma unroll
-                for (int z = 0; z < 8; ++z) {
-                    int k = gk + z;
-                    float2 wv = make_float2(0.f, 0.f);
-                    float dl = 0.f;
-                    if (k < kend) {
-                        wv = w[k];
-                        dl = delta[k] * vs;
-                    }
-                    vr[z] = wv.x * dl;
-                    vi[z] = wv.y * dl;
-                }
-            }
-            // 8 consecutive K of one row of G (both parts), zero beyond the chunk end
-            auto row8 = [&](int grow, T *re, T *im) {
-                if (grow < n && kvec && gk + 7 < kend) {
-                    uint4 a = *reinterpret_cast<const uint4 *>(Gp + (size_t)grow * ld + gk);
-                    uint4 b = *reinterpret_cast<const uint4 *>(Gp + gplane + (size_t)grow * ld + gk);
-                    __builtin_memcpy(re, &a, 16);
-                    __builtin_memcpy(im, &b, 16);
-                } else {
-#pragma unroll
-                    for (int z = 0; z < 8; ++z) {
-                        bool ok = grow < n && gk + z < kend;
-                        re[z] = ok ? Gp[(size_t)grow * ld + gk + z] : to_lp<T>(0.f);
-                        im[z] = ok ? Gp[gplane + (size_t)grow * ld + gk + z] : to_lp<T>(0.f);
-                    }
-                }
-            };
-            T ar[8], ai[8], br[8], bi[8];
-            row8(ge, ar, ai);
-            row8(gr, br, bi);
-            // A = G v, complex product in FP32 rounded once to the operand type
-            if (w) {
-#pragma unroll
-                for (int z = 0; z < 8; ++z) {
-                    float gre = from_lp<T>(ar[z]), gim = from_lp<T>(ai[z]);
-                    ar[z] = to_lp<T>(gre * vr[z] - gim * vi[z]);
-                    ai[z] = to_lp<T>(gre * vi[z] + gim * vr[z]);
-                }
-            }
-            *reinterpret_cast<uint4 *>(&a_s[0][row][ch * 8]) = __builtin_bit_cast(uint4, ar);
-            *reinterpret_cast<uint4 *>(&a_s[1][row][ch * 8]) = __builtin_bit_cast(uint4, ai);
-            *reinterpret_cast<uint4 *>(&b_s[0][row][ch * 8]) = __builtin_bit_cast(uint4, br);
-            *reinterpret_cast<uint4 *>(&b_s[1][row][ch * 8]) = __builtin_bit_cast(uint4, bi);
+            o.a[u] = G + (size_t)min(ra + 64 * u, n - 1) * ld;
+            o.b[u] = G + (size_t)min(rb + 64 * u, n - 1) * ld;
         }
-        __syncthreads();
+    }
+    // eight consecutive values of a row (rows are whole stages long), zero from kend on
+    static __device__ __forceinline__ uint4 get(const T *row, int k, int kend) {
+        uint4 x = *reinterpret_cast<const uint4 *>(row + k);
+        if (k + 8 > kend) {
+            uint32_t *p = reinterpret_cast<uint32_t *>(&x);
 #pragma unroll
-        for (int ks = 0; ks < LF_BK; ks += 16) {
-            int kk = ks + (lane >> 5) * 8;
-            uint4 ar[2], ai[2], nai[2], br[2], bi[2];
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt) {
-                int m = wm * 64 + mt * 32 + (lane & 31);
-                ar[mt] = *reinterpret_cast<const uint4 *>(&a_s[0][m][kk]);
-                ai[mt] = *reinterpret_cast<const uint4 *>(&a_s[1][m][kk]);
-                nai[mt] = neg8(ai[mt]);
+            for (int i = 0; i < 4; ++i) {
+                if (k + 2 * i >= kend) p[i] = 0;
+                else if (k + 2 * i + 1 >= kend) p[i] &= 0xffffu;
             }
+        }
+        return x;
+    }
+    __device__ __forceinline__ void load(Raw &x, const Rows &o, int k, int kend) const {
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                int cn = wn * 64 + nt * 32 + (lane & 31);
-                br[nt] = *reinterpret_cast<const uint4 *>(&b_s[0][cn][kk]);
-                bi[nt] = *reinterpret_cast<const uint4 *>(&b_s[1][cn][kk]);
+        for (int u = 0; u < 2; ++u) {
+            x.are[u] = get(o.a[u], k, kend);
+            x.aim[u] = get(o.a[u] + o.plane, k, kend);
+            x.bre[u] = get(o.b[u], k, kend);
+            x.bim[u] = get(o.b[u] + o.plane, k, kend);
+        }
+        if constexpr (WEIGHTS) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x.w[i] = reinterpret_cast<const float4 *>(v + k)[i];
+        }
+    }
+    static __device__ __forceinline__ void put(uint4 re, uint4 im, int q, char *dst) {
+        dst += (q >> 1) * 2 * rb_fwd::FF + (q & 1) * rb_fwd::FH;
+        *reinterpret_cast<uint4 *>(dst) = re;
+        *reinterpret_cast<uint4 *>(dst + rb_fwd::FF) = im;
+    }
+    __device__ __forceinline__ void put_a(const Raw &x, Rows &, int u, int q, char *dst) const {
+        if constexpr (WEIGHTS) {
+            T re[8], im[8];
+            __builtin_memcpy(re, &x.are[u], 16);
+            __builtin_memcpy(im, &x.aim[u], 16);
+            const float *w = reinterpret_cast<const float *>(x.w);
+#pragma unroll
+            for (int z = 0; z < 8; ++z) {
+                const float gre = from_lp<T>(re[z]), gim = from_lp<T>(im[z]);
+                const float vr = w[2 * z], vi = w[2 * z + 1];
+                re[z] = to_lp<T>(gre * vr - gim * vi);
+                im[z] = to_lp<T>(gre * vi + gim * vr);
             }
+            put(__builtin_bit_cast(uint4, re), __builtin_bit_cast(uint4, im), q, dst);
+        } else {
+            put(x.are[u], x.aim[u], q, dst);
+        }
+    }
+    __device__ __forceinline__ void put_b(const Raw &x, Rows &, int u, int q, char *dst) const {
+        put(x.bre[u], x.bim[u], q, dst);
+    }
+    __device__ __forceinline__ void multiply(const char *pa, const char *pb,
+                                             floatx16 (&acc_re)[2][2],
+                                             floatx16 (&acc_im)[2][2]) const {
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub) {
+            uint4 a[2][2];
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-                for (int nt = 0; nt < 2; ++nt) {
-                    acc_re[mt][nt] =
-                        Lp<T>::mfma(as_vec<T>(ar[mt]), as_vec<T>(br[nt]), acc_re[mt][nt]);
-                    acc_re[mt][nt] =
-                        Lp<T>::mfma(as_vec<T>(nai[mt]), as_vec<T>(bi[nt]), acc_re[mt][nt]);
-                    acc_im[mt][nt] =
-                        Lp<T>::mfma(as_vec<T>(ar[mt]), as_vec<T>(bi[nt]), acc_im[mt][nt]);
-                    acc_im[mt][nt] =
-                        Lp<T>::mfma(as_vec<T>(ai[mt]), as_vec<T>(br[nt]), acc_im[mt][nt]);
-                }
-        }
-        __syncthreads();
-    }
-    float2 *out = dpart + (size_t)split * n * n;
+                for (int p = 0; p < 2; ++p)
+                    a[mt][p] = *reinterpret_cast<const uint4 *>(pa + (mt * 4 + sub * 2 + p) *
+                                                                         rb_fwd::FF);
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+            for (int nt = 0; nt < 2; ++nt) {
+                const char *b = pb + (nt * 4 + sub * 2) * rb_fwd::FF;
+                const uint4 br = *reinterpret_cast<const uint4 *>(b);
+                const uint4 bi = *reinterpret_cast<const uint4 *>(b + rb_fwd::FF);
+                const uint4 bn = neg8(bi);
+                auto term = [&](int p, uint4 x, uint4 y) {
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            int gc = col0 + wn * 64 + nt * 32 + (lane & 31);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                int gr = row0 + wm * 64 + mt * 32 + mfma_row(lane, i);
-                if (gr < n && gc < n)
-                    out[(size_t)gr * n + gc] = make_float2(acc_re[mt][nt][i], acc_im[mt][nt][i]);
+                    for (int mt = 0; mt < 2; ++mt) {
+                        acc_re[mt][nt] = Lp<T>::mfma(as_vec<T>(a[mt][p]), as_vec<T>(x),
+                                                     acc_re[mt][nt]);
+                        acc_im[mt][nt] = Lp<T>::mfma(as_vec<T>(a[mt][p]), as_vec<T>(y),
+                                                     acc_im[mt][nt]);
+                    }
+                };
+                term(0, br, bi);
+                term(1, bn, br);
             }
         }
-}
+    }
+    __device__ void finish(Rows &, int, int, int, int) const {}
+};
 
 // Forward on operands that already carry sqrt(v): d[e][r] = sum_q G[e][q] G[r][q], on the
 // pipelined K loop of the back-projection. Tiles LR_BM (e) x LR_BN (r) cover the upper
@@ -1562,23 +1541,6 @@ __global__ void __launch_bounds__(LR_THREADS) forward_pipe_kernel(const FwdGroup
                     out[(size_t)gr * n + gc] = make_float2(acc_re[mt][nt][i], acc_im[mt][nt][i]);
             }
     }
-}
-
-__global__ void forward_reduce_lp(const float2 *__restrict__ dpart, int n, int splitk,
-                                  const float *__restrict__ vscale,
-                                  const float *__restrict__ rows, float2 *__restrict__ d) {
-    int r = blockIdx.x * blockDim.x + threadIdx.x, e = blockIdx.y;
-    if (r >= n) return;
-    size_t src = (e <= r) ? (size_t)e * n + r : (size_t)r * n + e;
-    float sr = 0.f, si = 0.f;
-    for (int s = 0; s < splitk; ++s) {
-        float2 v = dpart[(size_t)s * n * n + src];
-        sr += v.x;
-        si += v.y;
-    }
-    // the rows of G carry the per-transducer scales (powers of two: exact)
-    float inv = vscale[1] / (rows[e] * rows[r]);
-    d[(size_t)e * n + r] = make_float2(sr * inv, si * inv);
 }
 
 // Seeded operand of the autotuner: magnitude in [0.5, 1), sign and phase from a hash of the
@@ -1874,25 +1836,17 @@ struct FwdShape {
     unsigned nblk;
 };
 
-// Tiles and K split of the 16-bit forward for n transducers over K nodes (rows ld long).
-// pipe: the pipelined kernel (256 x 128 upper tiles); else the 128 x 128 kernel. splitk > 0
-// overrides the built-in K split (a tuned configuration).
-FwdShape forward_shape(int n, int K, int ld, bool pipe, int n_cu, int splitk = 0) {
+// Tiles and K split of the pipelined forward (256 x 128 upper tiles) of n transducers, rows ld
+// long. splitk > 0 overrides the built-in K split (a tuned configuration).
+FwdShape forward_shape(int n, int ld, int n_cu, int splitk = 0) {
     FwdShape f{};
-    const int ksteps = pipe ? ld / LR_BK : (K + LF_BK - 1) / LF_BK;
+    const int ksteps = ld / LR_BK;
+    f.nT = (n + LR_BN - 1) / LR_BN;
+    f.tiles = 0;
+    for (int tm = 0; tm * (LR_BM / LR_BN) < f.nT; ++tm) f.tiles += f.nT - tm * (LR_BM / LR_BN);
     if (splitk > 0) {
-        f.nT = pipe ? (n + LR_BN - 1) / LR_BN : (n + LF_B - 1) / LF_B;
-        f.tiles = 0;
-        if (pipe)
-            for (int tm = 0; tm * (LR_BM / LR_BN) < f.nT; ++tm)
-                f.tiles += f.nT - tm * (LR_BM / LR_BN);
-        else
-            f.tiles = f.nT * (f.nT + 1) / 2;
-        f.splitk = std::max(1, std::min(splitk, ksteps));
-    } else if (pipe) {
-        f.nT = (n + LR_BN - 1) / LR_BN;
-        f.tiles = 0;
-        for (int tm = 0; tm * (LR_BM / LR_BN) < f.nT; ++tm) f.tiles += f.nT - tm * (LR_BM / LR_BN);
+        f.splitk = splitk;
+    } else {
         // K chunks in multiples of 8 (one XCD per chunk group): the fewest that fill the
         // device at least 1.5 times over with at most 7 % of the last round idle
         const int cu = std::max(8, n_cu);
@@ -1903,14 +1857,8 @@ FwdShape forward_shape(int n, int K, int ld, bool pipe, int n_cu, int splitk = 0
             if (ksteps / s8 < 8) break;
             if (2 * blocks >= 3L * cu && (double)blocks / (double)(rounds * cu) >= 0.93) break;
         }
-        f.splitk = std::max(1, std::min(f.splitk, ksteps));
-    } else {
-        f.nT = (n + LF_B - 1) / LF_B;
-        f.tiles = f.nT * (f.nT + 1) / 2;
-        f.splitk = (1024 + f.tiles - 1) / f.tiles;
-        f.splitk = std::max(1, std::min(f.splitk, std::max(1, ksteps / 4)));
-        f.splitk = (f.splitk + 7) / 8 * 8;  // K chunks spread evenly over the 8 XCDs
     }
+    f.splitk = std::max(1, std::min(f.splitk, ksteps));
     f.kchunk = (ksteps + f.splitk - 1) / f.splitk;
     f.splitk = (ksteps + f.kchunk - 1) / f.kchunk;
     f.nblk = (unsigned)(f.tiles * ((f.splitk + 7) / 8) * 8);
@@ -1923,15 +1871,21 @@ bool forward_pipe_fits(int n, int n_mask) {
 }  // namespace
 
 int rb_forward_lp_default_splitk(int n, int n_mask, int pipe, int n_cu) {
-    return forward_shape(n, n_mask, rb_lp_pad(n_mask), pipe && forward_pipe_fits(n, n_mask),
-                         n_cu).splitk;
+    if (pipe && forward_pipe_fits(n, n_mask)) return forward_shape(n, rb_lp_pad(n_mask), n_cu).splitk;
+    return rb_fwd::make_shape(n, n_mask, 32, n_cu, 0).splitk;
+}
+
+// Workspace of a forward: partial sums, the sum's scale, the node weights.
+static size_t forward_lp_bytes(int n, int n_mask, int splitk) {
+    return rb_align((size_t)splitk * n * n * sizeof(float2)) + rb_align(8) +
+           rb_align((size_t)rb_lp_pad(n_mask) * sizeof(float2));
 }
 
 size_t rb_forward_lp_ws_bytes(int n, int n_mask, int n_cu) {
     int spk = RB_TUNE_SPLITK_MAX;
     spk = std::max(spk, rb_forward_lp_default_splitk(n, n_mask, 1, n_cu));
     spk = std::max(spk, rb_forward_lp_default_splitk(n, n_mask, 0, n_cu));
-    return rb_align((size_t)spk * n * n * sizeof(float2)) + rb_align(8);
+    return forward_lp_bytes(n, n_mask, spk);
 }
 
 // Tuned configuration of the forward on operands that carry sqrt(v): kernel and K split.
@@ -1949,10 +1903,9 @@ rb_status rb_forward_lp_plan(rb_ctx *ctx, const rb_green *gr, const float *gscal
     const int n = gr->n, K = gr->n_mask, ld = rb_lp_pad(K);
     int spk = 0;
     forward_choice(ctx, gr, &pl->pipe, &spk);
-    const FwdShape f = forward_shape(n, K, ld, pl->pipe, ctx->n_cu, spk);
+    const FwdShape f = forward_shape(n, ld, ctx->n_cu, spk);
     ctx->ws.used = 0;
-    RB_TRY(rb_arena_reserve(
-        ctx, &ctx->ws, rb_align((size_t)f.splitk * n * n * sizeof(float2)) + rb_align(8)));
+    RB_TRY(rb_arena_reserve(ctx, &ctx->ws, forward_lp_bytes(n, K, f.splitk)));
     pl->gr = *gr;
     pl->gscale = gscale;
     pl->n = n;
@@ -2011,9 +1964,10 @@ rb_status rb_launch_forward_lp_group(rb_ctx *ctx, rb_prec prec, const rb_fwd_pla
 
 rb_status rb_forward_lp_reduce(rb_ctx *ctx, const rb_fwd_plan *pl, float *d) {
     rb_prof_begin(ctx, ST_FORWARD_REDUCE);
-    hipLaunchKernelGGL(forward_reduce_lp, dim3((pl->n + 255) / 256, pl->n), dim3(256), 0,
-                       ctx->stream, pl->dpart, pl->n, pl->splitk, pl->vscale, pl->gr.scales,
-                       (float2 *)d);
+    // the rows of G carry the per-transducer scales (powers of two: exact)
+    hipLaunchKernelGGL(rb_fwd::reduce_kernel<rb_fwd::NoCheck>, dim3(rb_fwd::reduce_grid(pl->n)),
+                       dim3(256), 0, ctx->stream, pl->dpart, pl->n, pl->splitk, pl->vscale, 1,
+                       pl->gr.scales, rb_fwd::NoCheck{}, (float2 *)d);
     RB_CHECK_LAUNCH(ctx);
     rb_prof_end(ctx);
     return RB_OK;
@@ -2034,34 +1988,40 @@ rb_status rb_launch_forward_lp(rb_ctx *ctx, const rb_green *gr, const float *w,
         RB_TRY(rb_launch_forward_lp_group(ctx, gr->prec, &pl, 1));
         return rb_forward_lp_reduce(ctx, &pl, d);
     }
-    const FwdShape f = forward_shape(n, K, ld, false, ctx->n_cu, spk);
+    const rb_fwd::Shape f = rb_fwd::make_shape(n, K, 32, ctx->n_cu, spk);
     ctx->ws.used = 0;
-    RB_TRY(rb_arena_reserve(
-        ctx, &ctx->ws, rb_align((size_t)f.splitk * n * n * sizeof(float2)) + rb_align(8)));
+    RB_TRY(rb_arena_reserve(ctx, &ctx->ws, forward_lp_bytes(n, K, f.splitk)));
     rb_fwd_plan pl;
     pl.gr = *gr;
     pl.n = n;
     pl.splitk = f.splitk;
     pl.dpart = rb_carve<float2>(&ctx->ws, (size_t)f.splitk * n * n);
     pl.vscale = rb_carve<float>(&ctx->ws, 2);
+    float2 *v = rb_carve<float2>(&ctx->ws, ld);
     rb_prof_begin(ctx, ST_FORWARD);
     if (w) {
         // range scale of v = w delta (the node weights are folded into the A operand): the
         // parts of v below 1, so that |G v| < 2^15 with G's rows scaled below 2^14 per part
         RB_TRY(launch_range_scale(ctx, (const float2 *)w, (size_t)K, delta, 0, pl.vscale));
+        hipLaunchKernelGGL(node_weight_kernel, dim3((ld + 255) / 256), dim3(256), 0, ctx->stream,
+                           (const float2 *)w, delta, K, ld, pl.vscale, v);
+        RB_CHECK_LAUNCH(ctx);
     } else {
         hipLaunchKernelGGL(square_scale_kernel, dim3(1), dim3(1), 0, ctx->stream, gscale,
                            pl.vscale);
         RB_CHECK_LAUNCH(ctx);
     }
-    if (gr->prec == RB_BF16)
-        hipLaunchKernelGGL(forward_lp_kernel<__bf16>, dim3(f.nblk), dim3(256), 0, ctx->stream,
-                           (const __bf16 *)gr->G, (const float2 *)w, delta, n, K, ld, f.nT,
-                           f.kchunk * LF_BK, f.splitk, pl.vscale, pl.dpart);
-    else
-        hipLaunchKernelGGL(forward_lp_kernel<_Float16>, dim3(f.nblk), dim3(256), 0, ctx->stream,
-                           (const _Float16 *)gr->G, (const float2 *)w, delta, n, K, ld, f.nT,
-                           f.kchunk * LF_BK, f.splitk, pl.vscale, pl.dpart);
+    auto launch = [&](auto op) {
+        hipLaunchKernelGGL(rb_fwd::forward_reg_kernel<decltype(op)>, dim3(rb_fwd::grid_of(f)),
+                           dim3(rb_fwd::FTHREADS), 0, ctx->stream, op, f, pl.dpart);
+    };
+    if (gr->prec == RB_BF16) {
+        if (w) launch(LpFwd<__bf16, true>{(const __bf16 *)gr->G, v, ld});
+        else launch(LpFwd<__bf16, false>{(const __bf16 *)gr->G, v, ld});
+    } else {
+        if (w) launch(LpFwd<_Float16, true>{(const _Float16 *)gr->G, v, ld});
+        else launch(LpFwd<_Float16, false>{(const _Float16 *)gr->G, v, ld});
+    }
     RB_CHECK_LAUNCH(ctx);
     rb_prof_end(ctx);
     return rb_forward_lp_reduce(ctx, &pl, d);
