@@ -706,15 +706,23 @@ __device__ __forceinline__ bool mesh_walk(const float2 *__restrict__ posE,
                                           float pv, int &j, int &i, uint32_t vb[3], float lam[3],
                                           int &half, int max_it = LOCATE_MAX_IT) {
     for (int it = 0; it < max_it; ++it) {
-        // rays j and j+1 are adjacent in memory: one load per pair (j <= n_rays - 2)
+        // rays j and j+1 are adjacent in memory: one load per pair (j <= n_rays - 2). The
+        // positions are fetched with M (i <= S - 2, so both rows lie in the buffer) and again in
+        // the rare case that i is past the rays' ends.
         const i2u Mv = *reinterpret_cast<const i2u *>(Mrow + j);
+        uint32_t b00 = (uint32_t)(i * n_rays + j), b01 = b00 + (uint32_t)n_rays;
+        f4u q0 = *reinterpret_cast<const f4u *>(posE + b00);
+        f4u q1 = *reinterpret_cast<const f4u *>(posE + b01);
         const int Mj = Mv.x, Mj1 = Mv.y;
         int top = min(Mj, Mj1) - 1;  // last quad index along the rays
         if (Mj < 0 || Mj1 < 0 || top < 1) return false;
-        if (i > top) i = top;
-        const uint32_t b00 = (uint32_t)(i * n_rays + j), b01 = b00 + (uint32_t)n_rays;
-        const f4u q0 = *reinterpret_cast<const f4u *>(posE + b00);
-        const f4u q1 = *reinterpret_cast<const f4u *>(posE + b01);
+        if (i > top) {
+            i = top;
+            b00 = (uint32_t)(i * n_rays + j);
+            b01 = b00 + (uint32_t)n_rays;
+            q0 = *reinterpret_cast<const f4u *>(posE + b00);
+            q1 = *reinterpret_cast<const f4u *>(posE + b01);
+        }
         const float2 p00 = make_float2(q0.x, q0.y), p10 = make_float2(q0.z, q0.w);
         const float2 p01 = make_float2(q1.x, q1.y), p11 = make_float2(q1.z, q1.w);
         const int h = quad_test(p00, p10, p01, p11, pu, pv, lam);
@@ -1021,6 +1029,8 @@ __device__ __forceinline__ void raster_tri(const float *tu, const float *tv,
                                            uint8_t *__restrict__ changed,
                                            const uint8_t *__restrict__ marks, int mtx,
                                            uint32_t tid) {
+    // the vertices' travel times are fetched with the marks, before either is looked at
+    const float tdT[3] = {fld[vb[0]].x, fld[vb[1]].x, fld[vb[2]].x};
     {
         int ti0, ti1, tj0, tj1;
         bbox_tiles(tu, tv, nx, ny, ti0, ti1, tj0, tj1);
@@ -1029,7 +1039,6 @@ __device__ __forceinline__ void raster_tri(const float *tu, const float *tv,
             for (int ti = ti0; ti <= ti1; ++ti) any |= marks[tj * mtx + ti] != 0;
         if (!any) return;
     }
-    const float tdT[3] = {fld[vb[0]].x, fld[vb[1]].x, fld[vb[2]].x};
     float umin = fminf(fminf(tu[0], tu[1]), tu[2]), umax = fmaxf(fmaxf(tu[0], tu[1]), tu[2]);
     float vmin = fminf(fminf(tv[0], tv[1]), tv[2]), vmax = fmaxf(fmaxf(tv[0], tv[1]), tv[2]);
     int i0 = max((int)ceilf(umin - 1e-4f), 0), i1 = min((int)floorf(umax + 1e-4f), nx - 1);
@@ -1039,12 +1048,15 @@ __device__ __forceinline__ void raster_tri(const float *tu, const float *tv,
     // coverage tolerance and the rounding of the barycentric test, so the nodes skipped are
     // nodes the test rejects; long thin triangles of a folding fan cost their rows and the
     // nodes they cover instead of their bounding box.
+    // A box at most two nodes wide is tested whole: its bounds would cost more than its nodes.
     const float m = 0.05f + 1e-4f * ((umax - umin) + (vmax - vmin));
+    const bool narrow = i1 - i0 < 2;
     for (int jj = j0; jj <= j1; ++jj) {
         const float y = (float)jj;
-        float lo = 3.0e38f, hi = -3.0e38f;
+        float lo = narrow ? umin : 3.0e38f, hi = narrow ? umax : -3.0e38f;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
+            if (narrow) break;
             const int k1 = k == 2 ? 0 : k + 1;
             const float ua = tu[k], va = tv[k], ub = tu[k1], vb_ = tv[k1];
             if (fmaxf(va, vb_) < y - m || fminf(va, vb_) > y + m) continue;
@@ -1082,93 +1094,69 @@ __device__ __forceinline__ void raster_tri(const float *tu, const float *tv,
 // The general path runs over the folded transducers of a chunk only: flist[0] = their count,
 // flist[1 ..] = their chunk indices in increasing order. Its kernels are grid-stride loops
 // over that list, so a chunk without folded fans costs one short launch each.
-__global__ void folded_list(const int32_t *__restrict__ folded, int E, int32_t *flist,
-                            unsigned long long *next) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        int c = 0;
-        for (int el = 0; el < E; ++el)
-            if (folded[el]) flist[1 + c++] = el;
-        flist[0] = c;
-        *next = 0ull;  // the smallest-key pass's work counter
+// count: the smallest-key pass's triangle counters (RSHARDS, RSTRIDE words apart), cleared here.
+constexpr int RSHARDS = 64, RSTRIDE = 32;
+__global__ void __launch_bounds__(1024) folded_list(const int32_t *__restrict__ folded, int E,
+                                                    int32_t *flist, uint32_t *count) {
+    __shared__ int wsum[16];
+    int base = 0;
+    for (int e0 = 0; e0 < E; e0 += 1024) {
+        const int el = e0 + (int)threadIdx.x;
+        const bool f = el < E && folded[el] != 0;
+        const unsigned long long m = __ballot(f);
+        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+        if (lane == 0) wsum[w] = __popcll(m);
+        __syncthreads();
+        int before = base, all = 0;
+        for (int k = 0; k < 16; ++k) {
+            if (k < w) before += wsum[k];
+            all += wsum[k];
+        }
+        if (f) flist[1 + before + __popcll(m & ((1ull << lane) - 1ull))] = el;
+        base += all;
+        __syncthreads();
     }
+    if (threadIdx.x == 0) flist[0] = base;
+    if (threadIdx.x < RSHARDS) count[threadIdx.x * RSTRIDE] = 0u;
 }
 
 constexpr int FOLD_GRID = 2048;  // workgroups of the grid-stride kernels
 
-// One item per run of RCH quads along a pair of neighbouring rays (j, j+1; samples i to
-// i + RCH, i >= 1, i + 1 <= min(M_j, M_j+1)). The edge at sample i + 1 of one quad is the
-// edge at sample i of the next, so each step loads one new pair of positions (one 16-byte
-// load: rays j, j+1 are adjacent) and the two travel-time residuals; consecutive items
-// are consecutive ray pairs, so their loads are coalesced.
+// The rasterisation's item is a run of RCH quads along a pair of neighbouring rays (j, j+1;
+// samples i0 to i1, i0 >= 1, i1 <= min(M_j, M_j+1)). A run's positions are loaded at once (one
+// 16-byte load per sample: rays j, j+1 are adjacent); consecutive items are consecutive ray
+// pairs, so their loads are coalesced.
 constexpr int RCH = 8;
+struct RasterRun {
+    f4u q[RCH + 1];  // samples i0 .. i1, the last one repeated
+    int i0, i1;      // empty: i0 >= i1
+};
 
-template <bool MARK>
-__device__ __forceinline__ void raster_run(const SampleBufs &sb, int n_rays, int S, int el,
-                                           int c, int j, int nx, int ny, int n_mask,
-                                           const int2 *qrow,
-                                           unsigned long long *__restrict__ keys,
-                                           uint8_t *__restrict__ changed,
-                                           uint8_t *__restrict__ marks, int mtx, int mtiles) {
+__device__ __forceinline__ RasterRun raster_run(const SampleBufs &sb, int n_rays, int S, int el,
+                                                int c, int j) {
+    RasterRun r;
     const i2u Mv = *reinterpret_cast<const i2u *>(sb.M + (size_t)el * n_rays + j);
-    if (Mv.x < 0 || Mv.y < 0) return;
-    const int top = min(Mv.x, Mv.y);  // quads i with i + 1 <= top
-    const int i0 = max(c * RCH, 1), i1 = min(c * RCH + RCH, top);
-    if (i0 >= i1) return;
-    unsigned long long *ek = keys + (size_t)el * n_mask;
-    uint8_t *ec = changed + (size_t)el * n_mask;
-    uint8_t *em = marks + (size_t)el * mtiles;
-    if (!MARK) {
-        // The run's bounding box holds every triangle's: if its tiles hold no mark, no
-        // triangle of the run touches a marked tile and each would return at its own test.
-        float umin = 3.0e38f, umax = -3.0e38f, vmin = 3.0e38f, vmax = -3.0e38f;
-        size_t bb = ((size_t)el * S + i0) * n_rays + j;
-        for (int i = i0; i <= i1; ++i, bb += n_rays) {
-            const f4u q = *reinterpret_cast<const f4u *>(sb.pos + bb);
-            umin = fminf(umin, fminf(q.x, q.z));
-            umax = fmaxf(umax, fmaxf(q.x, q.z));
-            vmin = fminf(vmin, fminf(q.y, q.w));
-            vmax = fmaxf(vmax, fmaxf(q.y, q.w));
-        }
-        const float bu[3] = {umin, umax, umax}, bv[3] = {vmin, vmax, vmax};
-        int ti0, ti1, tj0, tj1;
-        bbox_tiles(bu, bv, nx, ny, ti0, ti1, tj0, tj1);
-        bool any = false;
-        for (int tj = tj0; tj <= tj1 && !any; ++tj)
-            for (int ti = ti0; ti <= ti1; ++ti) any |= em[tj * mtx + ti] != 0;
-        if (!any) return;
-    }
-    size_t b = ((size_t)el * S + i0) * n_rays + j;
-    f4u q = *reinterpret_cast<const f4u *>(sb.pos + b);
-    float u0 = q.x, v0 = q.y, u1 = q.z, v1 = q.w;
-    for (int i = i0; i < i1; ++i) {
-        const size_t bp = b;  // row i
-        b += n_rays;          // row i + 1
-        q = *reinterpret_cast<const f4u *>(sb.pos + b);
-        const float u2 = q.z, v2 = q.w, u3 = q.x, v3 = q.y;  // (j+1, i+1), (j, i+1)
-        const uint32_t id0 = (uint32_t)(((size_t)j * S + i) * 2);
-        float tu0[3] = {u0, u1, u2}, tv0[3] = {v0, v1, v2};
-        float tu1[3] = {u0, u2, u3}, tv1[3] = {v0, v2, v3};
-        const size_t vb0[3] = {bp, bp + 1, b + 1}, vb1[3] = {bp, b + 1, b};
-        if (MARK) {
+    const int top = min(Mv.x, Mv.y);  // quads i with i + 1 <= top; -1: no ray
+    r.i0 = max(c * RCH, 1);
+    r.i1 = min(c * RCH + RCH, top);
+    if (r.i0 >= r.i1) return r;
+    const float2 *p = sb.pos + ((size_t)el * S + r.i0) * n_rays + j;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const float *tu = h ? tu1 : tu0, *tv = h ? tv1 : tv0;
-                const float area =
-                    (tu[1] - tu[0]) * (tv[2] - tv[0]) - (tv[1] - tv[0]) * (tu[2] - tu[0]);
-                if (area > AREA_MARK) {
-                    int ti0, ti1, tj0, tj1;
-                    bbox_tiles(tu, tv, nx, ny, ti0, ti1, tj0, tj1);
-                    for (int tj = tj0; tj <= tj1; ++tj)
-                        for (int ti = ti0; ti <= ti1; ++ti) em[tj * mtx + ti] = 1;
-                }
-            }
-        } else {
-            raster_tri(tu0, tv0, sb.fld, vb0, nx, ny, qrow, ek, ec, em, mtx, id0);
-            raster_tri(tu1, tv1, sb.fld, vb1, nx, ny, qrow, ek, ec, em, mtx, id0 + 1);
-        }
-        u0 = u3; v0 = v3;  // (j, i+1)
-        u1 = u2; v1 = v2;  // (j+1, i+1)
-    }
+    for (int k = 0; k <= RCH; ++k)
+        r.q[k] = *reinterpret_cast<const f4u *>(p + (size_t)min(k, r.i1 - r.i0) * n_rays);
+    return r;
+}
+
+// Triangle h of the run's quad k: half 0 = (j, i), (j+1, i), (j+1, i+1), half 1 = (j, i),
+// (j+1, i+1), (j, i+1).
+__device__ __forceinline__ void raster_half(const f4u &a, const f4u &b, int h, float (&tu)[3],
+                                            float (&tv)[3]) {
+    tu[0] = a.x;
+    tv[0] = a.y;
+    tu[1] = h ? b.z : a.z;
+    tv[1] = h ? b.w : a.w;
+    tu[2] = h ? b.x : b.z;
+    tv[2] = h ? b.y : b.w;
 }
 
 constexpr int RASTER_ROWS = 4096;  // grid rows of the LDS copy of the mask's row table
@@ -1179,55 +1167,224 @@ inline size_t raster_lds_bytes(int ny) {
     return ny <= RASTER_ROWS ? (size_t)ny * sizeof(int2) : 0;
 }
 
-constexpr int RCHUNK = 1024;  // items a wave of the smallest-key pass takes at a time
+// Marking pass: the tiles that inverted or near-degenerate triangles touch.
+__global__ void __launch_bounds__(256) mark_kernel(SampleBufs sb, int n_rays, int S, int nx,
+                                                   int ny, const int32_t *__restrict__ flist,
+                                                   uint8_t *__restrict__ marks, int mtx,
+                                                   int mtiles) {
+    const uint32_t nq = (uint32_t)n_rays - 1, per = (uint32_t)((S + RCH - 1) / RCH) * nq;
+    const uint32_t blocks = (per + 255) / 256;  // workgroups' worth of items of one fan
+    const size_t total = (size_t)flist[0] * blocks;
+    for (size_t b = blockIdx.x; b < total; b += gridDim.x) {  // uniform over the workgroup
+        const uint32_t f = (uint32_t)(b / blocks);
+        const uint32_t r = (uint32_t)(b - (size_t)f * blocks) * 256 + threadIdx.x;
+        if (r >= per) continue;
+        const int el = flist[1 + f], c = (int)(r / nq), j = (int)(r - (uint32_t)c * nq);
+        const RasterRun run = raster_run(sb, n_rays, S, el, c, j);
+        uint8_t *em = marks + (size_t)el * mtiles;
+#pragma unroll
+        for (int k = 0; k < RCH; ++k) {
+            if (run.i0 + k >= run.i1) break;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                float tu[3], tv[3];
+                raster_half(run.q[k], run.q[k + 1], h, tu, tv);
+                const float area =
+                    (tu[1] - tu[0]) * (tv[2] - tv[0]) - (tv[1] - tv[0]) * (tu[2] - tu[0]);
+                if (area > AREA_MARK) {
+                    int ti0, ti1, tj0, tj1;
+                    bbox_tiles(tu, tv, nx, ny, ti0, ti1, tj0, tj1);
+                    for (int tj = tj0; tj <= tj1; ++tj)
+                        for (int ti = ti0; ti <= ti1; ++ti) em[tj * mtx + ti] = 1;
+                }
+            }
+        }
+    }
+}
 
-template <bool MARK>
-__global__ void __launch_bounds__(256) raster_kernel(SampleBufs sb, int n_rays, int S, int nx,
-                                                     int ny, int n_mask,
+// Smallest-key pass, in two kernels. raster_kernel sorts out the triangles to rasterise: runs
+// whose bounding box touches no marked tile end there (each of their triangles would return at its
+// own test), and of the others' triangles those whose box holds no node (a quad of 0.2 mm steps on
+// a 0.8 mm grid covers a seventh of one), from the positions a lane has in registers. The rest is
+// queued per wave in LDS and appended to one of RSHARDS lists of `cap` triangles in memory; what
+// does not fit is rasterised on the spot. raster_list_kernel then takes one triangle of a list per
+// lane, so that the fans' folds, where every triangle spans many rows of nodes, spread over all
+// waves. Nothing in the first kernel depends on how its runs are dealt out, so waves take segments
+// of 64 in a fixed order: a counter that handed out the work cost an atomic on one address per
+// turn, about 15 ns each, which bound the pass. Both kernels together, against that counter and a
+// lane per run rasterising its triangles in turn: 0.08 against 0.69 ms (64 transducers, 128^2
+// nodes), 1.8 against 2.3 ms (256, 512^2, narrow window), 2.0 against 2.7 ms (1024, 1024^2). The lists' counters lie in lines of their
+// own for the same reason.
+// A queued triangle: x = 2 i + half, y = chunk transducer << 11 | ray.
+struct RasterOut {
+    unsigned long long *keys;
+    uint8_t *changed;
+    const uint8_t *marks;
+    int nx, ny, n_mask, mtx, mtiles;
+};
+__device__ __forceinline__ void raster_queued(const SampleBufs &sb, int n_rays, int S,
+                                              const RasterOut &o, const int2 *qrow, uint2 t) {
+    const int i = (int)(t.x >> 1), h = (int)(t.x & 1u);
+    const int el = (int)(t.y >> 11), j = (int)(t.y & 2047u);
+    const size_t b = ((size_t)el * S + i) * n_rays + j;
+    const f4u qa = *reinterpret_cast<const f4u *>(sb.pos + b);
+    const f4u qb = *reinterpret_cast<const f4u *>(sb.pos + b + n_rays);
+    float tu[3], tv[3];
+    raster_half(qa, qb, h, tu, tv);
+    const size_t vb[3] = {b, h ? b + n_rays + 1 : b + 1, h ? b + n_rays : b + n_rays + 1};
+    raster_tri(tu, tv, sb.fld, vb, o.nx, o.ny, qrow, o.keys + (size_t)el * o.n_mask,
+               o.changed + (size_t)el * o.n_mask, o.marks + (size_t)el * o.mtiles, o.mtx,
+               (uint32_t)(((size_t)j * S + i) * 2) + (uint32_t)h);
+}
+
+// The mask's row table in LDS where it fits (raster_lds_bytes), for the whole workgroup.
+__device__ __forceinline__ const int2 *raster_rows(const int2 *qrow_g, int2 *s_qrow, int ny) {
+    if (ny > RASTER_ROWS) return qrow_g;
+    for (int r = threadIdx.x; r < ny; r += blockDim.x) s_qrow[r] = qrow_g[r];
+    __syncthreads();
+    return s_qrow;
+}
+
+__global__ void __launch_bounds__(256) raster_list_kernel(SampleBufs sb, int n_rays, int S,
+                                                          const int2 *__restrict__ qrow_g,
+                                                          RasterOut o,
+                                                          const uint2 *__restrict__ list,
+                                                          uint32_t cap,
+                                                          const uint32_t *__restrict__ count) {
+    extern __shared__ int2 s_qrow[];
+    // workgroups of a shard: blockIdx.x / RSHARDS of gridDim.x / RSHARDS. Appends that did not
+    // fit have advanced the counter past the last entry written.
+    const uint32_t shard = blockIdx.x % RSHARDS, first = blockIdx.x / RSHARDS * 256;
+    const uint32_t total = min(count[shard * RSTRIDE], cap);
+    if (first >= total) return;  // the whole workgroup
+    const int2 *qrow = raster_rows(qrow_g, s_qrow, o.ny);
+    list += (size_t)shard * cap;
+    for (uint32_t t = first + threadIdx.x; t < total; t += gridDim.x / RSHARDS * 256) {
+        const uint2 e = list[t];
+        if (e.y != ~0u) raster_queued(sb, n_rays, S, o, qrow, e);
+    }
+}
+
+constexpr int RFLUSH = 256;        // triangles a wave appends at a time
+constexpr int RQ = RFLUSH + 64;    // its queue: fewer than RFLUSH left over, at most 64 more
+__global__ void __launch_bounds__(256) raster_kernel(SampleBufs sb, int n_rays, int S,
                                                      const int2 *__restrict__ qrow_g,
                                                      const int32_t *__restrict__ flist,
-                                                     unsigned long long *__restrict__ keys,
-                                                     uint8_t *__restrict__ changed,
-                                                     uint8_t *__restrict__ marks, int mtx,
-                                                     int mtiles, unsigned long long *next) {
-    extern __shared__ int2 s_qrow[];  // raster_lds_bytes(ny) in the smallest-key pass
-    const int2 *qrow = qrow_g;
-    if (!MARK && ny <= RASTER_ROWS) {
-        for (int r = threadIdx.x; r < ny; r += blockDim.x) s_qrow[r] = qrow_g[r];
-        __syncthreads();
-        qrow = s_qrow;
-    }
-    const size_t nq = (size_t)n_rays - 1, nc = (size_t)(S + RCH - 1) / RCH, per = nc * nq;
-    const size_t total = (size_t)flist[0] * per;
-    auto item = [&](size_t t) {
-        const int f = (int)(t / per);
-        const size_t rest = t - (size_t)f * per;
-        const int c = (int)(rest / nq), j = (int)(rest - (size_t)c * nq);
-        raster_run<MARK>(sb, n_rays, S, flist[1 + f], c, j, nx, ny, n_mask, qrow, keys, changed,
-                         marks, mtx, mtiles);
-    };
-    if (MARK) {
-        for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-             t += (size_t)gridDim.x * blockDim.x)
-            item(t);
-        return;
-    }
-    // Runs differ widely in cost (those near marked tiles rasterise, the others return after
-    // their bounding-box test), so each wave takes RCHUNK consecutive items at a time from a
-    // counter (zeroed by folded_list) instead of a fixed share; every wave leaves once the
-    // counter has passed the last item.
-    if (total == 0) return;  // no folded fan: not even one atomic per wave
+                                                     RasterOut o, uint2 *__restrict__ list,
+                                                     uint32_t cap, uint32_t *__restrict__ count) {
+    extern __shared__ int2 s_qrow[];  // raster_lds_bytes(ny)
+    __shared__ uint2 s_queue[4][RQ];
+    const int nx = o.nx, ny = o.ny, mtx = o.mtx;
+    const uint32_t nq = (uint32_t)n_rays - 1, per = (uint32_t)((S + RCH - 1) / RCH) * nq;
+    const int nf = flist[0];
+    if (nf == 0) return;  // no folded fan
+    const int2 *qrow = raster_rows(qrow_g, s_qrow, ny);
     const int lane = threadIdx.x & 63;
-    for (;;) {
-        unsigned long long base = 0;
-        if (lane == 0) base = atomicAdd(next, (unsigned long long)RCHUNK);
-        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
-        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
-        const size_t b0 = ((size_t)hi << 32) | lo;
-        if (b0 >= total) break;
-        const size_t b1 = min(b0 + (size_t)RCHUNK, total);
-        for (size_t t = b0 + lane; t < b1; t += 64) item(t);
+    uint2 *queue = s_queue[threadIdx.x >> 6];
+    const uint32_t shard = blockIdx.x % RSHARDS;
+    list += (size_t)shard * cap;
+    count += shard * RSTRIDE;
+    int cnt = 0;  // queued triangles (uniform)
+    // append the first n queued triangles to the list, or rasterise them here if it is full
+    auto flush = [&](int n) {
+        uint32_t at = 0;
+        if (lane == 0) {
+            at = *reinterpret_cast<volatile const uint32_t *>(count);  // a full list stays full
+            if (at < cap) at = atomicAdd(count, (uint32_t)n);
+        }
+        at = __builtin_amdgcn_readfirstlane(at);
+        const bool fits = at + (uint32_t)n <= cap;
+        for (int k = lane; k < n; k += 64) {
+            const uint2 t = queue[k];
+            if (fits) {
+                list[at + k] = t;
+            } else {
+                if (at + k < cap) list[at + k] = make_uint2(0u, ~0u);  // an entry of nobody
+                raster_queued(sb, n_rays, S, o, qrow, t);
+            }
+        }
+    };
+    // segments of 64 runs of one fan: segs per fan, `stride` segments on from one to the next
+    const uint32_t segs = (per + 63) / 64;
+    const uint32_t wave = blockIdx.x * 4 + (threadIdx.x >> 6), stride = gridDim.x * 4;
+    const uint32_t df = stride / segs, ds = stride - df * segs;
+    uint32_t f = __builtin_amdgcn_readfirstlane(wave / segs);
+    uint32_t sg = __builtin_amdgcn_readfirstlane(wave) - f * segs;
+    for (; f < (uint32_t)nf; f += df, sg += ds) {
+        if (sg >= segs) {
+            sg -= segs;
+            if (++f >= (uint32_t)nf) break;
+        }
+        {
+            const uint32_t r = sg * 64 + (uint32_t)lane;
+            const bool live = r < per;
+            RasterRun run;
+            run.i0 = 1;
+            run.i1 = 0;
+            int el = 0, j = 0;
+            bool any = false;
+            if (live) {
+                const uint32_t c = r / nq;
+                el = flist[1 + f];
+                j = (int)(r - c * nq);
+                run = raster_run(sb, n_rays, S, el, (int)c, j);
+                if (run.i0 < run.i1) {
+                    float umin = 3.0e38f, umax = -3.0e38f, vmin = 3.0e38f, vmax = -3.0e38f;
+#pragma unroll
+                    for (int k = 0; k <= RCH; ++k) {
+                        umin = fminf(umin, fminf(run.q[k].x, run.q[k].z));
+                        umax = fmaxf(umax, fmaxf(run.q[k].x, run.q[k].z));
+                        vmin = fminf(vmin, fminf(run.q[k].y, run.q[k].w));
+                        vmax = fmaxf(vmax, fmaxf(run.q[k].y, run.q[k].w));
+                    }
+                    const float bu[3] = {umin, umax, umax}, bv[3] = {vmin, vmax, vmax};
+                    int ti0, ti1, tj0, tj1;
+                    bbox_tiles(bu, bv, nx, ny, ti0, ti1, tj0, tj1);
+                    const uint8_t *em = o.marks + (size_t)el * o.mtiles;
+                    for (int tj = tj0; tj <= tj1 && !any; ++tj)
+                        for (int ti = ti0; ti <= ti1; ++ti) any |= em[tj * mtx + ti] != 0;
+                }
+            }
+            if (!__any(any)) continue;
+#pragma unroll
+            for (int k = 0; k < RCH; ++k) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    float tu[3], tv[3];
+                    raster_half(run.q[k], run.q[k + 1], h, tu, tv);
+                    // the box raster_tri tests nodes of (before its clip to the grid)
+                    const float umin = fminf(fminf(tu[0], tu[1]), tu[2]);
+                    const float umax = fmaxf(fmaxf(tu[0], tu[1]), tu[2]);
+                    const float vmin = fminf(fminf(tv[0], tv[1]), tv[2]);
+                    const float vmax = fmaxf(fmaxf(tv[0], tv[1]), tv[2]);
+                    const bool hold = any && run.i0 + k < run.i1 &&
+                                      ceilf(umin - 1e-4f) <= floorf(umax + 1e-4f) &&
+                                      ceilf(vmin - 1e-4f) <= floorf(vmax + 1e-4f);
+                    const unsigned long long m = __ballot(hold);
+                    if (m == 0) continue;
+                    if (hold) {
+                        const int at = cnt + (int)__builtin_amdgcn_mbcnt_hi(
+                                                 (uint32_t)(m >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                        queue[at] = make_uint2((uint32_t)(2 * (run.i0 + k) + h),
+                                               ((uint32_t)el << 11) | (uint32_t)j);
+                    }
+                    cnt += __popcll(m);
+                    __builtin_amdgcn_wave_barrier();
+                    if (cnt >= RFLUSH) {
+                        flush(RFLUSH);
+                        cnt -= RFLUSH;
+                        // the rest moves to the front
+                        const uint2 t = queue[RFLUSH + lane];
+                        __builtin_amdgcn_wave_barrier();
+                        queue[lane] = t;
+                        __builtin_amdgcn_wave_barrier();
+                    }
+                }
+            }
+        }
     }
+    if (cnt > 0) flush(cnt);
 }
 
 // General path: per (folded transducer, mask node) whose walk result the rasterisation
@@ -1695,6 +1852,12 @@ static size_t mtiles_of(const rb_grid *g) {
 }
 
 // Workspace of one tracer launch of C emitters (`tiles` walk tiles over the mask).
+// Triangles a list of the smallest-key pass holds: all RSHARDS together an eighth of the samples,
+// at most 2^24 (128 MB). A fuller list only means that the rest is rasterised where it is found.
+static size_t raster_cap(size_t plane) {
+    return std::min(plane / 8, (size_t)1 << 24) / RSHARDS;
+}
+
 static size_t trace_bytes(const rb_grid *g, const rb_ring *r, const rb_trace_params *tp,
                           int64_t n_mask, int C, size_t tiles) {
     const size_t nr = tp->n_rays, S = (size_t)tp->max_steps + 1;
@@ -1703,7 +1866,8 @@ static size_t trace_bytes(const rb_grid *g, const rb_ring *r, const rb_trace_par
            rb_align(plane) + 2 * rb_align((size_t)C * nr * sizeof(int32_t)) +
            rb_align((size_t)C * nr * sizeof(double)) +
            2 * rb_align((size_t)C * nr * sizeof(float)) + rb_align((size_t)C * nr) +
-           rb_align((size_t)C * sizeof(int32_t)) + rb_align(((size_t)C + 4) * sizeof(int32_t)) +
+           rb_align((size_t)C * sizeof(int32_t)) + rb_align(((size_t)C + 1) * sizeof(int32_t)) +
+           rb_align(RSHARDS * RSTRIDE * sizeof(uint32_t)) +
            rb_align((size_t)r->n * sizeof(double2)) + rb_align((size_t)r->n * sizeof(float4)) +
            rb_align((size_t)C * tiles * sizeof(int2)) +
            rb_align((size_t)C * n_mask * sizeof(unsigned long long)) +
@@ -1711,7 +1875,8 @@ static size_t trace_bytes(const rb_grid *g, const rb_ring *r, const rb_trace_par
            2 * rb_align((size_t)(g->nx + 2 * MPAD) * (g->ny + 2 * MPAD) * sizeof(float)) +
            rb_align((size_t)(g->nx + 3) * (g->ny + 3) * 4 * sizeof(float4)) +
            rb_align((size_t)C * r->n * sizeof(int32_t)) +
-           rb_align((size_t)C * tiles * LOCATE_WAVES * 2 * sizeof(float));
+           rb_align((size_t)C * tiles * LOCATE_WAVES * 2 * sizeof(float)) +
+           rb_align(RSHARDS * raster_cap(plane) * sizeof(uint2));
 }
 
 size_t rb_trace_ws_bytes(const rb_grid *g, const rb_ring *r, const rb_trace_params *tp,
@@ -1743,8 +1908,8 @@ rb_status rb_launch_trace(rb_ctx *ctx, const rb_grid *g, const rb_ring *r,
     sb.ex_L = rb_carve<float>(&ctx->ws, (size_t)C * nr);
     sb.ex_K = rb_carve<uint8_t>(&ctx->ws, (size_t)C * nr);
     sb.folded = rb_carve<int32_t>(&ctx->ws, (size_t)C);
-    int32_t *flist = rb_carve<int32_t>(&ctx->ws, (size_t)C + 4);  // + the 8-byte counter
-    unsigned long long *rnext = reinterpret_cast<unsigned long long *>(flist + ((C + 2) & ~1));
+    int32_t *flist = rb_carve<int32_t>(&ctx->ws, (size_t)C + 1);
+    uint32_t *rcount = rb_carve<uint32_t>(&ctx->ws, RSHARDS * RSTRIDE);
     double2 *ringpos = rb_carve<double2>(&ctx->ws, (size_t)N);
     float4 *wcon = rb_carve<float4>(&ctx->ws, (size_t)N);
     if (ring_out) ringpos = ring_out;
@@ -1765,6 +1930,7 @@ rb_status rb_launch_trace(rb_ctx *ctx, const rb_grid *g, const rb_ring *r,
     const AbsMap amap{a_w ? apad : nullptr, g->nx, g->ny, nxp};
     int32_t *rx_j = rb_carve<int32_t>(&ctx->ws, (size_t)C * N);
     float4 *coef = rb_carve<float4>(&ctx->ws, (size_t)(g->nx + 3) * (g->ny + 3) * 4);
+    uint2 *rlist = rb_carve<uint2>(&ctx->ws, RSHARDS * raster_cap(plane));
     SplineMap smap{coef, g->nx, g->ny, g->nx + 3, (float)(1.0 / g->dx)};
 
     GridP gp{g->nx, g->ny, g->dx, g->x0, g->y0, 1.0 / g->dx};
@@ -1807,12 +1973,11 @@ rb_status rb_launch_trace(rb_ctx *ctx, const rb_grid *g, const rb_ring *r,
         rb_prof_end(ctx);
         // folded fans: tiles near inverted triangles
         rb_prof_begin(ctx, ST_RASTER);
-        hipLaunchKernelGGL(folded_list, dim3(1), dim3(64), 0, ctx->stream, sb.folded, E, flist,
-                           rnext);
+        hipLaunchKernelGGL(folded_list, dim3(1), dim3(1024), 0, ctx->stream, sb.folded, E, flist,
+                           rcount);
         RB_CHECK_LAUNCH(ctx);
-        hipLaunchKernelGGL(raster_kernel<true>, dim3(FOLD_GRID), dim3(256), 0, ctx->stream, sb,
-                           nr, S, g->nx, g->ny, n_mask, ctx->d_qrow, flist, keys, changed, marks,
-                           mtx, mtiles, rnext);
+        hipLaunchKernelGGL(mark_kernel, dim3(FOLD_GRID), dim3(256), 0, ctx->stream, sb, nr, S,
+                           g->nx, g->ny, flist, marks, mtx, mtiles);
         RB_CHECK_LAUNCH(ctx);
         rb_prof_end(ctx);
         // every fan: walk per (transducer, node); for folded fans also the seed keys
@@ -1851,15 +2016,18 @@ rb_status rb_launch_trace(rb_ctx *ctx, const rb_grid *g, const rb_ring *r,
         // the counter folded_list zeroed
         const size_t rlds = raster_lds_bytes(g->ny);
         int rpc = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&rpc, raster_kernel<false>, 256, rlds) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&rpc, raster_kernel, 256, rlds) !=
                 hipSuccess ||
             rpc < 1) {
             (void)hipGetLastError();  // a failed query is no launch error
             rpc = 4;
         }
-        hipLaunchKernelGGL(raster_kernel<false>, dim3(rpc * ctx->n_cu), dim3(256), rlds,
-                           ctx->stream, sb, nr, S, g->nx, g->ny, n_mask, ctx->d_qrow, flist, keys,
-                           changed, marks, mtx, mtiles, rnext);
+        const RasterOut ro{keys, changed, marks, g->nx, g->ny, n_mask, mtx, mtiles};
+        hipLaunchKernelGGL(raster_kernel, dim3(rpc * ctx->n_cu), dim3(256), rlds, ctx->stream, sb,
+                           nr, S, ctx->d_qrow, flist, ro, rlist, (uint32_t)raster_cap(plane), rcount);
+        RB_CHECK_LAUNCH(ctx);
+        hipLaunchKernelGGL(raster_list_kernel, dim3(RSHARDS * 32), dim3(256), rlds, ctx->stream,
+                           sb, nr, S, ctx->d_qrow, ro, rlist, (uint32_t)raster_cap(plane), rcount);
         RB_CHECK_LAUNCH(ctx);
         hipLaunchKernelGGL(resolve_kernel, dim3(FOLD_GRID), dim3(256), 0, ctx->stream, sb, nr, S,
                            e0, gp, tp->ds, tp->c0, n_mask, ctx->d_mask_index, flist, keys,
