@@ -700,12 +700,23 @@ __device__ __forceinline__ int quad_test(float2 p00, float2 p10, float2 p01, flo
 }
 
 // posE, Mrow: the transducer's samples and last-sample indices (uniform over a workgroup in
-// the walk); vb: the found triangle's vertices as sample offsets from posE.
+// the walk); vb: the found triangle's vertices as sample offsets from posE. CYCLES: give up once
+// the walk returns to a quad it has been at (the next quad depends on the quad alone, so it would
+// go round until max_it); the quad it is compared with is renewed at each power of two steps.
+template <bool CYCLES = false>
 __device__ __forceinline__ bool mesh_walk(const float2 *__restrict__ posE,
                                           const int32_t *__restrict__ Mrow, int n_rays, float pu,
                                           float pv, int &j, int &i, uint32_t vb[3], float lam[3],
                                           int &half, int max_it = LOCATE_MAX_IT) {
+    int js = -1, is = 0;
     for (int it = 0; it < max_it; ++it) {
+        if constexpr (CYCLES) {
+            if (j == js && i == is) return false;
+            if ((it & (it + 1)) == 0) {  // 0, 1, 3, 7, ...
+                js = j;
+                is = i;
+            }
+        }
         // rays j and j+1 are adjacent in memory: one load per pair (j <= n_rays - 2). The
         // positions are fetched with M (i <= S - 2, so both rows lie in the buffer) and again in
         // the rare case that i is past the rays' ends.
@@ -798,7 +809,8 @@ __global__ void __launch_bounds__(256) tile_offset_kernel(SampleBufs sb, int n_r
                                                           int e0, GridP g, double psi0, int N,
                                                           double ds, int tile_i0, int tile_j0,
                                                           int tiles_x, int tiles_y,
-                                                          float dpsi, double ids,
+                                                          float dpsi, double ids, float cxn,
+                                                          float cyn, float rt2,
                                                           int2 *__restrict__ off) {
     const int ntiles = tiles_x * tiles_y;
     const int tid = blockIdx.x * blockDim.x + threadIdx.x;
@@ -821,8 +833,12 @@ __global__ void __launch_bounds__(256) tile_offset_kernel(SampleBufs sb, int n_r
         uint32_t vb[3];
         float lam[3];
         int half;
-        if (d >= 2.0 * ds && mesh_walk(sb.pos + (size_t)el * S * n_rays, sb.M + (size_t)el * n_rays,
-                                       n_rays, (float)cu, (float)cv, j, i, vb, lam, half))
+        // a tile that reaches no mask node (farther from the disc than half its diagonal) needs no
+        // offset: walks to points outside the ring end on the mesh's edge after many quads
+        const float tu = (float)cu - cxn, tv = (float)cv - cyn;
+        if (d >= 2.0 * ds && tu * tu + tv * tv <= rt2 &&
+            mesh_walk<true>(sb.pos + (size_t)el * S * n_rays, sb.M + (size_t)el * n_rays, n_rays,
+                            (float)cu, (float)cv, j, i, vb, lam, half))
             o = make_int2(j - jw, i - iw);
     }
     off[tid] = o;
@@ -1213,8 +1229,8 @@ __global__ void __launch_bounds__(256) mark_kernel(SampleBufs sb, int n_rays, in
 // of 64 in a fixed order: a counter that handed out the work cost an atomic on one address per
 // turn, about 15 ns each, which bound the pass. Both kernels together, against that counter and a
 // lane per run rasterising its triangles in turn: 0.08 against 0.69 ms (64 transducers, 128^2
-// nodes), 1.8 against 2.3 ms (256, 512^2, narrow window), 2.0 against 2.7 ms (1024, 1024^2). The lists' counters lie in lines of their
-// own for the same reason.
+// nodes), 1.8 against 2.3 ms (256, 512^2, narrow window), 2.0 against 2.7 ms (1024, 1024^2). The
+// lists' counters lie in lines of their own for the same reason.
 // A queued triangle: x = 2 i + half, y = chunk transducer << 11 | ray.
 struct RasterOut {
     unsigned long long *keys;
@@ -1983,10 +1999,12 @@ rb_status rb_launch_trace(rb_ctx *ctx, const rb_grid *g, const rb_ring *r,
         // every fan: walk per (transducer, node); for folded fans also the seed keys
         rb_prof_begin(ctx, ST_RESOLVE);
         int ntiles = ctx->tiles_x * ctx->tiles_y;
+        const double rtile = g->mask_radius / g->dx + 0.5 * std::hypot(LTX, LTY) + 1.0;
         hipLaunchKernelGGL(tile_offset_kernel, dim3((E * ntiles + 255) / 256), dim3(256), 0,
                            ctx->stream, sb, nr, S, E, e0, gp, r->psi0, N, tp->ds, ctx->tile_i0,
                            ctx->tile_j0, ctx->tiles_x, ctx->tiles_y, (float)(RB_TWO_PI / N),
-                           1.0 / tp->ds, toff);
+                           1.0 / tp->ds, (float)(-g->x0 / g->dx), (float)(-g->y0 / g->dx),
+                           (float)(rtile * rtile), toff);
         RB_CHECK_LAUNCH(ctx);
         const long G = (long)LOCATE_GROUP_ROWS * ctx->tiles_x;
         const long groups = ((long)E * ntiles + G - 1) / G;
