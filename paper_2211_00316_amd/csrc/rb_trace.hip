@@ -1038,15 +1038,12 @@ __global__ void __launch_bounds__(LOCATE_THREADS, 8) locate_kernel(SampleBufs sb
 // marked changed (its record is then rebuilt by the resolve pass).
 // qrow: per grid row, the mask's run of nodes (first | last << 16) and the mask index of node
 // i of the row minus i (the mask is a disc: one run per row).
-__device__ __forceinline__ void raster_tri(const float *tu, const float *tv,
-                                           const float4 *__restrict__ fld, const size_t *vb,
+__device__ __forceinline__ void raster_tri(const float *tu, const float *tv, const float *tdT,
                                            int nx, int ny, const int2 *qrow,
                                            unsigned long long *__restrict__ keys,
                                            uint8_t *__restrict__ changed,
                                            const uint8_t *__restrict__ marks, int mtx,
                                            uint32_t tid) {
-    // the vertices' travel times are fetched with the marks, before either is looked at
-    const float tdT[3] = {fld[vb[0]].x, fld[vb[1]].x, fld[vb[2]].x};
     {
         int ti0, ti1, tj0, tj1;
         bbox_tiles(tu, tv, nx, ny, ti0, ti1, tj0, tj1);
@@ -1110,7 +1107,7 @@ __device__ __forceinline__ void raster_tri(const float *tu, const float *tv,
 // The general path runs over the folded transducers of a chunk only: flist[0] = their count,
 // flist[1 ..] = their chunk indices in increasing order. Its kernels are grid-stride loops
 // over that list, so a chunk without folded fans costs one short launch each.
-// count: the smallest-key pass's triangle counters (RSHARDS, RSTRIDE words apart), cleared here.
+// count: the smallest-key pass's quad counters (RSHARDS, RSTRIDE words apart), cleared here.
 constexpr int RSHARDS = 64, RSTRIDE = 32;
 __global__ void __launch_bounds__(1024) folded_list(const int32_t *__restrict__ folded, int E,
                                                     int32_t *flist, uint32_t *count) {
@@ -1183,6 +1180,20 @@ inline size_t raster_lds_bytes(int ny) {
     return ny <= RASTER_ROWS ? (size_t)ny * sizeof(int2) : 0;
 }
 
+// Tiles a run's bounding box touches.
+__device__ __forceinline__ void run_tiles(const RasterRun &run, int nx, int ny, int &ti0,
+                                          int &ti1, int &tj0, int &tj1) {
+    float umin = 3.0e38f, umax = -3.0e38f, vmin = 3.0e38f, vmax = -3.0e38f;
+#pragma unroll
+    for (int k = 0; k <= RCH; ++k) {
+        umin = fminf(umin, fminf(run.q[k].x, run.q[k].z));
+        umax = fmaxf(umax, fmaxf(run.q[k].x, run.q[k].z));
+        vmin = fminf(vmin, fminf(run.q[k].y, run.q[k].w));
+        vmax = fmaxf(vmax, fmaxf(run.q[k].y, run.q[k].w));
+    }
+    const float bu[3] = {umin, umax, umax}, bv[3] = {vmin, vmax, vmax};
+    bbox_tiles(bu, bv, nx, ny, ti0, ti1, tj0, tj1);
+}
 // Marking pass: the tiles that inverted or near-degenerate triangles touch.
 __global__ void __launch_bounds__(256) mark_kernel(SampleBufs sb, int n_rays, int S, int nx,
                                                    int ny, const int32_t *__restrict__ flist,
@@ -1218,20 +1229,21 @@ __global__ void __launch_bounds__(256) mark_kernel(SampleBufs sb, int n_rays, in
     }
 }
 
-// Smallest-key pass, in two kernels. raster_kernel sorts out the triangles to rasterise: runs
-// whose bounding box touches no marked tile end there (each of their triangles would return at its
-// own test), and of the others' triangles those whose box holds no node (a quad of 0.2 mm steps on
-// a 0.8 mm grid covers a seventh of one), from the positions a lane has in registers. The rest is
-// queued per wave in LDS and appended to one of RSHARDS lists of `cap` triangles in memory; what
-// does not fit is rasterised on the spot. raster_list_kernel then takes one triangle of a list per
-// lane, so that the fans' folds, where every triangle spans many rows of nodes, spread over all
-// waves. Nothing in the first kernel depends on how its runs are dealt out, so waves take segments
-// of 64 in a fixed order: a counter that handed out the work cost an atomic on one address per
-// turn, about 15 ns each, which bound the pass. Both kernels together, against that counter and a
-// lane per run rasterising its triangles in turn: 0.08 against 0.69 ms (64 transducers, 128^2
-// nodes), 1.8 against 2.3 ms (256, 512^2, narrow window), 2.0 against 2.7 ms (1024, 1024^2). The
-// lists' counters lie in lines of their own for the same reason.
-// A queued triangle: x = 2 i + half, y = chunk transducer << 11 | ray.
+// Smallest-key pass, in two kernels. raster_kernel sorts out the quads to rasterise: runs whose
+// bounding box touches no marked tile end there (each of their triangles would return at its own
+// test), and of the others' quads those whose box holds no node (a quad of 0.2 mm steps on a
+// 0.8 mm grid covers a seventh of one), from the positions a lane has in registers. The rest is
+// queued per wave in LDS and appended to one of RSHARDS lists of `cap` quads in memory; what does
+// not fit is rasterised on the spot. raster_list_kernel then takes one quad of a list per lane, so
+// that the fans' folds, where every triangle spans many rows of nodes, spread over all waves.
+// Nothing in the first kernel depends on how its runs are dealt out, so waves take segments of 64
+// in a fixed order: a counter that handed out the work cost an atomic on one address per turn,
+// about 15 ns each, which bound the pass. Both kernels together, against that counter and a lane
+// per run rasterising its triangles in turn: 0.08 against 0.69 ms (64 transducers, 128^2 nodes),
+// 1.4 against 2.3 ms (256, 512^2, narrow window), 2.0 against 2.7 ms (1024, 1024^2). The lists'
+// counters lie in lines of their own for the same reason. (Writing each run's tiles in the marking pass, 4 bytes a run, to read those
+// instead of the positions here gained nothing: the sorting is bound by its instructions.)
+// A queued quad: x = i, y = chunk transducer << 11 | ray.
 struct RasterOut {
     unsigned long long *keys;
     uint8_t *changed;
@@ -1240,17 +1252,22 @@ struct RasterOut {
 };
 __device__ __forceinline__ void raster_queued(const SampleBufs &sb, int n_rays, int S,
                                               const RasterOut &o, const int2 *qrow, uint2 t) {
-    const int i = (int)(t.x >> 1), h = (int)(t.x & 1u);
-    const int el = (int)(t.y >> 11), j = (int)(t.y & 2047u);
+    const int i = (int)t.x, el = (int)(t.y >> 11), j = (int)(t.y & 2047u);
     const size_t b = ((size_t)el * S + i) * n_rays + j;
     const f4u qa = *reinterpret_cast<const f4u *>(sb.pos + b);
     const f4u qb = *reinterpret_cast<const f4u *>(sb.pos + b + n_rays);
-    float tu[3], tv[3];
-    raster_half(qa, qb, h, tu, tv);
-    const size_t vb[3] = {b, h ? b + n_rays + 1 : b + 1, h ? b + n_rays : b + n_rays + 1};
-    raster_tri(tu, tv, sb.fld, vb, o.nx, o.ny, qrow, o.keys + (size_t)el * o.n_mask,
-               o.changed + (size_t)el * o.n_mask, o.marks + (size_t)el * o.mtiles, o.mtx,
-               (uint32_t)(((size_t)j * S + i) * 2) + (uint32_t)h);
+    const float d00 = sb.fld[b].x, d10 = sb.fld[b + 1].x;
+    const float d01 = sb.fld[b + n_rays].x, d11 = sb.fld[b + n_rays + 1].x;
+    const uint32_t id = (uint32_t)(((size_t)j * S + i) * 2);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        float tu[3], tv[3];
+        raster_half(qa, qb, h, tu, tv);
+        const float tdT[3] = {d00, h ? d11 : d10, h ? d01 : d11};
+        raster_tri(tu, tv, tdT, o.nx, o.ny, qrow, o.keys + (size_t)el * o.n_mask,
+                   o.changed + (size_t)el * o.n_mask, o.marks + (size_t)el * o.mtiles, o.mtx,
+                   id + (uint32_t)h);
+    }
 }
 
 // The mask's row table in LDS where it fits (raster_lds_bytes), for the whole workgroup.
@@ -1281,7 +1298,7 @@ __global__ void __launch_bounds__(256) raster_list_kernel(SampleBufs sb, int n_r
     }
 }
 
-constexpr int RFLUSH = 256;        // triangles a wave appends at a time
+constexpr int RFLUSH = 256;        // quads a wave appends at a time
 constexpr int RQ = RFLUSH + 64;    // its queue: fewer than RFLUSH left over, at most 64 more
 __global__ void __launch_bounds__(256) raster_kernel(SampleBufs sb, int n_rays, int S,
                                                      const int2 *__restrict__ qrow_g,
@@ -1300,8 +1317,8 @@ __global__ void __launch_bounds__(256) raster_kernel(SampleBufs sb, int n_rays, 
     const uint32_t shard = blockIdx.x % RSHARDS;
     list += (size_t)shard * cap;
     count += shard * RSTRIDE;
-    int cnt = 0;  // queued triangles (uniform)
-    // append the first n queued triangles to the list, or rasterise them here if it is full
+    int cnt = 0;  // queued quads (uniform)
+    // append the first n queued quads to the list, or rasterise them here if it is full
     auto flush = [&](int n) {
         uint32_t at = 0;
         if (lane == 0) {
@@ -1345,17 +1362,8 @@ __global__ void __launch_bounds__(256) raster_kernel(SampleBufs sb, int n_rays, 
                 j = (int)(r - c * nq);
                 run = raster_run(sb, n_rays, S, el, (int)c, j);
                 if (run.i0 < run.i1) {
-                    float umin = 3.0e38f, umax = -3.0e38f, vmin = 3.0e38f, vmax = -3.0e38f;
-#pragma unroll
-                    for (int k = 0; k <= RCH; ++k) {
-                        umin = fminf(umin, fminf(run.q[k].x, run.q[k].z));
-                        umax = fmaxf(umax, fmaxf(run.q[k].x, run.q[k].z));
-                        vmin = fminf(vmin, fminf(run.q[k].y, run.q[k].w));
-                        vmax = fmaxf(vmax, fmaxf(run.q[k].y, run.q[k].w));
-                    }
-                    const float bu[3] = {umin, umax, umax}, bv[3] = {vmin, vmax, vmax};
                     int ti0, ti1, tj0, tj1;
-                    bbox_tiles(bu, bv, nx, ny, ti0, ti1, tj0, tj1);
+                    run_tiles(run, nx, ny, ti0, ti1, tj0, tj1);
                     const uint8_t *em = o.marks + (size_t)el * o.mtiles;
                     for (int tj = tj0; tj <= tj1 && !any; ++tj)
                         for (int ti = ti0; ti <= ti1; ++ti) any |= em[tj * mtx + ti] != 0;
@@ -1364,15 +1372,13 @@ __global__ void __launch_bounds__(256) raster_kernel(SampleBufs sb, int n_rays, 
             if (!__any(any)) continue;
 #pragma unroll
             for (int k = 0; k < RCH; ++k) {
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    float tu[3], tv[3];
-                    raster_half(run.q[k], run.q[k + 1], h, tu, tv);
-                    // the box raster_tri tests nodes of (before its clip to the grid)
-                    const float umin = fminf(fminf(tu[0], tu[1]), tu[2]);
-                    const float umax = fmaxf(fmaxf(tu[0], tu[1]), tu[2]);
-                    const float vmin = fminf(fminf(tv[0], tv[1]), tv[2]);
-                    const float vmax = fmaxf(fmaxf(tv[0], tv[1]), tv[2]);
+                {
+                    // the box raster_tri tests nodes of (before its clip to the grid), of both halves
+                    const f4u qa = run.q[k], qb = run.q[k + 1];
+                    const float umin = fminf(fminf(qa.x, qa.z), fminf(qb.x, qb.z));
+                    const float umax = fmaxf(fmaxf(qa.x, qa.z), fmaxf(qb.x, qb.z));
+                    const float vmin = fminf(fminf(qa.y, qa.w), fminf(qb.y, qb.w));
+                    const float vmax = fmaxf(fmaxf(qa.y, qa.w), fmaxf(qb.y, qb.w));
                     const bool hold = any && run.i0 + k < run.i1 &&
                                       ceilf(umin - 1e-4f) <= floorf(umax + 1e-4f) &&
                                       ceilf(vmin - 1e-4f) <= floorf(vmax + 1e-4f);
@@ -1382,7 +1388,7 @@ __global__ void __launch_bounds__(256) raster_kernel(SampleBufs sb, int n_rays, 
                         const int at = cnt + (int)__builtin_amdgcn_mbcnt_hi(
                                                  (uint32_t)(m >> 32),
                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                        queue[at] = make_uint2((uint32_t)(2 * (run.i0 + k) + h),
+                        queue[at] = make_uint2((uint32_t)(run.i0 + k),
                                                ((uint32_t)el << 11) | (uint32_t)j);
                     }
                     cnt += __popcll(m);
@@ -1409,10 +1415,8 @@ __device__ __forceinline__ float resolve_node(const SampleBufs &sb, int n_rays, 
                                              int q, int e0, const GridP &g, double ds, double c0,
                                              int n_mask, const int32_t *__restrict__ mask_index,
                                              const unsigned long long *__restrict__ keys,
-                                             const uint8_t *__restrict__ changed,
                                              const TableOut &to) {
     const size_t tid = (size_t)el * n_mask + q;
-    if (!changed[tid]) return 0.f;
     int e = e0 + el;
     const TableOut toE = table_row(to, (size_t)e * n_mask);
     const uint32_t out = (uint32_t)q;
@@ -1467,21 +1471,65 @@ __global__ void __launch_bounds__(256) resolve_kernel(SampleBufs sb, int n_rays,
                                                       const unsigned long long *__restrict__ keys,
                                                       const uint8_t *__restrict__ changed,
                                                       TableOut to) {
-    // A workgroup takes 256 consecutive nodes of one folded transducer, so the largest A and
-    // 1/A it writes reach the per-row maxima as one atomic pair per wave (the walk's are
-    // folded in by tile_max_fold; max is order-independent).
-    const int per = (n_mask + 255) / 256;
+    // A workgroup takes 2048 consecutive nodes of one folded transducer, eight per lane (their
+    // change marks in one load); each wave queues its changed nodes in LDS and resolves 64 of them
+    // at a time, one per lane. A lane per node spent its time on the marks, 1.6 ms for 1024
+    // transducers of 636160 nodes against 0.5. The largest A and 1/A a wave writes reach the
+    // per-row maxima as one atomic pair (the walk's are folded in by tile_max_fold; max is
+    // order-independent).
+    __shared__ int s_q[4][128];
+    int *queue = s_q[threadIdx.x >> 6];
+    const int lane = threadIdx.x & 63;
+    const int per = (n_mask + 2047) / 2048;
     const size_t total = (size_t)flist[0] * per;
     for (size_t b = blockIdx.x; b < total; b += gridDim.x) {  // uniform over the workgroup
         const int f = (int)(b / per);
         const int el = flist[1 + f];
-        const int q = (int)(b - (size_t)f * per) * 256 + (int)threadIdx.x;
-        float A = 0.f;
-        if (q < n_mask)
-            A = resolve_node(sb, n_rays, S, el, q, e0, g, ds, c0, n_mask, mask_index, keys,
-                             changed, to);
+        const int q0 = ((int)(b - (size_t)f * per) * 256 + (int)threadIdx.x) * 8;
+        const uint8_t *ch = changed + (size_t)el * n_mask + q0;
+        uint32_t set = 0;  // changed nodes, one bit each
+        if (q0 + 8 <= n_mask) {
+            unsigned long long w;
+            __builtin_memcpy(&w, ch, 8);
+            if (w) {  // bytes 0 or 1
+#pragma unroll
+                for (int k = 0; k < 8; ++k) set |= (uint32_t)(w >> (8 * k) & 1ull) << k;
+            }
+        } else {
+            for (int k = 0; q0 + k < n_mask; ++k) set |= (ch[k] != 0 ? 1u : 0u) << k;
+        }
+        float amax = 0.f, iamax = 0.f;
+        int cnt = 0;
+        auto drain = [&](int n) {
+            if (lane >= n) return;
+            const float A = resolve_node(sb, n_rays, S, el, queue[lane], e0, g, ds, c0, n_mask,
+                                         mask_index, keys, to);
+            amax = fmaxf(amax, A);
+            iamax = fmaxf(iamax, A > 0.f ? 1.0f / A : 0.f);
+        };
+        for (int k = 0; k < 8; ++k) {
+            const bool c = set >> k & 1u;
+            const unsigned long long m = __ballot(c);
+            if (m == 0) continue;
+            if (c)
+                queue[cnt + (int)__builtin_amdgcn_mbcnt_hi(
+                                (uint32_t)(m >> 32),
+                                __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = q0 + k;
+            cnt += __popcll(m);
+            __builtin_amdgcn_wave_barrier();
+            if (cnt >= 64) {
+                drain(64);
+                cnt -= 64;
+                const int t = queue[64 + lane];
+                __builtin_amdgcn_wave_barrier();
+                queue[lane] = t;
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        drain(cnt);
+        __builtin_amdgcn_wave_barrier();
         if (to.rowmax) {
-            const float m0 = wave_max(A), m1 = wave_max(A > 0.f ? 1.0f / A : 0.f);
+            const float m0 = wave_max(amax), m1 = wave_max(iamax);
             if ((threadIdx.x & 63) == 0 && m0 > 0.f) {
                 atomicMax(to.rowmax + 2 * (e0 + el), __float_as_uint(m0));
                 atomicMax(to.rowmax + 2 * (e0 + el) + 1, __float_as_uint(m1));
@@ -1868,10 +1916,11 @@ static size_t mtiles_of(const rb_grid *g) {
 }
 
 // Workspace of one tracer launch of C emitters (`tiles` walk tiles over the mask).
-// Triangles a list of the smallest-key pass holds: all RSHARDS together an eighth of the samples,
-// at most 2^24 (128 MB). A fuller list only means that the rest is rasterised where it is found.
+// Quads a list of the smallest-key pass holds: all RSHARDS together an eighth of the samples (a
+// byte per sample, against the 24 of the samples themselves). A fuller list only means that the
+// rest is rasterised where it is found, which is several times slower.
 static size_t raster_cap(size_t plane) {
-    return std::min(plane / 8, (size_t)1 << 24) / RSHARDS;
+    return std::min(plane / 8 / RSHARDS, (size_t)1 << 31);
 }
 
 static size_t trace_bytes(const rb_grid *g, const rb_ring *r, const rb_trace_params *tp,
