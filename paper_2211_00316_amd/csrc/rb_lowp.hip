@@ -58,12 +58,8 @@ __device__ __forceinline__ double reduce_phase(double ph) {
 }
 
 // Green's functions --------------------------------------------------------------------
-// A workgroup covers 64 mask nodes (one per lane) x 64 transducers (16 consecutive ones per
-// wave). A lane keeps the directions and flags of its 16 transducers and their two
-// neighbours in registers, writes G rows coalesced over the nodes, and writes its 16 entries
-// of each transposed H row as two 16-byte stores.
-constexpr int GQ = 64;
-constexpr int GW = 16;       // transducers per wave
+constexpr int GQ = 64;       // mask nodes of an assembly workgroup, one per lane
+constexpr int GW = 16;       // transducers per wave of the plain 16-bit assembly from records
 constexpr int GE = 4 * GW;   // transducers per workgroup
 
 // Bit pattern of a value rounded to the 16-bit type.
@@ -85,20 +81,6 @@ __device__ __forceinline__ uint32_t lp_lo_bits(float x) {
 // Angle between two unit directions.
 __device__ __forceinline__ float angle_between(float ax, float ay, float bx, float by) {
     return fabsf(atan2f(ax * by - ay * bx, ax * bx + ay * by));
-}
-
-// Lanes of the nodes past the last one write G's zero padding (rows are rb_lp_pad(n_mask)
-// long) and nothing else.
-template <typename T>
-__device__ __forceinline__ void green_pad_g(T *Gp, size_t gplane, int Mp, int N, int e0, int q) {
-#pragma unroll
-    for (int r = 0; r < GW; ++r) {
-        const int e = e0 + r;
-        if (e < N) {
-            Gp[(size_t)e * Mp + q] = to_lp<T>(0.f);
-            Gp[gplane + (size_t)e * Mp + q] = to_lp<T>(0.f);
-        }
-    }
 }
 
 // G = A k0^-1/2 e^{i phi} and H = a k0^1/2 A^-1 e^{-i phi}, phi = omega T + pi/4 - K pi/2
@@ -156,147 +138,49 @@ __global__ void __launch_bounds__(256) row_scale_kernel(const unsigned int *__re
     scales[N + e] = sh;
 }
 
-// Largest A and 1/A over the valid entries of each row of the ABI tables (one workgroup per
-// transducer), as the bits rowmax[2e], rowmax[2e+1].
+// Largest A and 1/A over the valid entries of each row of the ABI tables, as the bits rowmax[2e],
+// rowmax[2e+1] (cleared before): workgroups of AMAX_CHUNK nodes of one row, one atomic each. The
+// largest 1/A is that of the smallest A (a correctly rounded quotient is monotone).
+constexpr int AMAX_CHUNK = 16384;
 __global__ void __launch_bounds__(256) row_amax_kernel(rb_tables tb, int n_mask,
                                                        unsigned int *__restrict__ rowmax) {
     __shared__ float red[2][4];
-    const int e = blockIdx.x;
-    float m0 = 0.f, m1 = 0.f;
-    for (int q = threadIdx.x; q < n_mask; q += blockDim.x) {
+    const int e = blockIdx.y;
+    const int q0 = blockIdx.x * AMAX_CHUNK, q1 = min(n_mask, q0 + AMAX_CHUNK);
+    float m0 = 0.f, lo = INFINITY;
+#pragma unroll 4
+    for (int q = q0 + threadIdx.x; q < q1; q += 256) {
         const size_t o = (size_t)e * n_mask + q;
         const float A = tb.A[o];
         if ((tb.flags[o] & 0x80) && A > 0.f) {
             m0 = fmaxf(m0, A);
-            m1 = fmaxf(m1, 1.0f / A);
+            lo = fminf(lo, A);
         }
     }
     for (int o = 32; o > 0; o >>= 1) {
         m0 = fmaxf(m0, __shfl_xor(m0, o));
-        m1 = fmaxf(m1, __shfl_xor(m1, o));
+        lo = fminf(lo, __shfl_xor(lo, o));
     }
     if ((threadIdx.x & 63) == 0) {
         red[0][threadIdx.x >> 6] = m0;
-        red[1][threadIdx.x >> 6] = m1;
+        red[1][threadIdx.x >> 6] = lo;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        rowmax[2 * e] = __float_as_uint(fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3])));
-        rowmax[2 * e + 1] =
-            __float_as_uint(fmaxf(fmaxf(red[1][0], red[1][1]), fmaxf(red[1][2], red[1][3])));
+        m0 = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
+        lo = fminf(fminf(red[1][0], red[1][1]), fminf(red[1][2], red[1][3]));
+        if (m0 > 0.f) {
+            atomicMax(rowmax + 2 * e, __float_as_uint(m0));
+            atomicMax(rowmax + 2 * e + 1, __float_as_uint(1.0f / lo));
+        }
     }
 }
 
-template <typename T, bool SPLIT>
-__global__ void __launch_bounds__(256) green_lp_kernel(rb_tables tb, int N, int n_mask,
-                                                       double omega, double c0,
-                                                       const float2 *__restrict__ gs,
-                                                       const float *__restrict__ gscale,
-                                                       int write_g, T *__restrict__ Gp,
-                                                       T *__restrict__ Ht,
-                                                       const unsigned int *__restrict__ rowmax,
-                                                       float gmax, float *__restrict__ scales,
-                                                       T *__restrict__ Htlo) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int q = blockIdx.x * GQ + lane;
-    const int e0 = blockIdx.y * GE + w * GW;
-    const int Np = rb_lp_pad(N), Mp = rb_lp_pad(n_mask);
-    const size_t gplane = (size_t)N * Mp;
-    if (q >= Mp || e0 >= Np) return;  // no barrier in this kernel
-    if (q >= n_mask) {
-        if (write_g) green_pad_g(Gp, gplane, Mp, N, e0, q);
-        return;
-    }
-    // rows e0 - 1 .. e0 + GW (indices mod N)
-    float ux[GW + 2], uy[GW + 2];
-    uint32_t valid = 0;
-#pragma unroll
-    for (int r = 0; r < GW + 2; ++r) {
-        int e = e0 - 1 + r;
-        e = e < 0 ? e + N : (e >= N ? e - N : e);
-        if (e >= N) e = 0;  // rows past the padding end: never used
-        size_t o = (size_t)e * n_mask + q;
-        valid |= (tb.flags[o] & 0x80) ? (1u << r) : 0u;
-        ux[r] = tb.ux[o];
-        uy[r] = tb.uy[o];
-    }
-    const double k0 = omega / c0;
-    const float sk = (float)sqrt(k0), isk = 1.0f / sk;
-    float2 f2 = make_float2(1.f, 0.f);
-    if (write_g && gs) {
-        f2 = gs[q];
-        float sc = gscale[0];
-        f2.x *= sc;
-        f2.y *= sc;
-    }
-    uint32_t hp[6][GW / 2];  // (c, part) rows, two transducers per dword
-    uint32_t hl[6][GW / 2];  // their low parts (split form)
-#pragma unroll
-    for (int r = 0; r < GW; ++r) {
-        const int e = e0 + r;
-        float gr = 0.f, gi = 0.f, hr = 0.f, hi = 0.f, vx = 0.f, vy = 0.f;
-        if (e < N) {
-            float sg, sh;
-            row_scales(rowmax, e, sk, isk, gmax, sg, sh);
-            if (blockIdx.x == 0 && lane == 0) {
-                scales[e] = sg;
-                scales[N + e] = sh;
-            }
-            size_t o = (size_t)e * n_mask + q;
-            if (valid >> (r + 1) & 1u) {
-                vx = ux[r + 1];
-                vy = uy[r + 1];
-                const bool vm = valid >> r & 1u, vp = valid >> (r + 2) & 1u;
-                float a = 0.f;
-                if (vm && vp) a = 0.5f * angle_between(ux[r], uy[r], ux[r + 2], uy[r + 2]);
-                else if (vp) a = angle_between(vx, vy, ux[r + 2], uy[r + 2]);
-                else if (vm) a = angle_between(ux[r], uy[r], vx, vy);
-                green_entry(omega, tb.T[o], tb.flags[o], tb.A[o], a, sk, isk, gr, gi, hr, hi);
-                gr *= sg;
-                gi *= sg;
-                hr *= sh;
-                hi *= sh;
-            }
-            if (write_g) {
-                const size_t og = (size_t)e * Mp + q;
-                float tr = gr * f2.x - gi * f2.y;
-                gi = gr * f2.y + gi * f2.x;
-                Gp[og] = to_lp<T>(tr);
-                Gp[gplane + og] = to_lp<T>(gi);
-            }
-        }
-        float v[6] = {hr, hi, hr * vx, hi * vx, hr * vy, hi * vy};
-#pragma unroll
-        for (int cp = 0; cp < 6; ++cp) {
-            if (r & 1) hp[cp][r >> 1] |= lp_bits<T>(v[cp]) << 16;
-            else hp[cp][r >> 1] = lp_bits<T>(v[cp]);
-            if constexpr (SPLIT) {
-                if (r & 1) hl[cp][r >> 1] |= lp_lo_bits<T>(v[cp]) << 16;
-                else hl[cp][r >> 1] = lp_lo_bits<T>(v[cp]);
-            }
-        }
-    }
-    // transposed rows (c, part, q), Np long (zeros past N)
-    const size_t hplane = (size_t)n_mask * Np;
-    auto store = [&](const uint32_t (&src)[6][GW / 2], T *base) {
-#pragma unroll
-        for (int cp = 0; cp < 6; ++cp) {
-            T *dst = base + (size_t)cp * hplane + (size_t)q * Np + e0;
-            *reinterpret_cast<uint4 *>(dst) =
-                make_uint4(src[cp][0], src[cp][1], src[cp][2], src[cp][3]);
-            if (e0 + 8 < Np)
-                *reinterpret_cast<uint4 *>(dst + 8) =
-                    make_uint4(src[cp][4], src[cp][5], src[cp][6], src[cp][7]);
-        }
-    };
-    store(hp, Ht);
-    if constexpr (SPLIT) store(hl, Htlo);
-}
-
-// The same assembly from the compact records of a frequency step (rb_launch_trace): one
-// 16-byte load per (transducer, node) gives dT, A, the ray angle theta and the flags;
-// T = dT + d / c0 with d the node's distance from the transducer, and the angle between
-// neighbouring transducers' rays is the wrapped difference of their thetas.
+// The assembly from the compact records of a frequency step (rb_launch_trace): one 16-byte load
+// per (transducer, node) gives dT, A, the ray angle theta and the flags; T = dT + d / c0 with d
+// the node's distance from the transducer, and the angle between neighbouring transducers' rays is
+// the wrapped difference of their thetas. Or (TAB) from the tables of the C ABI, with the ABI's
+// components H, H u_x, H u_y and 16-bit low parts.
 __device__ __forceinline__ float wrap_pi(float x) {
     return x - (float)RB_TWO_PI * rintf(x * (float)(1.0 / RB_TWO_PI));
 }
@@ -315,9 +199,9 @@ __device__ __forceinline__ double dist_newton(double a) {
 // piece written by consecutive threads, 16 bytes each (H in two halves of three planes; one
 // buffer for all, its pitch 8 elements longer than a row so 16-byte lane writes miss no bank).
 
-template <typename T, bool SPLIT, int GWt, int NW>
+template <typename T, bool SPLIT, int GWt, int NW, bool TAB>
 __global__ void __launch_bounds__(64 * NW) green_lp_rec_kernel(
-    const float4 *__restrict__ rec, const int32_t *__restrict__ mask_index,
+    const rb_tables tb, const float4 *__restrict__ rec, const int32_t *__restrict__ mask_index,
     const double2 *__restrict__ ring, double x0, double y0, double dx, int nx, int N, int n_mask,
     double omega, double c0, const float2 *__restrict__ gs, const float *__restrict__ gscale,
     int write_g, T *__restrict__ Gp, T *__restrict__ Ht, const float *__restrict__ scales,
@@ -333,29 +217,46 @@ __global__ void __launch_bounds__(64 * NW) green_lp_rec_kernel(
     const int Np = rb_lp_pad(N), Mp = rb_lp_pad(n_mask);
     const size_t gplane = (size_t)N * Mp;
     const bool node = q < n_mask;
-    float th[GWt + 2], dTr[GWt], Ar[GWt];
+    constexpr int RW = TAB ? 1 : GWt, TW = TAB ? GWt : 1;
+    float th[RW + 2], dTr[RW], Ar[GWt];
+    float ux[TW + 2], uy[TW + 2];
+    double Tr[TW];
     uint32_t valid = 0, Kb = 0;
     double px = 0.0, py = 0.0;
     float2 f2 = make_float2(1.f, 0.f);
     if (node) {
-        const int p = mask_index[q];
-        px = x0 + (p % nx) * dx;
-        py = y0 + (p / nx) * dx;
-        // records of rows e0 - 1 .. e0 + GWt (indices mod N)
+        if constexpr (!TAB) {
+            const int p = mask_index[q];
+            px = x0 + (p % nx) * dx;
+            py = y0 + (p / nx) * dx;
+        }
+        // records (or table entries) of rows e0 - 1 .. e0 + GWt (indices mod N)
 #pragma unroll
         for (int r = 0; r < GWt + 2; ++r) {
             int e = e0 - 1 + r;
             e = e < 0 ? e + N : (e >= N ? e - N : e);
             if (e >= N) e = 0;  // rows past the padding end: never used
-            const float4 v = rec[(size_t)e * n_mask + q];
-            const uint32_t f = __float_as_uint(v.w);
-            valid |= (f & 0x80) ? (1u << r) : 0u;
-            th[r] = v.z;
-            if (r >= 1 && r <= GWt) {
-                dTr[r - 1] = v.x;
-                Ar[r - 1] = v.y;
-                Kb |= (f & 3) << (2 * (r - 1));
+            const size_t o = (size_t)e * n_mask + q;
+            uint32_t f;
+            if constexpr (TAB) {
+                f = tb.flags[o];
+                ux[r] = tb.ux[o];
+                uy[r] = tb.uy[o];
+                if (r >= 1 && r <= GWt) {
+                    Tr[r - 1] = tb.T[o];
+                    Ar[r - 1] = tb.A[o];
+                }
+            } else {
+                const float4 v = rec[o];
+                f = __float_as_uint(v.w);
+                th[r] = v.z;
+                if (r >= 1 && r <= GWt) {
+                    dTr[r - 1] = v.x;
+                    Ar[r - 1] = v.y;
+                }
             }
+            valid |= (f & 0x80) ? (1u << r) : 0u;
+            if (r >= 1 && r <= GWt) Kb |= (f & 3) << (2 * (r - 1));
         }
         if (write_g && gs) {
             f2 = gs[q];
@@ -368,7 +269,8 @@ __global__ void __launch_bounds__(64 * NW) green_lp_rec_kernel(
     const float sk = (float)sqrt(k0), isk = 1.0f / sk;
     T *sg = stage;  // G tile [2][GEt][GQ]
     uint32_t hp[6][GWt / 2];  // (c, part) rows, two transducers per dword
-    uint32_t b8[6][GWt / 4];  // split form: their low parts times 2^6 as FP8, four per dword
+    uint32_t hl[6][GWt / 2];  // split form from tables: their low parts
+    uint32_t b8[6][GWt / 4];  // split form of a step: their low parts times 2^6 as FP8
     float b8p[6];
 #pragma unroll
     for (int cp = 0; cp < 6; ++cp) {
@@ -386,15 +288,25 @@ __global__ void __launch_bounds__(64 * NW) green_lp_rec_kernel(
             rsh = scales[N + e];
         }
         if (node && e < N && (valid >> (r + 1) & 1u)) {
-            __sincosf(th[r + 1], &vy, &vx);
             const bool vm = valid >> r & 1u, vp = valid >> (r + 2) & 1u;
             float a = 0.f;
-            if (vm && vp) a = 0.5f * fabsf(wrap_pi(th[r + 2] - th[r]));
-            else if (vp) a = fabsf(wrap_pi(th[r + 2] - th[r + 1]));
-            else if (vm) a = fabsf(wrap_pi(th[r + 1] - th[r]));
-            const double2 xe = ring[e];
-            const double ddx = px - xe.x, ddy = py - xe.y;
-            const double Tt = (double)dTr[r] + dist_newton(ddx * ddx + ddy * ddy) * ic0;
+            double Tt;
+            if constexpr (TAB) {
+                vx = ux[r + 1];
+                vy = uy[r + 1];
+                if (vm && vp) a = 0.5f * angle_between(ux[r], uy[r], ux[r + 2], uy[r + 2]);
+                else if (vp) a = angle_between(vx, vy, ux[r + 2], uy[r + 2]);
+                else if (vm) a = angle_between(ux[r], uy[r], vx, vy);
+                Tt = Tr[r];
+            } else {
+                __sincosf(th[r + 1], &vy, &vx);
+                if (vm && vp) a = 0.5f * fabsf(wrap_pi(th[r + 2] - th[r]));
+                else if (vp) a = fabsf(wrap_pi(th[r + 2] - th[r + 1]));
+                else if (vm) a = fabsf(wrap_pi(th[r + 1] - th[r]));
+                const double2 xe = ring[e];
+                const double ddx = px - xe.x, ddy = py - xe.y;
+                Tt = (double)dTr[r] + dist_newton(ddx * ddx + ddy * ddy) * ic0;
+            }
             green_entry(omega, Tt, Kb >> (2 * r), Ar[r], a, sk, isk, gr, gi, hr, hi);
             gr *= rsg;
             gi *= rsg;
@@ -407,13 +319,22 @@ __global__ void __launch_bounds__(64 * NW) green_lp_rec_kernel(
         // the rotated components H, b = H (u_x - i u_y), a = H (u_x + i u_y): the bilinear
         // form a^T Rs b is the sum of the quadratic forms of H u_x and H u_y (Rs symmetric),
         // so the back-projection needs two contractions
-        const float v[6] = {hr, hi, hr * vx + hi * vy, hi * vx - hr * vy, hr * vx - hi * vy,
-                            hi * vx + hr * vy};
+        float v[6] = {hr, hi, hr * vx + hi * vy, hi * vx - hr * vy, hr * vx - hi * vy,
+                      hi * vx + hr * vy};
+        if constexpr (TAB) {  // H u_x, H u_y
+            v[2] = hr * vx;
+            v[3] = hi * vx;
+            v[4] = hr * vy;
+            v[5] = hi * vy;
+        }
 #pragma unroll
         for (int cp = 0; cp < 6; ++cp) {
             if (r & 1) hp[cp][r >> 1] |= lp_bits<T>(v[cp]) << 16;
             else hp[cp][r >> 1] = lp_bits<T>(v[cp]);
-            if constexpr (SPLIT) {
+            if constexpr (SPLIT && TAB) {
+                if (r & 1) hl[cp][r >> 1] |= lp_lo_bits<T>(v[cp]) << 16;
+                else hl[cp][r >> 1] = lp_lo_bits<T>(v[cp]);
+            } else if constexpr (SPLIT) {
                 // low part: |lo| <= 4 (half an FP16 ulp below 2^14), times 2^6 in FP8 (E4M3);
                 // a correction of relative size 2^-11 needs no more than its 3 bits. Clamped
                 // to the format's largest value (448; beyond it the conversion gives NaN), which
@@ -474,7 +395,9 @@ __global__ void __launch_bounds__(64 * NW) green_lp_rec_kernel(
             }
         }
     };
-    if constexpr (SPLIT) {
+    if constexpr (SPLIT && TAB) {
+        store(hl, Htlo);
+    } else if constexpr (SPLIT) {
         // FP8 low parts: component c's planes [2][Np8 / 64][n_mask][64 bytes] at the start
         // of its low-part slot (a block of 64 transducers per workgroup: its 64 nodes are
         // 4 KiB in a row), staged [plane][node][GEt bytes]
@@ -1615,28 +1538,38 @@ constexpr float GS_MAX = 2.8285f;
 rb_status rb_launch_green_lp(rb_ctx *ctx, const rb_tables *tb, double omega, double c0,
                              const rb_green *out, const float *gs, const float *gscale,
                              int write_g, unsigned int *rowmax) {
-    dim3 grd((tb->n_mask + GQ - 1) / GQ, (tb->n + GE - 1) / GE);
+    const int N = tb->n, n_mask = tb->n_mask;
     rb_prof_begin(ctx, ST_GREEN);
-    hipLaunchKernelGGL(row_amax_kernel, dim3(tb->n), dim3(256), 0, ctx->stream, *tb, tb->n_mask,
-                       rowmax);
+    RB_TRY(rb_launch_fill_i32(ctx, reinterpret_cast<int32_t *>(rowmax), 2 * N, 0));
+    hipLaunchKernelGGL(row_amax_kernel, dim3((n_mask + AMAX_CHUNK - 1) / AMAX_CHUNK, N), dim3(256),
+                       0, ctx->stream, *tb, n_mask, rowmax);
     RB_CHECK_LAUNCH(ctx);
     const float gmax = gs ? GS_MAX : 1.f;
-    const size_t hlo = 6 * (size_t)tb->n_mask * rb_lp_pad(tb->n);  // low parts follow H
-    if (out->prec == RB_BF16)
-        hipLaunchKernelGGL((green_lp_kernel<__bf16, false>), grd, dim3(256), 0, ctx->stream, *tb,
-                           tb->n, tb->n_mask, omega, c0, (const float2 *)gs, gscale, write_g,
-                           (__bf16 *)out->G, (__bf16 *)out->H, rowmax, gmax, out->scales,
-                           nullptr);
-    else if (rb_prec_split(out->prec))
-        hipLaunchKernelGGL((green_lp_kernel<_Float16, true>), grd, dim3(256), 0, ctx->stream, *tb,
-                           tb->n, tb->n_mask, omega, c0, (const float2 *)gs, gscale, write_g,
-                           (_Float16 *)out->G, (_Float16 *)out->H, rowmax, gmax, out->scales,
-                           (_Float16 *)out->H + hlo);
-    else
-        hipLaunchKernelGGL((green_lp_kernel<_Float16, false>), grd, dim3(256), 0, ctx->stream,
-                           *tb, tb->n, tb->n_mask, omega, c0, (const float2 *)gs, gscale,
-                           write_g, (_Float16 *)out->G, (_Float16 *)out->H, rowmax, gmax,
-                           out->scales, nullptr);
+    hipLaunchKernelGGL(row_scale_kernel, dim3((N + 255) / 256), dim3(256), 0, ctx->stream, rowmax,
+                       N, omega, c0, gmax, out->scales);
+    RB_CHECK_LAUNCH(ctx);
+    // 64 transducers x 64 nodes a workgroup, as in the split form of a step: G leaves as rows of
+    // 128 bytes and each node's H as 128-byte pieces (16 bytes per lane otherwise: 512
+    // transducers and 152 053 nodes took 1.80 ms in the split form and 1.27 in BF16, now 0.92
+    // and 0.73)
+    const size_t hlo = 6 * (size_t)n_mask * rb_lp_pad(N);  // low parts follow H
+    dim3 grd((n_mask + GQ - 1) / GQ, (N + 63) / 64);
+    auto launch = [&](auto kernel, auto *G, auto *H, auto *Hlo) {
+        hipLaunchKernelGGL(kernel, grd, dim3(512), 0, ctx->stream, *tb, (const float4 *)nullptr,
+                           (const int32_t *)nullptr, (const double2 *)nullptr, 0.0, 0.0, 0.0, 1, N,
+                           n_mask, omega, c0, (const float2 *)gs, gscale, write_g, G, H,
+                           (const float *)out->scales, Hlo);
+    };
+    if (out->prec == RB_BF16) {
+        launch(green_lp_rec_kernel<__bf16, false, 8, 8, true>, (__bf16 *)out->G, (__bf16 *)out->H,
+               (__bf16 *)nullptr);
+    } else {
+        _Float16 *G = (_Float16 *)out->G, *H = (_Float16 *)out->H;
+        if (rb_prec_split(out->prec))
+            launch(green_lp_rec_kernel<_Float16, true, 8, 8, true>, G, H, H + hlo);
+        else
+            launch(green_lp_rec_kernel<_Float16, false, 8, 8, true>, G, H, (_Float16 *)nullptr);
+    }
     RB_CHECK_LAUNCH(ctx);
     rb_prof_end(ctx);
     return RB_OK;
@@ -1659,18 +1592,18 @@ rb_status rb_launch_green_lp_rec(rb_ctx *ctx, const float4 *rec, const double2 *
                        n, omega, c0, gmax, out->scales);
     RB_CHECK_LAUNCH(ctx);
     if (out->prec == RB_BF16)
-        hipLaunchKernelGGL((green_lp_rec_kernel<__bf16, false, GW, 4>), grd, dim3(256), 0, ctx->stream,
-                           rec, ctx->d_mask_index, ring, g.x0, g.y0, g.dx, g.nx, n, nm, omega,
+        hipLaunchKernelGGL((green_lp_rec_kernel<__bf16, false, GW, 4, false>), grd, dim3(256), 0, ctx->stream,
+                           rb_tables{}, rec, ctx->d_mask_index, ring, g.x0, g.y0, g.dx, g.nx, n, nm, omega,
                            c0, (const float2 *)gs, gscale, write_g, (__bf16 *)out->G,
                            (__bf16 *)out->H, out->scales, nullptr);
     else if (rb_prec_split(out->prec))
-        hipLaunchKernelGGL((green_lp_rec_kernel<_Float16, true, GWS, 8>), grd, dim3(512), 0, ctx->stream,
-                           rec, ctx->d_mask_index, ring, g.x0, g.y0, g.dx, g.nx, n, nm, omega,
+        hipLaunchKernelGGL((green_lp_rec_kernel<_Float16, true, GWS, 8, false>), grd, dim3(512), 0, ctx->stream,
+                           rb_tables{}, rec, ctx->d_mask_index, ring, g.x0, g.y0, g.dx, g.nx, n, nm, omega,
                            c0, (const float2 *)gs, gscale, write_g, (_Float16 *)out->G,
                            (_Float16 *)out->H, out->scales, (_Float16 *)out->H + hlo);
     else
-        hipLaunchKernelGGL((green_lp_rec_kernel<_Float16, false, GW, 4>), grd, dim3(256), 0,
-                           ctx->stream, rec, ctx->d_mask_index, ring, g.x0, g.y0, g.dx, g.nx, n,
+        hipLaunchKernelGGL((green_lp_rec_kernel<_Float16, false, GW, 4, false>), grd, dim3(256), 0,
+                           ctx->stream, rb_tables{}, rec, ctx->d_mask_index, ring, g.x0, g.y0, g.dx, g.nx, n,
                            nm, omega, c0, (const float2 *)gs, gscale, write_g,
                            (_Float16 *)out->G, (_Float16 *)out->H, out->scales, nullptr);
     RB_CHECK_LAUNCH(ctx);
