@@ -519,17 +519,19 @@ __device__ __forceinline__ uint32_t ordered_bits(float f) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// Barycentric coordinates of node (pu, pv) in triangle (a, b, c), node-index units.
+// Barycentric coordinates of node (pu, pv) in triangle (a, b, c), node-index units. The fused
+// operations are spelled out: the walk, the rasterisation and the resolve pass must agree in every
+// bit, whatever each of them shares with its surroundings. False (with coordinates that mean
+// nothing) for a triangle without area.
 __device__ __forceinline__ bool barycentric(float au, float av, float bu, float bv, float cu,
                                             float cv, float pu, float pv, float &la, float &lb,
                                             float &lc) {
-    float area = (bu - au) * (cv - av) - (bv - av) * (cu - au);
-    if (!(fabsf(area) > 1e-30f)) return false;
-    float ia = __builtin_amdgcn_rcpf(area);
-    la = ((bu - pu) * (cv - pv) - (bv - pv) * (cu - pu)) * ia;
-    lb = ((cu - pu) * (av - pv) - (cv - pv) * (au - pu)) * ia;
-    lc = ((au - pu) * (bv - pv) - (av - pv) * (bu - pu)) * ia;
-    return true;
+    const float area = fmaf(bu - au, cv - av, -((bv - av) * (cu - au)));
+    const float ia = __builtin_amdgcn_rcpf(area);
+    la = fmaf(bu - pu, cv - pv, -((bv - pv) * (cu - pu))) * ia;
+    lb = fmaf(cu - pu, av - pv, -((cv - pv) * (au - pu))) * ia;
+    lc = fmaf(au - pu, bv - pv, -((av - pv) * (bu - pu))) * ia;
+    return fabsf(area) > 1e-30f;
 }
 
 // Coverage tolerance of the barycentric test in FP32: nodes on a shared edge are claimed by
@@ -607,9 +609,10 @@ __device__ __forceinline__ float ray_atan2(float y, float x) {
 }
 
 // Table rows of transducer e (uniform over a workgroup): entry q of the row is out + q.
+template <bool REC>
 __device__ __forceinline__ TableOut table_row(const TableOut &to, size_t off) {
     TableOut r = to;
-    if (to.rec) {
+    if constexpr (REC) {
         r.rec = to.rec + off;
     } else {
         r.tb.T = to.tb.T + off;
@@ -681,22 +684,18 @@ constexpr int LOCATE_GROUP_ROWS = 2;  // tile rows per XCD group
 // the half that holds (pu, pv) with its barycentric coordinates, or -1.
 __device__ __forceinline__ int quad_test(float2 p00, float2 p10, float2 p01, float2 p11,
                                          float pu, float pv, float lam[3]) {
-    float la, lb, lc;
-    if (barycentric(p00.x, p00.y, p10.x, p10.y, p11.x, p11.y, pu, pv, la, lb, lc) &&
-        la >= -RB_BARY_EPS && lb >= -RB_BARY_EPS && lc >= -RB_BARY_EPS) {
-        lam[0] = la;
-        lam[1] = lb;
-        lam[2] = lc;
-        return 0;
-    }
-    if (barycentric(p00.x, p00.y, p11.x, p11.y, p01.x, p01.y, pu, pv, la, lb, lc) &&
-        la >= -RB_BARY_EPS && lb >= -RB_BARY_EPS && lc >= -RB_BARY_EPS) {
-        lam[0] = la;
-        lam[1] = lb;
-        lam[2] = lc;
-        return 1;
-    }
-    return -1;
+    // both triangles without a branch: the lanes of a wave hold both kinds
+    float l0[3] = {}, l1[3] = {};
+    const bool a0 = barycentric(p00.x, p00.y, p10.x, p10.y, p11.x, p11.y, pu, pv, l0[0], l0[1],
+                                l0[2]);
+    const bool a1 = barycentric(p00.x, p00.y, p11.x, p11.y, p01.x, p01.y, pu, pv, l1[0], l1[1],
+                                l1[2]);
+    const float eps = -RB_BARY_EPS;
+    const bool h0 = a0 & (l0[0] >= eps) & (l0[1] >= eps) & (l0[2] >= eps);
+    const bool h1 = a1 & (l1[0] >= eps) & (l1[1] >= eps) & (l1[2] >= eps);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) lam[k] = h0 ? l0[k] : l1[k];
+    return h0 ? 0 : h1 ? 1 : -1;
 }
 
 // posE, Mrow: the transducer's samples and last-sample indices (uniform over a workgroup in
@@ -724,9 +723,11 @@ __device__ __forceinline__ bool mesh_walk(const float2 *__restrict__ posE,
         uint32_t b00 = (uint32_t)(i * n_rays + j), b01 = b00 + (uint32_t)n_rays;
         f4u q0 = *reinterpret_cast<const f4u *>(posE + b00);
         f4u q1 = *reinterpret_cast<const f4u *>(posE + b01);
-        const int Mj = Mv.x, Mj1 = Mv.y;
-        int top = min(Mj, Mj1) - 1;  // last quad index along the rays
-        if (Mj < 0 || Mj1 < 0 || top < 1) return false;
+        // one wait for all three: the compiler moved the positions' loads behind the test of M
+        int Mj = Mv.x, Mj1 = Mv.y;
+        asm volatile("" : "+v"(q0), "+v"(q1), "+v"(Mj), "+v"(Mj1));
+        const int top = min(Mj, Mj1) - 1;  // last quad index along the rays
+        if (top < 1) return false;
         if (i > top) {
             i = top;
             b00 = (uint32_t)(i * n_rays + j);
@@ -758,19 +759,11 @@ __device__ __forceinline__ bool mesh_walk(const float2 *__restrict__ posE,
         float s_j0 = side(p01, p00);   // edge along ray j
         float worst = fminf(fminf(s_i0, s_j1), fminf(s_i1, s_j0));
         if (worst >= 0.f) return false;  // inside the quad but in neither triangle
-        if (worst == s_i0) {
-            if (i <= 1) return false;
-            --i;
-        } else if (worst == s_i1) {
-            if (i >= top) return false;
-            ++i;
-        } else if (worst == s_j0) {
-            if (j <= 0) return false;
-            --j;
-        } else {
-            if (j >= n_rays - 2) return false;
-            ++j;
-        }
+        const bool i0 = worst == s_i0, i1 = !i0 & (worst == s_i1);
+        const bool j0 = !i0 & !i1 & (worst == s_j0);
+        i += (int)i1 - (int)i0;
+        j += (int)!(i0 | i1 | j0) - (int)j0;
+        if ((i < 1) | (i > top) | (j < 0) | (j > n_rays - 2)) return false;
     }
     return false;
 }
@@ -965,12 +958,18 @@ __device__ __forceinline__ float wave_max(float x) {
 // In a fan that folds, the walk's triangle is one candidate of the smallest-key rule: its
 // record is written and its key seeds keys[] (changed[] cleared); the rasterisation of the
 // fan then replaces it where a triangle with a smaller key covers the node.
+// The walks are chains of dependent gathers (2.4 quads a node, 8 for a wave's two rows), half of
+// them served by HBM. One wait a quad instead of two, both triangles tested without a branch, no
+// scratch (a choice of row pointers at run time had gone there) and 6 waves per SIMD, whose
+// registers end the spills: 1735 -> 1540 us for 256 transducers of 152088 nodes, 3.0 + 2.1 -> 2.6
+// + 1.7 GB. Wider strips of nodes (64 x 4: slower; 32 x 8, 8 x 8 per wave: the same), stores past
+// the cache (slower) and other groups of rows (the same) were tried.
 // Workgroups are dealt to the 8 XCDs round-robin by launch index. The (transducer, tile)
 // sequence is cut into groups of LOCATE_GROUP_ROWS tile rows and group g goes to XCD g mod 8,
 // so neighbouring tiles share their ray samples through one L2 while every XCD still gets an
 // even mix of the disk-shaped mask. The launch is padded to a multiple of 8 groups.
 template <bool REC>
-__global__ void __launch_bounds__(LOCATE_THREADS, 8) locate_kernel(SampleBufs sb, int n_rays, int S, int E,
+__global__ void __launch_bounds__(LOCATE_THREADS, 6) locate_kernel(SampleBufs sb, int n_rays, int S, int E,
                                                      int e0, GridP g, double R, double psi0,
                                                      int N, double ds, double c0, int n_mask,
                                                      int tile_i0, int tile_j0, int tiles_x,
@@ -991,7 +990,7 @@ __global__ void __launch_bounds__(LOCATE_THREADS, 8) locate_kernel(SampleBufs sb
     const bool fold = sb.folded[el] != 0;  // uniform over the block
     const int ti = t % tiles_x, tj = t / tiles_x;
     const int ii = tile_i0 + ti * LTX + (threadIdx.x % LTX);
-    const TableOut toE = table_row(to, (size_t)(e0 + el) * n_mask);
+    const TableOut toE = table_row<REC>(to, (size_t)(e0 + el) * n_mask);
     const int2 o = off[item];
     const float4 wc = wcon[e0 + el];
     // largest A and 1/A of the lane's records (bits of non-negative floats)
@@ -1411,6 +1410,7 @@ __global__ void __launch_bounds__(256) raster_kernel(SampleBufs sb, int n_rays, 
 
 // General path: per (folded transducer, mask node) whose walk result the rasterisation
 // replaced, interpolate the winning triangle. Returns the amplitude written (0 if none).
+template <bool REC>
 __device__ __forceinline__ float resolve_node(const SampleBufs &sb, int n_rays, int S, int el,
                                              int q, int e0, const GridP &g, double ds, double c0,
                                              int n_mask, const int32_t *__restrict__ mask_index,
@@ -1418,7 +1418,7 @@ __device__ __forceinline__ float resolve_node(const SampleBufs &sb, int n_rays, 
                                              const TableOut &to) {
     const size_t tid = (size_t)el * n_mask + q;
     int e = e0 + el;
-    const TableOut toE = table_row(to, (size_t)e * n_mask);
+    const TableOut toE = table_row<REC>(to, (size_t)e * n_mask);
     const uint32_t out = (uint32_t)q;
     unsigned long long key = keys[tid];
     int p = mask_index[q];
@@ -1428,8 +1428,7 @@ __device__ __forceinline__ float resolve_node(const SampleBufs &sb, int n_rays, 
     double px = g.x0 + ii * g.dx, py = g.y0 + jj * g.dx;
     double d = sqrt_newton((px - xe) * (px - xe) + (py - ye) * (py - ye));
     if (key == ~0ull || d < 2.0 * ds) {
-        if (to.rec) write_invalid<true>(toE, out);
-        else write_invalid<false>(toE, out);
+        write_invalid<REC>(toE, out);
         return 0.f;
     }
     uint32_t tri = (uint32_t)(key & 0xffffffffu);
@@ -1455,15 +1454,12 @@ __device__ __forceinline__ float resolve_node(const SampleBufs &sb, int n_rays, 
     const int K = tri_K(sb, n_rays, S, el, j, i, half, vb);
     const float4 *fldE = sb.fld + ebase;
     float A;
-    if (to.rec)
-        write_entry_f<true>(fldE[vb[0]], fldE[vb[1]], fldE[vb[2]], lam, K, (float)d, d, c0, toE,
-                            out, A);
-    else
-        write_entry_f<false>(fldE[vb[0]], fldE[vb[1]], fldE[vb[2]], lam, K, (float)d, d, c0, toE,
-                             out, A);
+    write_entry_f<REC>(fldE[vb[0]], fldE[vb[1]], fldE[vb[2]], lam, K, (float)d, d, c0, toE, out,
+                       A);
     return A;
 }
 
+template <bool REC>
 __global__ void __launch_bounds__(256) resolve_kernel(SampleBufs sb, int n_rays, int S, int e0,
                                                       GridP g, double ds, double c0, int n_mask,
                                                       const int32_t *__restrict__ mask_index,
@@ -1502,7 +1498,7 @@ __global__ void __launch_bounds__(256) resolve_kernel(SampleBufs sb, int n_rays,
         int cnt = 0;
         auto drain = [&](int n) {
             if (lane >= n) return;
-            const float A = resolve_node(sb, n_rays, S, el, queue[lane], e0, g, ds, c0, n_mask,
+            const float A = resolve_node<REC>(sb, n_rays, S, el, queue[lane], e0, g, ds, c0, n_mask,
                                          mask_index, keys, to);
             amax = fmaxf(amax, A);
             iamax = fmaxf(iamax, A > 0.f ? 1.0f / A : 0.f);
@@ -2096,7 +2092,7 @@ rb_status rb_launch_trace(rb_ctx *ctx, const rb_grid *g, const rb_ring *r,
         hipLaunchKernelGGL(raster_list_kernel, dim3(RSHARDS * 32), dim3(256), rlds, ctx->stream,
                            sb, nr, S, ctx->d_qrow, ro, rlist, (uint32_t)raster_cap(plane), rcount);
         RB_CHECK_LAUNCH(ctx);
-        hipLaunchKernelGGL(resolve_kernel, dim3(FOLD_GRID), dim3(256), 0, ctx->stream, sb, nr, S,
+        hipLaunchKernelGGL(rec ? resolve_kernel<true> : resolve_kernel<false>, dim3(FOLD_GRID), dim3(256), 0, ctx->stream, sb, nr, S,
                            e0, gp, tp->ds, tp->c0, n_mask, ctx->d_mask_index, flist, keys,
                            changed, to);
         RB_CHECK_LAUNCH(ctx);
