@@ -74,53 +74,90 @@ typedef int i2u __attribute__((ext_vector_type(2), aligned(4)));
 // (m.patch). A step is shorter than a cell, so consecutive evaluations (predictor,
 // corrector, next predictor) mostly fall in the same cell and read them from LDS instead of
 // loading them again; kept in LDS rather than in registers, they cost no register copies.
+// AHEAD (launches of few wavefronts, rb_launch_trace): the coefficients stay in registers, and
+// those of the cell that the next evaluation away from here needs are loaded ahead (prefetch).
+template <bool AHEAD>
 struct Patch {
     int cell = -1;  // (iv + 2) (nx + 3) + iu + 2 of the stored cell, -1 for none
 };
+template <>
+struct Patch<true> {
+    int cell = -1, next = -1;  // the cells of cur and nxt
+    float4 cur[4], nxt[4];
+};
 
-// Value, gradient and Hessian (per metre) of the spline at node-index coordinates (u, v).
-__device__ __forceinline__ Spline spline_eval(const SplineMap &m, double u, double v,
-                                              Patch &pc) {
-    double fu = floor(u), fv = floor(v);
-    const float tx = (float)(u - fu), ty = (float)(v - fv);
+// Cell of the point (u, v), whose floors are fu, fv.
+__device__ __forceinline__ int cell_of(const SplineMap &m, double fu, double fv) {
     int iu = min(max((int)fu, -2), m.nx), iv = min(max((int)fv, -2), m.ny);
-    const int cell = (iv + 2) * m.ncx + (iu + 2);
-    if (cell != pc.cell) {
+    return (iv + 2) * m.ncx + (iu + 2);
+}
+
+// Starts the loads of the cell of (u, v) unless the lane holds it.
+__device__ __forceinline__ void prefetch(const SplineMap &m, double u, double v,
+                                         Patch<true> &pc) {
+    const int cell = cell_of(m, floor(u), floor(v));
+    if (cell != pc.cell && cell != pc.next) {
         const float4 *p = m.coef + (size_t)cell * 4;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) m.patch[b * PATCH_STRIDE] = p[b];
+        for (int b = 0; b < 4; ++b) pc.nxt[b] = p[b];
+        pc.next = cell;
+    }
+}
+
+// Value, gradient and Hessian (per metre) of the spline at node-index coordinates (u, v).
+template <bool AHEAD>
+__device__ __forceinline__ Spline spline_eval(const SplineMap &m, double u, double v,
+                                              Patch<AHEAD> &pc) {
+    double fu = floor(u), fv = floor(v);
+    const float tx = (float)(u - fu), ty = (float)(v - fv);
+    const int cell = cell_of(m, fu, fv);
+    if (cell != pc.cell) {
+        if constexpr (AHEAD) {
+            prefetch(m, u, v, pc);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) pc.cur[b] = pc.nxt[b];
+        } else {
+            const float4 *p = m.coef + (size_t)cell * 4;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) m.patch[b * PATCH_STRIDE] = p[b];
+        }
         pc.cell = cell;
     }
     float f[16];
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        const float4 q = m.patch[b * PATCH_STRIDE];
+        float4 q;
+        if constexpr (AHEAD) q = pc.cur[b];
+        else q = m.patch[b * PATCH_STRIDE];
         f[4 * b] = q.x;
         f[4 * b + 1] = q.y;
         f[4 * b + 2] = q.z;
         f[4 * b + 3] = q.w;
     }
     // Row polynomials Q_j(tx) = sum_i a_ji tx^i and their first two tx-derivatives (Horner),
-    // then the same in ty: value, gradient and Hessian of the bicubic.
-    float q0[4], q1[4], q2[4];
+    // then the same in ty: value, gradient and Hessian of the bicubic. The second derivatives
+    // are carried halved and the factors 2 of the first go with t (2 t): multiplications by
+    // powers of two are exact, so each sum is the plain Horner form's, with fewer instructions.
+    const float tx2 = tx + tx, ty2 = ty + ty;
+    float q0[4], q1[4], q2[4];  // Q_j, Q_j', Q_j'' / 2
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const float a0 = f[4 * j], a1 = f[4 * j + 1], a2 = f[4 * j + 2];
         const float a3 = f[4 * j + 3];
-        const float b3 = 3.0f * a3, b2 = a2 + a2;
+        const float b3 = 1.5f * a3;
         q0[j] = fmaf(fmaf(fmaf(a3, tx, a2), tx, a1), tx, a0);
-        q1[j] = fmaf(fmaf(b3, tx, b2), tx, a1);
-        q2[j] = fmaf(b3 + b3, tx, b2);
+        q1[j] = fmaf(fmaf(b3, tx, a2), tx2, a1);
+        q2[j] = fmaf(b3, tx2, a2);
     }
     const float s_v = fmaf(fmaf(fmaf(q0[3], ty, q0[2]), ty, q0[1]), ty, q0[0]);
     const float s_gx = fmaf(fmaf(fmaf(q1[3], ty, q1[2]), ty, q1[1]), ty, q1[0]);
     const float s_xx = fmaf(fmaf(fmaf(q2[3], ty, q2[2]), ty, q2[1]), ty, q2[0]);
-    const float c3 = 3.0f * q0[3], c2 = q0[2] + q0[2];
-    const float s_gy = fmaf(fmaf(c3, ty, c2), ty, q0[1]);
-    const float s_xy = fmaf(fmaf(3.0f * q1[3], ty, q1[2] + q1[2]), ty, q1[1]);
-    const float s_yy = fmaf(c3 + c3, ty, c2);
-    float ih = m.ih, ih2 = ih * ih;
-    return Spline{s_v + 1.0f, s_gx * ih, s_gy * ih, s_xx * ih2, s_xy * ih2, s_yy * ih2};
+    const float c3 = 1.5f * q0[3];
+    const float s_gy = fmaf(fmaf(c3, ty, q0[2]), ty2, q0[1]);
+    const float s_xy = fmaf(fmaf(1.5f * q1[3], ty, q1[2]), ty2, q1[1]);
+    const float s_yy = fmaf(c3, ty2, q0[2]);
+    const float ih = m.ih, ih2 = ih * ih, ih22 = ih2 + ih2;
+    return Spline{s_v + 1.0f, s_gx * ih, s_gy * ih, s_xx * ih22, s_xy * ih2, s_yy * ih22};
 }
 
 // Absorption map alpha (Np/m) with MPAD replicated nodes on every side, as stored by pad_map
@@ -182,52 +219,85 @@ __device__ __forceinline__ double rsqrt_newton(double a) {
     return y * fma(-0.5 * a * y, y, 1.5);
 }
 
-// Paraxial right-hand side (Eq. ray-equation-paraxial with k -> n).
+// Paraxial right-hand side (Eq. ray-equation-paraxial with k -> n). The fused operations of the
+// ray's step are spelled out, here and below: near a caustic the amplitude magnifies a last bit of
+// the paraxial system several thousand times, and the compiler's own choice of the product to fuse
+// in a sum of two changes with the code around it. (The order is the one it had chosen; FIRST: at
+// the step's start, otherwise at the predicted point.)
+template <bool FIRST>
 __device__ __forceinline__ void paraxial_rhs(const Spline &s, float kx, float ky, float dxx,
                                              float dxy, float dkx, float dky, float q[4]) {
-    float n = s.v, in = __builtin_amdgcn_rcpf(n), in2 = in * in;
-    float gdx = s.gx * dxx + s.gy * dxy;
-    float kdk = kx * dkx + ky * dky;
-    q[0] = -gdx * in2 * kx + dkx * in;
-    q[1] = -gdx * in2 * ky + dky * in;
-    q[2] = s.hxx * dxx + s.hxy * dxy - gdx * in * s.gx + kdk * in2 * s.gx;
-    q[3] = s.hxy * dxx + s.hyy * dxy - gdx * in * s.gy + kdk * in2 * s.gy;
+    const float n = s.v, in = __builtin_amdgcn_rcpf(n), in2 = in * in;
+    float gdx, h0, h1;
+    if constexpr (FIRST) {
+        gdx = fmaf(s.gy, dxy, s.gx * dxx);
+        h0 = fmaf(s.hxy, dxy, s.hxx * dxx);
+        h1 = fmaf(s.hyy, dxy, s.hxy * dxx);
+    } else {
+        gdx = fmaf(s.gx, dxx, s.gy * dxy);
+        h0 = fmaf(s.hxx, dxx, s.hxy * dxy);
+        h1 = fmaf(s.hxy, dxx, s.hyy * dxy);
+    }
+    const float kdk = fmaf(kx, dkx, ky * dky);
+    const float c = -gdx * in2, gi = gdx * in, ki = kdk * in2;
+    q[0] = fmaf(dkx, in, c * kx);
+    q[1] = fmaf(dky, in, c * ky);
+    q[2] = fmaf(s.gx, ki, fmaf(-s.gx, gi, h0));
+    q[3] = fmaf(s.gy, ki, fmaf(-s.gy, gi, h1));
 }
 
-// One step of Algorithm 1 of length h (metres), given the spline at the current point.
+// The predictor of a step of hu node units from r: unit ray direction and the point it leads to.
+// It needs no spline.
+struct Predictor {
+    double kx, ky, u, v;
+    float qx, qy;
+};
+
+__device__ __forceinline__ Predictor predict(const Ray &r, double hu) {
+    Predictor p;
+    const double ikn = rsqrt_newton(fma(r.ky, r.ky, r.kx * r.kx));
+    p.kx = r.kx * ikn;
+    p.ky = r.ky * ikn;
+    p.qx = (float)p.kx;
+    p.qy = (float)p.ky;
+    p.u = fma(hu, (double)p.qx, r.u);
+    p.v = fma(hu, (double)p.qy, r.v);
+    return p;
+}
+
+// One step of Algorithm 1 of length hf (metres) = hu (node units), given the spline at the current
+// point and the step's predictor.
+template <bool AHEAD>
 __device__ __forceinline__ Ray heun_step(const SplineMap &m, const Spline &s1, const Ray &r,
-                                         double h, double idx, Patch &pc) {
-    float hf = (float)h;
-    double hu = h * idx;                                    // step in node units
+                                         const Predictor &p, float hf, double hu,
+                                         Patch<AHEAD> &pc) {
     float n = s1.v;
-    const double ikn = rsqrt_newton(r.kx * r.kx + r.ky * r.ky);
-    const double kxd = (double)n * (r.kx * ikn), kyd = (double)n * (r.ky * ikn);
-    float qxx = (float)(r.kx * ikn), qxy = (float)(r.ky * ikn);  // unit ray direction
+    const double kxd = (double)n * p.kx, kyd = (double)n * p.ky;
+    const float qxx = p.qx, qxy = p.qy;
     float kx = (float)kxd, ky = (float)kyd;                 // normalised wave vector
-    float kpx = kx + hf * s1.gx, kpy = ky + hf * s1.gy;     // auxiliary ray direction
-    Spline s2 = spline_eval(m, r.u + hu * (double)qxx, r.v + hu * (double)qxy, pc);
+    float kpx = fmaf(hf, s1.gx, kx), kpy = fmaf(hf, s1.gy, ky);  // auxiliary ray direction
+    Spline s2 = spline_eval(m, p.u, p.v, pc);
     float n2 = s2.v;
-    float ikpn = __builtin_amdgcn_rsqf(kpx * kpx + kpy * kpy);
-    float qxx2 = kpx * ikpn, qxy2 = kpy * ikpn;
-    kpx = n2 * qxx2;
-    kpy = n2 * qxy2;
-    float sx = qxx + qxx2, sy = qxy + qxy2;
-    float isn = __builtin_amdgcn_rsqf(sx * sx + sy * sy);
+    float ikpn = __builtin_amdgcn_rsqf(fmaf(kpx, kpx, kpy * kpy));
+    const float sx = fmaf(kpx, ikpn, qxx), sy = fmaf(kpy, ikpn, qxy);
+    kpx = n2 * (kpx * ikpn);
+    kpy = n2 * (kpy * ikpn);
+    float isn = __builtin_amdgcn_rsqf(fmaf(sx, sx, sy * sy));
     Ray o;
-    o.u = r.u + hu * (double)(sx * isn);                    // position along mean direction
-    o.v = r.v + hu * (double)(sy * isn);
+    o.u = fma(hu, (double)(sx * isn), r.u);                 // position along mean direction
+    o.v = fma(hu, (double)(sy * isn), r.v);
     o.kx = kxd + (double)(hf * (s1.gx + s2.gx) * 0.5f);
     o.ky = kyd + (double)(hf * (s1.gy + s2.gy) * 0.5f);
     float a[4], b[4];
     const float dxx = (float)r.dxx, dxy = (float)r.dxy;
-    paraxial_rhs(s1, kx, ky, dxx, dxy, r.dkx, r.dky, a);
-    float dkpx = r.dkx + hf * a[2], dkpy = r.dky + hf * a[3];
-    float dxpx = dxx + hf * a[0], dxpy = dxy + hf * a[1];
-    paraxial_rhs(s2, kpx, kpy, dxpx, dxpy, dkpx, dkpy, b);
+    paraxial_rhs<true>(s1, kx, ky, dxx, dxy, r.dkx, r.dky, a);
+    const float dkpx = fmaf(a[2], hf, r.dkx), dkpy = fmaf(a[3], hf, r.dky);
+    const float dxpx = fmaf(a[0], hf, dxx), dxpy = fmaf(a[1], hf, dxy);
+    paraxial_rhs<false>(s2, kpx, kpy, dxpx, dxpy, dkpx, dkpy, b);
     o.dxx = r.dxx + (double)(hf * (a[0] + b[0]) * 0.5f);
     o.dxy = r.dxy + (double)(hf * (a[1] + b[1]) * 0.5f);
-    o.dkx = r.dkx + hf * (a[2] + b[2]) * 0.5f;
-    o.dky = r.dky + hf * (a[3] + b[3]) * 0.5f;
+    o.dkx = fmaf(0.5f, hf * (a[2] + b[2]), r.dkx);
+    o.dky = fmaf(0.5f, hf * (a[3] + b[3]), r.dky);
     return o;
 }
 
@@ -266,7 +336,7 @@ struct RayEnd {
 // ray j of chunk transducer el go to sb; otherwise only the terminal state goes to *end.
 // Returns the index of the last sample, -1 if the ray did not reach the ring within
 // max_steps.
-template <bool STORE, bool ABS>
+template <bool STORE, bool ABS, bool AHEAD>
 __device__ __forceinline__ int trace_core(const SplineMap &m, const AbsMap &am, const GridP &g,
                                           double R, double psi, double2 xy, double cg,
                                           double sg, int n_rays, int max_steps, double ds,
@@ -276,7 +346,7 @@ __device__ __forceinline__ int trace_core(const SplineMap &m, const AbsMap &am, 
     const double ue = (xy.x - g.x0) * g.idx, ve = (xy.y - g.y0) * g.idx;
     const double uc = -g.x0 * g.idx, vc = -g.y0 * g.idx;  // ring centre
     const double Ru2 = R * R * g.idx * g.idx;              // ring radius squared, node units
-    Patch pc;
+    Patch<AHEAD> pc;
     Ray r;
     r.u = ue;
     r.v = ve;
@@ -305,42 +375,37 @@ __device__ __forceinline__ int trace_core(const SplineMap &m, const AbsMap &am, 
     int K = 0;
     int M = -1;
     const double ic0 = 1.0 / c0;
-    double h = ds;
-    bool last = false;
     int i = 0;
-    while (i < max_steps) {
-        Ray nr = heun_step(m, sc, r, h, g.idx, pc);
-        if (!last) {
-            double pu = nr.u - uc, pv = nr.v - vc;
-            if (pu * pu + pv * pv >= Ru2) {
-                // Definition 1: redo the step with ds' = distance along the unit direction
-                // to the ring.
-                double kn = sqrt(r.kx * r.kx + r.ky * r.ky);
-                double tx = r.kx / kn, ty = r.ky / kn;
-                double qu = r.u - uc, qv = r.v - vc;
-                double b = (qu * tx + qv * ty) * g.dx;
-                double disc = b * b + R * R - (qu * qu + qv * qv) * g.dx * g.dx;
-                h = fmin(fmax(-b + sqrt(fmax(disc, 0.0)), 0.0), ds);
-                last = true;
-                continue;
-            }
-        }
+    double d_end = 0.0;
+    float dT_end = 0.0f, L_end = 0.0f;
+    // Whole steps, whose length and what follows from it stay constants (the last step, apart, has
+    // a length of the lane's own), until one would reach the ring.
+    const float dsf = (float)ds;
+    const double dsu = ds * g.idx, dsB = ds * 0.5, dsT = ds * 0.5 * ic0;
+    Predictor p;
+    if constexpr (AHEAD) p = predict(r, dsu);
+    // the sample at the end of a step (hT, hB: half its length, by ic0 and as it is)
+    auto take = [&](const Ray &nr, double hT, double hB) {
         r = nr;
+        if constexpr (AHEAD) {  // the next predictor's cell, in flight while this step ends
+            p = predict(r, dsu);
+            prefetch(m, p.u, p.v, pc);
+        }
         sc = spline_eval(m, r.u, r.v, pc);
         float n_new = sc.v;
-        T += h * 0.5 * ic0 * ((double)n_cur + (double)n_new);
+        T = fma(hT, (double)n_cur + (double)n_new, T);
         if constexpr (ABS) {
             const float a_new = abs_value(am, r.u, r.v);
-            Babs += h * 0.5 * ((double)a_cur + (double)a_new);
+            Babs = fma(hB, (double)a_cur + (double)a_new, Babs);
             a_cur = a_new;
         }
         const float kxf = (float)r.kx, kyf = (float)r.ky;
-        float ikn = __builtin_amdgcn_rsqf(kxf * kxf + kyf * kyf);
+        float ikn = __builtin_amdgcn_rsqf(fmaf(kxf, kxf, kyf * kyf));
         float tx = kxf * ikn, ty = kyf * ikn;
-        float J = (float)r.dxx * (-ty) + (float)r.dxy * tx;
+        float J = fmaf(tx, (float)r.dxy, -(ty * (float)r.dxx));
         if (i >= 1 && J * J_prev < 0.0f) ++K;
         double du = r.u - ue, dv = r.v - ve;
-        double d = sqrt_newton(du * du + dv * dv) * g.dx;   // distance from the source
+        double d = sqrt_newton(fma(du, du, dv * dv)) * g.dx;  // distance from the source
         float df = (float)d;
         float nJ = n_new * fabsf(J);
         // Eq. attenuation_geom_reference with the first sample as reference, as a logarithm:
@@ -366,20 +431,42 @@ __device__ __forceinline__ int trace_core(const SplineMap &m, const AbsMap &am, 
         }
         J_prev = J;
         n_cur = n_new;
-        if (last) {
-            M = i;
-            if constexpr (STORE) {
-                size_t x = (size_t)el * n_rays + j;
-                sb.ex_dT[x] = dT;
-                sb.ex_L[x] = L;
-                sb.ex_K[x] = (uint8_t)min(K, 255);
-            } else {
-                end->T = T;
-                end->d = d;
-                end->L = L;
-                end->K = K;
-            }
+        d_end = d;
+        dT_end = dT;
+        L_end = L;
+    };
+    bool hit = false;
+    while (i < max_steps) {
+        if constexpr (!AHEAD) p = predict(r, dsu);
+        const Ray nr = heun_step(m, sc, r, p, dsf, dsu, pc);
+        const double pu = nr.u - uc, pv = nr.v - vc;
+        if (fma(pu, pu, pv * pv) >= Ru2) {
+            hit = true;
             break;
+        }
+        take(nr, dsT, dsB);
+    }
+    if (hit) {
+        // Definition 1: redo the step with ds' = distance along the unit direction to the ring
+        double kn = sqrt(fma(r.ky, r.ky, r.kx * r.kx));
+        double tx = r.kx / kn, ty = r.ky / kn;
+        double qu = r.u - uc, qv = r.v - vc;
+        double b = fma(qu, tx, qv * ty) * g.dx;
+        double disc = fma(b, b, R * R) - fma(qv, qv, qu * qu) * g.dx * g.dx;
+        const double h = fmin(fmax(-b + sqrt(fmax(disc, 0.0)), 0.0), ds);
+        p = predict(r, h * g.idx);
+        take(heun_step(m, sc, r, p, (float)h, h * g.idx, pc), h * 0.5 * ic0, h * 0.5);
+        M = i;
+        if constexpr (STORE) {
+            size_t x = (size_t)el * n_rays + j;
+            sb.ex_dT[x] = dT_end;
+            sb.ex_L[x] = L_end;
+            sb.ex_K[x] = (uint8_t)min(K, 255);
+        } else {
+            end->T = T;
+            end->d = d_end;
+            end->L = L_end;
+            end->K = K;
         }
     }
     if (M >= 0) {
@@ -399,7 +486,7 @@ __device__ __forceinline__ int trace_core(const SplineMap &m, const AbsMap &am, 
 
 // Fan ray j of transducer e0 + el (Section 4.4: launch angle gamma = psi + pi + delta,
 // |delta| < pi / 2), samples to sb.
-template <bool ABS>
+template <bool ABS, bool AHEAD>
 __device__ __forceinline__ int trace_ray(const SplineMap &m, const AbsMap &am, const GridP &g,
                                          double R,
                                          double psi0, int N, int n_rays, int max_steps,
@@ -412,7 +499,7 @@ __device__ __forceinline__ int trace_ray(const SplineMap &m, const AbsMap &am, c
     sincospi(((double)j + 0.5 - 0.5 * (double)n_rays) / (double)n_rays, &sd, &cd);
     const double cp = xy.x / R, sp = xy.y / R;
     const double cg = -(cp * cd - sp * sd), sg = -(sp * cd + cp * sd);
-    return trace_core<true, ABS>(m, am, g, R, psi, xy, cg, sg, n_rays, max_steps, ds, c0, el,
+    return trace_core<true, ABS, AHEAD>(m, am, g, R, psi, xy, cg, sg, n_rays, max_steps, ds, c0, el,
                                  j, sb, flag, nullptr);
 }
 
@@ -422,23 +509,33 @@ __device__ __forceinline__ int trace_ray(const SplineMap &m, const AbsMap &am, c
 // from the fan's middle (rank r: groups mid, mid - 1, mid + 1, ...), over all transducers:
 // the longest run first and the shortest fill the end of the launch. Also counts the
 // samples written (one atomic per wavefront; the workgroup is a whole number of them).
-// Four waves per SIMD (128 registers, a few spilled) hide more of the coefficient loads'
-// latency than three without spills.
+// Four waves per SIMD (128 registers) hide more of the coefficient loads' latency than three.
+// Bound by the instructions of a step (about 300, a quarter of them FP64). With the step's length and
+// its multiples constants of the loop, whole traces of 512 transducers of 1024 rays on a ring of
+// 50 mm went from 3.81 to 3.56 ms and nothing is spilled.
 // Workgroups (four transducers of one rank) are dealt to the 8 XCDs round-robin by launch
 // index. When E is a multiple of 32 the transducer groups of a rank are renamed so that each
 // XCD traces one contiguous arc of E / 8 transducers: same-rank rays of neighbouring
 // transducers cross nearly the same cells at about the same time, so that XCD's L2 fetches
 // their spline coefficients once instead of once per group of four. (Which wave traces which
 // ray changes nothing in the results.)
-template <bool ABS>
-__global__ void __launch_bounds__(PATCH_STRIDE) __attribute__((amdgpu_waves_per_eu(4))) trace_kernel(SplineMap m, AbsMap am, GridP g,
-                                                             double R, double psi0, int N,
-                                                             int n_rays, int max_steps,
-                                                             double ds, double c0, int e0, int E,
-                                                             SampleBufs sb, int *flag,
-                                                             unsigned long long *n_samples) {
-    __shared__ float4 s_patch[4 * PATCH_STRIDE];
-    m.patch = s_patch + threadIdx.x;
+//
+// trace_ahead_kernel, for launches that leave a SIMD one or two waves: nothing then hides the wait
+// for the coefficients of a new cell, which some lane of a wave enters at almost every evaluation.
+// A step's predictor needs no spline, so its cell is known, and its loads are issued, before the
+// current sample is worked out; coefficients stay in registers (152, without LDS), and
+// workgroups of one wave spread over all CUs. 64 transducers of 360 rays 590 -> 440 us. Against
+// trace_kernel, whole traces of fans of 1024 rays, lossless: 1536 waves 976 us against 1048, 2048 waves
+// 1277 against 1219, 4096 waves 2048 against 1952; in an absorbing medium (whose sixteen control points of
+// the absorption are one more wait a step) 3584 waves 1963 against 2015, 4096 waves 2248 against 2162.
+constexpr int AHEAD_WAVES = 6, AHEAD_WAVES_LOSSY = 14;  // most waves per CU of a launch
+
+template <bool ABS, bool AHEAD>
+__device__ __forceinline__ void trace_wave(const SplineMap &m, const AbsMap &am, const GridP &g,
+                                           double R, double psi0, int N, int n_rays,
+                                           int max_steps, double ds, double c0, int e0, int E,
+                                           const SampleBufs &sb, int *flag,
+                                           unsigned long long *n_samples) {
     const int wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int n_groups = (n_rays + 63) / 64;
     const int rank = wave / E;
@@ -453,13 +550,34 @@ __global__ void __launch_bounds__(PATCH_STRIDE) __attribute__((amdgpu_waves_per_
         const int grp = (rank & 1) ? mid - 1 - (rank >> 1) : mid + (rank >> 1);
         const int j = grp * 64 + (threadIdx.x & 63);
         if (j < n_rays)
-            M = trace_ray<ABS>(m, am, g, R, psi0, N, n_rays, max_steps, ds, c0, e0, el, j, sb,
-                               flag);
+            M = trace_ray<ABS, AHEAD>(m, am, g, R, psi0, N, n_rays, max_steps, ds, c0, e0, el, j,
+                                      sb, flag);
     }
     int cnt = M >= 0 ? M + 1 : 0;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
     if ((threadIdx.x & 63) == 0 && cnt > 0) atomicAdd(n_samples, (unsigned long long)cnt);
+}
+
+template <bool ABS>
+__global__ void __launch_bounds__(PATCH_STRIDE) __attribute__((amdgpu_waves_per_eu(4)))
+trace_kernel(SplineMap m, AbsMap am, GridP g, double R, double psi0, int N, int n_rays,
+             int max_steps, double ds, double c0, int e0, int E, SampleBufs sb, int *flag,
+             unsigned long long *n_samples) {
+    __shared__ float4 s_patch[4 * PATCH_STRIDE];
+    m.patch = s_patch + threadIdx.x;
+    trace_wave<ABS, false>(m, am, g, R, psi0, N, n_rays, max_steps, ds, c0, e0, E, sb, flag,
+                           n_samples);
+}
+
+template <bool ABS>
+__global__ void __launch_bounds__(64) trace_ahead_kernel(SplineMap m, AbsMap am, GridP g, double R,
+                                                         double psi0, int N, int n_rays,
+                                                         int max_steps, double ds, double c0,
+                                                         int e0, int E, SampleBufs sb, int *flag,
+                                                         unsigned long long *n_samples) {
+    trace_wave<ABS, true>(m, am, g, R, psi0, N, n_rays, max_steps, ds, c0, e0, E, sb, flag,
+                          n_samples);
 }
 
 // Map minus `off` (the index map stores n - 1, exact in FP32 for n in [1/2, 2]; the absorption
@@ -1704,7 +1822,7 @@ __global__ void __launch_bounds__(PATCH_STRIDE) __attribute__((amdgpu_waves_per_
         double sgm, cgm;
         sincos(cand, &sgm, &cgm);
         RayEnd end;
-        if (trace_core<false, ABS>(m, am, g, R, psi, xy, cgm, sgm, n_rays, max_steps, ds, c0, el,
+        if (trace_core<false, ABS, false>(m, am, g, R, psi, xy, cgm, sgm, n_rays, max_steps, ds, c0, el,
                                    0, sb, nullptr, &end) < 0)
             break;  // the ray did not reach the ring: the pair ends here
         const double f = end.beta - br;
@@ -2026,9 +2144,11 @@ rb_status rb_launch_trace(rb_ctx *ctx, const rb_grid *g, const rb_ring *r,
         RB_CHECK_LAUNCH(ctx);
         rb_prof_begin(ctx, ST_TRACE);
         const int waves = E * ((nr + 63) / 64);
-        hipLaunchKernelGGL(a_w ? trace_kernel<true> : trace_kernel<false>,
-                           dim3((waves + 3) / 4), dim3(256), 0, ctx->stream, smap, amap, gp,
-                           r->radius, r->psi0, N, nr, tp->max_steps, tp->ds, tp->c0, e0, E, sb,
+        const bool ahead = waves <= (a_w ? AHEAD_WAVES_LOSSY : AHEAD_WAVES) * ctx->n_cu;
+        hipLaunchKernelGGL(ahead ? (a_w ? trace_ahead_kernel<true> : trace_ahead_kernel<false>)
+                                 : (a_w ? trace_kernel<true> : trace_kernel<false>),
+                           dim3(ahead ? waves : (waves + 3) / 4), dim3(ahead ? 64 : 256), 0,
+                           ctx->stream, smap, amap, gp, r->radius, r->psi0, N, nr, tp->max_steps, tp->ds, tp->c0, e0, E, sb,
                            ctx->d_flag, nsamp);
         RB_CHECK_LAUNCH(ctx);
         rb_prof_end(ctx);
