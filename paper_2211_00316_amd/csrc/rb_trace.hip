@@ -797,27 +797,10 @@ constexpr int LOCATE_THREADS = LTX * LTY / LOCATE_NPL;
 constexpr int LOCATE_WAVES = LOCATE_THREADS / 64;
 constexpr int LOCATE_GROUP_ROWS = 2;  // tile rows per XCD group
 
-// The two triangles of quad (j, i) with corners p00 (ray j, step i), p10 (ray j + 1, step i),
-// p01 (ray j, step i + 1), p11: half 0 = (p00, p10, p11), half 1 = (p00, p11, p01). Returns
-// the half that holds (pu, pv) with its barycentric coordinates, or -1.
-__device__ __forceinline__ int quad_test(float2 p00, float2 p10, float2 p01, float2 p11,
-                                         float pu, float pv, float lam[3]) {
-    // both triangles without a branch: the lanes of a wave hold both kinds
-    float l0[3] = {}, l1[3] = {};
-    const bool a0 = barycentric(p00.x, p00.y, p10.x, p10.y, p11.x, p11.y, pu, pv, l0[0], l0[1],
-                                l0[2]);
-    const bool a1 = barycentric(p00.x, p00.y, p11.x, p11.y, p01.x, p01.y, pu, pv, l1[0], l1[1],
-                                l1[2]);
-    const float eps = -RB_BARY_EPS;
-    const bool h0 = a0 & (l0[0] >= eps) & (l0[1] >= eps) & (l0[2] >= eps);
-    const bool h1 = a1 & (l1[0] >= eps) & (l1[1] >= eps) & (l1[2] >= eps);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) lam[k] = h0 ? l0[k] : l1[k];
-    return h0 ? 0 : h1 ? 1 : -1;
-}
-
 // posE, Mrow: the transducer's samples and last-sample indices (uniform over a workgroup in
-// the walk); vb: the found triangle's vertices as sample offsets from posE. CYCLES: give up once
+// the walk); vb: the found triangle's vertices as sample offsets from posE. The two triangles of
+// quad (j, i) with corners p00 (ray j, step i), p10 (ray j + 1, step i), p01 (ray j, step i + 1),
+// p11: half 0 = (p00, p10, p11), half 1 = (p00, p11, p01). CYCLES: give up once
 // the walk returns to a quad it has been at (the next quad depends on the quad alone, so it would
 // go round until max_it); the quad it is compared with is renewed at each power of two steps.
 template <bool CYCLES = false>
@@ -825,10 +808,18 @@ __device__ __forceinline__ bool mesh_walk(const float2 *__restrict__ posE,
                                           const int32_t *__restrict__ Mrow, int n_rays, float pu,
                                           float pv, int &j, int &i, uint32_t vb[3], float lam[3],
                                           int &half, int max_it = LOCATE_MAX_IT) {
+    // Byte offsets fit 32 bits: n_rays <= 2048 and i <= 100000 (checked by the entry points), 16 bytes
+    // a sample at most.
+    const char *row0 = reinterpret_cast<const char *>(posE);
+    const char *row1 = reinterpret_cast<const char *>(posE + n_rays);
+    const char *ends = reinterpret_cast<const char *>(Mrow);
     int js = -1, is = 0;
+    bool found = false;
+    bool h0 = false;
+    float l0[3], l1[3];
     for (int it = 0; it < max_it; ++it) {
         if constexpr (CYCLES) {
-            if (j == js && i == is) return false;
+            if (j == js && i == is) break;
             if ((it & (it + 1)) == 0) {  // 0, 1, 3, 7, ...
                 js = j;
                 is = i;
@@ -837,53 +828,64 @@ __device__ __forceinline__ bool mesh_walk(const float2 *__restrict__ posE,
         // rays j and j+1 are adjacent in memory: one load per pair (j <= n_rays - 2). The
         // positions are fetched with M (i <= S - 2, so both rows lie in the buffer) and again in
         // the rare case that i is past the rays' ends.
-        const i2u Mv = *reinterpret_cast<const i2u *>(Mrow + j);
-        uint32_t b00 = (uint32_t)(i * n_rays + j), b01 = b00 + (uint32_t)n_rays;
-        f4u q0 = *reinterpret_cast<const f4u *>(posE + b00);
-        f4u q1 = *reinterpret_cast<const f4u *>(posE + b01);
+        const i2u Mv = *reinterpret_cast<const i2u *>(ends + ((uint32_t)j << 2));
+        uint32_t at = (__umul24((uint32_t)i, (uint32_t)n_rays) + (uint32_t)j) << 3;
+        f4u q0 = *reinterpret_cast<const f4u *>(row0 + at);
+        f4u q1 = *reinterpret_cast<const f4u *>(row1 + at);
         // one wait for all three: the compiler moved the positions' loads behind the test of M
         int Mj = Mv.x, Mj1 = Mv.y;
         asm volatile("" : "+v"(q0), "+v"(q1), "+v"(Mj), "+v"(Mj1));
         const int top = min(Mj, Mj1) - 1;  // last quad index along the rays
-        if (top < 1) return false;
+        if (top < 1) break;
         if (i > top) {
             i = top;
-            b00 = (uint32_t)(i * n_rays + j);
-            b01 = b00 + (uint32_t)n_rays;
-            q0 = *reinterpret_cast<const f4u *>(posE + b00);
-            q1 = *reinterpret_cast<const f4u *>(posE + b01);
+            at = (__umul24((uint32_t)i, (uint32_t)n_rays) + (uint32_t)j) << 3;
+            q0 = *reinterpret_cast<const f4u *>(row0 + at);
+            q1 = *reinterpret_cast<const f4u *>(row1 + at);
         }
         const float2 p00 = make_float2(q0.x, q0.y), p10 = make_float2(q0.z, q0.w);
         const float2 p01 = make_float2(q1.x, q1.y), p11 = make_float2(q1.z, q1.w);
-        const int h = quad_test(p00, p10, p01, p11, pu, pv, lam);
-        if (h >= 0) {
-            vb[0] = b00;
-            vb[1] = h == 0 ? b00 + 1 : b01 + 1;
-            vb[2] = h == 0 ? b01 + 1 : b01;
-            half = h;
-            return true;
+        // both triangles without a branch: the lanes of a wave hold both kinds
+        const bool a0 = barycentric(p00.x, p00.y, p10.x, p10.y, p11.x, p11.y, pu, pv, l0[0],
+                                    l0[1], l0[2]);
+        const bool a1 = barycentric(p00.x, p00.y, p11.x, p11.y, p01.x, p01.y, pu, pv, l1[0],
+                                    l1[1], l1[2]);
+        h0 = a0 & (fminf(fminf(l0[0], l0[1]), l0[2]) >= -RB_BARY_EPS);
+        const bool h1 = a1 & (fminf(fminf(l1[0], l1[1]), l1[2]) >= -RB_BARY_EPS);
+        if (h0 | h1) {
+            found = true;
+            break;
         }
         // step across the quad edge the point lies farthest outside of
         float area = (p10.x - p00.x) * (p01.y - p00.y) - (p10.y - p00.y) * (p01.x - p00.x);
         float sg = area >= 0.f ? 1.f : -1.f;
         auto side = [&](float2 a, float2 b) {
             float ex = b.x - a.x, ey = b.y - a.y;
-            float cr = ex * (pv - a.y) - ey * (pu - a.x);
-            return sg * cr * __builtin_amdgcn_rsqf(ex * ex + ey * ey + 1e-30f);
+            float cr = fmaf(ex, pv - a.y, -(ey * (pu - a.x)));
+            return sg * cr * __builtin_amdgcn_rsqf(fmaf(ex, ex, fmaf(ey, ey, 1e-30f)));
         };
         float s_i0 = side(p00, p10);   // edge at step i
         float s_j1 = side(p10, p11);   // edge along ray j+1
         float s_i1 = side(p11, p01);   // edge at step i+1
         float s_j0 = side(p01, p00);   // edge along ray j
         float worst = fminf(fminf(s_i0, s_j1), fminf(s_i1, s_j0));
-        if (worst >= 0.f) return false;  // inside the quad but in neither triangle
         const bool i0 = worst == s_i0, i1 = !i0 & (worst == s_i1);
         const bool j0 = !i0 & !i1 & (worst == s_j0);
         i += (int)i1 - (int)i0;
         j += (int)!(i0 | i1 | j0) - (int)j0;
-        if ((i < 1) | (i > top) | (j < 0) | (j > n_rays - 2)) return false;
+        // (worst >= 0: inside the quad but in neither triangle)
+        if ((worst >= 0.f) | (i < 1) | (i > top) | (j < 0) | (j > n_rays - 2)) break;
     }
-    return false;
+    if (!found) return false;
+    const uint32_t b00 = __umul24((uint32_t)i, (uint32_t)n_rays) + (uint32_t)j;
+    const uint32_t b01 = b00 + (uint32_t)n_rays;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) lam[k] = h0 ? l0[k] : l1[k];
+    vb[0] = b00;
+    vb[1] = h0 ? b00 + 1 : b01 + 1;
+    vb[2] = h0 ? b01 + 1 : b01;
+    half = h0 ? 0 : 1;
+    return true;
 }
 
 // Straight-ray guess of the quad holding the point at (ddx, ddy) from the source: launch
@@ -1077,17 +1079,19 @@ __device__ __forceinline__ float wave_max(float x) {
 // record is written and its key seeds keys[] (changed[] cleared); the rasterisation of the
 // fan then replaces it where a triangle with a smaller key covers the node.
 // The walks are chains of dependent gathers (2.4 quads a node, 8 for a wave's two rows), half of
-// them served by HBM. One wait a quad instead of two, both triangles tested without a branch, no
-// scratch (a choice of row pointers at run time had gone there) and 6 waves per SIMD, whose
-// registers end the spills: 1735 -> 1540 us for 256 transducers of 152088 nodes, 3.0 + 2.1 -> 2.6
-// + 1.7 GB. Wider strips of nodes (64 x 4: slower; 32 x 8, 8 x 8 per wave: the same), stores past
-// the cache (slower) and other groups of rows (the same) were tried.
+// them served by HBM, with about as many vector instructions in between. One wait a quad instead of
+// two, both triangles tested without a branch, 32-bit offsets, no scratch (a choice of row pointers
+// at run time had gone there) and no spilled scalars: tables of 256 transducers of 152088 nodes
+// 1735 -> 1550 us, 3.0 + 2.1 -> 2.6 + 1.7 GB; records of 1024 transducers of 636160 nodes 13.1 ->
+// 12.1 ms. 6 waves per SIMD for tables (8: 1630 us), 8 for records (6: half a millisecond more). Wider strips of
+// nodes (64 x 4: slower; 32 x 8, 8 x 8 per wave: the same), stores past the cache (slower) and
+// other groups of rows (the same) were tried.
 // Workgroups are dealt to the 8 XCDs round-robin by launch index. The (transducer, tile)
 // sequence is cut into groups of LOCATE_GROUP_ROWS tile rows and group g goes to XCD g mod 8,
 // so neighbouring tiles share their ray samples through one L2 while every XCD still gets an
 // even mix of the disk-shaped mask. The launch is padded to a multiple of 8 groups.
 template <bool REC>
-__global__ void __launch_bounds__(LOCATE_THREADS, 6) locate_kernel(SampleBufs sb, int n_rays, int S, int E,
+__global__ void __launch_bounds__(LOCATE_THREADS, REC ? 8 : 6) locate_kernel(SampleBufs sb, int n_rays, int S, int E,
                                                      int e0, GridP g, double R, double psi0,
                                                      int N, double ds, double c0, int n_mask,
                                                      int tile_i0, int tile_j0, int tiles_x,
