@@ -1255,6 +1255,10 @@ __global__ void __launch_bounds__(1024) folded_list(const int32_t *__restrict__ 
 }
 
 constexpr int FOLD_GRID = 2048;  // workgroups of the grid-stride kernels
+// Most workgroups of the marking pass: segments past the rays' ends cost little and the others much,
+// which evens out over more than the 6 per CU that are resident (256 transducers: 416 us with 1536
+// workgroups, 369 with 8192, 358 with 16384, 457 with one segment per wave).
+constexpr size_t MARK_GRID = 16384;
 
 // The rasterisation's item is a run of RCH quads along a pair of neighbouring rays (j, j+1;
 // samples i0 to i1, i0 >= 1, i1 <= min(M_j, M_j+1)). A run's positions are loaded at once (one
@@ -1266,18 +1270,62 @@ struct RasterRun {
     int i0, i1;      // empty: i0 >= i1
 };
 
+// The runs of a fan in segments of 64, one wave each: lane's run (chunk c of RCH quads, ray pair
+// j of nq), false past the last one. magic: 2^32 / nq, rounded up.
+inline __host__ __device__ uint32_t raster_segs(int n_rays, int S) {
+    return ((uint32_t)((S + RCH - 1) / RCH) * (uint32_t)(n_rays - 1) + 63) / 64;
+}
+__device__ __forceinline__ bool segment_run(uint32_t sg, uint32_t nq, uint32_t per, uint32_t magic,
+                                            int lane, int &c, int &j) {
+    const uint32_t r0 = sg * 64, r = r0 + (uint32_t)lane;
+    if (nq < 64) {
+        c = (int)(r / nq);
+        j = (int)(r - (uint32_t)c * nq);
+    } else {  // scalar: the quotient of r0 is exact or one too large
+        c = (int)__umulhi(r0, magic);
+        int rem = (int)(r0 - (uint32_t)c * nq);
+        if (rem < 0) {
+            --c;
+            rem += (int)nq;
+        }
+        j = rem + lane;
+        if (j >= (int)nq) {
+            ++c;
+            j -= (int)nq;
+        }
+    }
+    return r < per;
+}
+
+// The run of every lane of a wave (live: it has one). 32-bit byte offsets as in mesh_walk.
 __device__ __forceinline__ RasterRun raster_run(const SampleBufs &sb, int n_rays, int S, int el,
-                                                int c, int j) {
+                                                bool live, int c, int j) {
     RasterRun r;
-    const i2u Mv = *reinterpret_cast<const i2u *>(sb.M + (size_t)el * n_rays + j);
-    const int top = min(Mv.x, Mv.y);  // quads i with i + 1 <= top; -1: no ray
-    r.i0 = max(c * RCH, 1);
-    r.i1 = min(c * RCH + RCH, top);
-    if (r.i0 >= r.i1) return r;
-    const float2 *p = sb.pos + ((size_t)el * S + r.i0) * n_rays + j;
+    r.i0 = 1;
+    r.i1 = 0;
+    if (live) {
+        const i2u Mv = *reinterpret_cast<const i2u *>(
+            reinterpret_cast<const char *>(sb.M + (size_t)el * n_rays) + ((uint32_t)j << 2));
+        // quads i with i + 1 <= min(M_j, M_j+1); -1: no ray
+        r.i0 = max(c * RCH, 1);
+        r.i1 = min(c * RCH + RCH, min(Mv.x, Mv.y));
+    }
+    const bool some = r.i0 < r.i1, whole = __all(!some || r.i1 - r.i0 == RCH);
+    if (!some) return r;
+    const float2 *p = sb.pos + (size_t)el * S * n_rays;
+    const uint32_t at = (__umul24((uint32_t)r.i0, (uint32_t)n_rays) + (uint32_t)j) << 3;
+    if (whole) {
 #pragma unroll
-    for (int k = 0; k <= RCH; ++k)
-        r.q[k] = *reinterpret_cast<const f4u *>(p + (size_t)min(k, r.i1 - r.i0) * n_rays);
+        for (int k = 0; k <= RCH; ++k)
+            r.q[k] = *reinterpret_cast<const f4u *>(
+                reinterpret_cast<const char *>(p + (size_t)k * n_rays) + at);
+    } else {
+#pragma unroll
+        for (int k = 0; k <= RCH; ++k)
+            r.q[k] = *reinterpret_cast<const f4u *>(
+                reinterpret_cast<const char *>(p) +
+                (at + (__umul24((uint32_t)min(k, r.i1 - r.i0), (uint32_t)n_rays) << 3)));
+    }
     return r;
 }
 
@@ -1302,8 +1350,7 @@ inline size_t raster_lds_bytes(int ny) {
 }
 
 // Tiles a run's bounding box touches.
-__device__ __forceinline__ void run_tiles(const RasterRun &run, int nx, int ny, int &ti0,
-                                          int &ti1, int &tj0, int &tj1) {
+__device__ __forceinline__ void run_box(const RasterRun &run, float (&bu)[3], float (&bv)[3]) {
     float umin = 3.0e38f, umax = -3.0e38f, vmin = 3.0e38f, vmax = -3.0e38f;
 #pragma unroll
     for (int k = 0; k <= RCH; ++k) {
@@ -1312,40 +1359,99 @@ __device__ __forceinline__ void run_tiles(const RasterRun &run, int nx, int ny, 
         vmin = fminf(vmin, fminf(run.q[k].y, run.q[k].w));
         vmax = fmaxf(vmax, fmaxf(run.q[k].y, run.q[k].w));
     }
-    const float bu[3] = {umin, umax, umax}, bv[3] = {vmin, vmax, vmax};
-    bbox_tiles(bu, bv, nx, ny, ti0, ti1, tj0, tj1);
+    bu[0] = umin;
+    bu[1] = bu[2] = umax;
+    bv[0] = vmin;
+    bv[1] = bv[2] = vmax;
 }
-// Marking pass: the tiles that inverted or near-degenerate triangles touch.
+
+// Smallest value over the 16 lanes of a row, in each of them.
+template <int CTRL>
+__device__ __forceinline__ float dpp_min(float x) {
+    return fminf(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF,
+                                                               0xF, false)));
+}
+__device__ __forceinline__ float row_min(float x) {
+    return dpp_min<0x140>(dpp_min<0x141>(dpp_min<0x4E>(dpp_min<0xB1>(x))));
+}
+
+// A segment's boxes cover 16 runs each: the tiles they touch. x: first tile row, y: first and last
+// tile column (13 bits each: a grid has at most 65535 columns; none where first > last) and the
+// rows past the first, RBOX_TALL for as many or more (then the box counts as touched).
+constexpr uint32_t RBOX_TALL = 63;
+constexpr int RBOX = 16, RBOXES = 64 / RBOX;
+
+// Marking pass: the tiles that inverted or near-degenerate triangles touch, and the segments'
+// boxes for the smallest-key pass. Bound by its loads' latency (6 waves per SIMD) and about 300
+// vector instructions a segment: the areas of a run are formed without a branch, a whole segment
+// reads its rows at scalar offsets, and quotients by the ray pairs are scalar.
 __global__ void __launch_bounds__(256) mark_kernel(SampleBufs sb, int n_rays, int S, int nx,
                                                    int ny, const int32_t *__restrict__ flist,
                                                    uint8_t *__restrict__ marks, int mtx,
-                                                   int mtiles) {
+                                                   int mtiles, uint2 *__restrict__ boxes) {
     const uint32_t nq = (uint32_t)n_rays - 1, per = (uint32_t)((S + RCH - 1) / RCH) * nq;
-    const uint32_t blocks = (per + 255) / 256;  // workgroups' worth of items of one fan
-    const size_t total = (size_t)flist[0] * blocks;
-    for (size_t b = blockIdx.x; b < total; b += gridDim.x) {  // uniform over the workgroup
-        const uint32_t f = (uint32_t)(b / blocks);
-        const uint32_t r = (uint32_t)(b - (size_t)f * blocks) * 256 + threadIdx.x;
-        if (r >= per) continue;
-        const int el = flist[1 + f], c = (int)(r / nq), j = (int)(r - (uint32_t)c * nq);
-        const RasterRun run = raster_run(sb, n_rays, S, el, c, j);
-        uint8_t *em = marks + (size_t)el * mtiles;
-#pragma unroll
-        for (int k = 0; k < RCH; ++k) {
-            if (run.i0 + k >= run.i1) break;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
+    const uint32_t segs = raster_segs(n_rays, S), magic = ~0u / nq + 1;
+    const int lane = threadIdx.x & 63, nf = flist[0];
+    const uint32_t wave = blockIdx.x * 4 + (threadIdx.x >> 6), stride = gridDim.x * 4;
+    const uint32_t df = stride / segs, ds = stride - df * segs;
+    uint32_t f = __builtin_amdgcn_readfirstlane(wave / segs);
+    uint32_t sg = __builtin_amdgcn_readfirstlane(wave) - f * segs;
+    for (; f < (uint32_t)nf; f += df, sg += ds) {
+        if (sg >= segs) {
+            sg -= segs;
+            if (++f >= (uint32_t)nf) break;
+        }
+        const int el = flist[1 + f];
+        int c, j;
+        const bool live = segment_run(sg, nq, per, magic, lane, c, j);
+        const RasterRun run = raster_run(sb, n_rays, S, el, live, c, j);
+        float bu[3] = {3.0e38f, -3.0e38f, -3.0e38f}, bv[3] = {3.0e38f, -3.0e38f, -3.0e38f};
+        if (run.i0 < run.i1) {
+            run_box(run, bu, bv);
+            auto area = [&](int k, int h) {
                 float tu[3], tv[3];
                 raster_half(run.q[k], run.q[k + 1], h, tu, tv);
-                const float area =
-                    (tu[1] - tu[0]) * (tv[2] - tv[0]) - (tv[1] - tv[0]) * (tu[2] - tu[0]);
-                if (area > AREA_MARK) {
-                    int ti0, ti1, tj0, tj1;
-                    bbox_tiles(tu, tv, nx, ny, ti0, ti1, tj0, tj1);
-                    for (int tj = tj0; tj <= tj1; ++tj)
-                        for (int ti = ti0; ti <= ti1; ++ti) em[tj * mtx + ti] = 1;
+                return fmaf(tu[1] - tu[0], tv[2] - tv[0], -((tv[1] - tv[0]) * (tu[2] - tu[0])));
+            };
+            float worst = -3.0e38f;
+#pragma unroll
+            for (int k = 0; k < RCH; ++k) {
+                const float a = fmaxf(area(k, 0), area(k, 1));
+                worst = run.i0 + k < run.i1 ? fmaxf(worst, a) : worst;
+            }
+            if (worst > AREA_MARK) {
+                uint8_t *em = marks + (size_t)el * mtiles;
+#pragma unroll
+                for (int k = 0; k < RCH; ++k) {
+                    if (run.i0 + k >= run.i1) break;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        if (area(k, h) > AREA_MARK) {
+                            float tu[3], tv[3];
+                            raster_half(run.q[k], run.q[k + 1], h, tu, tv);
+                            int ti0, ti1, tj0, tj1;
+                            bbox_tiles(tu, tv, nx, ny, ti0, ti1, tj0, tj1);
+                            for (int tj = tj0; tj <= tj1; ++tj)
+                                for (int ti = ti0; ti <= ti1; ++ti) em[tj * mtx + ti] = 1;
+                        }
+                    }
                 }
             }
+        }
+        bu[0] = row_min(bu[0]);
+        bu[1] = bu[2] = -row_min(-bu[1]);
+        bv[0] = row_min(bv[0]);
+        bv[1] = bv[2] = -row_min(-bv[1]);
+        if ((lane & (RBOX - 1)) == 0) {
+            int ti0 = 1, ti1 = 0, tj0 = 0, tj1 = 0;
+            if (bu[0] <= bu[1] && bu[0] < (float)nx && bv[0] < (float)ny && bu[1] > -1.0f &&
+                bv[1] > -1.0f)
+                bbox_tiles(bu, bv, nx, ny, ti0, ti1, tj0, tj1);
+            boxes[((size_t)el * segs + sg) * RBOXES + lane / RBOX] =
+                ti0 > ti1 || tj0 > tj1
+                    ? make_uint2(0u, 1u)
+                    : make_uint2((uint32_t)tj0, (uint32_t)ti0 | (uint32_t)ti1 << 13 |
+                                                    min((uint32_t)(tj1 - tj0), RBOX_TALL) << 26);
         }
     }
 }
@@ -1362,8 +1468,11 @@ __global__ void __launch_bounds__(256) mark_kernel(SampleBufs sb, int n_rays, in
 // about 15 ns each, which bound the pass. Both kernels together, against that counter and a lane
 // per run rasterising its triangles in turn: 0.08 against 0.69 ms (64 transducers, 128^2 nodes),
 // 1.4 against 2.3 ms (256, 512^2, narrow window), 2.0 against 2.7 ms (1024, 1024^2). The lists'
-// counters lie in lines of their own for the same reason. (Writing each run's tiles in the marking pass, 4 bytes a run, to read those
-// instead of the positions here gained nothing: the sorting is bound by its instructions.)
+// counters lie in lines of their own for the same reason. The marking pass leaves
+// the tiles of every 16 runs, 8 bytes; where none of them is marked, the positions are not read
+// again. Both passes, with those boxes: 1024 transducers of 1024 rays 3.10 -> 2.24 ms, 256 of 720
+// 0.81 -> 0.69 ms at a narrow window and 0.69 -> 0.55 ms at a wide one. (Boxes of single runs gained
+// nothing: this pass is bound by its instructions.)
 // A queued quad: x = i, y = chunk transducer << 11 | ray.
 struct RasterOut {
     unsigned long long *keys;
@@ -1424,8 +1533,10 @@ constexpr int RQ = RFLUSH + 64;    // its queue: fewer than RFLUSH left over, at
 __global__ void __launch_bounds__(256) raster_kernel(SampleBufs sb, int n_rays, int S,
                                                      const int2 *__restrict__ qrow_g,
                                                      const int32_t *__restrict__ flist,
-                                                     RasterOut o, uint2 *__restrict__ list,
-                                                     uint32_t cap, uint32_t *__restrict__ count) {
+                                                     RasterOut o,
+                                                     const uint2 *__restrict__ boxes,
+                                                     uint2 *__restrict__ list, uint32_t cap,
+                                                     uint32_t *__restrict__ count) {
     extern __shared__ int2 s_qrow[];  // raster_lds_bytes(ny)
     __shared__ uint2 s_queue[4][RQ];
     const int nx = o.nx, ny = o.ny, mtx = o.mtx;
@@ -1459,7 +1570,7 @@ __global__ void __launch_bounds__(256) raster_kernel(SampleBufs sb, int n_rays, 
         }
     };
     // segments of 64 runs of one fan: segs per fan, `stride` segments on from one to the next
-    const uint32_t segs = (per + 63) / 64;
+    const uint32_t segs = raster_segs(n_rays, S), magic = ~0u / nq + 1;
     const uint32_t wave = blockIdx.x * 4 + (threadIdx.x >> 6), stride = gridDim.x * 4;
     const uint32_t df = stride / segs, ds = stride - df * segs;
     uint32_t f = __builtin_amdgcn_readfirstlane(wave / segs);
@@ -1470,25 +1581,31 @@ __global__ void __launch_bounds__(256) raster_kernel(SampleBufs sb, int n_rays, 
             if (++f >= (uint32_t)nf) break;
         }
         {
-            const uint32_t r = sg * 64 + (uint32_t)lane;
-            const bool live = r < per;
-            RasterRun run;
-            run.i0 = 1;
-            run.i1 = 0;
-            int el = 0, j = 0;
+            const int el = flist[1 + f];
+            const uint8_t *em = o.marks + (size_t)el * o.mtiles;
+            // sixteen runs whose box touches no marked tile end before their positions are read
+            const uint2 bx = boxes[((size_t)el * segs + sg) * RBOXES + lane / RBOX];
+            const uint32_t rows = bx.y >> 26;
+            const int ti1 = (int)(bx.y >> 13 & 8191u);
+            bool touched = rows == RBOX_TALL;
+            if (!touched)
+                for (uint32_t tj = bx.x; tj <= bx.x + rows; ++tj)
+                    for (int ti = (int)(bx.y & 8191u) + (lane & (RBOX - 1)); ti <= ti1; ti += RBOX)
+                        touched |= em[tj * mtx + ti] != 0;
+            const unsigned long long hit = __ballot(touched);
+            if (hit == 0) continue;
+            int c, j;
+            const bool live = segment_run(sg, nq, per, magic, lane, c, j) &&
+                              (hit >> (lane & ~(RBOX - 1)) & ((1ull << RBOX) - 1)) != 0;
+            const RasterRun run = raster_run(sb, n_rays, S, el, live, c, j);
             bool any = false;
-            if (live) {
-                const uint32_t c = r / nq;
-                el = flist[1 + f];
-                j = (int)(r - c * nq);
-                run = raster_run(sb, n_rays, S, el, (int)c, j);
-                if (run.i0 < run.i1) {
-                    int ti0, ti1, tj0, tj1;
-                    run_tiles(run, nx, ny, ti0, ti1, tj0, tj1);
-                    const uint8_t *em = o.marks + (size_t)el * o.mtiles;
-                    for (int tj = tj0; tj <= tj1 && !any; ++tj)
-                        for (int ti = ti0; ti <= ti1; ++ti) any |= em[tj * mtx + ti] != 0;
-                }
+            if (run.i0 < run.i1) {
+                float bu[3], bv[3];
+                run_box(run, bu, bv);
+                int ti0, ti1, tj0, tj1;
+                bbox_tiles(bu, bv, nx, ny, ti0, ti1, tj0, tj1);
+                for (int tj = tj0; tj <= tj1 && !any; ++tj)
+                    for (int ti = ti0; ti <= ti1; ++ti) any |= em[tj * mtx + ti] != 0;
             }
             if (!__any(any)) continue;
 #pragma unroll
@@ -2059,7 +2176,8 @@ static size_t trace_bytes(const rb_grid *g, const rb_ring *r, const rb_trace_par
            rb_align((size_t)(g->nx + 3) * (g->ny + 3) * 4 * sizeof(float4)) +
            rb_align((size_t)C * r->n * sizeof(int32_t)) +
            rb_align((size_t)C * tiles * LOCATE_WAVES * 2 * sizeof(float)) +
-           rb_align(RSHARDS * raster_cap(plane) * sizeof(uint2));
+           rb_align(RSHARDS * raster_cap(plane) * sizeof(uint2)) +
+           rb_align((size_t)C * raster_segs(nr, S) * RBOXES * sizeof(uint2));
 }
 
 size_t rb_trace_ws_bytes(const rb_grid *g, const rb_ring *r, const rb_trace_params *tp,
@@ -2114,6 +2232,7 @@ rb_status rb_launch_trace(rb_ctx *ctx, const rb_grid *g, const rb_ring *r,
     int32_t *rx_j = rb_carve<int32_t>(&ctx->ws, (size_t)C * N);
     float4 *coef = rb_carve<float4>(&ctx->ws, (size_t)(g->nx + 3) * (g->ny + 3) * 4);
     uint2 *rlist = rb_carve<uint2>(&ctx->ws, RSHARDS * raster_cap(plane));
+    uint2 *boxes = rb_carve<uint2>(&ctx->ws, (size_t)C * raster_segs(nr, S) * RBOXES);
     SplineMap smap{coef, g->nx, g->ny, g->nx + 3, (float)(1.0 / g->dx)};
 
     GridP gp{g->nx, g->ny, g->dx, g->x0, g->y0, 1.0 / g->dx};
@@ -2161,8 +2280,10 @@ rb_status rb_launch_trace(rb_ctx *ctx, const rb_grid *g, const rb_ring *r,
         hipLaunchKernelGGL(folded_list, dim3(1), dim3(1024), 0, ctx->stream, sb.folded, E, flist,
                            rcount);
         RB_CHECK_LAUNCH(ctx);
-        hipLaunchKernelGGL(mark_kernel, dim3(FOLD_GRID), dim3(256), 0, ctx->stream, sb, nr, S,
-                           g->nx, g->ny, flist, marks, mtx, mtiles);
+        const uint32_t mark_grid = (uint32_t)std::min<size_t>(
+            ((size_t)E * raster_segs(nr, S) + 3) / 4, MARK_GRID);
+        hipLaunchKernelGGL(mark_kernel, dim3(mark_grid), dim3(256), 0, ctx->stream, sb, nr, S,
+                           g->nx, g->ny, flist, marks, mtx, mtiles, boxes);
         RB_CHECK_LAUNCH(ctx);
         rb_prof_end(ctx);
         // every fan: walk per (transducer, node); for folded fans also the seed keys
@@ -2199,8 +2320,7 @@ rb_status rb_launch_trace(rb_ctx *ctx, const rb_grid *g, const rb_ring *r,
         // the nodes it changed
         rb_prof_begin(ctx, ST_RASTER);
         // as many workgroups as are resident at once (with 2048, registers and LDS let 5 or 6
-        // per CU run and the rest waited for a second round); their waves take the items from
-        // the counter folded_list zeroed
+        // per CU run and the rest waited for a second round)
         const size_t rlds = raster_lds_bytes(g->ny);
         int rpc = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&rpc, raster_kernel, 256, rlds) !=
@@ -2211,7 +2331,8 @@ rb_status rb_launch_trace(rb_ctx *ctx, const rb_grid *g, const rb_ring *r,
         }
         const RasterOut ro{keys, changed, marks, g->nx, g->ny, n_mask, mtx, mtiles};
         hipLaunchKernelGGL(raster_kernel, dim3(rpc * ctx->n_cu), dim3(256), rlds, ctx->stream, sb,
-                           nr, S, ctx->d_qrow, flist, ro, rlist, (uint32_t)raster_cap(plane), rcount);
+                           nr, S, ctx->d_qrow, flist, ro, boxes, rlist, (uint32_t)raster_cap(plane),
+                           rcount);
         RB_CHECK_LAUNCH(ctx);
         hipLaunchKernelGGL(raster_list_kernel, dim3(RSHARDS * 32), dim3(256), rlds, ctx->stream,
                            sb, nr, S, ctx->d_qrow, ro, rlist, (uint32_t)raster_cap(plane), rcount);
