@@ -1155,8 +1155,9 @@ __global__ void __launch_bounds__(LOCATE_THREADS, REC ? 8 : 6) locate_kernel(Sam
 
 
 // Offer triangle tid to every mask node it covers. Keys only decrease, so a stale read of a
-// node's key costs at most a needless atomic; a node whose key this triangle lowers is
-// marked changed (its record is then rebuilt by the resolve pass).
+// node's key costs at most a needless atomic; a node whose key this triangle finds larger is
+// marked changed (its record is then rebuilt by the resolve pass): if this triangle did not lower
+// it, one with a smaller key has. So nothing waits for the atomic.
 // qrow: per grid row, the mask's run of nodes (first | last << 16) and the mask index of node
 // i of the row minus i (the mask is a disc: one run per row).
 __device__ __forceinline__ void raster_tri(const float *tu, const float *tv, const float *tdT,
@@ -1218,8 +1219,8 @@ __device__ __forceinline__ void raster_tri(const float *tu, const float *tv, con
             if (la < -RB_BARY_EPS || lb < -RB_BARY_EPS || lc < -RB_BARY_EPS) continue;
             const unsigned long long key = tri_key(tri_dT(la, lb, lc, tdT[0], tdT[1], tdT[2]), tid);
             if (key < keys[q]) {
-                const unsigned long long old = atomicMin(keys + q, key);
-                if (key < old) changed[q] = 1;
+                atomicMin(keys + q, key);
+                changed[q] = 1;
             }
         }
     }
@@ -1254,7 +1255,10 @@ __global__ void __launch_bounds__(1024) folded_list(const int32_t *__restrict__ 
     if (threadIdx.x < RSHARDS) count[threadIdx.x * RSTRIDE] = 0u;
 }
 
-constexpr int FOLD_GRID = 2048;  // workgroups of the grid-stride kernels
+// Workgroups of the resolve pass: more than are resident, since nodes to rebuild are few and far
+// between in most blocks (256 transducers 406 us with 2048, 340 with 8192; 1024 transducers 453 and
+// 345, 430 with 65536).
+constexpr int FOLD_GRID = 8192;
 // Most workgroups of the marking pass: segments past the rays' ends cost little and the others much,
 // which evens out over more than the 6 per CU that are resident (256 transducers: 416 us with 1536
 // workgroups, 369 with 8192, 358 with 16384, 457 with one segment per wave).
@@ -1508,7 +1512,9 @@ __device__ __forceinline__ const int2 *raster_rows(const int2 *qrow_g, int2 *s_q
     return s_qrow;
 }
 
-__global__ void __launch_bounds__(256) raster_list_kernel(SampleBufs sb, int n_rays, int S,
+// Bound by waiting for gathers (marks, samples, keys), hence 8 waves per SIMD, all resident: 256
+// transducers of 720 rays at a narrow window 1065 -> 745 us.
+__global__ void __launch_bounds__(256, 8) raster_list_kernel(SampleBufs sb, int n_rays, int S,
                                                           const int2 *__restrict__ qrow_g,
                                                           RasterOut o,
                                                           const uint2 *__restrict__ list,
@@ -2337,8 +2343,8 @@ rb_status rb_launch_trace(rb_ctx *ctx, const rb_grid *g, const rb_ring *r,
         hipLaunchKernelGGL(raster_list_kernel, dim3(RSHARDS * 32), dim3(256), rlds, ctx->stream,
                            sb, nr, S, ctx->d_qrow, ro, rlist, (uint32_t)raster_cap(plane), rcount);
         RB_CHECK_LAUNCH(ctx);
-        hipLaunchKernelGGL(rec ? resolve_kernel<true> : resolve_kernel<false>, dim3(FOLD_GRID), dim3(256), 0, ctx->stream, sb, nr, S,
-                           e0, gp, tp->ds, tp->c0, n_mask, ctx->d_mask_index, flist, keys,
+        hipLaunchKernelGGL(rec ? resolve_kernel<true> : resolve_kernel<false>, dim3(FOLD_GRID),
+                           dim3(256), 0, ctx->stream, sb, nr, S, e0, gp, tp->ds, tp->c0, n_mask, ctx->d_mask_index, flist, keys,
                            changed, to);
         RB_CHECK_LAUNCH(ctx);
         rb_prof_end(ctx);
