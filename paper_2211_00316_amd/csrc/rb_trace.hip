@@ -1384,6 +1384,7 @@ __device__ __forceinline__ float row_min(float x) {
 // rows past the first, RBOX_TALL for as many or more (then the box counts as touched).
 constexpr uint32_t RBOX_TALL = 63;
 constexpr int RBOX = 16, RBOXES = 64 / RBOX;
+constexpr uint32_t RTURN = 64 / RBOXES;  // most segments whose boxes a wave looks at together
 
 // Marking pass: the tiles that inverted or near-degenerate triangles touch, and the segments'
 // boxes for the smallest-key pass. Bound by its loads' latency (6 waves per SIMD) and about 300
@@ -1474,8 +1475,8 @@ __global__ void __launch_bounds__(256) mark_kernel(SampleBufs sb, int n_rays, in
 // 1.4 against 2.3 ms (256, 512^2, narrow window), 2.0 against 2.7 ms (1024, 1024^2). The lists'
 // counters lie in lines of their own for the same reason. The marking pass leaves
 // the tiles of every 16 runs, 8 bytes; where none of them is marked, the positions are not read
-// again. Both passes, with those boxes: 1024 transducers of 1024 rays 3.10 -> 2.24 ms, 256 of 720
-// 0.81 -> 0.69 ms at a narrow window and 0.69 -> 0.55 ms at a wide one. (Boxes of single runs gained
+// again. Both passes, with those boxes: 1024 transducers of 1024 rays 3.10 -> 1.64 ms, 256 of 720
+// 0.81 -> 0.59 ms at a narrow window and 0.69 -> 0.44 ms at a wide one. (Boxes of single runs gained
 // nothing: this pass is bound by its instructions.)
 // A queued quad: x = i, y = chunk transducer << 11 | ray.
 struct RasterOut {
@@ -1575,34 +1576,45 @@ __global__ void __launch_bounds__(256) raster_kernel(SampleBufs sb, int n_rays, 
             }
         }
     };
-    // segments of 64 runs of one fan: segs per fan, `stride` segments on from one to the next
+    // Turns of `len` segments of one fan, `stride` turns on from one to the next: a lane looks up
+    // the marks under one of their boxes, then the wave takes the segments that have any. Sixteen
+    // where a wave has four such turns or more, shorter ones for less work, whose longest wave
+    // sets the time (64 transducers: 30 us with single segments, 45 with sixteen; 256: 226 and
+    // 118 us).
     const uint32_t segs = raster_segs(n_rays, S), magic = ~0u / nq + 1;
     const uint32_t wave = blockIdx.x * 4 + (threadIdx.x >> 6), stride = gridDim.x * 4;
-    const uint32_t df = stride / segs, ds = stride - df * segs;
-    uint32_t f = __builtin_amdgcn_readfirstlane(wave / segs);
-    uint32_t sg = __builtin_amdgcn_readfirstlane(wave) - f * segs;
-    for (; f < (uint32_t)nf; f += df, sg += ds) {
-        if (sg >= segs) {
-            sg -= segs;
+    uint32_t len = RTURN;
+    while (len > 1 && (size_t)nf * segs < (size_t)stride * 4 * len) len >>= 1;
+    const uint32_t turns = (segs + len - 1) / len;
+    const uint32_t df = stride / turns, ds = stride - df * turns;
+    uint32_t f = __builtin_amdgcn_readfirstlane(wave / turns);
+    uint32_t turn = __builtin_amdgcn_readfirstlane(wave) - f * turns;
+    for (; f < (uint32_t)nf; f += df, turn += ds) {
+        if (turn >= turns) {
+            turn -= turns;
             if (++f >= (uint32_t)nf) break;
         }
-        {
-            const int el = flist[1 + f];
-            const uint8_t *em = o.marks + (size_t)el * o.mtiles;
-            // sixteen runs whose box touches no marked tile end before their positions are read
-            const uint2 bx = boxes[((size_t)el * segs + sg) * RBOXES + lane / RBOX];
+        const int el = flist[1 + f];
+        const uint8_t *em = o.marks + (size_t)el * o.mtiles;
+        bool touched = false;
+        if ((uint32_t)lane < len * RBOXES && turn * len + (uint32_t)lane / RBOXES < segs) {
+            const uint2 bx = boxes[((size_t)el * segs + turn * len) * RBOXES + lane];
             const uint32_t rows = bx.y >> 26;
-            const int ti1 = (int)(bx.y >> 13 & 8191u);
-            bool touched = rows == RBOX_TALL;
+            const int ti0 = (int)(bx.y & 8191u), ti1 = (int)(bx.y >> 13 & 8191u);
+            touched = rows == RBOX_TALL;
             if (!touched)
                 for (uint32_t tj = bx.x; tj <= bx.x + rows; ++tj)
-                    for (int ti = (int)(bx.y & 8191u) + (lane & (RBOX - 1)); ti <= ti1; ti += RBOX)
-                        touched |= em[tj * mtx + ti] != 0;
-            const unsigned long long hit = __ballot(touched);
-            if (hit == 0) continue;
+                    for (int ti = ti0; ti <= ti1; ++ti) touched |= em[tj * mtx + ti] != 0;
+        }
+        unsigned long long hits = __ballot(touched);
+        while (hits != 0) {
+            const int first = __builtin_ctzll(hits) & ~(RBOXES - 1);
+            const uint32_t hit = (uint32_t)(hits >> first) & ((1u << RBOXES) - 1);
+            hits &= ~((unsigned long long)hit << first);
+            const uint32_t sg = turn * len + (uint32_t)first / RBOXES;
             int c, j;
             const bool live = segment_run(sg, nq, per, magic, lane, c, j) &&
-                              (hit >> (lane & ~(RBOX - 1)) & ((1ull << RBOX) - 1)) != 0;
+                              (hit >> (lane / RBOX) & 1u) != 0;
             const RasterRun run = raster_run(sb, n_rays, S, el, live, c, j);
             bool any = false;
             if (run.i0 < run.i1) {
