@@ -1256,9 +1256,8 @@ __global__ void __launch_bounds__(1024) folded_list(const int32_t *__restrict__ 
 }
 
 // Workgroups of the resolve pass: more than are resident, since nodes to rebuild are few and far
-// between in most blocks (256 transducers 406 us with 2048, 340 with 8192; 1024 transducers 453 and
-// 345, 430 with 65536).
-constexpr int FOLD_GRID = 8192;
+// between in most of their strips.
+constexpr int FOLD_GRID = 16384;
 // Most workgroups of the marking pass: segments past the rays' ends cost little and the others much,
 // which evens out over more than the 6 per CU that are resident (256 transducers: 416 us with 1536
 // workgroups, 369 with 8192, 358 with 16384, 457 with one segment per wave).
@@ -1669,8 +1668,8 @@ __global__ void __launch_bounds__(256) raster_kernel(SampleBufs sb, int n_rays, 
 // replaced, interpolate the winning triangle. Returns the amplitude written (0 if none).
 template <bool REC>
 __device__ __forceinline__ float resolve_node(const SampleBufs &sb, int n_rays, int S, int el,
-                                             int q, int e0, const GridP &g, double ds, double c0,
-                                             int n_mask, const int32_t *__restrict__ mask_index,
+                                             int q, int ii, int jj, int e0, const GridP &g,
+                                             double ds, double c0, int n_mask,
                                              const unsigned long long *__restrict__ keys,
                                              const TableOut &to) {
     const size_t tid = (size_t)el * n_mask + q;
@@ -1678,8 +1677,6 @@ __device__ __forceinline__ float resolve_node(const SampleBufs &sb, int n_rays, 
     const TableOut toE = table_row<REC>(to, (size_t)e * n_mask);
     const uint32_t out = (uint32_t)q;
     unsigned long long key = keys[tid];
-    int p = mask_index[q];
-    int ii = p % g.nx, jj = p / g.nx;
     const double2 xy = sb.ring[e];
     double xe = xy.x, ye = xy.y;
     double px = g.x0 + ii * g.dx, py = g.y0 + jj * g.dx;
@@ -1716,70 +1713,76 @@ __device__ __forceinline__ float resolve_node(const SampleBufs &sb, int n_rays, 
     return A;
 }
 
+// A wave takes strips of 64 x 8 nodes of one folded transducer, eight nodes of a row per lane: it
+// queues the changed ones in LDS, row by row, and resolves 64 at a time, one per lane. Neighbouring
+// nodes lie in neighbouring triangles, so a strip shares the lines of its samples, and a row's
+// entries leave together (in mask order, queued eight apart, a node fetched 218 and wrote 77 bytes).
+// Bound by those gathers: 1024 transducers at a narrow window, where half the nodes are rebuilt, 9.2
+// -> 3.9 ms; 256 transducers 340 -> 268 us. The largest A and 1/A a wave writes reach the
+// per-row maxima as one atomic pair (the walk's are folded in by tile_max_fold; max is
+// order-independent).
+constexpr int RES_W = 64, RES_H = 8;
 template <bool REC>
 __global__ void __launch_bounds__(256) resolve_kernel(SampleBufs sb, int n_rays, int S, int e0,
                                                       GridP g, double ds, double c0, int n_mask,
-                                                      const int32_t *__restrict__ mask_index,
+                                                      int tile_i0, int tile_j0, int tiles_x,
+                                                      int tiles_y,
+                                                      const int2 *__restrict__ qrow,
                                                       const int32_t *__restrict__ flist,
                                                       const unsigned long long *__restrict__ keys,
                                                       const uint8_t *__restrict__ changed,
                                                       TableOut to) {
-    // A workgroup takes 2048 consecutive nodes of one folded transducer, eight per lane (their
-    // change marks in one load); each wave queues its changed nodes in LDS and resolves 64 of them
-    // at a time, one per lane. A lane per node spent its time on the marks, 1.6 ms for 1024
-    // transducers of 636160 nodes against 0.5. The largest A and 1/A a wave writes reach the
-    // per-row maxima as one atomic pair (the walk's are folded in by tile_max_fold; max is
-    // order-independent).
-    __shared__ int s_q[4][128];
-    int *queue = s_q[threadIdx.x >> 6];
+    __shared__ uint16_t s_q[4][RES_W * RES_H];  // row of the strip * RES_W + column
+    uint16_t *queue = s_q[threadIdx.x >> 6];
     const int lane = threadIdx.x & 63;
-    const int per = (n_mask + 2047) / 2048;
-    const size_t total = (size_t)flist[0] * per;
-    for (size_t b = blockIdx.x; b < total; b += gridDim.x) {  // uniform over the workgroup
-        const int f = (int)(b / per);
+    const int strips = tiles_y * (LTY / RES_H), per = (tiles_x * LTX + RES_W - 1) / RES_W * strips;
+    // (32 bits: the keys of 2^32 strips would take 16 TB)
+    const uint32_t total = (uint32_t)flist[0] * (uint32_t)per;
+    for (uint32_t b = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); b < total;
+         b += gridDim.x * 4) {
+        const uint32_t f = b / (uint32_t)per;
+        const int t = (int)(b - f * (uint32_t)per);
         const int el = flist[1 + f];
-        const int q0 = ((int)(b - (size_t)f * per) * 256 + (int)threadIdx.x) * 8;
-        const uint8_t *ch = changed + (size_t)el * n_mask + q0;
-        uint32_t set = 0;  // changed nodes, one bit each
-        if (q0 + 8 <= n_mask) {
-            unsigned long long w;
-            __builtin_memcpy(&w, ch, 8);
-            if (w) {  // bytes 0 or 1
+        const int i0 = tile_i0 + t / strips * RES_W, j0 = tile_j0 + t % strips * RES_H;
+        const uint8_t *ch = changed + (size_t)el * n_mask;
+        const int cell = lane * 8, ii = i0 + cell % RES_W, jj = j0 + cell / RES_W;
+        const int2 qr = jj < g.ny ? qrow[jj] : make_int2(1, 0);
+        const int lo = max(ii, (int)((uint32_t)qr.x & 0xffffu)) - ii;
+        const int hi = min(ii + 7, (int)((uint32_t)qr.x >> 16)) - ii, q0 = qr.y + ii;
+        uint32_t set = 0;  // changed nodes of the lane's eight, one bit each
+        if (lo <= hi) {
+            if (q0 >= 0 && q0 + 8 <= n_mask) {
+                unsigned long long w;
+                __builtin_memcpy(&w, ch + q0, 8);
+                if (w) {  // bytes 0 or 1
 #pragma unroll
-                for (int k = 0; k < 8; ++k) set |= (uint32_t)(w >> (8 * k) & 1ull) << k;
+                    for (int k = 0; k < 8; ++k) set |= (uint32_t)(w >> (8 * k) & 1ull) << k;
+                }
+                set &= (2u << hi) - (1u << lo);
+            } else {
+                for (int k = lo; k <= hi; ++k) set |= (ch[q0 + k] != 0 ? 1u : 0u) << k;
             }
-        } else {
-            for (int k = 0; q0 + k < n_mask; ++k) set |= (ch[k] != 0 ? 1u : 0u) << k;
         }
+        if (!__any(set != 0)) continue;
+        int at = __popc(set);  // inclusive sum over the lanes: rows in order
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int v = __shfl_up(at, o);
+            if (lane >= o) at += v;
+        }
+        const int cnt = __shfl(at, 63);
+        at -= __popc(set);
+        for (uint32_t left = set; left; left &= left - 1)
+            queue[at++] = (uint16_t)(cell + __builtin_ctz(left));
+        __builtin_amdgcn_wave_barrier();
         float amax = 0.f, iamax = 0.f;
-        int cnt = 0;
-        auto drain = [&](int n) {
-            if (lane >= n) return;
-            const float A = resolve_node<REC>(sb, n_rays, S, el, queue[lane], e0, g, ds, c0, n_mask,
-                                         mask_index, keys, to);
+        for (int k = lane; k < cnt; k += 64) {
+            const int c = queue[k], ni = i0 + c % RES_W, nj = j0 + c / RES_W;
+            const float A = resolve_node<REC>(sb, n_rays, S, el, qrow[nj].y + ni, ni, nj, e0, g,
+                                              ds, c0, n_mask, keys, to);
             amax = fmaxf(amax, A);
             iamax = fmaxf(iamax, A > 0.f ? 1.0f / A : 0.f);
-        };
-        for (int k = 0; k < 8; ++k) {
-            const bool c = set >> k & 1u;
-            const unsigned long long m = __ballot(c);
-            if (m == 0) continue;
-            if (c)
-                queue[cnt + (int)__builtin_amdgcn_mbcnt_hi(
-                                (uint32_t)(m >> 32),
-                                __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = q0 + k;
-            cnt += __popcll(m);
-            __builtin_amdgcn_wave_barrier();
-            if (cnt >= 64) {
-                drain(64);
-                cnt -= 64;
-                const int t = queue[64 + lane];
-                __builtin_amdgcn_wave_barrier();
-                queue[lane] = t;
-                __builtin_amdgcn_wave_barrier();
-            }
         }
-        drain(cnt);
         __builtin_amdgcn_wave_barrier();
         if (to.rowmax) {
             const float m0 = wave_max(amax), m1 = wave_max(iamax);
@@ -2356,8 +2359,9 @@ rb_status rb_launch_trace(rb_ctx *ctx, const rb_grid *g, const rb_ring *r,
                            sb, nr, S, ctx->d_qrow, ro, rlist, (uint32_t)raster_cap(plane), rcount);
         RB_CHECK_LAUNCH(ctx);
         hipLaunchKernelGGL(rec ? resolve_kernel<true> : resolve_kernel<false>, dim3(FOLD_GRID),
-                           dim3(256), 0, ctx->stream, sb, nr, S, e0, gp, tp->ds, tp->c0, n_mask, ctx->d_mask_index, flist, keys,
-                           changed, to);
+                           dim3(256), 0, ctx->stream, sb, nr, S, e0, gp, tp->ds, tp->c0, n_mask,
+                           ctx->tile_i0, ctx->tile_j0, ctx->tiles_x, ctx->tiles_y, ctx->d_qrow,
+                           flist, keys, changed, to);
         RB_CHECK_LAUNCH(ctx);
         rb_prof_end(ctx);
         rb_prof_begin(ctx, ST_RECEIVERS);
