@@ -27,7 +27,6 @@ if ROOT not in sys.path:
 import hashlib
 import re
 
-FP32_MFMA_PEAK_TFLOPS = 157.3   # MI355X dense FP32 matrix
 HBM_PEAK_GBS = 8000.0
 # FP32 vector arithmetic without packed FP32 instructions (the library is built without
 # them): 256 CUs x 64 lanes x 2 flop (FMA) x 2.4 GHz
@@ -52,8 +51,8 @@ STAGE_KERNELS = {
     "trace": (["trace_kernel"], ["trace_kernel"]),
     "resolve": (["tile_offset_kernel", "locate_kernel"], ["tile_offset_kernel", "locate_kernel"]),
     "build_green": (["green_kernel"], ["green_lp_rec_kernel"]),
-    "forward_gemm": (["forward_kernel"], ["forward_pipe_kernel"]),
-    "backproject_gemm": (["rowred_kernel"], ["rowred_lp_kernel"]),
+    "forward_gemm": (["forward_reg_kernel"], ["forward_pipe_kernel"]),
+    "backproject_gemm": (["rowred_split_kernel"], ["rowred_lp_kernel"]),
 }
 
 
@@ -173,7 +172,7 @@ def cpu_baseline(w):
     }
 
 
-PEAKS = {"f32": (FP32_MFMA_PEAK_TFLOPS, "fp32 MFMA"), "bf16": (2500.0, "bf16 MFMA dense"),
+PEAKS = {"f32": (2500.0, "fp16 MFMA dense (FP32 operands split in two)"), "bf16": (2500.0, "bf16 MFMA dense"),
          "f16": (2500.0, "fp16 MFMA dense"), "f16x": (2500.0, "fp16 MFMA dense")}
 
 
@@ -189,26 +188,27 @@ def contraction_flops(stage, N, Pm, prec):
     complex GEMM count (8 N^2 P_m for the forward, three of them for the back-projection)."""
     own_pairs = N * (N + 1) // 2
     if stage == "forward_gemm":
-        if prec == "f32":   # 128 x 128 upper tiles over K = P_m
+        if prec == "f32":   # 128 x 128 upper tiles over K = P_m, three FP16 products
             nT = _pad(N, 128) // 128
-            issued = 8.0 * nT * (nT + 1) // 2 * 128 * 128 * Pm
+            issued = 3 * 8.0 * (nT * (nT + 1) // 2) * 128 * 128 * Pm
         else:               # 256 x 128 upper tiles over K = P_m padded to 32
             nT = _pad(N, 128) // 128
             tiles = sum(nT - 2 * tm for tm in range((nT + 1) // 2))
             issued = 8.0 * tiles * 256 * 128 * _pad(Pm, 32)
         return issued, 8.0 * own_pairs * Pm, 8.0 * N * N * Pm
     # back-projection: row slabs of 256, K over the transducers (block upper triangle of R, or
-    # the whole symmetric R in the split form), node tiles of 128 (64 in FP32)
+    # the whole symmetric R in the split form), node tiles of 128
     Np = _pad(N, 32)
     mb = _pad(N, 256) // 256
-    cols = _pad(Pm, 64 if prec == "f32" else 128)
+    cols = _pad(Pm, 128)
     tri = sum(256 * (Np - 256 * i) for i in range(mb))   # K values of the block triangle
     if prec == "f16x":
         # two FP16 products over all of Rs (H; b) and one FP8 product (b's low part, K rows
         # padded to 64)
         issued = 16.0 * mb * 256 * Np * cols + 0.5 * 8.0 * mb * 256 * _pad(N, 64) * cols
     elif prec == "f32":
-        issued = 24.0 * tri * cols   # H, H u_x, H u_y over the block triangle
+        # H, H u_x, H u_y over the triangle of 64-row blocks, three FP16 products each
+        issued = 3 * 24.0 * sum(64 * (Np - i) for i in range(0, N, 64)) * cols
     else:
         # H over the block triangle, the bilinear form a^T Rs b over all of Rs
         issued = 8.0 * tri * cols + 8.0 * mb * 256 * Np * cols
@@ -330,12 +330,14 @@ def kernel_rooflines(stages, steps, N, Pm, samples, prec, workload):
         "forward_gemm": ("mfma", contraction_flops("forward_gemm", N, Pm, prec)[0] / 1e12,
                          "TFLOP/s", peak, peak_name,
                          "flop the kernel issues (upper 256 x 128 tiles of the symmetric "
-                         "N x N product, 8 per complex multiply-add over P_m)"),
+                         "N x N product, 8 per complex multiply-add over P_m; FP32: 128 x 128 "
+                         "tiles, 3 products of split operands)"),
         "backproject_gemm": ("mfma",
                              contraction_flops("backproject_gemm", N, Pm, prec)[0] / 1e12,
                              "TFLOP/s", peak, peak_name,
                              "flop the kernel issues (row slabs of 256; FP32: 3 complex "
-                             "products over the block upper triangle of R; 16-bit: H over it "
+                             "products over the upper triangle of R in blocks of 64, each as 3 "
+                             "products of split operands; 16-bit: H over the triangle in slabs "
                              "and the bilinear form a^T Rs b over all of Rs; split: 2 FP16 "
                              "products over all of Rs + 1 FP8 product counted at half)"),
     }

@@ -1078,14 +1078,15 @@ __device__ __forceinline__ float wave_max(float x) {
 // In a fan that folds, the walk's triangle is one candidate of the smallest-key rule: its
 // record is written and its key seeds keys[] (changed[] cleared); the rasterisation of the
 // fan then replaces it where a triangle with a smaller key covers the node.
-// The walks are chains of dependent gathers (2.4 quads a node, 8 for a wave's two rows), half of
-// them served by HBM, with about as many vector instructions in between. One wait a quad instead of
-// two, both triangles tested without a branch, 32-bit offsets, no scratch (a choice of row pointers
-// at run time had gone there) and no spilled scalars: tables of 256 transducers of 152088 nodes
-// 1735 -> 1550 us, 3.0 + 2.1 -> 2.6 + 1.7 GB; records of 1024 transducers of 636160 nodes 13.1 ->
-// 12.1 ms. 6 waves per SIMD for tables (8: 1630 us), 8 for records (6: half a millisecond more). Wider strips of
-// nodes (64 x 4: slower; 32 x 8, 8 x 8 per wave: the same), stores past the cache (slower) and
-// other groups of rows (the same) were tried.
+// The walks are chains of dependent gathers (2.4 quads a node, 8 for a wave's two rows) with about as
+// many vector instructions in between; tables move 6.8 GB for 256 transducers of 152088 nodes in 1.55
+// ms, close to the rate of a copy, of which samples, entries and keys are 4.3. One wait a quad
+// instead of two, both triangles tested without a branch, 32-bit offsets, no scratch (a choice of
+// row pointers at run time had gone there) and no spilled scalars: those tables 1735 -> 1550 us
+// (8.2 GB), records of 1024 transducers of 636160 nodes 13.1 -> 12.1 ms. 6 waves per SIMD for tables
+// (8: 1630 us), 8 for records (6: half a millisecond more). Wider strips of nodes (64 x 4: slower;
+// 32 x 8, 8 x 8 per wave: the same), stores past the cache (slower) and other groups of rows (the
+// same) were tried.
 // Workgroups are dealt to the 8 XCDs round-robin by launch index. The (transducer, tile)
 // sequence is cut into groups of LOCATE_GROUP_ROWS tile rows and group g goes to XCD g mod 8,
 // so neighbouring tiles share their ray samples through one L2 while every XCD still gets an
@@ -1716,7 +1717,7 @@ __device__ __forceinline__ float resolve_node(const SampleBufs &sb, int n_rays, 
 // A wave takes strips of 64 x 8 nodes of one folded transducer, eight nodes of a row per lane: it
 // queues the changed ones in LDS, row by row, and resolves 64 at a time, one per lane. Neighbouring
 // nodes lie in neighbouring triangles, so a strip shares the lines of its samples, and a row's
-// entries leave together (in mask order, queued eight apart, a node fetched 218 and wrote 77 bytes).
+// entries leave together (in mask order, queued eight apart, a node fetched 440 and wrote 77 bytes).
 // Bound by those gathers: 1024 transducers at a narrow window, where half the nodes are rebuilt, 9.2
 // -> 3.9 ms; 256 transducers 340 -> 268 us. The largest A and 1/A a wave writes reach the
 // per-row maxima as one atomic pair (the walk's are folded in by tile_max_fold; max is
