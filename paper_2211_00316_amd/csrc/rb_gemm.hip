@@ -19,10 +19,11 @@
 // runs at 3/16 of the FP32 instructions' cost and, with 16 instead of 2 K values per
 // accumulation, rounds its partial sums less often. The scales bring each row's mean exponent
 // (over a sample of the row) to 4 (2 for Green's functions, whose caustic peaks are higher),
-// which leaves 2^12 (2^14) above it. Where that does not hold, the kernels notice and the FP32 kernel after them
-// recomputes everything: a value past FP16's range (or an infinity or NaN of the operand) makes
-// the sums of its column not finite, and a column (or row) whose largest scaled value is below
-// 2^-2 is seen by the maxima the loaders keep. The FP32 kernels return at once otherwise.
+// which leaves 2^12 (2^14) above it. Where that does not hold, the kernels notice and the FP32
+// kernel after them recomputes everything: a value past FP16's range (or an infinity or NaN of the
+// operand) makes the sums of its column not finite, and a column (or row) whose largest scaled
+// value is below 2^-2 is seen by the maxima the loaders keep. The FP32 kernels return at once
+// otherwise.
 #include "rb_internal.h"
 #include "rb_mfma.h"
 #include "rb_fwd.h"
@@ -295,9 +296,9 @@ __global__ void __launch_bounds__(256) split_residual_kernel(
 // four 16-byte pieces to LDS. Waves 0-3 and 4-7 stage alternate K steps, so that a wave's loads
 // are in flight for two steps. R's triangle has blocks of 64, a wave's rows: a wave skips the K
 // blocks left of its own, which the FP32 kernel's 256-row blocks multiply as zeros. No operand is
-// written to memory in split form: converting once in a pass of its own would move 31 GB more at 1024 transducers and 636160 nodes, where the
-// back-projection takes 24.9 ms (1.0 PFLOP/s of MFMAs; the FP32 kernel 128.9 ms) with an error of
-// 3.9e-7 against FP64 sums (5.4e-7).
+// written to memory in split form: converting once in a pass of its own would move 31 GB more at
+// 1024 transducers and 636160 nodes, where the back-projection takes 24.9 ms (1.0 PFLOP/s of MFMAs;
+// the FP32 kernel 128.9 ms) with an error of 3.9e-7 against FP64 sums (5.4e-7).
 __global__ void __launch_bounds__(SR_THREADS) rowred_split_kernel(
     const _Float16 *__restrict__ Rf, const float2 *__restrict__ B, const float *__restrict__ tsc,
     int n, int np, int n_cols, int n_comp, int conj_b, int mblocks, int nblocks,

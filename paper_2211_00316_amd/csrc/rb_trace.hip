@@ -499,8 +499,8 @@ __device__ __forceinline__ int trace_ray(const SplineMap &m, const AbsMap &am, c
     sincospi(((double)j + 0.5 - 0.5 * (double)n_rays) / (double)n_rays, &sd, &cd);
     const double cp = xy.x / R, sp = xy.y / R;
     const double cg = -(cp * cd - sp * sd), sg = -(sp * cd + cp * sd);
-    return trace_core<true, ABS, AHEAD>(m, am, g, R, psi, xy, cg, sg, n_rays, max_steps, ds, c0, el,
-                                 j, sb, flag, nullptr);
+    return trace_core<true, ABS, AHEAD>(m, am, g, R, psi, xy, cg, sg, n_rays, max_steps, ds, c0,
+                                        el, j, sb, flag, nullptr);
 }
 
 // One lane per ray; a wavefront holds 64 neighbouring rays of one transducer, so the
@@ -510,24 +510,24 @@ __device__ __forceinline__ int trace_ray(const SplineMap &m, const AbsMap &am, c
 // the longest run first and the shortest fill the end of the launch. Also counts the
 // samples written (one atomic per wavefront; the workgroup is a whole number of them).
 // Four waves per SIMD (128 registers) hide more of the coefficient loads' latency than three.
-// Bound by the instructions of a step (about 300, a quarter of them FP64). With the step's length and
-// its multiples constants of the loop, whole traces of 512 transducers of 1024 rays on a ring of
-// 50 mm went from 3.81 to 3.56 ms and nothing is spilled.
-// Workgroups (four transducers of one rank) are dealt to the 8 XCDs round-robin by launch
-// index. When E is a multiple of 32 the transducer groups of a rank are renamed so that each
-// XCD traces one contiguous arc of E / 8 transducers: same-rank rays of neighbouring
-// transducers cross nearly the same cells at about the same time, so that XCD's L2 fetches
-// their spline coefficients once instead of once per group of four. (Which wave traces which
-// ray changes nothing in the results.)
+// Bound by the instructions of a step (about 300, a quarter of them FP64). With the step's length
+// and its multiples constants of the loop, whole traces of 512 transducers of 1024 rays on a ring
+// of 50 mm went from 3.81 to 3.56 ms and nothing is spilled. Workgroups (four transducers of one
+// rank) are dealt to the 8 XCDs round-robin by launch index. When E is a multiple of 32 the
+// transducer groups of a rank are renamed so that each XCD traces one contiguous arc of E / 8
+// transducers: same-rank rays of neighbouring transducers cross nearly the same cells at about the
+// same time, so that XCD's L2 fetches their spline coefficients once instead of once per group of
+// four. (Which wave traces which ray changes nothing in the results.)
 //
 // trace_ahead_kernel, for launches that leave a SIMD one or two waves: nothing then hides the wait
 // for the coefficients of a new cell, which some lane of a wave enters at almost every evaluation.
 // A step's predictor needs no spline, so its cell is known, and its loads are issued, before the
 // current sample is worked out; coefficients stay in registers (152, without LDS), and
 // workgroups of one wave spread over all CUs. 64 transducers of 360 rays 590 -> 440 us. Against
-// trace_kernel, whole traces of fans of 1024 rays, lossless: 1536 waves 976 us against 1048, 2048 waves
-// 1277 against 1219, 4096 waves 2048 against 1952; in an absorbing medium (whose sixteen control points of
-// the absorption are one more wait a step) 3584 waves 1963 against 2015, 4096 waves 2248 against 2162.
+// trace_kernel, whole traces of fans of 720 and 1024 rays, lossless: 1536 waves 976 us against
+// 1048, 2048 waves 1277 against 1219, 4096 waves 2048 against 1952; in an absorbing medium (whose
+// sixteen control points of the absorption are one more wait a step) 3584 waves 1963 against 2015,
+// 4096 waves 2248 against 2162.
 constexpr int AHEAD_WAVES = 6, AHEAD_WAVES_LOSSY = 14;  // most waves per CU of a launch
 
 template <bool ABS, bool AHEAD>
@@ -808,8 +808,8 @@ __device__ __forceinline__ bool mesh_walk(const float2 *__restrict__ posE,
                                           const int32_t *__restrict__ Mrow, int n_rays, float pu,
                                           float pv, int &j, int &i, uint32_t vb[3], float lam[3],
                                           int &half, int max_it = LOCATE_MAX_IT) {
-    // Byte offsets fit 32 bits: n_rays <= 2048 and i <= 100000 (checked by the entry points), 16 bytes
-    // a sample at most.
+    // Byte offsets fit 32 bits: n_rays <= 2048 and i <= 100000 (checked by the entry points), 16
+    // bytes a sample at most.
     const char *row0 = reinterpret_cast<const char *>(posE);
     const char *row1 = reinterpret_cast<const char *>(posE + n_rays);
     const char *ends = reinterpret_cast<const char *>(Mrow);
@@ -1078,22 +1078,21 @@ __device__ __forceinline__ float wave_max(float x) {
 // In a fan that folds, the walk's triangle is one candidate of the smallest-key rule: its
 // record is written and its key seeds keys[] (changed[] cleared); the rasterisation of the
 // fan then replaces it where a triangle with a smaller key covers the node.
-// The walks are chains of dependent gathers (2.4 quads a node, 8 for a wave's two rows) with about as
-// many vector instructions in between; tables move 6.8 GB for 256 transducers of 152088 nodes in 1.55
-// ms, close to the rate of a copy, of which samples, entries and keys are 4.3. One wait a quad
+// The walks are chains of dependent gathers (2.4 quads a node, 8 for a wave's two rows) with about
+// as many vector instructions in between; tables move 6.8 GB for 256 transducers of 152088 nodes in
+// 1.55 ms, close to the rate of a copy, of which samples, entries and keys are 4.3. One wait a quad
 // instead of two, both triangles tested without a branch, 32-bit offsets, no scratch (a choice of
 // row pointers at run time had gone there) and no spilled scalars: those tables 1735 -> 1550 us
-// (8.2 GB), records of 1024 transducers of 636160 nodes 13.1 -> 12.1 ms. 6 waves per SIMD for tables
-// (8: 1630 us), 8 for records (6: half a millisecond more). Wider strips of nodes (64 x 4: slower;
-// 32 x 8, 8 x 8 per wave: the same), stores past the cache (slower) and other groups of rows (the
-// same) were tried.
-// Workgroups are dealt to the 8 XCDs round-robin by launch index. The (transducer, tile)
-// sequence is cut into groups of LOCATE_GROUP_ROWS tile rows and group g goes to XCD g mod 8,
-// so neighbouring tiles share their ray samples through one L2 while every XCD still gets an
-// even mix of the disk-shaped mask. The launch is padded to a multiple of 8 groups.
+// (8.2 GB), records of 1024 transducers of 636160 nodes 13.1 -> 12.1 ms. 6 waves per SIMD for
+// tables (8: 1630 us), 8 for records (6: half a millisecond more). Wider strips of nodes (64 x 4:
+// slower; 32 x 8, 8 x 8 per wave: the same), stores past the cache (slower) and other groups of
+// rows (the same) were tried. Workgroups are dealt to the 8 XCDs round-robin by launch index. The
+// (transducer, tile) sequence is cut into groups of LOCATE_GROUP_ROWS tile rows and group g goes to
+// XCD g mod 8, so neighbouring tiles share their ray samples through one L2 while every XCD still
+// gets an even mix of the disk-shaped mask. The launch is padded to a multiple of 8 groups.
 template <bool REC>
-__global__ void __launch_bounds__(LOCATE_THREADS, REC ? 8 : 6) locate_kernel(SampleBufs sb, int n_rays, int S, int E,
-                                                     int e0, GridP g, double R, double psi0,
+__global__ void __launch_bounds__(LOCATE_THREADS, REC ? 8 : 6)
+locate_kernel(SampleBufs sb, int n_rays, int S, int E, int e0, GridP g, double R, double psi0,
                                                      int N, double ds, double c0, int n_mask,
                                                      int tile_i0, int tile_j0, int tiles_x,
                                                      int tiles_y, const int32_t *__restrict__ qmap,
@@ -1259,9 +1258,9 @@ __global__ void __launch_bounds__(1024) folded_list(const int32_t *__restrict__ 
 // Workgroups of the resolve pass: more than are resident, since nodes to rebuild are few and far
 // between in most of their strips.
 constexpr int FOLD_GRID = 16384;
-// Most workgroups of the marking pass: segments past the rays' ends cost little and the others much,
-// which evens out over more than the 6 per CU that are resident (256 transducers: 416 us with 1536
-// workgroups, 369 with 8192, 358 with 16384, 457 with one segment per wave).
+// Most workgroups of the marking pass: segments past the rays' ends cost little and the others
+// much, which evens out over more than the 6 per CU that are resident (256 transducers: 416 us with
+// 1536 workgroups, 369 with 8192, 358 with 16384, 457 with one segment per wave).
 constexpr size_t MARK_GRID = 16384;
 
 // The rasterisation's item is a run of RCH quads along a pair of neighbouring rays (j, j+1;
@@ -1476,9 +1475,9 @@ __global__ void __launch_bounds__(256) mark_kernel(SampleBufs sb, int n_rays, in
 // counters lie in lines of their own for the same reason. The marking pass leaves
 // the tiles of every 16 runs, 8 bytes; where none of them is marked, the positions are not read
 // again. Both passes, with those boxes: 1024 transducers of 1024 rays 3.10 -> 1.64 ms, 256 of 720
-// 0.81 -> 0.59 ms at a narrow window and 0.69 -> 0.44 ms at a wide one. (Boxes of single runs gained
-// nothing: this pass is bound by its instructions.)
-// A queued quad: x = i, y = chunk transducer << 11 | ray.
+// 0.81 -> 0.59 ms at a narrow window and 0.69 -> 0.44 ms at a wide one. (Boxes of single runs
+// gained nothing: this pass is bound by its instructions.) A queued quad: x = i, y = chunk
+// transducer << 11 | ray.
 struct RasterOut {
     unsigned long long *keys;
     uint8_t *changed;
@@ -1629,7 +1628,8 @@ __global__ void __launch_bounds__(256) raster_kernel(SampleBufs sb, int n_rays, 
 #pragma unroll
             for (int k = 0; k < RCH; ++k) {
                 {
-                    // the box raster_tri tests nodes of (before its clip to the grid), of both halves
+                    // the box raster_tri tests nodes of (before its clip to the grid), of both
+                    // halves
                     const f4u qa = run.q[k], qb = run.q[k + 1];
                     const float umin = fminf(fminf(qa.x, qa.z), fminf(qb.x, qb.z));
                     const float umax = fmaxf(fmaxf(qa.x, qa.z), fmaxf(qb.x, qb.z));
@@ -1717,10 +1717,10 @@ __device__ __forceinline__ float resolve_node(const SampleBufs &sb, int n_rays, 
 // A wave takes strips of 64 x 8 nodes of one folded transducer, eight nodes of a row per lane: it
 // queues the changed ones in LDS, row by row, and resolves 64 at a time, one per lane. Neighbouring
 // nodes lie in neighbouring triangles, so a strip shares the lines of its samples, and a row's
-// entries leave together (in mask order, queued eight apart, a node fetched 440 and wrote 77 bytes).
-// Bound by those gathers: 1024 transducers at a narrow window, where half the nodes are rebuilt, 9.2
-// -> 3.9 ms; 256 transducers 340 -> 268 us. The largest A and 1/A a wave writes reach the
-// per-row maxima as one atomic pair (the walk's are folded in by tile_max_fold; max is
+// entries leave together (in mask order, queued eight apart, a node fetched 440 and wrote 77
+// bytes). Bound by those gathers: 1024 transducers at a narrow window, where half the nodes are
+// rebuilt, 9.2 -> 3.9 ms; 256 transducers 340 -> 268 us. The largest A and 1/A a wave writes reach
+// the per-row maxima as one atomic pair (the walk's are folded in by tile_max_fold; max is
 // order-independent).
 constexpr int RES_W = 64, RES_H = 8;
 template <bool REC>

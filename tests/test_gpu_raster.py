@@ -1,7 +1,8 @@
 """The smallest-key pass of folded fans against the oracle where its segments of 64 runs and their
 boxes of 16 have edges: fewer than 64 ray pairs (several rows of runs in a segment), exactly 64,
 one more, segments that end inside a row, and a grid so fine that a box is taller than its height
-field holds.
+field holds and that the lists of quads overflow (every quad there holds nodes; without the quads
+that are then rasterised on the spot 4 % of the nodes differ).
 
 Tolerances: the travel time and amplitude bounds of the parity tests (FP32 fields along a ray and
 in a triangle; 1e-5 and 1e-4), on the nodes where both sides kept the same arrival; where two
