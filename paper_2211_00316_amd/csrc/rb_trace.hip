@@ -207,6 +207,7 @@ __device__ __forceinline__ float abs_value(const AbsMap &a, double u, double v) 
 struct Ray {
     double u, v;
     double kx, ky, dxx, dxy;
+    float dxf, dyf;  // (float) dxx, dxy
     float dkx, dky;
 };
 
@@ -266,13 +267,12 @@ __device__ __forceinline__ Predictor predict(const Ray &r, double hu) {
 }
 
 // One step of Algorithm 1 of length hf (metres) = hu (node units), given the spline at the current
-// point and the step's predictor.
+// point (n1: its value) and the step's predictor.
 template <bool AHEAD>
-__device__ __forceinline__ Ray heun_step(const SplineMap &m, const Spline &s1, const Ray &r,
-                                         const Predictor &p, float hf, double hu,
+__device__ __forceinline__ Ray heun_step(const SplineMap &m, const Spline &s1, double n1,
+                                         const Ray &r, const Predictor &p, float hf, double hu,
                                          Patch<AHEAD> &pc) {
-    float n = s1.v;
-    const double kxd = (double)n * p.kx, kyd = (double)n * p.ky;
+    const double kxd = n1 * p.kx, kyd = n1 * p.ky;
     const float qxx = p.qx, qxy = p.qy;
     float kx = (float)kxd, ky = (float)kyd;                 // normalised wave vector
     float kpx = fmaf(hf, s1.gx, kx), kpy = fmaf(hf, s1.gy, ky);  // auxiliary ray direction
@@ -289,13 +289,15 @@ __device__ __forceinline__ Ray heun_step(const SplineMap &m, const Spline &s1, c
     o.kx = kxd + (double)(hf * (s1.gx + s2.gx) * 0.5f);
     o.ky = kyd + (double)(hf * (s1.gy + s2.gy) * 0.5f);
     float a[4], b[4];
-    const float dxx = (float)r.dxx, dxy = (float)r.dxy;
+    const float dxx = r.dxf, dxy = r.dyf;
     paraxial_rhs<true>(s1, kx, ky, dxx, dxy, r.dkx, r.dky, a);
     const float dkpx = fmaf(a[2], hf, r.dkx), dkpy = fmaf(a[3], hf, r.dky);
     const float dxpx = fmaf(a[0], hf, dxx), dxpy = fmaf(a[1], hf, dxy);
     paraxial_rhs<false>(s2, kpx, kpy, dxpx, dxpy, dkpx, dkpy, b);
     o.dxx = r.dxx + (double)(hf * (a[0] + b[0]) * 0.5f);
     o.dxy = r.dxy + (double)(hf * (a[1] + b[1]) * 0.5f);
+    o.dxf = (float)o.dxx;
+    o.dyf = (float)o.dxy;
     o.dkx = fmaf(0.5f, hf * (a[2] + b[2]), r.dkx);
     o.dky = fmaf(0.5f, hf * (a[3] + b[3]), r.dky);
     return o;
@@ -351,22 +353,29 @@ __device__ __forceinline__ int trace_core(const SplineMap &m, const AbsMap &am, 
     r.u = ue;
     r.v = ve;
     Spline sc = spline_eval(m, r.u, r.v, pc);
-    float n_cur = sc.v;
-    r.kx = (double)n_cur * cg;
-    r.ky = (double)n_cur * sg;
+    double n_cur = (double)sc.v;
+    r.kx = n_cur * cg;
+    r.ky = n_cur * sg;
     r.dxx = 0.0;
     r.dxy = 0.0;
-    r.dkx = (float)(-(double)n_cur * sg);
-    r.dky = (float)((double)n_cur * cg);
+    r.dxf = 0.0f;
+    r.dyf = 0.0f;
+    r.dkx = (float)(-n_cur * sg);
+    r.dky = (float)(n_cur * cg);
     double T = 0.0;
     double Babs = 0.0;  // int alpha ds from the source (absorbing media)
     float a_cur = 0.0f;
     if constexpr (ABS) a_cur = abs_value(am, r.u, r.v);
 
-    size_t o = (size_t)el * S * n_rays + j;
+    // the transducer's samples (el is uniform over a wave) and 32-bit byte offsets as in mesh_walk
+    const size_t first = (size_t)el * S * n_rays;
+    char *posE = reinterpret_cast<char *>(sb.pos + first);
+    char *fldE = reinterpret_cast<char *>(sb.fld + first);
+    uint32_t o = (uint32_t)j;
     if constexpr (STORE) {
-        sb.pos[o] = make_float2((float)r.u, (float)r.v);
-        sb.fld[o] = make_float4(0.0f, 0.0f, (float)cg, (float)sg);
+        *reinterpret_cast<float2 *>(posE + (o << 3)) = make_float2((float)r.u, (float)r.v);
+        *reinterpret_cast<float4 *>(fldE + (o << 4)) =
+            make_float4(0.0f, 0.0f, (float)cg, (float)sg);
     }
     int kfirst = S;  // K is monotone along a ray: zero before kfirst, stored from it on
 
@@ -393,7 +402,8 @@ __device__ __forceinline__ int trace_core(const SplineMap &m, const AbsMap &am, 
         }
         sc = spline_eval(m, r.u, r.v, pc);
         float n_new = sc.v;
-        T = fma(hT, (double)n_cur + (double)n_new, T);
+        const double n_end = (double)n_new;
+        T = fma(hT, n_cur + n_end, T);
         if constexpr (ABS) {
             const float a_new = abs_value(am, r.u, r.v);
             Babs = fma(hB, (double)a_cur + (double)a_new, Babs);
@@ -402,7 +412,7 @@ __device__ __forceinline__ int trace_core(const SplineMap &m, const AbsMap &am, 
         const float kxf = (float)r.kx, kyf = (float)r.ky;
         float ikn = __builtin_amdgcn_rsqf(fmaf(kxf, kxf, kyf * kyf));
         float tx = kxf * ikn, ty = kyf * ikn;
-        float J = fmaf(tx, (float)r.dxy, -(ty * (float)r.dxx));
+        float J = fmaf(tx, r.dyf, -(ty * r.dxf));
         if (i >= 1 && J * J_prev < 0.0f) ++K;
         double du = r.u - ue, dv = r.v - ve;
         double d = sqrt_newton(fma(du, du, dv * dv)) * g.dx;  // distance from the source
@@ -420,17 +430,17 @@ __device__ __forceinline__ int trace_core(const SplineMap &m, const AbsMap &am, 
         if constexpr (ABS) L -= (float)Babs;  // ln A_abs (Eq. amplitude-abs-discretised)
         float dT = (float)(T - d * ic0);
         ++i;
-        o += n_rays;
+        o += (uint32_t)n_rays;
         if constexpr (STORE) {
-            sb.pos[o] = make_float2((float)r.u, (float)r.v);
-            sb.fld[o] = make_float4(dT, L, tx, ty);
+            *reinterpret_cast<float2 *>(posE + (o << 3)) = make_float2((float)r.u, (float)r.v);
+            *reinterpret_cast<float4 *>(fldE + (o << 4)) = make_float4(dT, L, tx, ty);
             if (K > 0) {
-                sb.K[o] = (uint8_t)min(K, 255);
+                sb.K[first + o] = (uint8_t)min(K, 255);
                 if (kfirst == S) kfirst = i;
             }
         }
         J_prev = J;
-        n_cur = n_new;
+        n_cur = n_end;
         d_end = d;
         dT_end = dT;
         L_end = L;
@@ -438,7 +448,7 @@ __device__ __forceinline__ int trace_core(const SplineMap &m, const AbsMap &am, 
     bool hit = false;
     while (i < max_steps) {
         if constexpr (!AHEAD) p = predict(r, dsu);
-        const Ray nr = heun_step(m, sc, r, p, dsf, dsu, pc);
+        const Ray nr = heun_step(m, sc, n_cur, r, p, dsf, dsu, pc);
         const double pu = nr.u - uc, pv = nr.v - vc;
         if (fma(pu, pu, pv * pv) >= Ru2) {
             hit = true;
@@ -455,7 +465,7 @@ __device__ __forceinline__ int trace_core(const SplineMap &m, const AbsMap &am, 
         double disc = fma(b, b, R * R) - fma(qv, qv, qu * qu) * g.dx * g.dx;
         const double h = fmin(fmax(-b + sqrt(fmax(disc, 0.0)), 0.0), ds);
         p = predict(r, h * g.idx);
-        take(heun_step(m, sc, r, p, (float)h, h * g.idx, pc), h * 0.5 * ic0, h * 0.5);
+        take(heun_step(m, sc, n_cur, r, p, (float)h, h * g.idx, pc), h * 0.5 * ic0, h * 0.5);
         M = i;
         if constexpr (STORE) {
             size_t x = (size_t)el * n_rays + j;
@@ -512,7 +522,9 @@ __device__ __forceinline__ int trace_ray(const SplineMap &m, const AbsMap &am, c
 // Four waves per SIMD (128 registers) hide more of the coefficient loads' latency than three.
 // Bound by the instructions of a step (about 300, a quarter of them FP64). With the step's length
 // and its multiples constants of the loop, whole traces of 512 transducers of 1024 rays on a ring
-// of 50 mm went from 3.81 to 3.56 ms and nothing is spilled. Workgroups (four transducers of one
+// of 50 mm went from 3.81 to 3.56 ms and nothing is spilled. FP32 copies of FP64 values carried to
+// the next step and 32-bit sample offsets from scalar bases: 3.28 to 3.23 ms, in an absorbing medium
+// 3.64 to 3.55. Workgroups (four transducers of one
 // rank) are dealt to the 8 XCDs round-robin by launch index. When E is a multiple of 32 the
 // transducer groups of a rank are renamed so that each XCD traces one contiguous arc of E / 8
 // transducers: same-rank rays of neighbouring transducers cross nearly the same cells at about the
@@ -536,7 +548,8 @@ __device__ __forceinline__ void trace_wave(const SplineMap &m, const AbsMap &am,
                                            int max_steps, double ds, double c0, int e0, int E,
                                            const SampleBufs &sb, int *flag,
                                            unsigned long long *n_samples) {
-    const int wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const int wave =
+        __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
     const int n_groups = (n_rays + 63) / 64;
     const int rank = wave / E;
     int el = wave % E;
