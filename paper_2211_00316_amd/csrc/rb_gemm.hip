@@ -526,8 +526,10 @@ __global__ void __launch_bounds__(SR_THREADS) rowred_split_kernel(
                                             (red[1][2][tid] + red[1][3][tid]), -rs);
                 parts[(size_t)mb * n_cols + gc] = sr;
                 parts[(size_t)(mblocks + mb) * n_cols + gc] = si;
-                const float m = fmaxf(fmaxf(cmax[0][tid], cmax[1][tid]),
-                                      fmaxf(cmax[2][tid], cmax[3][tid]));
+                // slab 0 stages every row of a column, later ones only those from their own first
+                const float m = mb == 0 ? fmaxf(fmaxf(cmax[0][tid], cmax[1][tid]),
+                                                fmaxf(cmax[2][tid], cmax[3][tid]))
+                                        : 0.f;
                 if (!isfinite(sr) || !isfinite(si) || (m > 0.f && m < SPLIT_LEAST)) head->bad = 1;
             }
             __syncthreads();  // red[] and the stages are reused by the next slab
