@@ -11,19 +11,16 @@
 // multiplies Y_c by the same operand at the output position (E_c[e][q] = B_c[e][q]) and
 // sums over the rows e of the tile, giving per-column partial sums (re, im) per row block.
 //
-// Split operands. The FP32 matrix instructions run at 1/16 of the FP16 rate. A value x under a
-// power-of-two row scale is x = hi + lo + r with hi and lo FP16 (lo: the rounded error of hi):
-// |r| <= 2^-24 |x|, half a unit of FP32, down to an absolute floor of 2^-25 (FP16's smallest
-// subnormal halved). A product then is hi hi' + hi lo' + lo hi' (three FP16 MFMAs with exact
-// products and FP32 accumulators; lo lo' is at most 2^-24 of the product), so the contraction
-// runs at 3/16 of the FP32 instructions' cost and, with 16 instead of 2 K values per
-// accumulation, rounds its partial sums less often. The scales bring each row's mean exponent
-// (over a sample of the row) to 4 (2 for Green's functions, whose caustic peaks are higher),
-// which leaves 2^12 (2^14) above it. Where that does not hold, the kernels notice and the FP32
-// kernel after them recomputes everything: a value past FP16's range (or an infinity or NaN of the
-// operand) makes the sums of its column not finite, and a column (or row) whose largest scaled
-// value is below 2^-2 is seen by the maxima the loaders keep. The FP32 kernels return at once
-// otherwise.
+// Split operands. The FP32 matrix instructions run at 1/16 of the 16-bit rate. The row-reduced
+// product takes an FP32 value as the sum of three BF16 values, each the rounded error of the ones
+// before it: 8 + 8 + 8 bits hold FP32's 24 exactly, with FP32's exponents, whatever else its row or
+// column holds. Of a product's nine terms the six of up to 2^-16 are formed (BF16 MFMAs, exact
+// products, FP32 accumulators); the other three come to at most 2^-24 of it. The contraction runs
+// at 6/16 of the FP32 instructions' cost. An infinity or NaN of an operand (or a value that
+// BF16's rounding takes past the largest) makes the sums of its column not finite, and a value
+// below 2^-100, whose last part could leave the normal range, is noticed as it is split: either way
+// the FP32 kernel after the split one recomputes everything, which returns at once otherwise.
+// The forward takes two FP16 parts of values under a power-of-two row scale.
 #include "rb_internal.h"
 #include "rb_mfma.h"
 #include "rb_fwd.h"
@@ -55,6 +52,13 @@ __device__ __forceinline__ float2 sym_upper(const float2 *__restrict__ R, int n,
 // Split operands --------------------------------------------------------------------------
 typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ floatx16 mfma_bf16(bf16x8 a, bf16x8 b, floatx16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
 
 __device__ __forceinline__ floatx16 mfma16(halfx8 a, halfx8 b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
@@ -88,228 +92,143 @@ __device__ __forceinline__ void split_terms(const halfx8 (&a)[2][4], const halfx
     term(3, bn[0], b[0]);
 }
 
-// State of a split contraction in device memory. plain: set before it where no scale can be
-// chosen (an infinity or NaN in a sampled row or in R); bad: set by it where a scaled value left
-// its range. Either makes the FP32 kernels after it recompute the result.
+__device__ __forceinline__ bf16x8 negate(bf16x8 x) {
+    return __builtin_bit_cast(bf16x8, __builtin_bit_cast(uintx4, x) ^ 0x80008000u);
+}
+
+// Three BF16 parts of a pair of values, each packed in a word; least: the smallest magnitude of a
+// value seen that is not zero, as its bits doubled less one.
+constexpr int PARTS = 6;  // (re, im) x three parts
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t &least, uint32_t &w0,
+                                           uint32_t &w1, uint32_t &w2) {
+    least = min(least, min((__float_as_uint(a) << 1) - 1u, (__float_as_uint(b) << 1) - 1u));
+    auto part = [&](uint32_t &w) {
+        const bf16x2 h = {(__bf16)a, (__bf16)b};
+        w = __builtin_bit_cast(uint32_t, h);
+        a -= __uint_as_float(w << 16);
+        b -= __uint_as_float(w & 0xffff0000u);
+    };
+    part(w0);
+    part(w1);
+    part(w2);
+}
+constexpr uint32_t SPLIT_TINY = (27u << 24) - 1u;  // 2^-100
+
+// A stage's 16 K of a wave: two row tiles and two column tiles, PARTS fragments of FRAG bytes
+// each, at pa and pb. The stage's products are summed on their own and added to the accumulators
+// once: a dozen MFMAs that each rounded the long sum would leave more error than FP32's
+// instructions, this leaves less. Fragments are read as they are needed (the columns' twice, LDS
+// has the time): more of them at once than there are registers for.
+template <int FRAG>
+__device__ __forceinline__ void split_multiply(const char *pa, const char *pb,
+                                               floatx16 (&acc_re)[2][2],
+                                               floatx16 (&acc_im)[2][2]) {
+    auto frag = [](const char *p, int tile, int part) {
+        return *reinterpret_cast<const bf16x8 *>(p + (tile * PARTS + part) * FRAG);
+    };
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+        bf16x8 a[PARTS];
+#pragma unroll
+        for (int pl = 0; pl < PARTS; ++pl) a[pl] = frag(pa, mt, pl);
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            floatx16 re, im;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) re[i] = im[i] = 0.f;
+            // part j of the columns with the rows' parts i, i + j <= 2, the smallest first
+#pragma unroll
+            for (int j = 2; j >= 0; --j) {
+                const bf16x8 br = frag(pb, nt, j), bi = frag(pb, nt, 3 + j), bn = negate(bi);
+#pragma unroll
+                for (int i = 2 - j; i >= 0; --i) {
+                    re = mfma_bf16(a[i], br, re);
+                    im = mfma_bf16(a[i], bi, im);
+                    re = mfma_bf16(a[3 + i], bn, re);
+                    im = mfma_bf16(a[3 + i], br, im);
+                }
+            }
+            acc_re[mt][nt] += re;
+            acc_im[mt][nt] += im;
+        }
+        asm volatile("" ::: "memory");
+    }
+}
+
+// State of a split contraction in device memory. plain: set before it (a value of R below 2^-100;
+// no scale for the forward's rows); bad: set by it (the same of the other operand; sums that are
+// not finite; the forward's scaled values out of range). Either makes the FP32 kernels after it
+// recompute the result.
 struct SplitHead {
     int plain, bad, rs, pad;
 };
 
-// Scaled values below this, over a whole column (row) of an operand, send the call to the
+// Scaled values below this, over a whole row of an operand, send the forward to the
 // FP32 kernels: the floor of 2^-25 is then 2^-23 of the largest value.
 constexpr float SPLIT_LEAST = 0.25f;
-// What the scales bring a row's mean exponent to: back-projection operands (no high peaks) and
-// Green's functions (caustic peaks, up to sqrt(1 / |J|)).
-constexpr int SPLIT_TOP_H = 4, SPLIT_TOP_G = 2;
+// What the scales bring a row's rms to (caustic peaks reach up to sqrt(1 / |J|)).
+constexpr int SPLIT_TOP_G = 2;
 
-// Mean binary exponent of a row's sample (32 pieces of 64 columns spread over the row,
-// everything where the row is shorter; all components; zeros left out): few peaks do not move
-// it, where they would an rms. ROW_ZERO: nothing but zeros; ROW_BAD: an infinity or NaN. One
-// workgroup per row.
-constexpr float ROW_ZERO = -1e9f, ROW_BAD = 1e9f;
-__global__ void __launch_bounds__(256) split_stat_kernel(const float2 *__restrict__ B, int n,
-                                                         int n_cols, int n_comp,
-                                                         float *__restrict__ mexp) {
-    __shared__ int red[4][3];
-    const int e = blockIdx.x;
-    const int pieces = 32, len = 64, total = min(n_cols, pieces * len);
-    int sum = 0, cnt = 0, bad = 0;
-    for (int c = 0; c < n_comp; ++c) {
-        const float2 *row = B + ((size_t)c * n + e) * n_cols;
-#pragma unroll 4
-        for (int i = threadIdx.x; i < total; i += 256) {
-            size_t q = i;
-            if (n_cols > pieces * len)
-                q = (size_t)(i / len) * (size_t)(n_cols - len) / (pieces - 1) + i % len;
-            const float2 x = row[q];
-            const uint32_t m = max(__float_as_uint(x.x) & 0x7fffffffu,
-                                   __float_as_uint(x.y) & 0x7fffffffu);
-            if (m == 0) continue;
-            bad |= m >= 0x7f800000u;
-            sum += (int)(m >> 23) - 126;  // 2^(e-1) <= |x| < 2^e
-            ++cnt;
-        }
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        sum += __shfl_xor(sum, off);
-        cnt += __shfl_xor(cnt, off);
-        bad |= __shfl_xor(bad, off);
-    }
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        red[w][0] = sum;
-        red[w][1] = cnt;
-        red[w][2] = bad;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        sum = red[0][0] + red[1][0] + red[2][0] + red[3][0];
-        cnt = red[0][1] + red[1][1] + red[2][1] + red[3][1];
-        bad = red[0][2] | red[1][2] | red[2][2] | red[3][2];
-        mexp[e] = bad ? ROW_BAD : cnt ? (float)sum / (float)cnt : ROW_ZERO;
-    }
-}
-
-// Scale exponent of a row: its mean exponent brought to `top`.
-__device__ __forceinline__ int split_exp(float mexp, int top) {
-    return max(-100, min(100, top - (int)rintf(mexp)));
-}
-
-// What the scale kernels derive from all rows' samples: the mean of the mean exponents (for
-// rows whose sample is zero) and whether every sample is finite. Result in every thread of a
-// 256-thread workgroup.
-struct SplitAll {
-    float mean;
-    bool finite;
-};
-__device__ __forceinline__ SplitAll split_all(const float *__restrict__ mexp, int n) {
-    __shared__ float s_sum[4];
-    __shared__ int s_cnt[4], s_bad[4];
-    float sum = 0.f;
-    int cnt = 0, bad = 0;
-    for (int i = threadIdx.x; i < n; i += 256) {
-        const float v = mexp[i];
-        if (v == ROW_BAD) bad = 1;
-        else if (v != ROW_ZERO) {
-            sum += v;
-            ++cnt;
-        }
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        sum += __shfl_xor(sum, off);
-        cnt += __shfl_xor(cnt, off);
-        bad |= __shfl_xor(bad, off);
-    }
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        s_sum[w] = sum;
-        s_cnt[w] = cnt;
-        s_bad[w] = bad;
-    }
-    __syncthreads();
-    SplitAll a;
-    cnt = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
-    a.mean = cnt ? ((s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3])) / (float)cnt : 0.f;
-    a.finite = !(s_bad[0] | s_bad[1] | s_bad[2] | s_bad[3]);
-    return a;
-}
-
-// Largest exponent of the scaled residual in a row: R[e][r] / (t_e t_r) < 2^rmax[e]
-// (R_NONE: the row is zero, R_BAD: an infinity or NaN); the scales' exponents to xexp. One
-// workgroup per row.
-constexpr int R_NONE = -(1 << 20), R_BAD = 1 << 20;
-__global__ void __launch_bounds__(256) split_range_kernel(const float2 *__restrict__ R, int n,
-                                                          int top,
-                                                          const float *__restrict__ mexp,
-                                                          int *__restrict__ xexp,
-                                                          int *__restrict__ rmax) {
-    __shared__ int red[4];
-    const SplitAll all = split_all(mexp, n);
-    auto row_exp = [&](int i) {
-        const float v = mexp[i];
-        return all.finite ? split_exp(v != ROW_ZERO ? v : all.mean, top) : 0;
-    };
-    const int e = blockIdx.x, xe = row_exp(e);
-    int m = all.finite ? R_NONE : R_BAD;
-    for (int r = threadIdx.x; r < n; r += 256) {
-        const float2 x = R[(size_t)e * n + r];
-        const uint32_t b = max(__float_as_uint(x.x) & 0x7fffffffu,
-                               __float_as_uint(x.y) & 0x7fffffffu);
-        if (b >= 0x7f800000u) m = R_BAD;
-        else if (b != 0) m = max(m, (int)(b >> 23) - 126 - xe - row_exp(r));
-    }
-    for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        xexp[e] = xe;
-        rmax[e] = max(max(red[0], red[1]), max(red[2], red[3]));
-    }
-}
-
-// Layout of the split residual operand: fragments of 32 rows x 16 K as one lane-ordered KiB
-// (lane l: row l & 31, K 8 (l >> 5) .. + 7), [K / 16][row / 32][re hi, re lo, im hi, im lo], so
-// that a row slab's K step is contiguous and a fragment read touches every LDS bank once.
+// R' on its way into the row-reduced product: fragments of 32 rows x 16 K as one lane-ordered KiB
+// (lane l: row l & 31, K 8 (l >> 5) .. + 7), [K / 16][row / 32][part], so that a row slab's K step
+// is contiguous and a fragment read touches every LDS bank once.
 constexpr int SR_FRAG = 512;  // values of a fragment
 constexpr int SR_BM = RR_BM, SR_BN = 128, SR_BK = 16, SR_THREADS = 512;
 constexpr int SR_WM = 64;  // rows of a wave, the block of R's triangle
-constexpr int SR_A = (SR_BM / 32) * 4 * SR_FRAG, SR_B = (SR_BN / 32) * 4 * SR_FRAG;
+constexpr int SR_A = (SR_BM / 32) * PARTS * SR_FRAG, SR_B = (SR_BN / 32) * PARTS * SR_FRAG;
+inline __host__ __device__ int split_rows(int n) { return (n + SR_WM - 1) / SR_WM * SR_WM; }
+inline size_t split_residual_bytes(int n) {
+    return (size_t)split_rows(n) * rb_lp_pad(n) * (PARTS * 2);
+}
 
-// R' scaled by 2^rs / (t_e t_r) (t: the rows' scales of the other operand, powers of two) in
-// split form, zero past n; the scales t (zero past n up to a whole slab) and the head. A
-// workgroup covers 32 rows x 64 columns. rs brings the largest |R| / (t t) below 2^14 (R + R^T
-// above the diagonal blocks: below 2^15).
-__global__ void __launch_bounds__(256) split_residual_kernel(
-    const float2 *__restrict__ R, int n, int np, const int *__restrict__ xexp,
-    const int *__restrict__ rmax, float *__restrict__ tsc, SplitHead *__restrict__ head,
-    _Float16 *__restrict__ Rf) {
-    __shared__ int red[4];
-    int rm = R_NONE;
-    for (int i = threadIdx.x; i < n; i += 256) rm = max(rm, rmax[i]);
-    for (int off = 32; off > 0; off >>= 1) rm = max(rm, __shfl_xor(rm, off));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = rm;
-    __syncthreads();
-    rm = max(max(red[0], red[1]), max(red[2], red[3]));
-    const bool finite = rm != R_BAD;
-    const int rs = finite && rm != R_NONE ? 14 - rm : 0;
+// R' in parts, zero past n: np columns, split_rows(n) rows. A workgroup covers 32 rows x 64
+// columns. head: cleared before.
+__global__ void __launch_bounds__(256) split_residual_kernel(const float2 *__restrict__ R, int n,
+                                                             int np, SplitHead *__restrict__ head,
+                                                             __bf16 *__restrict__ Rf) {
     const int row = blockIdx.y * 32 + (threadIdx.x & 31);
     const int c0 = blockIdx.x * 64 + (threadIdx.x >> 5) * 8;
-    if (blockIdx.x == 0) {
-        if (threadIdx.x < 32) tsc[row] = row < n ? ldexpf(1.f, xexp[row]) : 0.f;
-        // zeros from np up to a whole slab
-        if (blockIdx.y == 0)
-            for (int i = np + threadIdx.x; i < (n + SR_BM - 1) / SR_BM * SR_BM; i += 256)
-                tsc[i] = 0.f;
-        if (blockIdx.y == 0 && threadIdx.x == 0) *head = SplitHead{finite ? 0 : 1, 0, rs, 0};
-    }
-    if (!finite || c0 >= np) return;
-    uint32_t w[4][4];
-    const int xe = row < n ? xexp[row] : 0;
+    if (c0 >= np) return;
+    uint32_t w[PARTS][4], least = ~0u;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        float2 v[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int col = c0 + 2 * k + u;
-            v[u] = sym_upper<SR_WM>(R, n, row, col);
-            const int x = col < n ? rs - xe - xexp[col] : 0;
-            v[u] = make_float2(ldexpf(v[u].x, x), ldexpf(v[u].y, x));
-        }
-        split2(v[0].x, v[1].x, w[0][k], w[1][k]);
-        split2(v[0].y, v[1].y, w[2][k], w[3][k]);
+        const float2 a = sym_upper<SR_WM>(R, n, row, c0 + 2 * k);
+        const float2 b = sym_upper<SR_WM>(R, n, row, c0 + 2 * k + 1);
+        split_pair(a.x, b.x, least, w[0][k], w[1][k], w[2][k]);
+        split_pair(a.y, b.y, least, w[3][k], w[4][k], w[5][k]);
     }
-    const size_t frag = ((size_t)(c0 / SR_BK) * (np / 32) + blockIdx.y) * 4;
-    _Float16 *dst = Rf + frag * SR_FRAG + ((c0 >> 3) & 1) * 256 + (threadIdx.x & 31) * 8;
+    if (least < SPLIT_TINY) head->plain = 1;
+    const size_t frag = ((size_t)(c0 / SR_BK) * gridDim.y + blockIdx.y) * PARTS;
+    __bf16 *dst = Rf + frag * SR_FRAG + ((c0 >> 3) & 1) * 256 + (threadIdx.x & 31) * 8;
 #pragma unroll
-    for (int pl = 0; pl < 4; ++pl)
+    for (int pl = 0; pl < PARTS; ++pl)
         *reinterpret_cast<uint4 *>(dst + pl * SR_FRAG) =
             make_uint4(w[pl][0], w[pl][1], w[pl][2], w[pl][3]);
 }
 
-// The row-reduced products on split operands. Bound by the matrix pipes: 12 FP16 MFMAs of
-// 32x32x16 per complex 32x32 tile and 16 K values, 1.5 times the MFMAs per staged byte of the
+// The row-reduced products on split operands. Bound by the matrix pipes: 24 BF16 MFMAs of
+// 32x32x16 per complex 32x32 tile and 16 K values, twice the MFMAs per staged byte of the
 // 16-bit form, so the same workgroup (256 rows x 128 columns, eight waves of 64 x 64, two per
-// SIMD, three LDS stages of 48 KiB) leaves LDS at about half its rate. R' comes in fragment
-// order straight into LDS, two K steps ahead. B stays as the caller keeps it (FP32, complex,
-// [row][column]): a lane takes one column of 8 consecutive rows (512-byte runs per wave), which
-// is a fragment's 8 K values, splits them in registers (about 5 instructions a pair) and writes
-// four 16-byte pieces to LDS. Waves 0-3 and 4-7 stage alternate K steps, so that a wave's loads
-// are in flight for two steps. R's triangle has blocks of 64, a wave's rows: a wave skips the K
-// blocks left of its own, which the FP32 kernel's 256-row blocks multiply as zeros. No operand is
-// written to memory in split form: converting once in a pass of its own would move 31 GB more at
-// 1024 transducers and 636160 nodes, where the back-projection takes 24.9 ms (1.0 PFLOP/s of MFMAs;
-// the FP32 kernel 128.9 ms) with an error of 3.9e-7 against FP64 sums (5.4e-7).
+// SIMD) leaves LDS at about a third of its rate; a K step's MFMAs take a wave 3000 cycles, so
+// one step ahead is far enough (two LDS stages of 72 KiB). R' comes in fragment order straight into
+// LDS. B stays as the caller keeps it (FP32, complex, [row][column]): a lane takes one column of 8
+// consecutive rows (512-byte runs per wave), which is a fragment's 8 K values, splits them in
+// registers (about 12 instructions a pair) and writes six 16-byte pieces to LDS. Waves 0-3 and 4-7
+// stage alternate K steps, so that a wave's loads are in flight for two steps. R's triangle has
+// blocks of 64, a wave's rows: a wave skips the K blocks left of its own, which the FP32 kernel's
+// 256-row blocks multiply as zeros. No operand is written to memory in split form: converting once
+// in a pass of its own would move 47 GB more at 1024 transducers and 636160 nodes, where the
+// back-projection takes 42.5 ms (1.2 PFLOP/s of MFMAs; the FP32 kernel 128.9 ms); its error against
+// FP64 sums is 2.4e-7 over 1024 transducers, 2.0e-7 over 301 (6.3e-7, 3.3e-7; random operands).
 __global__ void __launch_bounds__(SR_THREADS) rowred_split_kernel(
-    const _Float16 *__restrict__ Rf, const float2 *__restrict__ B, const float *__restrict__ tsc,
-    int n, int np, int n_cols, int n_comp, int conj_b, int mblocks, int nblocks,
-    SplitHead *__restrict__ head, float *__restrict__ parts) {
-    // R' and B of three K steps, in arrays of their own: the compiler then sees that neither
+    const __bf16 *__restrict__ Rf, const float2 *__restrict__ B, int n, int np, int n_cols,
+    int n_comp, int conj_b, int mblocks, int nblocks, SplitHead *__restrict__ head,
+    float *__restrict__ parts) {
+    // R' and B of two K steps, in arrays of their own: the compiler then sees that neither
     // the stores of B nor the reads of one step depend on loads in flight into another
-    __shared__ __attribute__((aligned(1024))) _Float16 a0[SR_A], a1[SR_A], a2[SR_A];
-    __shared__ __attribute__((aligned(1024))) _Float16 b0[SR_B], b1[SR_B], b2[SR_B];
+    __shared__ __attribute__((aligned(1024))) __bf16 a0[SR_A], a1[SR_A];
+    __shared__ __attribute__((aligned(1024))) __bf16 b0[SR_B], b1[SR_B];
     __shared__ float red[2][4][SR_BN];
-    __shared__ float cmax[4][SR_BN];
-    __shared__ __attribute__((aligned(16))) float ts[SR_BM];  // scales of the slab's rows
     if (head->plain) return;  // written before this launch
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -318,9 +237,9 @@ __global__ void __launch_bounds__(SR_THREADS) rowred_split_kernel(
     const int grp = wave >> 2, half = (wave >> 1) & 1;  // staging: K step parity, half of a step
     const int scol = (wave & 1) * 64 + lane;      // staged column of the tile
     const float bsign = conj_b ? -1.f : 1.f;
-    const int rs = head->rs;
-    const int ntile = np / 32, KT = np / SR_BK;
-    const __amdgpu_buffer_rsrc_t ra = plane_rsrc(Rf, (size_t)np * np * 8);
+    const int ntile = split_rows(n) / 32, KT = np / SR_BK;
+    const __amdgpu_buffer_rsrc_t ra = plane_rsrc(Rf, (size_t)ntile * 32 * np * (PARTS * 2));
+    uint32_t least = ~0u;  // of all this lane staged
 
     // Persistent, one workgroup per CU; items and XCD ranges as in the FP32 kernel. K runs from
     // the last block down, so that the epilogue finds its diagonal block of B in L2.
@@ -338,7 +257,6 @@ __global__ void __launch_bounds__(SR_THREADS) rowred_split_kernel(
             const int row0 = mb * SR_BM;
             const int steps = KT - row0 / SR_BK;
             float cs_re[2] = {0.f, 0.f}, cs_im[2] = {0.f, 0.f};
-            float mx = 0.f;  // largest scaled part this lane staged (its column)
             // this wave's rows meet K from their own block of R' on; nothing of rows past n
             const int wrow = row0 + wm * SR_WM;
             const int wsteps = wrow < n ? KT - wrow / SR_BK : 0;
@@ -351,45 +269,40 @@ __global__ void __launch_bounds__(SR_THREADS) rowred_split_kernel(
                 for (int u = 0; u < 8; ++u)
                     raw[u] = (Bc + (size_t)min(k0 + u, n - 1) * n_cols)[ccol];
             };
-            auto put_b = [&](int i, _Float16 *st) {
-                const int k0 = (KT - 1 - i) * SR_BK + half * 8;
-                uint32_t w[4][4];
+            auto put_b = [&](__bf16 *st) {
+                uint32_t w[PARTS][4];
+                // the values are used from here on (the signs were applied where they are loaded,
+                // which waited for the loads)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) asm volatile("" : "+v"(raw[u].x), "+v"(raw[u].y));
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const float t0 = tsc[min(k0 + 2 * u, n - 1)];
-                    const float t1 = tsc[min(k0 + 2 * u + 1, n - 1)];
-                    const float xr = raw[2 * u].x * t0, yr = raw[2 * u + 1].x * t1;
-                    const float xi = raw[2 * u].y * (t0 * bsign);
-                    const float yi = raw[2 * u + 1].y * (t1 * bsign);
-                    mx = fmaxf(fmaxf(mx, fabsf(xr)), fabsf(yr));
-                    mx = fmaxf(fmaxf(mx, fabsf(xi)), fabsf(yi));
-                    split2(xr, yr, w[0][u], w[1][u]);
-                    split2(xi, yi, w[2][u], w[3][u]);
+                    split_pair(raw[2 * u].x, raw[2 * u + 1].x, least, w[0][u], w[1][u], w[2][u]);
+                    split_pair(raw[2 * u].y * bsign, raw[2 * u + 1].y * bsign, least, w[3][u],
+                               w[4][u], w[5][u]);
                 }
-                _Float16 *dst = st + (scol >> 5) * 4 * SR_FRAG + half * 256 + (scol & 31) * 8;
+                __bf16 *dst = st + (scol >> 5) * PARTS * SR_FRAG + half * 256 + (scol & 31) * 8;
 #pragma unroll
-                for (int pl = 0; pl < 4; ++pl)
+                for (int pl = 0; pl < PARTS; ++pl)
                     *reinterpret_cast<uint4 *>(dst + pl * SR_FRAG) =
                         make_uint4(w[pl][0], w[pl][1], w[pl][2], w[pl][3]);
             };
-            auto fetch_a = [&](int i, _Float16 *st) {
+            auto fetch_a = [&](int i, __bf16 *st) {
                 const uint32_t kb = (uint32_t)((KT - 1 - i) * ntile + mb * (SR_BM / 32)) *
-                                    (4 * SR_FRAG * 2);
+                                    (PARTS * SR_FRAG * 2);
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
+                for (int u = 0; u < PARTS; ++u)
                     load_lds16(ra, st + (wave + 8 * u) * SR_FRAG, lane * 16,
                                kb + (uint32_t)(wave + 8 * u) * (SR_FRAG * 2));
             };
-            // the first loads of a component: R' of two steps, B of this wave's first
+            // the first loads of a component: R' of a step, B of this wave's first
             auto begin = [&](const float2 *Bc) {
                 fetch_a(0, a0);
-                if (steps > 1) fetch_a(1, a1);
                 __builtin_amdgcn_sched_barrier(0);
                 if (grp == 0 || steps > 1) load_b(Bc, grp);
                 __builtin_amdgcn_sched_barrier(0);
             };
             begin(B);
-            if (tid < SR_BM) ts[tid] = tsc[row0 + tid];
 
             for (int c = 0; c < n_comp; ++c) {
                 const float2 *Bc = B + (size_t)c * n * n_cols;
@@ -403,72 +316,61 @@ __global__ void __launch_bounds__(SR_THREADS) rowred_split_kernel(
                             acc_re[mt][nt][i] = 0.f;
                             acc_im[mt][nt][i] = 0.f;
                         }
-                auto multiply = [&](const _Float16 *sa, const _Float16 *sb) {
-                    halfx8 a[2][4], b[4], bn[2];
-#pragma unroll
-                    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                        for (int pl = 0; pl < 4; ++pl)
-                            a[mt][pl] = *reinterpret_cast<const halfx8 *>(
-                                sa + ((wm * 2 + mt) * 4 + pl) * SR_FRAG + lane * 8);
-#pragma unroll
-                    for (int nt = 0; nt < 2; ++nt) {
-#pragma unroll
-                        for (int pl = 0; pl < 4; ++pl)
-                            b[pl] = *reinterpret_cast<const halfx8 *>(
-                                sb + ((wn * 2 + nt) * 4 + pl) * SR_FRAG + lane * 8);
-                        bn[0] = -b[2];
-                        bn[1] = -b[3];
-                        split_terms(a, b, bn, acc_re, acc_im, nt);
-                    }
+                auto multiply = [&](const __bf16 *sa, const __bf16 *sb) {
+                    split_multiply<SR_FRAG * 2>(
+                        reinterpret_cast<const char *>(sa + wm * 2 * PARTS * SR_FRAG + lane * 8),
+                        reinterpret_cast<const char *>(sb + wn * 2 * PARTS * SR_FRAG + lane * 8),
+                        acc_re, acc_im);
                 };
-                // one step whose successors are in flight: R' of step i + 1 was fetched a step
-                // ago (4 loads), each wave's loads of B since then are 8 more and R' of step
-                // i + 2 another 4, so 12 outstanding loads mean step i + 1 is in LDS
-                auto step = [&](_Float16 *ca, _Float16 *cb, _Float16 *nb_, _Float16 *na, int i) {
-                    fetch_a(i + 2, na);
+                // A step whose successors are in flight. R' of step i + 1 is fetched here; the
+                // waves that stage then store B of that step and load B of step i + 3 (8 loads,
+                // younger than R'), the others' youngest loads are R' itself.
+                auto step = [&](__bf16 *ca, __bf16 *cb, __bf16 *nb_, __bf16 *na, int i) {
+                    const bool stage = ((grp ^ i) & 1) != 0;
+                    fetch_a(i + 1, na);
                     __builtin_amdgcn_sched_barrier(0);
-                    if (((grp ^ i) & 1) != 0) {
-                        put_b(i + 1, nb_);
-                        load_b(Bc, i + 3);
-                    }
+                    if (stage) put_b(nb_);
                     __builtin_amdgcn_sched_barrier(0);
                     if (i < wsteps) multiply(ca, cb);
-                    lr_sync<12>();
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (stage) {
+                        load_b(Bc, i + 3);
+                        lr_sync<8>();
+                    } else {
+                        lr_sync<0>();
+                    }
                 };
-                // a step without the loads of B, or one near the end: nothing is left in flight
-                auto last = [&](_Float16 *ca, _Float16 *cb, _Float16 *nb_, _Float16 *na, int i) {
-                    if (i + 2 < steps) fetch_a(i + 2, na);
+                // a step near the end: nothing is left in flight
+                auto last = [&](__bf16 *ca, __bf16 *cb, __bf16 *nb_, __bf16 *na, int i) {
+                    if (i + 1 < steps) fetch_a(i + 1, na);
                     if (((grp ^ i) & 1) != 0) {
-                        if (i + 1 < steps) put_b(i + 1, nb_);
+                        if (i + 1 < steps) put_b(nb_);
                         if (i + 3 < steps) load_b(Bc, i + 3);
                     }
                     if (i < wsteps) multiply(ca, cb);
                     lr_sync<0>();
                 };
                 if (grp == 0) {
-                    put_b(0, b0);
+                    put_b(b0);
                     if (steps > 2) load_b(Bc, 2);
                 }
-                // R' of step 0 is in LDS once only R' of step 1's younger loads of B are left
-                if (steps > 3) lr_sync<8>();
+                // R' of step 0 is older than each wave's 8 loads of B
+                if (steps > 2) lr_sync<8>();
                 else lr_sync<0>();
                 int i = 0;
-                for (; i + 5 < steps; i += 3) {
-                    step(a0, b0, b1, a2, i);
-                    step(a1, b1, b2, a0, i + 1);
-                    step(a2, b2, b0, a1, i + 2);
+                for (; i + 4 < steps; i += 2) {
+                    step(a0, b0, b1, a1, i);
+                    step(a1, b1, b0, a0, i + 1);
                 }
-                for (; i < steps; i += 3) {
-                    last(a0, b0, b1, a2, i);
-                    if (i + 1 < steps) last(a1, b1, b2, a0, i + 1);
-                    if (i + 2 < steps) last(a2, b2, b0, a1, i + 2);
+                for (; i < steps; i += 2) {
+                    last(a0, b0, b1, a1, i);
+                    if (i + 1 < steps) last(a1, b1, b0, a0, i + 1);
                 }
                 // every wave is past its reads: the next component's first loads run under
                 // the epilogue
                 if (c + 1 < n_comp) begin(Bc + (size_t)n * n_cols);
-                // epilogue: sum over the rows of t_e E_c[e][q] Y_c[e][q] (t zero past n), 32
-                // loads in flight. The asm keeps its 64 addresses from being formed before the
+                // epilogue: sum over the rows of E_c[e][q] Y_c[e][q] (Y zero past n), 16 loads in
+                // flight. The asm keeps its 64 addresses from being formed before the
                 // K loop and spilled.
                 int rbase = wrow, cbase = col0 + wn * 64 + (lane & 31);
                 asm volatile("" : "+s"(rbase), "+v"(cbase));
@@ -488,18 +390,11 @@ __global__ void __launch_bounds__(SR_THREADS) rowred_split_kernel(
                                     [(lane >> 5) * up + gc];
                             }
 #pragma unroll
-                            for (int k4 = 0; k4 < 4; ++k4) {
-                                float t[4];
-                                *reinterpret_cast<float4 *>(t) = *reinterpret_cast<const float4 *>(
-                                    ts + wm * SR_WM + mt * 32 + k4 * 8 + (lane >> 5) * 4);
-#pragma unroll
-                                for (int u = 0; u < 4; ++u) {
-                                    const int k = k4 * 4 + u;
-                                    const float er = ev[k].x * t[u], ei = ev[k].y * (t[u] * bsign);
-                                    const float yr = acc_re[mt][nt][k], yi = acc_im[mt][nt][k];
-                                    cs_re[nt] += er * yr - ei * yi;
-                                    cs_im[nt] += er * yi + ei * yr;
-                                }
+                            for (int k = 0; k < 16; ++k) {
+                                const float er = ev[k].x, ei = ev[k].y * bsign;
+                                const float yr = acc_re[mt][nt][k], yi = acc_im[mt][nt][k];
+                                cs_re[nt] += er * yr - ei * yi;
+                                cs_im[nt] += er * yi + ei * yr;
                             }
                             __builtin_amdgcn_sched_barrier(0);
                         }
@@ -516,25 +411,21 @@ __global__ void __launch_bounds__(SR_THREADS) rowred_split_kernel(
                     red[1][wm][wn * 64 + nt * 32 + lane] = cs_im[nt];
                 }
             }
-            cmax[grp * 2 + half][scol] = mx;
             __syncthreads();
             if (tid < SR_BN && col0 + tid < n_cols) {
                 const int gc = col0 + tid;
-                const float sr = ldexpf((red[0][0][tid] + red[0][1][tid]) +
-                                            (red[0][2][tid] + red[0][3][tid]), -rs);
-                const float si = ldexpf((red[1][0][tid] + red[1][1][tid]) +
-                                            (red[1][2][tid] + red[1][3][tid]), -rs);
+                const float sr = (red[0][0][tid] + red[0][1][tid]) +
+                                 (red[0][2][tid] + red[0][3][tid]);
+                const float si = (red[1][0][tid] + red[1][1][tid]) +
+                                 (red[1][2][tid] + red[1][3][tid]);
                 parts[(size_t)mb * n_cols + gc] = sr;
                 parts[(size_t)(mblocks + mb) * n_cols + gc] = si;
-                // slab 0 stages every row of a column, later ones only those from their own first
-                const float m = mb == 0 ? fmaxf(fmaxf(cmax[0][tid], cmax[1][tid]),
-                                                fmaxf(cmax[2][tid], cmax[3][tid]))
-                                        : 0.f;
-                if (!isfinite(sr) || !isfinite(si) || (m > 0.f && m < SPLIT_LEAST)) head->bad = 1;
+                if (!isfinite(sr) || !isfinite(si)) head->bad = 1;
             }
             __syncthreads();  // red[] and the stages are reused by the next slab
         }
     }
+    if (least < SPLIT_TINY) head->bad = 1;
 }
 
 // The FP32 form, for what the split form turns down (head: the split contraction before it,
@@ -1028,52 +919,39 @@ __global__ void __launch_bounds__(256) forward_kernel(const float2 *__restrict__
 
 int rb_rowred_mblocks(int n) { return (n + RR_BM - 1) / RR_BM; }
 
-// Scratch of the split form: the residual's fragments, the rows' samples and scales, the head
-// (nothing where R's fragments do not fit one buffer descriptor).
-static bool rowred_split_fits(int n) {
-    const size_t np = (size_t)rb_lp_pad(n);
-    return np * np * 8 <= (size_t)0xfffffff0u;
+// R's fragments fit one buffer descriptor, and a lane's offset of four rows of B 32 bits.
+static bool rowred_split_fits(int n, int n_mask) {
+    return split_residual_bytes(n) <= (size_t)0xfffffff0u && n_mask <= 1 << 26;
 }
-constexpr int SPLIT_COLS_MAX = 1 << 26;  // a lane's offset of four rows stays below 2^32 bytes
 
+// R in parts and the head.
 size_t rb_rowred_ws_bytes(int n) {
-    if (!rowred_split_fits(n)) return 0;
-    const size_t np = (size_t)rb_lp_pad(n), nb = (size_t)rb_rowred_mblocks(n) * RR_BM;
-    return rb_align(np * np * 8) + rb_align(nb * 16) + rb_align(sizeof(SplitHead));
+    return rowred_split_fits(n, 1)
+               ? rb_align(split_residual_bytes(n)) + rb_align(sizeof(SplitHead))
+               : 0;
 }
 
-// Split operands where R's fragments fit one buffer descriptor and the scratch; else (and for
-// calls whose values leave the split range) the FP32 kernel.
+// Split operands where the scratch holds R's; else (and for values that the split form turns
+// down) the FP32 kernel.
 rb_status rb_launch_rowred(rb_ctx *ctx, int n, int n_mask, const float *R, const float *B,
                            int n_comp, int conj_b, void *scratch, size_t scratch_bytes,
                            float *parts, int *mblocks_out) {
     const int mblocks = rb_rowred_mblocks(n);
     const int grid = std::max(8, ctx->n_cu / 8 * 8);  // one workgroup per CU (persistent)
     const int np = rb_lp_pad(n);
-    const bool split = scratch && rowred_split_fits(n) && n_mask <= SPLIT_COLS_MAX && scratch_bytes >= rb_rowred_ws_bytes(n);
     SplitHead *head = nullptr;
     rb_prof_begin(ctx, ST_BACKPROJECT);
-    if (split) {
-        char *p = static_cast<char *>(scratch);
-        const size_t nb = (size_t)mblocks * RR_BM;
-        _Float16 *Rf = reinterpret_cast<_Float16 *>(p);
-        p += rb_align((size_t)np * np * 8);
-        float *mexp = reinterpret_cast<float *>(p);
-        float *tsc = reinterpret_cast<float *>(p + nb * 4);
-        int *xexp = reinterpret_cast<int *>(p + nb * 8), *rmax = xexp + nb;
-        head = reinterpret_cast<SplitHead *>(p + rb_align(nb * 16));
-        const int top = conj_b ? SPLIT_TOP_G : SPLIT_TOP_H;
-        hipLaunchKernelGGL(split_stat_kernel, dim3(n), dim3(256), 0, ctx->stream,
-                           (const float2 *)B, n, n_mask, n_comp, mexp);
-        RB_CHECK_LAUNCH(ctx);
-        hipLaunchKernelGGL(split_range_kernel, dim3(n), dim3(256), 0, ctx->stream,
-                           (const float2 *)R, n, top, mexp, xexp, rmax);
-        RB_CHECK_LAUNCH(ctx);
-        hipLaunchKernelGGL(split_residual_kernel, dim3((np + 63) / 64, np / 32), dim3(256), 0,
-                           ctx->stream, (const float2 *)R, n, np, xexp, rmax, tsc, head, Rf);
+    if (scratch && rowred_split_fits(n, n_mask) && scratch_bytes >= rb_rowred_ws_bytes(n)) {
+        __bf16 *Rf = static_cast<__bf16 *>(scratch);
+        head = reinterpret_cast<SplitHead *>(static_cast<char *>(scratch) +
+                                             rb_align(split_residual_bytes(n)));
+        RB_TRY(rb_launch_fill_i32(ctx, reinterpret_cast<int32_t *>(head), sizeof(SplitHead) / 4,
+                                  0));
+        hipLaunchKernelGGL(split_residual_kernel, dim3((np + 63) / 64, split_rows(n) / 32),
+                           dim3(256), 0, ctx->stream, (const float2 *)R, n, np, head, Rf);
         RB_CHECK_LAUNCH(ctx);
         hipLaunchKernelGGL(rowred_split_kernel, dim3(grid), dim3(SR_THREADS), 0, ctx->stream, Rf,
-                           (const float2 *)B, tsc, n, np, n_mask, n_comp, conj_b, mblocks,
+                           (const float2 *)B, n, np, n_mask, n_comp, conj_b, mblocks,
                            (n_mask + SR_BN - 1) / SR_BN, head, parts);
         RB_CHECK_LAUNCH(ctx);
     }

@@ -46,3 +46,55 @@ def test_backproject_runs_split(ctx, n, small):
     plain = backproject(ctx, H, R)
     assert not torch.isfinite(plain[0]) and torch.isfinite(plain[1:]).all()
     assert not torch.equal(dm[1:], plain[1:])
+
+
+def rel(a, b):
+    return float(torch.linalg.norm(a.double() - b.double()) / torch.linalg.norm(b.double()))
+
+
+# A node's result keeps FP32's accuracy whatever else its column, its rows or R hold. dead: the
+# transducers with the large entries of the nodes looked at have no data, and what is left lies
+# 2^-18 (2^-40) below its rows' other nodes. outlier: one residual is 1e12 times the others,
+# between transducers that do not see the nodes looked at. K products of (3 x 2^-24) each and their
+# sum's roundings, as in the comparison with FP64 of the other operands.
+@pytest.mark.parametrize("case", ["dead18", "dead40", "outlier"])
+def test_backproject_keeps_small_entries(ctx, case):
+    n, nm, part = 70, 600, slice(100, 200)
+    g = torch.Generator(device="cuda:0").manual_seed(9)
+    H = torch.stack([randc(g, n, nm) for _ in range(3)]).contiguous()
+    R = randc(g, n, n)
+    if case == "outlier":
+        R[3, 9] = 1e12
+        H[:, [3, 9], part] = 0
+    else:
+        R[:35] = 0
+        R[:, :35] = 0
+        H[:, 35:, part] *= 2.0 ** -int(case[4:])
+    dm = backproject(ctx, H, R)[part]
+    Hd, Rd = H[:, :, part].to(torch.complex128), R.to(torch.complex128)
+    acc = sum((x * (Rd @ x)).sum(0) for x in Hd).real
+    ref = -2.0 * D_OMEGA / ((2.0 * math.pi) ** 3 * OMEGA * 1500.0 ** 2) * acc
+    assert rel(dm, ref) <= 2.0 * (3.0 + math.sqrt(n)) * 2.0 ** -24 * math.sqrt(3.0)
+
+
+# Values below 2^-100, whose last part FP32's exponents might not hold, go to the FP32 kernels (and
+# the smallest that do not run split). R is large enough for results in FP32's normal range.
+@pytest.mark.parametrize("exponent, split", [(-104, False), (-90, True)])
+def test_adjoint_of_tiny_entries(ctx, exponent, split):
+    from paper_2211_00316_amd import _lib
+
+    n, nm, part = 70, 600, slice(100, 200)
+    g = torch.Generator(device="cuda:0").manual_seed(11)
+    unit = torch.polar(1.0 + torch.rand(n, nm, generator=g, device="cuda:0"),
+                       math.pi / 4 + 0.5 * torch.rand(n, nm, generator=g, device="cuda:0"))
+    G = unit.clone()
+    G[:, part] *= 2.0 ** exponent
+    R = randc(g, n, n) * 2.0 ** 100
+    w = torch.ones(nm, dtype=torch.complex64, device="cuda:0")
+    out = ctx.born_adjoint(_lib.Green(G, G, _lib.RB_F32), w, R)
+    X = G.to(torch.complex128).conj().resolve_conj()
+    ref = (X * (R.to(torch.complex128) @ X)).sum(0).real
+    assert rel(out[part], ref[part]) <= 2.0 * (3.0 + math.sqrt(n)) * 2.0 ** -24 * math.sqrt(2.0)
+    G[0, 0] = complex(math.inf, 0.0)
+    plain = ctx.born_adjoint(_lib.Green(G, G, _lib.RB_F32), w, R)
+    assert torch.equal(out[1:], plain[1:]) != split
