@@ -1,6 +1,6 @@
 // Forward contraction d[e][r] = sum_q A[e][q] B[r][q] (A = G v, B = G; upper tiles, split-K) on
-// operands that pass through registers on their way to LDS: FP32 operands that are split into two
-// FP16 parts there, 16-bit operands whose A side carries node weights.
+// operands that pass through registers on their way to LDS: FP32 operands that are split into three
+// BF16 parts there, 16-bit operands whose A side carries node weights.
 #pragma once
 
 #include <algorithm>
@@ -12,14 +12,14 @@ namespace rb_fwd {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-// Workgroup tile FB x FB, four waves of 64 x 64 complex; two workgroups per CU (76 KiB of LDS
-// each), so that one stages while the other multiplies. A stage holds, for the 128 rows of A and
-// those of B, four fragments per 32 rows, each 32 rows x 16 K in lane order (a KiB) with its two
+// Workgroup tile FB x FB, four waves of 64 x 64 complex; two workgroups per CU, so that one stages
+// while the other multiplies. A stage holds, for the 128 rows of A and those of B, the operand
+// type's FRAGS fragments per 32 rows, each 32 rows x 16 K in lane order (a KiB) with its two
 // K halves FH bytes apart: the loaders' 8- and 16-byte pieces of a few rows then fall on distinct
-// banks, and a fragment read touches every bank once.
+// banks, and a fragment read touches every bank once. Four fragments leave room for two stages a
+// workgroup (76 KiB), so that it also stages while it multiplies; six (57 KiB) do not.
 constexpr int FB = 128, FTHREADS = 256;
 constexpr int FH = 576, FF = 1216;         // bytes between halves, between fragments
-constexpr int FSIDE = (FB / 32) * 4 * FF;  // bytes of one side of a stage
 
 // Upper-triangular tile index -> (tm, tn) with tm <= tn.
 __device__ __forceinline__ void upper_tile(int idx, int T, int &tm, int &tn) {
@@ -39,7 +39,7 @@ struct Shape {
 // K chunks of the kernel: a multiple of 8 (each XCD takes whole chunks, so that a chunk's columns
 // of G come from HBM once), around 1024 workgroups, with the least time by rounds of two workgroups
 // per CU. Fewer, longer chunks would round more (512 transducers, 152 053 nodes, FP32 operands:
-// error 4.2e-7 with 48 chunks, 2.6e-7 with 96 in the same time); chunks of less than four stages
+// error 1.1e-7 with 48 chunks, 8.3e-8 with 96 in the same time); chunks of less than four stages
 // are all start and end. want > 0: that many (a tuned configuration).
 constexpr int SPLITK_FEW = 64;  // chunks tried on rings with many tiles
 inline int splitk_base(int tiles) { return std::max(8, 1024 / tiles / 8 * 8); }
@@ -83,8 +83,10 @@ inline unsigned grid_of(const Shape &s) {
 template <class Op>
 __global__ void __launch_bounds__(FTHREADS, 2) forward_reg_kernel(const Op op, const Shape s,
                                                                   float2 *__restrict__ dpart) {
-    __shared__ __attribute__((aligned(64))) char st0[2 * FSIDE];
-    __shared__ __attribute__((aligned(64))) char st1[2 * FSIDE];
+    constexpr int TILE = Op::FRAGS * FF, SIDE = (FB / 32) * TILE;  // bytes of 32 rows, of a side
+    constexpr bool TWO = Op::FRAGS <= 4;
+    __shared__ __attribute__((aligned(64))) char st0[2 * SIDE];
+    __shared__ __attribute__((aligned(64))) char st1[TWO ? 2 * SIDE : 64];
     if (op.skip()) return;  // decided before this launch: the same for every workgroup
     const int kq = blockIdx.x >> 3;
     const int split = (kq / s.tiles) * 8 + (blockIdx.x & 7);
@@ -115,9 +117,9 @@ __global__ void __launch_bounds__(FTHREADS, 2) forward_reg_kernel(const Op op, c
     auto put = [&](char *st) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const int at = ((r + 64 * u) >> 5) * 4 * FF + (r & 31) * 16;
+            const int at = ((r + 64 * u) >> 5) * TILE + (r & 31) * 16;
             op.put_a(raw, rows, u, q, st + at);
-            op.put_b(raw, rows, u, q, st + FSIDE + at);
+            op.put_b(raw, rows, u, q, st + SIDE + at);
         }
     };
     // rows or columns past n, and in a diagonal tile a wave below the diagonal, have no output
@@ -125,9 +127,9 @@ __global__ void __launch_bounds__(FTHREADS, 2) forward_reg_kernel(const Op op, c
     const bool active = wr < s.n && wc < s.n && wr <= wc;
     auto multiply = [&](const char *st) {
         if (active)
-            op.multiply(st + wm * 2 * 4 * FF + (lane >> 5) * FH + (lane & 31) * 16,
-                        st + FSIDE + wn * 2 * 4 * FF + (lane >> 5) * FH + (lane & 31) * 16,
-                        acc_re, acc_im);
+            op.multiply(st + wm * 2 * TILE + (lane >> 5) * FH + (lane & 31) * 16,
+                        st + SIDE + wn * 2 * TILE + (lane >> 5) * FH + (lane & 31) * 16, acc_re,
+                        acc_im);
     };
     // one stage multiplied while the next is converted into the other buffer and the one after
     // it is being loaded
@@ -138,15 +140,28 @@ __global__ void __launch_bounds__(FTHREADS, 2) forward_reg_kernel(const Op op, c
         multiply(cur);
         __syncthreads();
     };
-    op.load(raw, rows, kbeg + q * Op::Q, kend);
-    put(st0);
-    if (kbeg + Op::BK < kend) op.load(raw, rows, kbeg + Op::BK + q * Op::Q, kend);
-    __syncthreads();
-    for (int k0 = kbeg; k0 < kend; k0 += 2 * Op::BK) {
-        step(st0, st1, k0);
-        if (k0 + Op::BK < kend) step(st1, st0, k0 + Op::BK);
+    if constexpr (TWO) {
+        op.load(raw, rows, kbeg + q * Op::Q, kend);
+        put(st0);
+        if (kbeg + Op::BK < kend) op.load(raw, rows, kbeg + Op::BK + q * Op::Q, kend);
+        __syncthreads();
+        for (int k0 = kbeg; k0 < kend; k0 += 2 * Op::BK) {
+            step(st0, st1, k0);
+            if (k0 + Op::BK < kend) step(st1, st0, k0 + Op::BK);
+        }
+    } else {
+        // one stage, and no loads in flight while it is multiplied (their registers would be
+        // spilled there): the CU's other workgroup multiplies while this one waits
+        for (int k0 = kbeg; k0 < kend; k0 += Op::BK) {
+            op.load(raw, rows, k0 + q * Op::Q, kend);
+            __syncthreads();  // the stage has been read
+            put(st0);
+            __syncthreads();
+            multiply(st0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
-    op.finish(rows, s.n, row0 + r, col0 + r, q);
+    op.finish(rows);
     float2 *out = dpart + (size_t)split * s.n * s.n;
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {

@@ -11,16 +11,15 @@
 // multiplies Y_c by the same operand at the output position (E_c[e][q] = B_c[e][q]) and
 // sums over the rows e of the tile, giving per-column partial sums (re, im) per row block.
 //
-// Split operands. The FP32 matrix instructions run at 1/16 of the 16-bit rate. The row-reduced
-// product takes an FP32 value as the sum of three BF16 values, each the rounded error of the ones
-// before it: 8 + 8 + 8 bits hold FP32's 24 exactly, with FP32's exponents, whatever else its row or
-// column holds. Of a product's nine terms the six of up to 2^-16 are formed (BF16 MFMAs, exact
+// Split operands. The FP32 matrix instructions run at 1/16 of the 16-bit rate. Both contractions
+// take an FP32 value as the sum of three BF16 values, each the rounded error of the ones before
+// it: 8 + 8 + 8 bits hold FP32's 24 exactly, with FP32's exponents, whatever else its row or column
+// holds. Of a product's nine terms the six of up to 2^-16 are formed (BF16 MFMAs, exact
 // products, FP32 accumulators); the other three come to at most 2^-24 of it. The contraction runs
 // at 6/16 of the FP32 instructions' cost. An infinity or NaN of an operand (or a value that
-// BF16's rounding takes past the largest) makes the sums of its column not finite, and a value
+// BF16's rounding takes past the largest) makes the sums it enters not finite, and a value
 // below 2^-100, whose last part could leave the normal range, is noticed as it is split: either way
 // the FP32 kernel after the split one recomputes everything, which returns at once otherwise.
-// The forward takes two FP16 parts of values under a power-of-two row scale.
 #include "rb_internal.h"
 #include "rb_mfma.h"
 #include "rb_fwd.h"
@@ -50,46 +49,12 @@ __device__ __forceinline__ float2 sym_upper(const float2 *__restrict__ R, int n,
 }
 
 // Split operands --------------------------------------------------------------------------
-typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
-typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ floatx16 mfma_bf16(bf16x8 a, bf16x8 b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ floatx16 mfma16(halfx8 a, halfx8 b, floatx16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
-}
-
-// hi and lo parts of a pair of scaled values, each packed in a word.
-__device__ __forceinline__ void split2(float a, float b, uint32_t &hi, uint32_t &lo) {
-    const halfx2 h = {(_Float16)a, (_Float16)b};
-    const halfx2 l = {(_Float16)(a - (float)h.x), (_Float16)(b - (float)h.y)};
-    hi = __builtin_bit_cast(uint32_t, h);
-    lo = __builtin_bit_cast(uint32_t, l);
-}
-
-// A stage's products for the column tile nt of a wave: planes (re hi, re lo, im hi, im lo) of the
-// two row tiles and of the columns, bn the negated imaginary planes of the columns.
-__device__ __forceinline__ void split_terms(const halfx8 (&a)[2][4], const halfx8 (&b)[4],
-                                            const halfx8 (&bn)[2], floatx16 (&acc_re)[2][2],
-                                            floatx16 (&acc_im)[2][2], int nt) {
-    auto term = [&](int pa, halfx8 br, halfx8 bi) {
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            acc_re[mt][nt] = mfma16(a[mt][pa], br, acc_re[mt][nt]);
-            acc_im[mt][nt] = mfma16(a[mt][pa], bi, acc_im[mt][nt]);
-        }
-    };
-    term(0, b[0], b[2]);   // re_hi (re_hi, im_hi)
-    term(2, bn[0], b[0]);  // im_hi (-im_hi, re_hi)
-    term(0, b[1], b[3]);   // re_hi (re_lo, im_lo)
-    term(2, bn[1], b[1]);
-    term(1, b[0], b[2]);   // re_lo (re_hi, im_hi)
-    term(3, bn[0], b[0]);
 }
 
 __device__ __forceinline__ bf16x8 negate(bf16x8 x) {
@@ -155,19 +120,13 @@ __device__ __forceinline__ void split_multiply(const char *pa, const char *pb,
     }
 }
 
-// State of a split contraction in device memory. plain: set before it (a value of R below 2^-100;
-// no scale for the forward's rows); bad: set by it (the same of the other operand; sums that are
-// not finite; the forward's scaled values out of range). Either makes the FP32 kernels after it
-// recompute the result.
+// State of a split contraction in device memory. plain: set before it (a value of R below 2^-100,
+// weights that are not finite); bad: set by it (a value of another operand below 2^-100, sums that
+// are not finite). Either makes the FP32 kernels after it recompute the result. rs: exponent of the
+// forward's scaled weights.
 struct SplitHead {
     int plain, bad, rs, pad;
 };
-
-// Scaled values below this, over a whole row of an operand, send the forward to the
-// FP32 kernels: the floor of 2^-25 is then 2^-23 of the largest value.
-constexpr float SPLIT_LEAST = 0.25f;
-// What the scales bring a row's rms to (caustic peaks reach up to sqrt(1 / |J|)).
-constexpr int SPLIT_TOP_G = 2;
 
 // R' on its way into the row-reduced product: fragments of 32 rows x 16 K as one lane-ordered KiB
 // (lane l: row l & 31, K 8 (l >> 5) .. + 7), [K / 16][row / 32][part], so that a row slab's K step
@@ -578,79 +537,46 @@ constexpr int FW_B = 128, FW_BK = 16;
 using rb_fwd::upper_tile;
 
 // Forward on split operands ------------------------------------------------------------------
-// Mean squares for the scales: of each row's sample (workgroups 0 .. n - 1; 128 pieces of 64
-// columns spread over the row) and, with weights, of v = w delta (the workgroups from n on, one
-// partial sum each). Here every sum runs along the row, so what counts is a row's rms, which
-// bounds a peak by the root of its length: rows near 2^2 and v near 1 leave 2^14 above them.
+// Largest |Re|, |Im| of v = w delta, as bits: one partial maximum per workgroup.
 constexpr int FS_PARTS = 64;
-__global__ void __launch_bounds__(256) split_fwd_stat_kernel(const float2 *__restrict__ G, int n,
-                                                             int K, const float2 *__restrict__ w,
-                                                             const float *__restrict__ delta,
-                                                             double *__restrict__ ms,
-                                                             double *__restrict__ vs) {
-    __shared__ double red[4];
-    double v = 0.0;
-    const int e = blockIdx.x;
-    if (e < n) {
-        const int pieces = 128, len = 64, total = min(K, pieces * len);
-        const float2 *row = G + (size_t)e * K;
-#pragma unroll 4
-        for (int i = threadIdx.x; i < total; i += 256) {
-            size_t q = i;
-            if (K > pieces * len)
-                q = (size_t)(i / len) * (size_t)(K - len) / (pieces - 1) + i % len;
-            const float2 x = row[q];
-            v += (double)x.x * x.x + (double)x.y * x.y;
-        }
-        v /= 2.0 * total;
-    } else {
-        for (int k = (e - n) * 256 + threadIdx.x; k < K; k += FS_PARTS * 256) {
-            const double dl = delta[k], a = w[k].x * dl, b = w[k].y * dl;
-            v += a * a + b * b;
-        }
-        v /= (double)K;
+__global__ void __launch_bounds__(256) weight_max_kernel(int K, const float2 *__restrict__ w,
+                                                         const float *__restrict__ delta,
+                                                         uint32_t *__restrict__ vmax) {
+    __shared__ uint32_t red[4];
+    uint32_t m = 0;
+    for (int k = blockIdx.x * 256 + threadIdx.x; k < K; k += FS_PARTS * 256) {
+        const float dl = delta[k];
+        m = max(m, max(__float_as_uint(w[k].x * dl) & 0x7fffffffu,
+                       __float_as_uint(w[k].y * dl) & 0x7fffffffu));
     }
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        v = (red[0] + red[1]) + (red[2] + red[3]);
-        if (e < n) ms[e] = v;
-        else vs[e - n] = v;
-    }
+    if (threadIdx.x == 0) vmax[blockIdx.x] = max(max(red[0], red[1]), max(red[2], red[3]));
 }
 
-// Exponent of the scale that brings the root of a mean square into [2^(top-1), 2^top).
-__device__ __forceinline__ int rms_exp(double ms, int top) {
-    int e = 0;
-    if (ms > 0.0) (void)frexp(sqrt(ms), &e);
-    return max(-100, min(100, top - e));
-}
-
-// Scales of the rows (a row whose sample is zero: that of the mean), v = w delta scaled (rounded
-// as a product of FP32 values, then by a power of two), zeros of the rows' maxima, and the head.
-__global__ void __launch_bounds__(256) split_fwd_scale_kernel(
-    int n, int K, const float2 *__restrict__ w, const float *__restrict__ delta,
-    const double *__restrict__ ms, const double *__restrict__ vs, float *__restrict__ tsc,
-    uint32_t *__restrict__ rmax, float2 *__restrict__ v, SplitHead *__restrict__ head) {
-    __shared__ double red[4];
-    double sum = 0.0, vsum = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) sum += ms[i];
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
-    __syncthreads();
-    sum = ((red[0] + red[1]) + (red[2] + red[3])) / n;
-    if (w)
-        for (int i = 0; i < FS_PARTS; ++i) vsum += vs[i];
-    const bool finite = isfinite(sum) && isfinite(vsum);
-    const int xv = w && finite ? rms_exp(vsum, 0) : 0;
+// v = w delta (rounded as a product of FP32 values) times the power of two that brings its largest
+// part to [2^(VTOP-1), 2^VTOP), and the head (K = 0: that alone). Where delta falls off towards
+// nothing (the tail of a Gaussian), G v keeps clear of 2^-100 with it, down to v's smallest
+// subnormal; sums of 2^20 terms stay finite up to |G| = 2^13.
+constexpr int VTOP = 80;
+__global__ void __launch_bounds__(256) weight_scale_kernel(int K, const float2 *__restrict__ w,
+                                                           const float *__restrict__ delta,
+                                                           const uint32_t *__restrict__ vmax,
+                                                           float2 *__restrict__ v,
+                                                           SplitHead *__restrict__ head) {
+    uint32_t m = 0;
+    if (K > 0)
+        for (int i = 0; i < FS_PARTS; ++i) m = max(m, vmax[i]);
+    const bool finite = m < 0x7f800000u;
+    int xv = 0;
+    if (finite && m > 0) {
+        (void)frexpf(__uint_as_float(m), &xv);
+        xv = VTOP - xv;
+    }
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i == 0) *head = SplitHead{finite ? 0 : 1, 0, xv, 0};
-    if (i < n) {
-        tsc[i] = finite ? ldexpf(1.f, rms_exp(ms[i] > 0.0 ? ms[i] : sum, SPLIT_TOP_G)) : 1.f;
-        rmax[i] = rmax[n + i] = 0;
-    }
-    if (w && i < K) {
+    if (i < K) {
         const float2 wv = w[i];
         const float dl = delta[i];
         v[i] = make_float2(ldexpf(wv.x * dl, xv), ldexpf(wv.y * dl, xv));
@@ -658,36 +584,31 @@ __global__ void __launch_bounds__(256) split_fwd_scale_kernel(
 }
 
 // FP32 rows G [n][K] (complex) for rb_fwd::forward_reg_kernel: a stage is 16 K as fragments
-// (re hi, re lo, im hi, im lo); WEIGHTS: the A side is G v. A lane's quarter of a stage is 32
-// consecutive bytes of a row. Bound by the matrix pipes: 512 transducers and 152 053 nodes take
-// 0.65 ms (0.92 PFLOP/s of MFMAs) where the FP32 kernel took 2.41 ms, and the error against FP64
-// sums is 2.6e-7 (3.7e-7), the sum of 16 products being rounded once per MFMA instead of every 2.
+// (three parts of re, of im); WEIGHTS: the A side is G v. A lane's quarter of a stage is 32
+// consecutive bytes of a row. Bound by the matrix pipes: 512 transducers and 152 053 nodes with
+// weights take 1.01 ms (1.2 PFLOP/s of MFMAs) where the FP32 kernel took 2.41 ms, and the error
+// against FP64 sums is 9.6e-8 (3.9e-7).
 template <bool WEIGHTS>
 struct SplitFwd {
-    static constexpr int BK = 16, Q = 4;
+    static constexpr int BK = 16, Q = 4, FRAGS = PARTS;
     const float2 *G, *v;
-    const float *tsc;
-    uint32_t *rmax;  // bits of the rows' largest scaled part: A [n], B [n]
-    const SplitHead *head;
+    SplitHead *head;
     typedef float f4 __attribute__((ext_vector_type(4), aligned(8)));
     struct Raw {
         f4 a[2][2], b[2][2], w[2];
     };
     struct Rows {
         const float2 *a[2], *b[2];
-        float ta[2], tb[2], ma[2], mb[2];
+        uint32_t least;
     };
     __device__ bool skip() const { return head->plain; }
     __device__ void rows(Rows &o, int n, int K, int ra, int rb, int) const {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const int ea = min(ra + 64 * u, n - 1), eb = min(rb + 64 * u, n - 1);
-            o.a[u] = G + (size_t)ea * K;
-            o.b[u] = G + (size_t)eb * K;
-            o.ta[u] = tsc[ea];
-            o.tb[u] = tsc[eb];
-            o.ma[u] = o.mb[u] = 0.f;
+            o.a[u] = G + (size_t)min(ra + 64 * u, n - 1) * K;
+            o.b[u] = G + (size_t)min(rb + 64 * u, n - 1) * K;
         }
+        o.least = ~0u;
     }
     // four consecutive values of a row, zero from kend on
     static __device__ __forceinline__ void get(const float2 *row, int k, int kend, f4 (&x)[2]) {
@@ -711,20 +632,17 @@ struct SplitFwd {
         }
         if constexpr (WEIGHTS) get(v, k, kend, x.w);
     }
-    static __device__ __forceinline__ void put(const f4 (&x)[2], float t, int q, float &m,
+    static __device__ __forceinline__ void put(const f4 (&x)[2], int q, uint32_t &least,
                                                char *dst) {
-        uint32_t w[4][2];
+        uint32_t w[PARTS][2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const float ar = x[i][0] * t, ai = x[i][1] * t, br = x[i][2] * t, bi = x[i][3] * t;
-            m = fmaxf(fmaxf(m, fabsf(ar)), fabsf(ai));
-            m = fmaxf(fmaxf(m, fabsf(br)), fabsf(bi));
-            split2(ar, br, w[0][i], w[1][i]);
-            split2(ai, bi, w[2][i], w[3][i]);
+            split_pair(x[i][0], x[i][2], least, w[0][i], w[1][i], w[2][i]);
+            split_pair(x[i][1], x[i][3], least, w[3][i], w[4][i], w[5][i]);
         }
         dst += (q >> 1) * rb_fwd::FH + (q & 1) * 8;
 #pragma unroll
-        for (int pl = 0; pl < 4; ++pl)
+        for (int pl = 0; pl < PARTS; ++pl)
             *reinterpret_cast<uint2 *>(dst + pl * rb_fwd::FF) = make_uint2(w[pl][0], w[pl][1]);
     }
     __device__ __forceinline__ void put_a(const Raw &x, Rows &o, int u, int q, char *dst) const {
@@ -739,61 +657,33 @@ struct SplitFwd {
                     y[i][h] = gx * vx - gy * vy;
                     y[i][h + 1] = gx * vy + gy * vx;
                 }
-            put(y, o.ta[u], q, o.ma[u], dst);
+            put(y, q, o.least, dst);
         } else {
-            put(x.a[u], o.ta[u], q, o.ma[u], dst);
+            put(x.a[u], q, o.least, dst);
         }
     }
     __device__ __forceinline__ void put_b(const Raw &x, Rows &o, int u, int q, char *dst) const {
-        put(x.b[u], o.tb[u], q, o.mb[u], dst);
+        put(x.b[u], q, o.least, dst);
     }
     __device__ __forceinline__ void multiply(const char *pa, const char *pb,
                                              floatx16 (&acc_re)[2][2],
                                              floatx16 (&acc_im)[2][2]) const {
-        halfx8 a[2][4], b[4], bn[2];
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-            for (int pl = 0; pl < 4; ++pl)
-                a[mt][pl] = *reinterpret_cast<const halfx8 *>(pa + (mt * 4 + pl) * rb_fwd::FF);
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-#pragma unroll
-            for (int pl = 0; pl < 4; ++pl)
-                b[pl] = *reinterpret_cast<const halfx8 *>(pb + (nt * 4 + pl) * rb_fwd::FF);
-            bn[0] = -b[2];
-            bn[1] = -b[3];
-            split_terms(a, b, bn, acc_re, acc_im, nt);
-        }
+        split_multiply<rb_fwd::FF>(pa, pb, acc_re, acc_im);
     }
-    __device__ void finish(Rows &o, int n, int ra, int rb, int q) const {
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            float a = o.ma[u], b = o.mb[u];
-            a = fmaxf(a, __shfl_xor(a, 1));
-            a = fmaxf(a, __shfl_xor(a, 2));
-            b = fmaxf(b, __shfl_xor(b, 1));
-            b = fmaxf(b, __shfl_xor(b, 2));
-            if (q == 0 && ra + 64 * u < n) atomicMax(rmax + ra + 64 * u, __float_as_uint(a));
-            if (q == 1 && rb + 64 * u < n) atomicMax(rmax + n + rb + 64 * u, __float_as_uint(b));
-        }
+    __device__ void finish(const Rows &o) const {
+        if (o.least < SPLIT_TINY) head->bad = 1;
     }
 };
 
-// The reduction's look at a split result: not finite, or a row of either side below its range.
+// The reduction's look at a split result.
 struct SplitCheck {
-    const uint32_t *rmax;
     SplitHead *head;
-    int n;
     __device__ bool skip() const { return head->plain; }
     __device__ float2 unscale(float2 v) const {  // the weights' power of two
         return make_float2(ldexpf(v.x, -head->rs), ldexpf(v.y, -head->rs));
     }
-    __device__ void see(int e, int r, float2 v) const {
-        const float a = __uint_as_float(rmax[e]), b = __uint_as_float(rmax[n + r]);
-        if (!isfinite(v.x) || !isfinite(v.y) || (a > 0.f && a < SPLIT_LEAST) ||
-            (b > 0.f && b < SPLIT_LEAST))
-            head->bad = 1;
+    __device__ void see(int, int, float2 v) const {
+        if (!isfinite(v.x) || !isfinite(v.y)) head->bad = 1;
     }
 };
 // The reduction after the FP32 kernel: only where that ran.
@@ -968,11 +858,11 @@ int rb_forward_default_splitk(int n, int n_mask, int n_cu) {
     return rb_fwd::make_shape(n, n_mask, FW_BK, n_cu, 0).splitk;
 }
 
-// Workspace of the FP32 forward: partial sums, the scaled weights, the rows' mean squares, scales
-// and maxima, the weights' partial sums, the head.
+// Workspace of the FP32 forward: partial sums, the scaled weights and their partial maxima, the
+// head.
 static size_t forward_bytes(int n, int K, int splitk) {
     return rb_align((size_t)splitk * n * n * sizeof(float2)) +
-           rb_align((size_t)K * sizeof(float2)) + rb_align((size_t)n * 20 + FS_PARTS * 8) +
+           rb_align((size_t)K * sizeof(float2)) + rb_align(FS_PARTS * sizeof(uint32_t)) +
            rb_align(sizeof(SplitHead));
 }
 
@@ -991,37 +881,32 @@ rb_status rb_launch_forward(rb_ctx *ctx, const rb_green *gr, const float *w, con
     RB_TRY(rb_arena_reserve(ctx, &ctx->ws, forward_bytes(n, K, s.splitk)));
     float2 *dpart = rb_carve<float2>(&ctx->ws, (size_t)s.splitk * n * n);
     float2 *v = rb_carve<float2>(&ctx->ws, K);
-    double *ms = reinterpret_cast<double *>(rb_carve<char>(&ctx->ws, (size_t)n * 20 + FS_PARTS * 8));
-    double *vs = ms + n;
-    float *tsc = reinterpret_cast<float *>(vs + FS_PARTS);
-    uint32_t *rmax = reinterpret_cast<uint32_t *>(tsc + n);
+    uint32_t *vmax = rb_carve<uint32_t>(&ctx->ws, FS_PARTS);
     SplitHead *head = rb_carve<SplitHead>(&ctx->ws, 1);
     const float2 *G = (const float2 *)gr->G, *wp = (const float2 *)w;
     rb_prof_begin(ctx, ST_FORWARD);
-    hipLaunchKernelGGL(split_fwd_stat_kernel, dim3(n + (w ? FS_PARTS : 0)), dim3(256), 0,
-                       ctx->stream, G, n, K, wp, delta, ms, vs);
-    RB_CHECK_LAUNCH(ctx);
-    const int items = w ? std::max(n, K) : n;
-    hipLaunchKernelGGL(split_fwd_scale_kernel, dim3((items + 255) / 256), dim3(256), 0,
-                       ctx->stream, n, K, wp, delta, ms, vs, tsc, rmax, v, head);
-    RB_CHECK_LAUNCH(ctx);
     if (w) {
-        const SplitFwd<true> op{G, v, tsc, rmax, head};
-        hipLaunchKernelGGL(rb_fwd::forward_reg_kernel<SplitFwd<true>>, dim3(rb_fwd::grid_of(s)),
-                           dim3(rb_fwd::FTHREADS), 0, ctx->stream, op, s, dpart);
-    } else {
-        const SplitFwd<false> op{G, v, tsc, rmax, head};
-        hipLaunchKernelGGL(rb_fwd::forward_reg_kernel<SplitFwd<false>>, dim3(rb_fwd::grid_of(s)),
-                           dim3(rb_fwd::FTHREADS), 0, ctx->stream, op, s, dpart);
+        hipLaunchKernelGGL(weight_max_kernel, dim3(FS_PARTS), dim3(256), 0, ctx->stream, K, wp,
+                           delta, vmax);
+        RB_CHECK_LAUNCH(ctx);
     }
+    const int kw = w ? K : 0;
+    hipLaunchKernelGGL(weight_scale_kernel, dim3(kw ? (kw + 255) / 256 : 1), dim3(256), 0,
+                       ctx->stream, kw, wp, delta, vmax, v, head);
+    RB_CHECK_LAUNCH(ctx);
+    auto launch = [&](auto op) {
+        hipLaunchKernelGGL(rb_fwd::forward_reg_kernel<decltype(op)>, dim3(rb_fwd::grid_of(s)),
+                           dim3(rb_fwd::FTHREADS), 0, ctx->stream, op, s, dpart);
+    };
+    if (w) launch(SplitFwd<true>{G, v, head});
+    else launch(SplitFwd<false>{G, v, head});
     RB_CHECK_LAUNCH(ctx);
     rb_prof_end(ctx);
     rb_prof_begin(ctx, ST_FORWARD_REDUCE);
     // the operand may carry sqrt(v) gscale[0]
     hipLaunchKernelGGL(rb_fwd::reduce_kernel<SplitCheck>, dim3(rb_fwd::reduce_grid(n)), dim3(256),
-                       0, ctx->stream, dpart, n, s.splitk, gscale, 2, tsc,
-                       SplitCheck{rmax, head, n},
-                       (float2 *)d);
+                       0, ctx->stream, dpart, n, s.splitk, gscale, 2, (const float *)nullptr,
+                       SplitCheck{head}, (float2 *)d);
     RB_CHECK_LAUNCH(ctx);
     hipLaunchKernelGGL(forward_kernel, dim3(s.tiles, s.splitk), dim3(256), 0, ctx->stream, G, wp,
                        delta, n, K, s.nT, s.kchunk * FW_BK, head, dpart);

@@ -1283,7 +1283,7 @@ __global__ void __launch_bounds__(256) node_weight_kernel(const float2 *__restri
 // loaded, converted and multiplied in turn, its weights node by node, took 9.6 ms.
 template <typename T, bool WEIGHTS>
 struct LpFwd {
-    static constexpr int BK = 32, Q = 8;
+    static constexpr int BK = 32, Q = 8, FRAGS = 4;
     const T *G;
     const float2 *v;
     int ld;
@@ -1388,7 +1388,7 @@ struct LpFwd {
             }
         }
     }
-    __device__ void finish(Rows &, int, int, int, int) const {}
+    __device__ void finish(const Rows &) const {}
 };
 
 // Forward on operands that already carry sqrt(v): d[e][r] = sum_q G[e][q] G[r][q], on the

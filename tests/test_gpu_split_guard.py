@@ -98,3 +98,42 @@ def test_adjoint_of_tiny_entries(ctx, exponent, split):
     G[0, 0] = complex(math.inf, 0.0)
     plain = ctx.born_adjoint(_lib.Green(G, G, _lib.RB_F32), w, R)
     assert torch.equal(out[1:], plain[1:]) != split
+
+
+def forward(ctx, G, delta):
+    from paper_2211_00316_amd import _lib
+
+    w = torch.ones(G.shape[1], dtype=torch.complex64, device="cuda:0")
+    return ctx.born_forward(_lib.Green(G, G, _lib.RB_F32), w, delta)
+
+
+# Every pair of transducers keeps FP32's accuracy. The first 35 and the others each see a node of
+# their own; what one of each see together are 100 nodes where both are 2^-16 (2^-40) of their
+# rows' others. gauss: a perturbation that falls off to FP32's smallest numbers, which must not
+# cost the second pass. K products of (3 x 2^-24) and the roundings of their sum, as in the
+# comparison with FP64 of the other operands, and those of G v.
+@pytest.mark.parametrize("case", ["cross16", "cross40", "gauss"])
+def test_forward_keeps_small_entries(ctx, case):
+    n, nm = 70, 20000
+    g = torch.Generator(device="cuda:0").manual_seed(6)
+    G = randc(g, n, nm)
+    delta = torch.zeros(nm, device="cuda:0")
+    if case == "gauss":
+        x = torch.linspace(-16.0, 16.0, nm, device="cuda:0", dtype=torch.float64)
+        delta = (1e-9 * torch.exp(-0.5 * x * x)).float()
+        assert (delta == 0).any() and ((delta > 0) & (delta < 1e-40)).any()
+    else:
+        G[:, 100:200] *= 2.0 ** -int(case[5:])
+        G[:35, 778] = 0
+        G[35:, 777] = 0
+        delta[100:200] = 1.0
+        delta[777:779] = 1.0
+    d = forward(ctx, G, delta)
+    X = G.to(torch.complex128)
+    ref = (X * delta.double()) @ X.t().contiguous()
+    pairs = slice(None) if case == "gauss" else slice(35, None)
+    K = int((delta != 0).sum())
+    err = rel(torch.view_as_real(d[:35, pairs]), torch.view_as_real(ref[:35, pairs]))
+    assert err <= 2.0 * (3.0 + math.sqrt(K)) * 2.0 ** -24 + 6 * 2.0 ** -24
+    G[0, 0] = complex(math.inf, 0.0)
+    assert not torch.equal(d[1:, 1:], forward(ctx, G, delta)[1:, 1:])
