@@ -564,8 +564,9 @@ static rb_status check_backproject(rb_ctx *ctx, const rb_green *gr, const float 
 }
 
 // The back-projection's contraction with its scratch (partial sums, the residual operand)
-// carved from `a`, which holds at least backproject_ws_bytes (FP32: at least the partial sums;
-// the split form of R where the rest fits): complex partial sums parts[2][mb][n_mask] of sum_{e,r} R[e][r] (H_e H_r + H^x_e H^x_r + H^y_e H^y_r).
+// carved from `a`, which holds at least backproject_ws_bytes (FP32: at least the partial sums and
+// n x n complex64; the parts of R where they fit): complex partial sums parts[2][mb][n_mask] of
+// sum_{e,r} R[e][r] (H_e H_r + H^x_e H^x_r + H^y_e H^y_r).
 static rb_status backproject_parts(rb_ctx *ctx, rb_arena *a, const rb_green *gr, const float *R,
                                    float **parts_out, int *mb_out) {
     const bool lp = gr->prec != RB_F32;

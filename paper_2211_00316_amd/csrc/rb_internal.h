@@ -233,8 +233,8 @@ rb_status rb_launch_forward(rb_ctx *ctx, const rb_green *gr, const float *w, con
                             float *d, const float *gscale);
 // Row-reduced complex GEMM: parts[2][mblocks][n_mask] (re, im) of
 // sum_e E_c[e][q] (R B_c)[e][q] summed over the n_comp components c (E_c = B_c, conjugated
-// with conj_b). scratch: rb_rowred_ws_bytes(n) for the split form of R (rb_gemm.hip); with less
-// the plain FP32 kernel runs.
+// with conj_b). scratch: rb_rowred_ws_bytes(n) for the split form of R (rb_gemm.hip); with less,
+// but at least n x n complex64, the plain FP32 kernel runs.
 rb_status rb_launch_rowred(rb_ctx *ctx, int n, int n_mask, const float *R, const float *B,
                            int n_comp, int conj_b, void *scratch, size_t scratch_bytes,
                            float *parts, int *mblocks);

@@ -137,3 +137,35 @@ def test_forward_keeps_small_entries(ctx, case):
     assert err <= 2.0 * (3.0 + math.sqrt(K)) * 2.0 ** -24 + 6 * 2.0 ** -24
     G[0, 0] = complex(math.inf, 0.0)
     assert not torch.equal(d[1:, 1:], forward(ctx, G, delta)[1:, 1:])
+
+
+# A call that the split form turns down pays for little more than the FP32 kernel. That issues 16/6
+# of the split kernel's MFMA time per product and 1.18 times its products (R's triangle in blocks
+# of 256 rows instead of 64), 3.14 together; the infinity is met in the first columns. A fifth of
+# that is left for what the MFMAs do not bound.
+def test_backproject_turned_down_time(ctx):
+    from paper_2211_00316_amd import _lib
+
+    n, nm = 1024, 40000
+    g = torch.Generator(device="cuda:0").manual_seed(4)
+    H = torch.stack([randc(g, n, nm) for _ in range(3)]).contiguous()
+    R = randc(g, n, n)
+    c = torch.full((nm,), 1500.0, device="cuda:0", dtype=torch.float64)
+    gr = _lib.Green(torch.zeros_like(H[0]), H, _lib.RB_F32)
+
+    def best():
+        times = []
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            ctx.backproject(gr, R, c, OMEGA, D_OMEGA)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times[1:])
+
+    split = best()
+    H[0, 0, 0] = complex(math.inf, 0.0)
+    down = best()
+    print(f"split {split:.2f} ms, turned down {down:.2f} ms")
+    assert down <= 1.2 * 3.14 * split
