@@ -223,13 +223,11 @@ __global__ void __launch_bounds__(256) reduce_kernel(const float2 *__restrict__ 
     float2 v;
     v.x = (red[0][a][b].x + red[1][a][b].x) + (red[2][a][b].x + red[3][a][b].x);
     v.y = (red[0][a][b].y + red[1][a][b].y) + (red[2][a][b].y + red[3][a][b].y);
+    // one factor: with large weights the sum times theirs alone can leave FP32's range
     float f = mul ? mul[1] : 1.f;
     if (mul_pow == 2) f *= f;
+    if (rows) f /= rows[ge] * rows[gr];
     v = make_float2(v.x * f, v.y * f);
-    if (rows) {
-        const float ie = 1.f / rows[ge], ir = 1.f / rows[gr];
-        v = make_float2(v.x * ie * ir, v.y * ie * ir);
-    }
     v = check.unscale(v);
     check.see(ge, gr, v);
     if (part == 0) d[(size_t)ge * n + gr] = v;
