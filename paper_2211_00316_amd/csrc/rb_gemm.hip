@@ -841,7 +841,11 @@ size_t rb_rowred_ws_bytes(int n) {
 }
 
 // Split operands where the scratch holds R's; else (and for values that the split form turns
-// down) the FP32 kernel.
+// down) the FP32 kernel. That alone also where a CU's column blocks take three of its K steps at
+// most: the split form has two launches more (us, FP32 / split: 4000 nodes, back-projections of 16
+// transducers 30.6 / 39.4, of 17 44.8 / 39.1, adjoints of 32 21.3 / 24.5, of 48 30.1 / 29.3, of 49
+// 41.8 / 30.2; 40 000 nodes, back-projection of 16 79 / 69, adjoint of 16 32.1 / 35.7, of 17 46.3 /
+// 35.4).
 rb_status rb_launch_rowred(rb_ctx *ctx, int n, int n_mask, const float *R, const float *B,
                            int n_comp, int conj_b, void *scratch, size_t scratch_bytes,
                            float *parts, int *mblocks_out) {
@@ -853,7 +857,9 @@ rb_status rb_launch_rowred(rb_ctx *ctx, int n, int n_mask, const float *R, const
         return rb_fail(ctx, RB_EINVAL, "no room for the symmetric residual");
     SplitHead *head = nullptr;
     rb_prof_begin(ctx, ST_BACKPROJECT);
-    if (rowred_split_fits(n, n_mask) && scratch_bytes >= rb_rowred_ws_bytes(n)) {
+    const int nblocks = (n_mask + RR_BN - 1) / RR_BN;
+    const bool brief = (long)n_comp * ((n + RR_BK - 1) / RR_BK) * ((nblocks + grid - 1) / grid) <= 3;
+    if (!brief && rowred_split_fits(n, n_mask) && scratch_bytes >= rb_rowred_ws_bytes(n)) {
         __bf16 *Rf = static_cast<__bf16 *>(scratch);
         head = reinterpret_cast<SplitHead *>(static_cast<char *>(scratch) +
                                              rb_align(split_residual_bytes(n)));
@@ -873,7 +879,7 @@ rb_status rb_launch_rowred(rb_ctx *ctx, int n, int n_mask, const float *R, const
     RB_CHECK_LAUNCH(ctx);
     hipLaunchKernelGGL(rowred_kernel, dim3(grid), dim3(256), 0, ctx->stream, Rs,
                        (const float2 *)B, n, n_mask, n_comp, conj_b, mblocks,
-                       (n_mask + RR_BN - 1) / RR_BN, head, parts);
+                       nblocks, head, parts);
     RB_CHECK_LAUNCH(ctx);
     rb_prof_end(ctx);
     if (mblocks_out) *mblocks_out = mblocks;

@@ -169,3 +169,27 @@ def test_backproject_turned_down_time(ctx):
     down = best()
     print(f"split {split:.2f} ms, turned down {down:.2f} ms")
     assert down <= 1.2 * 3.14 * split
+
+
+# Calls of which a CU's column blocks (64 nodes) take three steps of 16 transducers, over all
+# components, run on the FP32 kernel alone, longer ones split.
+@pytest.mark.parametrize("kind, n, nm, split", [
+    ("backproject", 16, 500, False), ("backproject", 17, 500, True),
+    ("backproject", 16, 40000, True), ("adjoint", 48, 500, False), ("adjoint", 49, 500, True),
+    ("adjoint", 16, 40000, False), ("adjoint", 17, 40000, True), ("adjoint", 8, 70000, True)])
+def test_short_calls_run_on_fp32_kernels(ctx, kind, n, nm, split):
+    from paper_2211_00316_amd import _lib
+
+    g = torch.Generator(device="cuda:0").manual_seed(n)
+    H = torch.stack([randc(g, n, nm) for _ in range(3)]).contiguous()
+    R = randc(g, n, n)
+    w = torch.ones(nm, dtype=torch.complex64, device="cuda:0")
+
+    def call():
+        if kind == "backproject":
+            return backproject(ctx, H, R)
+        return ctx.born_adjoint(_lib.Green(H[0].contiguous(), H, _lib.RB_F32), w, R)
+
+    out = call()
+    H[0, 0, 0] = complex(math.inf, 0.0)
+    assert torch.equal(out[1:], call()[1:]) != split
