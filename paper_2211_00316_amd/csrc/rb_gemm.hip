@@ -707,12 +707,12 @@ struct SplitCheck {
 // The reduction after the FP32 kernel: only where that ran.
 struct PlainCheck {
     const SplitHead *head;
-    __device__ bool skip() const { return !head->plain && !head->bad; }
+    __device__ bool skip() const { return head && !head->plain && !head->bad; }
     __device__ float2 unscale(float2 v) const { return v; }
     __device__ void see(int, int, float2) const {}
 };
 
-// The FP32 form, for what the split form turns down. dpart: [splitk][n][n] complex partial sums
+// The FP32 form, for what the split form turns down (head NULL: in any case). dpart: [splitk][n][n] complex partial sums
 // (only upper tiles written).
 __global__ void __launch_bounds__(256) forward_kernel(const float2 *__restrict__ G,
                                                       const float2 *__restrict__ w,
@@ -722,7 +722,7 @@ __global__ void __launch_bounds__(256) forward_kernel(const float2 *__restrict__
                                                       float2 *__restrict__ dpart) {
     __shared__ float a_re[FW_BK][FW_B], a_im[FW_BK][FW_B];
     __shared__ float b_re[FW_BK][FW_B], b_im[FW_BK][FW_B];
-    if (!head->plain && !head->bad) return;
+    if (head && !head->plain && !head->bad) return;
     int tm, tn;
     upper_tile(blockIdx.x, T, tm, tn);
     const int split = blockIdx.y;
@@ -904,47 +904,61 @@ size_t rb_forward_ws_bytes(int n, int n_mask) {
                          std::max(RB_TUNE_SPLITK_MAX, rb_fwd::splitk_most(T * (T + 1) / 2)));
 }
 
+// Split operands; the FP32 kernel after them for what they turn down. That alone where the nodes are
+// few: the split form has up to four launches more, and its eight K chunks write eight partial
+// sums (us without weights, FP32 / split: 300 transducers, 32 nodes 17.2 / 19.6, 33 22.2 / 19.1;
+// 1500 transducers, 128 nodes 50.1 / 62.0, 256 83.4 / 69.0; 2000, 128 81.0 / 89.6, 192 97.8 /
+// 89.1).
 rb_status rb_launch_forward(rb_ctx *ctx, const rb_green *gr, const float *w, const float *delta,
                             float *d, const float *gscale) {
     const int n = gr->n, K = gr->n_mask;
     const rb_tuning *t = rb_tuned(ctx, n, K, RB_F32);
-    const rb_fwd::Shape s = rb_fwd::make_shape(n, K, FW_BK, ctx->n_cu, t ? t->fwd_splitk : 0);
+    const bool brief = K <= (n > 1024 ? 160 : 32);
+    const int want = t ? t->fwd_splitk : brief ? std::max(1, (K + FW_BK - 1) / FW_BK / 4) : 0;
+    const rb_fwd::Shape s = rb_fwd::make_shape(n, K, FW_BK, ctx->n_cu, want);
     ctx->ws.used = 0;
     RB_TRY(rb_arena_reserve(ctx, &ctx->ws, forward_bytes(n, K, s.splitk)));
     float2 *dpart = rb_carve<float2>(&ctx->ws, (size_t)s.splitk * n * n);
     float2 *v = rb_carve<float2>(&ctx->ws, K);
     uint32_t *vmax = rb_carve<uint32_t>(&ctx->ws, FS_PARTS);
-    SplitHead *head = rb_carve<SplitHead>(&ctx->ws, 1);
+    SplitHead *head = brief ? nullptr : rb_carve<SplitHead>(&ctx->ws, 1);
     const float2 *G = (const float2 *)gr->G, *wp = (const float2 *)w;
-    rb_prof_begin(ctx, ST_FORWARD);
-    if (w) {
-        hipLaunchKernelGGL(weight_max_kernel, dim3(FS_PARTS), dim3(256), 0, ctx->stream, K, wp,
-                           delta, vmax);
-        RB_CHECK_LAUNCH(ctx);
-    }
-    const int kw = w ? K : 0;
-    hipLaunchKernelGGL(weight_scale_kernel, dim3(kw ? (kw + 255) / 256 : 1), dim3(256), 0,
-                       ctx->stream, kw, wp, delta, vmax, v, head);
-    RB_CHECK_LAUNCH(ctx);
+    const unsigned reduce_grid = rb_fwd::reduce_grid(n);
     auto launch = [&](auto op) {
         hipLaunchKernelGGL(rb_fwd::forward_reg_kernel<decltype(op)>, dim3(rb_fwd::grid_of(s)),
                            dim3(rb_fwd::FTHREADS), 0, ctx->stream, op, s, dpart);
     };
-    if (w) launch(SplitFwd<true>{G, v, head});
-    else launch(SplitFwd<false>{G, v, head});
-    RB_CHECK_LAUNCH(ctx);
-    rb_prof_end(ctx);
-    rb_prof_begin(ctx, ST_FORWARD_REDUCE);
-    // the operand may carry sqrt(v) gscale[0]
-    hipLaunchKernelGGL(rb_fwd::reduce_kernel<SplitCheck>, dim3(rb_fwd::reduce_grid(n)), dim3(256),
-                       0, ctx->stream, dpart, n, s.splitk, gscale, 2, (const float *)nullptr,
-                       SplitCheck{head}, (float2 *)d);
-    RB_CHECK_LAUNCH(ctx);
+    rb_prof_begin(ctx, ST_FORWARD);
+    if (!brief) {
+        if (w) {
+            hipLaunchKernelGGL(weight_max_kernel, dim3(FS_PARTS), dim3(256), 0, ctx->stream, K, wp,
+                               delta, vmax);
+            RB_CHECK_LAUNCH(ctx);
+        }
+        const int kw = w ? K : 0;
+        hipLaunchKernelGGL(weight_scale_kernel, dim3(kw ? (kw + 255) / 256 : 1), dim3(256), 0,
+                           ctx->stream, kw, wp, delta, vmax, v, head);
+        RB_CHECK_LAUNCH(ctx);
+        if (w) launch(SplitFwd<true>{G, v, head});
+        else launch(SplitFwd<false>{G, v, head});
+        RB_CHECK_LAUNCH(ctx);
+        rb_prof_end(ctx);
+        rb_prof_begin(ctx, ST_FORWARD_REDUCE);
+        // the operand may carry sqrt(v) gscale[0]
+        hipLaunchKernelGGL(rb_fwd::reduce_kernel<SplitCheck>, dim3(reduce_grid), dim3(256), 0,
+                           ctx->stream, dpart, n, s.splitk, gscale, 2, (const float *)nullptr,
+                           SplitCheck{head}, (float2 *)d);
+        RB_CHECK_LAUNCH(ctx);
+    }
     hipLaunchKernelGGL(forward_kernel, dim3(s.tiles, s.splitk), dim3(256), 0, ctx->stream, G, wp,
                        delta, n, K, s.nT, s.kchunk * FW_BK, head, dpart);
     RB_CHECK_LAUNCH(ctx);
-    hipLaunchKernelGGL(rb_fwd::reduce_kernel<PlainCheck>, dim3(rb_fwd::reduce_grid(n)), dim3(256),
-                       0, ctx->stream, dpart, n, s.splitk, gscale, 2, (const float *)nullptr,
+    if (brief) {
+        rb_prof_end(ctx);
+        rb_prof_begin(ctx, ST_FORWARD_REDUCE);
+    }
+    hipLaunchKernelGGL(rb_fwd::reduce_kernel<PlainCheck>, dim3(reduce_grid), dim3(256), 0,
+                       ctx->stream, dpart, n, s.splitk, gscale, 2, (const float *)nullptr,
                        PlainCheck{head}, (float2 *)d);
     RB_CHECK_LAUNCH(ctx);
     rb_prof_end(ctx);

@@ -193,3 +193,26 @@ def test_short_calls_run_on_fp32_kernels(ctx, kind, n, nm, split):
     out = call()
     H[0, 0, 0] = complex(math.inf, 0.0)
     assert torch.equal(out[1:], call()[1:]) != split
+
+
+# Forwards over few nodes run on the FP32 kernel alone (large rings up to 160 nodes), others split.
+@pytest.mark.parametrize("n, nm, split", [(70, 32, False), (70, 33, True), (1024, 33, True),
+                                          (1025, 160, False), (1025, 161, True)])
+@pytest.mark.parametrize("weights", [True, False])
+def test_short_forwards_run_on_fp32_kernels(ctx, n, nm, split, weights):
+    from paper_2211_00316_amd import _lib
+
+    g = torch.Generator(device="cuda:0").manual_seed(n + nm)
+    G = randc(g, n, nm)
+    w = randc(g, nm) if weights else None
+    delta = torch.randn(nm, generator=g, device="cuda:0") if weights else None
+    d = ctx.born_forward(_lib.Green(G, G, _lib.RB_F32), w, delta)
+    X = G.to(torch.complex128)
+    v = w.to(torch.complex128) * delta.double() if weights else 1.0
+    ref = (X * v) @ X.t().contiguous()
+    # K products of (3 x 2^-24), their sum's roundings and those of w delta and G v
+    err = rel(torch.view_as_real(d), torch.view_as_real(ref))
+    assert err <= 2.0 * (3.0 + math.sqrt(nm)) * 2.0 ** -24 + 6 * 2.0 ** -24
+    G[0, 0] = complex(math.inf, 0.0)
+    plain = ctx.born_forward(_lib.Green(G, G, _lib.RB_F32), w, delta)
+    assert torch.equal(d[1:, 1:], plain[1:, 1:]) != split
