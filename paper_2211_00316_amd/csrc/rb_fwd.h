@@ -73,8 +73,12 @@ inline Shape make_shape(int n, int K, int bk, int n_cu, int want) {
     return s;
 }
 
+// Workgroups are dealt to the 8 XCDs round-robin. Chunk c goes to XCD c mod 8, whole; where there
+// are fewer chunks than XCDs (a tuned configuration, few nodes) tiles and chunks are dealt one by
+// one instead, so that no XCD stays without (2048 transducers, 30 000 nodes, FP32: one chunk 21.1
+// -> 6.2 ms, two 11.2 -> 4.1).
 inline unsigned grid_of(const Shape &s) {
-    return (unsigned)(s.tiles * ((s.splitk + 7) / 8) * 8);
+    return (unsigned)(s.tiles * (s.splitk < 8 ? s.splitk : (s.splitk + 7) / 8 * 8));
 }
 
 // Op: the operand type (see rb_gemm.hip, rb_lowp.hip). A thread stages a quarter of a stage's K
@@ -88,8 +92,9 @@ __global__ void __launch_bounds__(FTHREADS, 2) forward_reg_kernel(const Op op, c
     __shared__ __attribute__((aligned(64))) char st0[2 * SIDE];
     __shared__ __attribute__((aligned(64))) char st1[TWO ? 2 * SIDE : 64];
     if (op.skip()) return;  // decided before this launch: the same for every workgroup
-    const int kq = blockIdx.x >> 3;
-    const int split = (kq / s.tiles) * 8 + (blockIdx.x & 7);
+    const bool few = s.splitk < 8;
+    const int kq = few ? blockIdx.x : blockIdx.x >> 3;
+    const int split = few ? kq / s.tiles : (kq / s.tiles) * 8 + (blockIdx.x & 7);
     if (split >= s.splitk) return;
     int tm, tn;
     upper_tile(kq % s.tiles, s.nT, tm, tn);
