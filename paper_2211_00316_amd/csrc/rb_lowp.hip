@@ -113,13 +113,12 @@ __device__ __forceinline__ float pow2_scale(float bound) {
     return ldexpf(1.f, 14 - e);
 }
 
-__device__ __forceinline__ void row_scales(const unsigned int *__restrict__ rowmax, int e,
-                                           float sk, float isk, float gmax, float &sg,
-                                           float &sh) {
-    const float amax = __uint_as_float(rowmax[2 * e]);
-    const float iamax = __uint_as_float(rowmax[2 * e + 1]);
-    sg = pow2_scale(amax * isk * gmax);
-    sh = pow2_scale((float)RB_PI * sk * iamax);
+__device__ __forceinline__ void row_scales(float amax, float iamax, int e, int N, double omega,
+                                           double c0, float gmax, float *__restrict__ scales) {
+    const double k0 = omega / c0;
+    const float sk = (float)sqrt(k0), isk = 1.0f / sk;
+    scales[e] = pow2_scale(amax * isk * gmax);
+    scales[N + e] = pow2_scale((float)RB_PI * sk * iamax);
 }
 
 // The scales of every row for one frequency, scales[e] (G) and scales[N + e] (H), before the
@@ -130,20 +129,20 @@ __global__ void __launch_bounds__(256) row_scale_kernel(const unsigned int *__re
                                                         float gmax, float *__restrict__ scales) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= N) return;
-    const double k0 = omega / c0;
-    const float sk = (float)sqrt(k0), isk = 1.0f / sk;
-    float sg, sh;
-    row_scales(rowmax, e, sk, isk, gmax, sg, sh);
-    scales[e] = sg;
-    scales[N + e] = sh;
+    row_scales(__uint_as_float(rowmax[2 * e]), __uint_as_float(rowmax[2 * e + 1]), e, N, omega, c0,
+               gmax, scales);
 }
 
 // Largest A and 1/A over the valid entries of each row of the ABI tables, as the bits rowmax[2e],
 // rowmax[2e+1] (cleared before): workgroups of AMAX_CHUNK nodes of one row, one atomic each. The
-// largest 1/A is that of the smallest A (a correctly rounded quotient is monotone).
+// largest 1/A is that of the smallest A (a correctly rounded quotient is monotone). Where a row is
+// one workgroup's, it gives the row's scales itself: nothing to clear and no scale kernel (24
+// transducers, 80^2 nodes, BF16: 25.7 -> 20.5 us).
 constexpr int AMAX_CHUNK = 16384;
 __global__ void __launch_bounds__(256) row_amax_kernel(rb_tables tb, int n_mask,
-                                                       unsigned int *__restrict__ rowmax) {
+                                                       unsigned int *__restrict__ rowmax,
+                                                       double omega, double c0, float gmax,
+                                                       float *__restrict__ scales) {
     __shared__ float red[2][4];
     const int e = blockIdx.y;
     const int q0 = blockIdx.x * AMAX_CHUNK, q1 = min(n_mask, q0 + AMAX_CHUNK);
@@ -169,9 +168,12 @@ __global__ void __launch_bounds__(256) row_amax_kernel(rb_tables tb, int n_mask,
     if (threadIdx.x == 0) {
         m0 = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
         lo = fminf(fminf(red[1][0], red[1][1]), fminf(red[1][2], red[1][3]));
-        if (m0 > 0.f) {
+        const float inv = m0 > 0.f ? 1.0f / lo : 0.f;
+        if (gridDim.x == 1) {
+            row_scales(m0, inv, e, (int)gridDim.y, omega, c0, gmax, scales);
+        } else if (m0 > 0.f) {
             atomicMax(rowmax + 2 * e, __float_as_uint(m0));
-            atomicMax(rowmax + 2 * e + 1, __float_as_uint(1.0f / lo));
+            atomicMax(rowmax + 2 * e + 1, __float_as_uint(inv));
         }
     }
 }
@@ -1540,14 +1542,18 @@ rb_status rb_launch_green_lp(rb_ctx *ctx, const rb_tables *tb, double omega, dou
                              int write_g, unsigned int *rowmax) {
     const int N = tb->n, n_mask = tb->n_mask;
     rb_prof_begin(ctx, ST_GREEN);
-    RB_TRY(rb_launch_fill_i32(ctx, reinterpret_cast<int32_t *>(rowmax), 2 * N, 0));
-    hipLaunchKernelGGL(row_amax_kernel, dim3((n_mask + AMAX_CHUNK - 1) / AMAX_CHUNK, N), dim3(256),
-                       0, ctx->stream, *tb, n_mask, rowmax);
-    RB_CHECK_LAUNCH(ctx);
+    const unsigned chunks = (n_mask + AMAX_CHUNK - 1) / AMAX_CHUNK;
     const float gmax = gs ? GS_MAX : 1.f;
-    hipLaunchKernelGGL(row_scale_kernel, dim3((N + 255) / 256), dim3(256), 0, ctx->stream, rowmax,
-                       N, omega, c0, gmax, out->scales);
+    if (chunks > 1)
+        RB_TRY(rb_launch_fill_i32(ctx, reinterpret_cast<int32_t *>(rowmax), 2 * N, 0));
+    hipLaunchKernelGGL(row_amax_kernel, dim3(chunks, N), dim3(256), 0, ctx->stream, *tb, n_mask,
+                       rowmax, omega, c0, gmax, out->scales);
     RB_CHECK_LAUNCH(ctx);
+    if (chunks > 1) {
+        hipLaunchKernelGGL(row_scale_kernel, dim3((N + 255) / 256), dim3(256), 0, ctx->stream,
+                           rowmax, N, omega, c0, gmax, out->scales);
+        RB_CHECK_LAUNCH(ctx);
+    }
     // 64 transducers x 64 nodes a workgroup, as in the split form of a step: G leaves as rows of
     // 128 bytes and each node's H as 128-byte pieces (16 bytes per lane otherwise: 512
     // transducers and 152 053 nodes took 1.80 ms in the split form and 1.27 in BF16, now 0.92
