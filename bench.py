@@ -172,7 +172,8 @@ def cpu_baseline(w):
     }
 
 
-PEAKS = {"f32": (2500.0, "fp16 MFMA dense (FP32 operands split in two)"), "bf16": (2500.0, "bf16 MFMA dense"),
+PEAKS = {"f32": (2500.0, "bf16 MFMA dense (FP32 operands in three parts)"),
+         "bf16": (2500.0, "bf16 MFMA dense"),
          "f16": (2500.0, "fp16 MFMA dense"), "f16x": (2500.0, "fp16 MFMA dense")}
 
 
@@ -188,9 +189,9 @@ def contraction_flops(stage, N, Pm, prec):
     complex GEMM count (8 N^2 P_m for the forward, three of them for the back-projection)."""
     own_pairs = N * (N + 1) // 2
     if stage == "forward_gemm":
-        if prec == "f32":   # 128 x 128 upper tiles over K = P_m, three FP16 products
+        if prec == "f32":   # 128 x 128 upper tiles over K = P_m, six BF16 products
             nT = _pad(N, 128) // 128
-            issued = 3 * 8.0 * (nT * (nT + 1) // 2) * 128 * 128 * Pm
+            issued = 6 * 8.0 * (nT * (nT + 1) // 2) * 128 * 128 * Pm
         else:               # 256 x 128 upper tiles over K = P_m padded to 32
             nT = _pad(N, 128) // 128
             tiles = sum(nT - 2 * tm for tm in range((nT + 1) // 2))
@@ -207,8 +208,8 @@ def contraction_flops(stage, N, Pm, prec):
         # padded to 64)
         issued = 16.0 * mb * 256 * Np * cols + 0.5 * 8.0 * mb * 256 * _pad(N, 64) * cols
     elif prec == "f32":
-        # H, H u_x, H u_y over the triangle of 64-row blocks, three FP16 products each
-        issued = 3 * 24.0 * sum(64 * (Np - i) for i in range(0, N, 64)) * cols
+        # H, H u_x, H u_y over the triangle of 64-row blocks, six BF16 products each
+        issued = 6 * 24.0 * sum(64 * (Np - i) for i in range(0, N, 64)) * cols
     else:
         # H over the block triangle, the bilinear form a^T Rs b over all of Rs
         issued = 8.0 * tri * cols + 8.0 * mb * 256 * Np * cols
@@ -331,12 +332,12 @@ def kernel_rooflines(stages, steps, N, Pm, samples, prec, workload):
                          "TFLOP/s", peak, peak_name,
                          "flop the kernel issues (upper 256 x 128 tiles of the symmetric "
                          "N x N product, 8 per complex multiply-add over P_m; FP32: 128 x 128 "
-                         "tiles, 3 products of split operands)"),
+                         "tiles, 6 products of split operands)"),
         "backproject_gemm": ("mfma",
                              contraction_flops("backproject_gemm", N, Pm, prec)[0] / 1e12,
                              "TFLOP/s", peak, peak_name,
                              "flop the kernel issues (row slabs of 256; FP32: 3 complex "
-                             "products over the upper triangle of R in blocks of 64, each as 3 "
+                             "products over the upper triangle of R in blocks of 64, each as 6 "
                              "products of split operands; 16-bit: H over the triangle in slabs "
                              "and the bilinear form a^T Rs b over all of Rs; split: 2 FP16 "
                              "products over all of Rs + 1 FP8 product counted at half)"),

@@ -712,8 +712,8 @@ struct PlainCheck {
     __device__ void see(int, int, float2) const {}
 };
 
-// The FP32 form, for what the split form turns down (head NULL: in any case). dpart: [splitk][n][n] complex partial sums
-// (only upper tiles written).
+// The FP32 form, for what the split form turns down (head NULL: in any case). dpart:
+// [splitk][n][n] complex partial sums (only upper tiles written).
 __global__ void __launch_bounds__(256) forward_kernel(const float2 *__restrict__ G,
                                                       const float2 *__restrict__ w,
                                                       const float *__restrict__ delta, int n,
@@ -858,7 +858,8 @@ rb_status rb_launch_rowred(rb_ctx *ctx, int n, int n_mask, const float *R, const
     SplitHead *head = nullptr;
     rb_prof_begin(ctx, ST_BACKPROJECT);
     const int nblocks = (n_mask + RR_BN - 1) / RR_BN;
-    const bool brief = (long)n_comp * ((n + RR_BK - 1) / RR_BK) * ((nblocks + grid - 1) / grid) <= 3;
+    const long ksteps = (n + RR_BK - 1) / RR_BK, rounds = (nblocks + grid - 1) / grid;
+    const bool brief = n_comp * ksteps * rounds <= 3;
     if (!brief && rowred_split_fits(n, n_mask) && scratch_bytes >= rb_rowred_ws_bytes(n)) {
         __bf16 *Rf = static_cast<__bf16 *>(scratch);
         head = reinterpret_cast<SplitHead *>(static_cast<char *>(scratch) +
@@ -904,8 +905,8 @@ size_t rb_forward_ws_bytes(int n, int n_mask) {
                          std::max(RB_TUNE_SPLITK_MAX, rb_fwd::splitk_most(T * (T + 1) / 2)));
 }
 
-// Split operands; the FP32 kernel after them for what they turn down. That alone where the nodes are
-// few: the split form has up to four launches more, and its eight K chunks write eight partial
+// Split operands; the FP32 kernel after them for what they turn down. That alone where the nodes
+// are few: the split form has up to four launches more, and its eight K chunks write eight partial
 // sums (us without weights, FP32 / split: 300 transducers, 32 nodes 17.2 / 19.6, 33 22.2 / 19.1;
 // 1500 transducers, 128 nodes 50.1 / 62.0, 256 83.4 / 69.0; 2000, 128 81.0 / 89.6, 192 97.8 /
 // 89.1).

@@ -1597,21 +1597,23 @@ rb_status rb_launch_green_lp_rec(rb_ctx *ctx, const float4 *rec, const double2 *
     hipLaunchKernelGGL(row_scale_kernel, dim3((n + 255) / 256), dim3(256), 0, ctx->stream, rowmax,
                        n, omega, c0, gmax, out->scales);
     RB_CHECK_LAUNCH(ctx);
-    if (out->prec == RB_BF16)
-        hipLaunchKernelGGL((green_lp_rec_kernel<__bf16, false, GW, 4, false>), grd, dim3(256), 0, ctx->stream,
-                           rb_tables{}, rec, ctx->d_mask_index, ring, g.x0, g.y0, g.dx, g.nx, n, nm, omega,
-                           c0, (const float2 *)gs, gscale, write_g, (__bf16 *)out->G,
-                           (__bf16 *)out->H, out->scales, nullptr);
-    else if (rb_prec_split(out->prec))
-        hipLaunchKernelGGL((green_lp_rec_kernel<_Float16, true, GWS, 8, false>), grd, dim3(512), 0, ctx->stream,
-                           rb_tables{}, rec, ctx->d_mask_index, ring, g.x0, g.y0, g.dx, g.nx, n, nm, omega,
-                           c0, (const float2 *)gs, gscale, write_g, (_Float16 *)out->G,
-                           (_Float16 *)out->H, out->scales, (_Float16 *)out->H + hlo);
-    else
-        hipLaunchKernelGGL((green_lp_rec_kernel<_Float16, false, GW, 4, false>), grd, dim3(256), 0,
-                           ctx->stream, rb_tables{}, rec, ctx->d_mask_index, ring, g.x0, g.y0, g.dx, g.nx, n,
-                           nm, omega, c0, (const float2 *)gs, gscale, write_g,
-                           (_Float16 *)out->G, (_Float16 *)out->H, out->scales, nullptr);
+    auto launch = [&](auto kernel, int threads, auto *G, auto *H, auto *Hlo) {
+        hipLaunchKernelGGL(kernel, grd, dim3(threads), 0, ctx->stream, rb_tables{}, rec,
+                           ctx->d_mask_index, ring, g.x0, g.y0, g.dx, g.nx, n, nm, omega, c0,
+                           (const float2 *)gs, gscale, write_g, G, H, (const float *)out->scales,
+                           Hlo);
+    };
+    if (out->prec == RB_BF16) {
+        launch(green_lp_rec_kernel<__bf16, false, GW, 4, false>, 256, (__bf16 *)out->G,
+               (__bf16 *)out->H, (__bf16 *)nullptr);
+    } else {
+        _Float16 *G = (_Float16 *)out->G, *H = (_Float16 *)out->H;
+        if (rb_prec_split(out->prec))
+            launch(green_lp_rec_kernel<_Float16, true, GWS, 8, false>, 512, G, H, H + hlo);
+        else
+            launch(green_lp_rec_kernel<_Float16, false, GW, 4, false>, 256, G, H,
+                   (_Float16 *)nullptr);
+    }
     RB_CHECK_LAUNCH(ctx);
     rb_prof_end(ctx);
     return RB_OK;
@@ -1810,7 +1812,8 @@ bool forward_pipe_fits(int n, int n_mask) {
 }  // namespace
 
 int rb_forward_lp_default_splitk(int n, int n_mask, int pipe, int n_cu) {
-    if (pipe && forward_pipe_fits(n, n_mask)) return forward_shape(n, rb_lp_pad(n_mask), n_cu).splitk;
+    if (pipe && forward_pipe_fits(n, n_mask))
+        return forward_shape(n, rb_lp_pad(n_mask), n_cu).splitk;
     return rb_fwd::make_shape(n, n_mask, 32, n_cu, 0).splitk;
 }
 

@@ -513,23 +513,22 @@ __device__ __forceinline__ int trace_ray(const SplineMap &m, const AbsMap &am, c
                                         el, j, sb, flag, nullptr);
 }
 
-// One lane per ray; a wavefront holds 64 neighbouring rays of one transducer, so the
-// per-step sample stores are coalesced. Rays near the middle of a fan cross the whole disk
-// and take the most steps, so wavefronts are dispatched by the distance of their ray group
-// from the fan's middle (rank r: groups mid, mid - 1, mid + 1, ...), over all transducers:
-// the longest run first and the shortest fill the end of the launch. Also counts the
-// samples written (one atomic per wavefront; the workgroup is a whole number of them).
-// Four waves per SIMD (128 registers) hide more of the coefficient loads' latency than three.
-// Bound by the instructions of a step (about 300, a quarter of them FP64). With the step's length
-// and its multiples constants of the loop, whole traces of 512 transducers of 1024 rays on a ring
-// of 50 mm went from 3.81 to 3.56 ms and nothing is spilled. FP32 copies of FP64 values carried to
-// the next step and 32-bit sample offsets from scalar bases: 3.28 to 3.23 ms, in an absorbing medium
-// 3.64 to 3.55. Workgroups (four transducers of one
-// rank) are dealt to the 8 XCDs round-robin by launch index. When E is a multiple of 32 the
-// transducer groups of a rank are renamed so that each XCD traces one contiguous arc of E / 8
-// transducers: same-rank rays of neighbouring transducers cross nearly the same cells at about the
-// same time, so that XCD's L2 fetches their spline coefficients once instead of once per group of
-// four. (Which wave traces which ray changes nothing in the results.)
+// One lane per ray; a wavefront holds 64 neighbouring rays of one transducer, so the per-step
+// sample stores are coalesced. Rays near the middle of a fan cross the whole disk and take the
+// most steps, so wavefronts are dispatched by the distance of their ray group from the fan's
+// middle (rank r: groups mid, mid - 1, mid + 1, ...), over all transducers: the longest run first
+// and the shortest fill the end of the launch. Also counts the samples written (one atomic per
+// wavefront; the workgroup is a whole number of them). Four waves per SIMD (128 registers) hide
+// more of the coefficient loads' latency than three. Bound by the instructions of a step (about
+// 300, a quarter of them FP64). With the step's length and its multiples constants of the loop,
+// whole traces of 512 transducers of 1024 rays on a ring of 50 mm went from 3.81 to 3.56 ms and
+// nothing is spilled. FP32 copies of FP64 values carried to the next step and 32-bit sample
+// offsets from scalar bases: 3.28 to 3.23 ms, in an absorbing medium 3.64 to 3.55. Workgroups
+// (four transducers of one rank) are dealt to the 8 XCDs round-robin by launch index. When E is a
+// multiple of 32 the transducer groups of a rank are renamed so that each XCD traces one
+// contiguous arc of E / 8 transducers: same-rank rays of neighbouring transducers cross nearly the
+// same cells at about the same time, so that XCD's L2 fetches their spline coefficients once
+// instead of once per group of four. (Which wave traces which ray changes nothing in the results.)
 //
 // trace_ahead_kernel, for launches that leave a SIMD one or two waves: nothing then hides the wait
 // for the coefficients of a new cell, which some lane of a wave enters at almost every evaluation.
@@ -1269,7 +1268,8 @@ __global__ void __launch_bounds__(1024) folded_list(const int32_t *__restrict__ 
 }
 
 // Workgroups of the resolve pass: more than are resident, since nodes to rebuild are few and far
-// between in most of their strips.
+// between in most of their strips. (4096 to 32768 take the same time within the spread of runs:
+// 256 transducers at a narrow window 4.7 to 4.8 ms in all, a step of 1024 41.4 to 42.8.)
 constexpr int FOLD_GRID = 16384;
 // Most workgroups of the marking pass: segments past the rays' ends cost little and the others
 // much, which evens out over more than the 6 per CU that are resident (256 transducers: 416 us with
@@ -1978,8 +1978,8 @@ __global__ void __launch_bounds__(PATCH_STRIDE) __attribute__((amdgpu_waves_per_
         double sgm, cgm;
         sincos(cand, &sgm, &cgm);
         RayEnd end;
-        if (trace_core<false, ABS, false>(m, am, g, R, psi, xy, cgm, sgm, n_rays, max_steps, ds, c0, el,
-                                   0, sb, nullptr, &end) < 0)
+        if (trace_core<false, ABS, false>(m, am, g, R, psi, xy, cgm, sgm, n_rays, max_steps, ds,
+                                          c0, el, 0, sb, nullptr, &end) < 0)
             break;  // the ray did not reach the ring: the pair ends here
         const double f = end.beta - br;
         if (fabs(f) < best_f) {
@@ -2306,8 +2306,8 @@ rb_status rb_launch_trace(rb_ctx *ctx, const rb_grid *g, const rb_ring *r,
         hipLaunchKernelGGL(ahead ? (a_w ? trace_ahead_kernel<true> : trace_ahead_kernel<false>)
                                  : (a_w ? trace_kernel<true> : trace_kernel<false>),
                            dim3(ahead ? waves : (waves + 3) / 4), dim3(ahead ? 64 : 256), 0,
-                           ctx->stream, smap, amap, gp, r->radius, r->psi0, N, nr, tp->max_steps, tp->ds, tp->c0, e0, E, sb,
-                           ctx->d_flag, nsamp);
+                           ctx->stream, smap, amap, gp, r->radius, r->psi0, N, nr, tp->max_steps,
+                           tp->ds, tp->c0, e0, E, sb, ctx->d_flag, nsamp);
         RB_CHECK_LAUNCH(ctx);
         rb_prof_end(ctx);
         // folded fans: tiles near inverted triangles
