@@ -604,7 +604,7 @@ __global__ void __launch_bounds__(256) weight_scale_kernel(int K, const float2 *
 // FP32 rows G [n][K] (complex) for rb_fwd::forward_reg_kernel: a stage is 16 K as fragments
 // (three parts of re, of im); WEIGHTS: the A side is G v. A lane's quarter of a stage is 32
 // consecutive bytes of a row. Bound by the matrix pipes: 512 transducers and 152 053 nodes with
-// weights take 1.01 ms (1.2 PFLOP/s of MFMAs) where the FP32 kernel took 2.41 ms, and the error
+// weights take 1.01 ms (1.1 PFLOP/s of MFMAs) where the FP32 kernel took 2.41 ms, and the error
 // against FP64 sums is 9.6e-8 (3.9e-7).
 template <bool WEIGHTS>
 struct SplitFwd {
